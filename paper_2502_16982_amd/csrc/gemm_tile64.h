@@ -1,0 +1,302 @@
+// 64 x 64 output tile of a bf16 Newton-Schulz product, for launches that hold few tiles (device code; the products, the
+// operand layouts and the split-plane arithmetic are described in kernels_gemm_bf16.hip, which includes this file).
+//
+// What bounds such a launch is not the matrix cores but latency: the first operands come from the memory-side cache
+// (about 2 us after the block starts), a block's K loop is a serial chain of slabs, and most compute units hold one
+// block or none.  So the tile is small - four waves with one 32 x 32 MFMA tile each - and the LDS is a ring of kRing64
+// slabs of 16 KB that are requested as early as a stage is free and waited for with a partial s_waitcnt vmcnt: only the
+// first slab's latency is seen, and three blocks fit a compute unit.  The fragments of the next slab are read while this
+// one is multiplied; one barrier per slab.
+// Addresses, swizzles and the order in which an output element's products are added are those of the large tiles: in
+// plain bf16 an element comes out with the same bits whichever tile computes it.
+// Measured (us per launch, 256-wide tiles of one block per compute unit / 128-wide tiles / these): Gram product of
+// 4 x 1024^2 and 3 x 1024 x 4096 75 / 43 / 34; products of nine matrices of 200 x 333 to 512 x 768 22 / 9 / 6; Gram
+// product of 4 x 512^2 and 3 x 512 x 1536 with three planes 230 / 87 / 53.  Rings of 2, 4 and 8 slabs took 1.17, 0.98 to
+// 1.07 and 1.1 to 1.4 times as long over whole steps.
+#pragma once
+
+namespace muon {
+namespace {
+
+constexpr int kRing64 = 3;
+constexpr size_t kLdsRing64 = (size_t)kRing64 * 128 * ROWB;
+
+// Fragments of one k-step of a wave, read by assembly (in front of an LDS read of its own the compiler puts a wait for
+// all vector memory, the slabs in flight included).  The transposing read of the K-major operand delivers two halves.
+template <bool LKM>
+struct Frag64 {
+  u32x4 a, b;
+  u32x2 h0, h1;
+};
+template <bool LKM>
+__device__ __forceinline__ void read64(Frag64<LKM>& f, unsigned a_addr, unsigned b_addr) {
+  if constexpr (LKM) {
+    asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(f.h0) : "v"(a_addr) : "memory");
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.h1) : "v"(a_addr), "n"(4 * ROWB) : "memory");
+  } else {
+    asm volatile("ds_read_b128 %0, %1" : "=v"(f.a) : "v"(a_addr) : "memory");
+  }
+  asm volatile("ds_read_b128 %0, %1" : "=v"(f.b) : "v"(b_addr) : "memory");
+}
+// The wait for all LDS reads, and a tie of further fragments to the same point of the instruction stream: the covered
+// registers are read-write operands, so every MFMA on them depends on the wait.
+template <bool LKM>
+__device__ __forceinline__ void tie64(Frag64<LKM>& f) {
+  if constexpr (LKM) asm volatile("" : "+v"(f.h0), "+v"(f.h1), "+v"(f.b) : : "memory");
+  else asm volatile("" : "+v"(f.a), "+v"(f.b) : : "memory");
+}
+template <bool LKM>
+__device__ __forceinline__ void land64(Frag64<LKM>& f) {
+  if constexpr (LKM) asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.h0), "+v"(f.h1), "+v"(f.b) : : "memory");
+  else asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a), "+v"(f.b) : : "memory");
+}
+
+// The tile at (row0, col0); `diagonal`: it lies on the diagonal of a symmetric product (its own mirror image).
+template <bool LKM, int PL>
+__device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem,
+                                                 float beta_acc, float beta_e, int alpha_idx, float diag_add) {
+  constexpr int NW = 4, BT = 64, NST = kRing64, NLOAD = 4;      // waves, tile side, stages, 1 KB requests per wave and slab
+  constexpr int STAGE_B = 2 * BT * ROWB, KSTEPS = BK / 16, NSEG = seg_count(PL);
+  static_assert(NST >= 3 && NLOAD * (NST - 1) < 64 && ROWB == 2 * BT, "ring shape");
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int fr = lane & 31, fh = lane >> 5;
+
+  // ---- requests: a wave instruction fills 8 LDS rows of 128 B (L rows, or k-rows of the K-major L: a slab is 64 x 64
+  // either way).  Row R keeps its 16-byte chunks XOR-swizzled: by (R / 2) % 8, and a k-row by 4 ((R / 2) % 2), which
+  // spreads the four k-rows one transposing read touches over the banks.
+  const int dma_row = wave * 8 + (lane >> 3);
+  const int dma_chunk = (lane & 7) ^ ((dma_row >> 1) & 7);
+  const int km_chunk = (lane & 7) ^ (4 * ((dma_row >> 1) & 1));
+  const u16* lsrc = LKM ? static_cast<const u16*>(p.L) + (size_t)dma_row * p.ldl + row0 + km_chunk * 8
+                        : static_cast<const u16*>(p.L) + (size_t)(row0 + dma_row) * p.ldl + dma_chunk * 8;
+  const u16* rsrc = static_cast<const u16*>(p.R) + (size_t)(col0 + dma_row) * p.ldr + dma_chunk * 8;
+  const size_t lstep = (size_t)(8 * NW) * p.ldl, rstep = (size_t)(8 * NW) * p.ldr;
+  const size_t lslab = LKM ? (size_t)BK * p.ldl : (size_t)BK;
+  const int KT1 = p.K / BK, KT = NSEG * KT1;
+  auto request_one = [&](int kt, int stage, auto n_tag) {
+    constexpr int n = decltype(n_tag)::value;
+    unsigned char* base = smem + stage * STAGE_B + wave * 1024;
+    int seg = 0, kl = kt, lpl = seg_plane(PL, 0, 0), rpl = seg_plane(PL, 0, 1);
+    if constexpr (PL > 1) {
+#pragma unroll
+      for (int sgm = 1; sgm < NSEG; ++sgm)
+        if (kt >= sgm * KT1) { seg = sgm; kl = kt - sgm * KT1; }
+#pragma unroll
+      for (int sgm = 1; sgm < NSEG; ++sgm)
+        if (seg == sgm) { lpl = seg_plane(PL, sgm, 0); rpl = seg_plane(PL, sgm, 1); }
+    }
+    if constexpr (n < 2) {
+      const size_t off = (size_t)kl * lslab + (PL > 1 ? (size_t)lpl * (size_t)p.l_plane : 0);
+      __builtin_amdgcn_global_load_lds((gptr)(lsrc + n * lstep + off), (lptr)(base + n * NW * 1024), 16, 0, 0);
+    } else {
+      const size_t off = (size_t)kl * BK + (PL > 1 ? (size_t)rpl * (size_t)p.r_plane : 0);
+      __builtin_amdgcn_global_load_lds((gptr)(rsrc + (n - 2) * rstep + off), (lptr)(base + BT * ROWB + (n - 2) * NW * 1024), 16, 0, 0);
+    }
+  };
+
+  // ---- fragment reads (lane addressing as in the large tiles) ----
+  const int fkey = (fr >> 1) & 7;
+  const unsigned lds0 = (unsigned)(size_t)(lptr)smem;
+  const unsigned a_base = (unsigned)((wm * 32 + fr) * ROWB), b_base = (unsigned)(BT * ROWB + (wn * 32 + fr) * ROWB);
+  const int l16 = lane & 15, grp = lane >> 4, r4 = l16 >> 2;
+  const unsigned a_km = (unsigned)((8 * (grp >> 1) + r4) * ROWB + (((4 * wm) ^ (4 * ((r4 >> 1) & 1))) + 2 * (grp & 1) + ((l16 & 3) >> 1)) * 16 +
+                                   (l16 & 1) * 8);
+  Frag64<LKM> fg[2][KSTEPS];                     // fragments of two slabs: one multiplied, one being read
+  auto read_slab = [&](int stage, auto set_tag) {
+    constexpr int set = decltype(set_tag)::value;
+    const unsigned sa = lds0 + (unsigned)(stage * STAGE_B);
+    static_for<0, KSTEPS>([&](auto kk_tag) {
+      constexpr int kk = decltype(kk_tag)::value;
+      const unsigned chunk = (unsigned)(((2 * kk + fh) ^ fkey) * 16);
+      read64(fg[set][kk], LKM ? sa + (unsigned)(16 * kk * ROWB) + a_km : sa + a_base + chunk, sa + b_base + chunk);
+    });
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+
+  // One slab, whose fragments are in set `set` or on their way there.  MORE: there is a next slab, with `behind` slabs
+  // requested after it; its fragments are read into the other set while this slab is multiplied.  REFILL: slab kt + NST
+  // exists and goes into this slab's stage, which every wave has read when the barrier opens; a request holds the
+  // wave's in-order issue port until the memory pipeline takes it, so each goes out behind an MFMA.
+  int kt = 0, stage = 0;
+  auto slab = [&](auto set_tag, auto more_tag, auto refill_tag, auto behind_tag) {
+    constexpr int set = decltype(set_tag)::value, behind = decltype(behind_tag)::value;
+    constexpr bool MORE = decltype(more_tag)::value, REFILL = decltype(refill_tag)::value;
+    land64(fg[set][0]);
+#pragma unroll
+    for (int kk = 1; kk < KSTEPS; ++kk) tie64(fg[set][kk]);
+    const int next = stage + 1 == NST ? 0 : stage + 1;
+    if constexpr (MORE) {
+      wait_vmcnt<NLOAD * behind>();              // my requests of the next slab have landed
+      __builtin_amdgcn_s_barrier();              // everybody's; and everybody has read this one
+      read_slab(next, std::integral_constant<int, set ^ 1>{});
+    }
+    static_for<0, KSTEPS>([&](auto kk_tag) {
+      constexpr int kk = decltype(kk_tag)::value;
+      bf16x8 a;
+      if constexpr (LKM) {
+        const u32x4 both = {fg[set][kk].h0.x, fg[set][kk].h0.y, fg[set][kk].h1.x, fg[set][kk].h1.y};
+        a = __builtin_bit_cast(bf16x8, both);
+      } else {
+        a = __builtin_bit_cast(bf16x8, fg[set][kk].a);
+      }
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, fg[set][kk].b), acc, 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (REFILL) request_one(kt + NST, stage, kk_tag);
+    });
+    stage = next;
+    ++kt;
+  };
+
+  // ---- the addend: this lane's pieces of its MFMA tile, 8 contiguous bytes each of the transposed addend.  Plain bf16
+  // requests them ahead of the first slab; being older than every slab they are never counted in a wait for one.
+  const u16* Et = static_cast<const u16*>(p.Et);
+  const bool has_e = Et != nullptr;
+  u32x2 ev[4];
+  auto load_e = [&](int plane) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      ev[q] = *reinterpret_cast<const u32x2*>(Et + (PL > 1 ? (size_t)plane * (size_t)p.et_plane : 0) +
+                                              (size_t)(col0 + wn * 32 + fr) * p.ldet + row0 + wm * 32 + 8 * q + 4 * fh);
+  };
+  if (PL == 1 && has_e) load_e(0);
+
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using T_ = std::true_type;
+  using F_ = std::false_type;
+  auto request_slab = [&](int s) { static_for<0, NLOAD>([&](auto n_tag) { request_one(s, s, n_tag); }); };
+  static_assert(NST == 3, "the slabs written out below: extents are padded to 128, so KT is even");
+  request_slab(0);
+  request_slab(1);
+  if (KT == 2) {                                 // K = 128, one plane: all of it is on its way
+    wait_vmcnt<NLOAD>();
+    __builtin_amdgcn_s_barrier();
+    read_slab(0, I0{});
+    slab(I0{}, T_{}, F_{}, I0{});
+    slab(I1{}, F_{}, F_{}, I0{});
+  } else {                                       // KT is even
+    request_slab(2);
+    wait_vmcnt<2 * NLOAD>();
+    __builtin_amdgcn_s_barrier();
+    read_slab(0, I1{});
+    slab(I1{}, T_{}, T_{}, I1{});
+    while (kt + NST < KT) {
+      slab(I0{}, T_{}, T_{}, I1{});
+      slab(I1{}, T_{}, T_{}, I1{});
+    }
+    slab(I0{}, T_{}, F_{}, I1{});
+    slab(I1{}, T_{}, F_{}, I0{});
+    slab(I0{}, F_{}, F_{}, I0{});
+  }
+  __syncthreads();                               // every wave has read the last slab: the LDS is free for the images
+
+  // ---- epilogue: val = alpha * (beta_acc * acc + beta_e * E) (+ the diagonal constant), in the large tiles' order ----
+  const float alpha = alpha_idx >= 0 ? p.scal[alpha_idx] : 1.f;
+  const float ab_acc = alpha * beta_acc, ab_e = alpha * beta_e;
+  u16* C = static_cast<u16*>(p.C);
+  u16* Ct = static_cast<u16*>(p.Ct);
+  int ldct = p.ldct;
+  if (p.symmetric) {                             // mirror store; the tile itself only off the diagonal
+    Ct = C;
+    ldct = p.ldc;
+    if (diagonal) C = nullptr;
+  }
+  auto add_e = [&]() {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      acc[4 * q + 0] = fmaf(ab_e, __uint_as_float(ev[q].x << 16), acc[4 * q + 0]);
+      acc[4 * q + 1] = fmaf(ab_e, __uint_as_float(ev[q].x & 0xffff0000u), acc[4 * q + 1]);
+      acc[4 * q + 2] = fmaf(ab_e, __uint_as_float(ev[q].y << 16), acc[4 * q + 2]);
+      acc[4 * q + 3] = fmaf(ab_e, __uint_as_float(ev[q].y & 0xffff0000u), acc[4 * q + 3]);
+    }
+  };
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] *= ab_acc;
+  if (PL == 1 && has_e) add_e();                 // plain bf16: addend, then diagonal; planes: the reverse
+  if (p.diag_add != 0 && row0 + wm * 32 == col0 + wn * 32) {     // wave-uniform
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] += (fr == 8 * (v >> 2) + 4 * fh + (v & 3)) ? diag_add : 0.f;
+  }
+  if constexpr (PL > 1) {
+    if (has_e) {
+#pragma unroll 1
+      for (int q = 0; q < PL; ++q) {
+        load_e(q);
+        add_e();
+      }
+    }
+  }
+
+  // ---- results leave plane by plane through swizzled LDS images of 64 rows x 128 B (chunk of row r at position
+  // chunk ^ (r / 2) % 8), 16 bytes per lane ----
+  auto slot = [&](int row, int chunk) -> u32x2* {
+    return reinterpret_cast<u32x2*>(smem + row * ROWB + ((chunk ^ ((row >> 1) & 7)) * 16) + fh * 8);
+  };
+  auto store_image = [&](u16* dst, int ld, int first_row, int first_col) {
+    u32x4 v[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) v[n] = *reinterpret_cast<const u32x4*>(smem + (n * NW + wave) * 1024 + lane * 16);
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+      const int r = n * 8 * NW + dma_row;
+      *(gvec_ptr)(dst + (size_t)(first_row + r) * ld + first_col + dma_chunk * 8) = v[n];
+    }
+  };
+  bf16x8 sel[2];                                 // 0/1 selector of the MFMA transpose
+#pragma unroll
+  for (int sx = 0; sx < 2; ++sx)
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int row = 16 * sx + 4 * fh + (t < 4 ? t : 4 + t);
+      sel[sx][t] = (__bf16)(fr == row ? 1.0f : 0.0f);
+    }
+  auto pack2f = [](float x, float y) {
+    const f32x2 v = {x, y};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
+  };
+#pragma unroll
+  for (int plane = 0; plane < PL; ++plane) {
+    u32x2 pk[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      pk[q] = u32x2{pack2f(acc[4 * q], acc[4 * q + 1]), pack2f(acc[4 * q + 2], acc[4 * q + 3])};
+      if (plane + 1 < PL) {                      // what this plane leaves of the value (exact)
+        acc[4 * q + 0] -= __uint_as_float(pk[q].x << 16);
+        acc[4 * q + 1] -= __uint_as_float(pk[q].x & 0xffff0000u);
+        acc[4 * q + 2] -= __uint_as_float(pk[q].y << 16);
+        acc[4 * q + 3] -= __uint_as_float(pk[q].y & 0xffff0000u);
+      }
+    }
+    if (Ct) {
+      if (plane) __syncthreads();                // the previous plane's image has been read out
+#pragma unroll
+      for (int q = 0; q < 4; ++q) *slot(wn * 32 + fr, 4 * wm + q) = pk[q];
+      __syncthreads();
+      store_image(Ct + (PL > 1 ? (size_t)plane * (size_t)(p.symmetric ? p.c_plane : p.ct_plane) : 0), ldct, col0, row0);
+    }
+    if (C) {
+      if (plane || Ct) __syncthreads();
+      f32x16 d;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) d[v] = 0.f;
+#pragma unroll
+      for (int sx = 0; sx < 2; ++sx) {
+        const u32x4 raw = {pk[2 * sx].x, pk[2 * sx].y, pk[2 * sx + 1].x, pk[2 * sx + 1].y};
+        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, raw), sel[sx], d, 0, 0, 0);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *slot(wm * 32 + fr, 4 * wn + q) = u32x2{pack2f(d[4 * q], d[4 * q + 1]), pack2f(d[4 * q + 2], d[4 * q + 3])};
+      __syncthreads();
+      store_image(C + (PL > 1 ? (size_t)plane * (size_t)p.c_plane : 0), p.ldc, row0, col0);
+    }
+  }
+}
+
+}  // namespace
+}  // namespace muon

@@ -1106,6 +1106,14 @@ __device__ __forceinline__ void diag_tile_body(const GemmProblem& p, const GemmT
   }
 }
 
+}  // namespace
+}  // namespace muon
+
+#include "gemm_tile64.h"
+
+namespace muon {
+namespace {
+
 // ---- kernels.  Fine launch: 128 x 128 tiles, two blocks per compute unit.  Coarse launch: one block per compute
 // unit, each block running the shape its table entry names - 256 x 256 (2 x 2 waves) or 512 x 128 (4 x 1 waves; the
 // 128-wide strips that an odd multiple of 128 leaves beside the 256-tiles).  Both coarse shapes give every wave a
@@ -1143,6 +1151,23 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_bf16_fine_kernel(const GemmPro
                                              __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
+// Each 128 x 128 table entry as four blocks of 64 x 64.  Block b: entry 8 (b / 32) + b % 8, so that an entry's quarters
+// run on the die its entry is dealt to; quarter (b / 8) % 4.
+template <bool LKM, int PL>
+__global__ __launch_bounds__(256, 3) void ns_tile64_gemm_bf16_kernel(const GemmProblem* __restrict__ probs,
+                                                                   const GemmTile* __restrict__ tiles, int n_tiles, float beta_acc,
+                                                                   float beta_e, int alpha_idx, float diag_add) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int t = (int)(blockIdx.x >> 5) * 8 + (int)(blockIdx.x & 7), quarter = (int)(blockIdx.x >> 3) & 3;
+  if (t >= n_tiles) return;
+  const GemmTile tile = load_tile(tiles, t);
+  const bool on_diag = (tile.flags & kTileDiagonal) != 0;
+  if (on_diag && quarter == 2) return;           // below the diagonal: the mirror image of quarter 1
+  const GemmProblem p = probs[tile.prob];
+  gemm_tile64_body<LKM, PL>(p, tile.r0 * kTileUnit + 64 * (quarter >> 1), tile.c0 * kTileUnit + 64 * (quarter & 1),
+                            on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, diag_add);
+}
+
 // Block b works through table entries b, b + gridDim.x, ...  Launched with one block per tile, or persistent: one
 // block per compute unit (a multiple of the 8 dies, so an entry still runs on die index % 8); a persistent block that
 // goes on to its next tile neither waits for its stores to drain nor is re-dispatched, and its next tile's first
@@ -1175,6 +1200,9 @@ template <bool LKM, int PL>
 hipError_t setup_pair() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_bf16_fine_kernel<LKM, PL>),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds128);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_tile64_gemm_bf16_kernel<LKM, PL>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsRing64);
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_bf16_kernel<LKM, PL>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds512);
@@ -1183,7 +1211,10 @@ hipError_t setup_pair() {
 template <bool LKM, int PL>
 void launch_one(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc,
                 float beta_e, int alpha_idx, float diag_add, hipStream_t s) {
-  if (!coarse)
+  if (!coarse && (flags & kGemmTile64))
+    ns_tile64_gemm_bf16_kernel<LKM, PL><<<(n_tiles + 7) / 8 * 32, 256, kLdsRing64, s>>>(probs, tiles, n_tiles, beta_acc, beta_e,
+                                                                                       alpha_idx, diag_add);
+  else if (!coarse)
     ns_gemm_bf16_fine_kernel<LKM, PL><<<n_tiles, 256, kLds128, s>>>(probs, tiles, beta_acc, beta_e, alpha_idx, diag_add);
   else
     ns_gemm_bf16_kernel<LKM, PL><<<(flags & kGemmPersistent) && n_tiles > g_coarse_grid ? g_coarse_grid : n_tiles, 256,

@@ -26,9 +26,10 @@ hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, 
 // allocation).  kGemmPersistent: one block per compute unit works through the table with stride gridDim (for launches
 // whose tiles run K loops of nearly the same length, which the planner balances statically; with a wide spread of K
 // the hardware's dynamic block dispatch does better).
+// kGemmTile64 (coarse = 0): every 128 x 128 entry of the table runs as four blocks of 64 x 64.
 // l_kmajor: every problem of the launch stores its L operand K-major (element (i, k) at L[k * ldl + i]).
 // planes: 1 = plain bf16; 2 or 3 = every matrix is a sum of that many bf16 planes (GemmProblem::*_plane strides).
-constexpr int kGemmStrips = 1, kGemmPersistent = 2;
+constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmTile64 = 4;
 hipError_t launch_gemm_bf16(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
                             float beta_acc, float beta_e, int alpha_idx, float diag_add, int l_kmajor, int planes,
                             hipStream_t s);

@@ -103,21 +103,24 @@ size_t move_tail_to_fine(const std::vector<int>& order, std::vector<std::vector<
 // of the MFMAs of a full one), so within every run of `slots` entries - the tiles the die runs at the same time,
 // whose set stays as it is - the tiles are handed to the slots most expensive first, each to the slot that has
 // accumulated least so far.
+// `join_equal` (fine tables): problems with K loops of one length are cut into the 8 runs together, not one by one, so that
+// a die works on an eighth of the problems instead of an eighth of each: with few tiles per problem every die fetched
+// nearly every operand (layer of 4 x 1024^2 and 3 x 1024 x 4096: fine launches -4 to -8 %, with two planes -4 to -17 %).
 size_t deal_tiles(const std::vector<int>& order, const std::vector<std::vector<GemmTile>>& per_problem,
                   const std::vector<std::vector<int>>& per_problem_cuts, const std::vector<int64_t>& weight, GemmTile* out,
-                  int slots = 0) {
+                  int slots = 0, bool join_equal = false) {
   std::vector<std::vector<GemmTile>> seq(kXcds);
   std::vector<int64_t> load(kXcds, 0);
   int rr = 0;
   size_t nonempty = 0;
   for (const auto& t : per_problem) nonempty += t.empty() ? 0 : 1;
   const bool whole = nonempty >= 4 * (size_t)kXcds;
-  for (int pi : order) {
-    const std::vector<GemmTile>& tiles = per_problem[pi];
-    const std::vector<int>& cuts = per_problem_cuts[pi];
-    if (tiles.empty()) continue;
+  for (size_t oi = 0; oi < order.size(); ++oi) {
+    const int pi = order[oi];
+    if (per_problem[pi].empty()) continue;
     if (whole) {
       // least-loaded XCD (tiles weighted by the length of their K loop), ties broken round-robin
+      const std::vector<GemmTile>& tiles = per_problem[pi];
       int best = rr;
       for (int x = 0; x < kXcds; ++x)
         if (load[(rr + x) % kXcds] < load[best]) best = (rr + x) % kXcds;
@@ -128,6 +131,13 @@ size_t deal_tiles(const std::vector<int>& order, const std::vector<std::vector<G
       // 8 contiguous runs of equal length (so that entry b of the dealt table still lands on die b % 8).  A run
       // starts and ends inside blocks; its whole blocks go first, so that the tiles a die runs together come from
       // one block, and the two partial blocks at its ends follow.
+      std::vector<GemmTile> tiles = per_problem[pi];
+      std::vector<int> cuts = per_problem_cuts[pi];
+      while (join_equal && oi + 1 < order.size() && weight[order[oi + 1]] == weight[pi]) {
+        const int pj = order[++oi];
+        for (int c : per_problem_cuts[pj]) cuts.push_back(c + (int)tiles.size());
+        tiles.insert(tiles.end(), per_problem[pj].begin(), per_problem[pj].end());
+      }
       const size_t n = tiles.size();
       for (int x = 0; x < kXcds; ++x) {
         const size_t lo = n * x / kXcds, hi = n * (x + 1) / kXcds;
@@ -181,6 +191,30 @@ size_t deal_tiles(const std::vector<int>& order, const std::vector<std::vector<G
     if (!any) break;
   }
   return o;
+}
+
+// Whether a product goes to the fine launch altogether: its coarse tiles (256 x 256, one block per compute unit) are so
+// few that they leave much of the chip idle.  Measured, us per launch, coarse / fine (128 x 128, or their quarters):
+//   Gram and polynomial: 2048^2 (36 tiles) 45 / 24, 3584^2 (105) 69 / 56, 4096^2 (136) 83 / 102; with a short K the line
+//   lies at one full round of coarse tiles: 16 of 1024^2 (160) 35 / 33, 12 of 2048 x 1408 (216) 68 / 67 and 56 / 51,
+//   84 of 1024^2 (840) 141 / 143.
+//   Apply: 2048^2 (64) 44 / 26, two of 1024 x 4096 (128) 31 / 24, 3072^2 (144) 63 / 78, four of 1024 x 4096 (256) 38 / 41.
+bool few_coarse_sym(size_t tiles, int64_t longest_k) { return tiles < 112 || (tiles < 256 && longest_k <= 2048); }
+bool few_coarse_apply(size_t tiles) { return tiles <= 128; }
+
+// Whether a fine bf16 launch runs each 128 x 128 entry as four 64 x 64 blocks, which are quicker through one tile (0.35
+// against 0.6 us per 64 of K) but need more of the compute unit for the same work: while the launch holds less work
+// than about 176 tiles of its longest K.  Measured, us per launch, 128 / 64: Gram product of 1024^2 (36 tiles) 16.2 / 10.4,
+// four of 1024 x 4096 (144) 42 / 39, four of 2048 x 1408 (264) 31 / 34; apply product of 1024^2 (64) 14.6 / 9.9, of
+// 32 of 256 x 384 (192) 8.4 / 8.0, of four of 1024^2 (256) 16.3 / 18.2.
+bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k) {
+  int64_t longest = 0, total = 0;
+  for (size_t i = 0; i < tiles.size(); ++i)
+    if (!tiles[i].empty()) {
+      longest = std::max(longest, k[i]);
+      total += k[i] * (int64_t)tiles[i].size();
+    }
+  return total <= 176 * longest;
 }
 
 void plan_matrices(const muon_param* p, int n, int ns_dtype, std::vector<MatPlan>& out, size_t& total_partials) {
@@ -503,6 +537,16 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         lo_m = std::min(lo_m, w_m[k]); hi_m = std::max(hi_m, w_m[k]);
       }
       const bool steady_n = 2 * hi_n <= 3 * lo_n, steady_m = 2 * hi_m <= 3 * lo_m;
+      size_t coarse_sym = 0, coarse_app = 0;
+      for (size_t k = 0; mc && k < np_; ++k) {
+        const MatPlan& q = plan.mats[members[k]];
+        const size_t cm = (size_t)(q.mp / kCoarse), cn = (size_t)(q.np / kCoarse);
+        const int strip_h = kShapeRows[kShape512x128];
+        const bool odd_m = (q.mp % kCoarse) != 0;
+        coarse_sym += cm * (cm + 1) / 2 + (odd_m && q.mp >= strip_h ? (size_t)((q.mp + strip_h - 1) / strip_h) : 0);
+        coarse_app += cm * cn + (odd_m && q.np >= strip_h ? (size_t)((q.np + strip_h - 1) / strip_h) : 0);
+      }
+      const bool few_sym = few_coarse_sym(coarse_sym, *std::max_element(w_n.begin(), w_n.end())), few_app = few_coarse_apply(coarse_app);
       std::vector<std::vector<GemmTile>> moved_sym(np_), moved_app(np_);   // coarse tiles handed to the fine level
       for (int level = 1; level >= 0; --level) {
         if (level == 1 && !mc) continue;
@@ -512,16 +556,17 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         bool strips = false;
         for (size_t k = 0; k < np_; ++k) {
           const MatPlan& q = plan.mats[members[k]];
-          const int cm = mc ? q.mp / kCoarse : 0, cn = mc ? q.np / kCoarse : 0;
+          const int cm_sym = mc && !few_sym ? q.mp / kCoarse : 0;            // coarse tiles along a side
+          const int cm = mc && !few_app ? q.mp / kCoarse : 0, cn = mc && !few_app ? q.np / kCoarse : 0;
           const int tm = q.mp / q.tile, tn = q.np / q.tile, r = kCoarse / q.tile;
           const int strip_h = kShapeRows[kShape512x128];
           // the 128 columns an odd multiple of 128 leaves beside the 256-tiles go to 512 x 128 tiles where the
           // output is at least 512 rows high
           const bool odd_m = mc && (q.mp % kCoarse) != 0;
-          const bool sym_strip = odd_m && q.mp >= strip_h, app_strip = odd_m && q.np >= strip_h;
+          const bool sym_strip = odd_m && !few_sym && q.mp >= strip_h, app_strip = odd_m && !few_app && q.np >= strip_h;
           if (level == 1) {
             // plain bf16: a diagonal tile is computed from its upper triangle of 32 x 32 blocks (9/16 of the MFMAs)
-            blocked_tiles((int32_t)k, kCoarse, kShape256, cm, cm, true, 0, 0, -1, sym[k], sym_cuts[k], 4, 8,
+            blocked_tiles((int32_t)k, kCoarse, kShape256, cm_sym, cm_sym, true, 0, 0, -1, sym[k], sym_cuts[k], 4, 8,
                           ns_dtype == MUON_BF16 ? (int)kShape256Diag : -1);
             if (sym_strip) strip_tiles((int32_t)k, q.mp, q.mp - q.tile, sym[k], sym_cuts[k]);
             // tiles of X'^T in 8 x 2 blocks: measured against 8 x 4, 4 x 8, 16 x 2 and whole-width blocks, 0.7 % (4096-wide
@@ -531,7 +576,7 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
             strips = strips || sym_strip || app_strip;
           } else {
             const int fine_shape = mc ? (int)kShape128 : 0;
-            blocked_tiles((int32_t)k, q.tile, fine_shape, tm, tm, true, cm * r, cm * r, sym_strip ? tm - 1 : -1, sym[k], sym_cuts[k]);
+            blocked_tiles((int32_t)k, q.tile, fine_shape, tm, tm, true, cm_sym * r, cm_sym * r, sym_strip ? tm - 1 : -1, sym[k], sym_cuts[k]);
             if (mc) blocked_tiles((int32_t)k, q.tile, fine_shape, tn, tm, false, cn * r, cm * r, app_strip ? tm - 1 : -1, app[k], app_cuts[k], 8, 4);
             else blocked_tiles((int32_t)k, q.tile, fine_shape, tm, tn, false, 0, 0, -1, app[k], app_cuts[k]);
             // the coarse tiles moved here: four fine tiles each (never a diagonal tile, so none of the four is one)
@@ -559,6 +604,11 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         }
         TileSet& ts = level ? g.coarse : g.fine;
         ts.strips = strips;
+        if (level == 0 && mc) {
+          ts.quarter_sym = runs_in_quarters(sym, w_n);
+          ts.quarter_poly = runs_in_quarters(sym, w_m);
+          ts.quarter_apply = runs_in_quarters(app, w_m);
+        }
         ts.persistent_n = steady_n;
         ts.persistent_m = steady_m;
         ts.sym = take(n_sym * sizeof(GemmTile));
@@ -570,10 +620,10 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         // evened out over a die's blocks where its launch is persistent (where the hardware hands out the blocks the
         // plain order measured better).
         const int slots = level == 1 ? plan.coarse_blocks / kXcds : 0;
-        ts.n_sym = (int)deal_tiles(by_n, sym, sym_cuts, w_n, reinterpret_cast<GemmTile*>(img.data() + ts.sym), steady_n ? slots : 0);
-        ts.n_poly = (int)deal_tiles(by_m, sym, sym_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.poly), steady_m ? slots : 0);
-        ts.n_apply = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply), steady_m ? slots : 0);
-        ts.n_apply_last = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply_last), steady_m ? slots : 0);
+        ts.n_sym = (int)deal_tiles(by_n, sym, sym_cuts, w_n, reinterpret_cast<GemmTile*>(img.data() + ts.sym), steady_n ? slots : 0, level == 0);
+        ts.n_poly = (int)deal_tiles(by_m, sym, sym_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.poly), steady_m ? slots : 0, level == 0);
+        ts.n_apply = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply), steady_m ? slots : 0, level == 0);
+        ts.n_apply_last = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply_last), steady_m ? slots : 0, level == 0);
       }
       ch.groups.push_back(g);
     }

@@ -34,12 +34,14 @@ struct TileSet {
   // the K loops of the launch's tiles are of nearly the same length (Gram product: n_pad; the other two: m_pad), so
   // the launch runs persistent blocks that take the planner's static assignment of tiles
   bool persistent_n = false, persistent_m = false;
+  bool quarter_sym = false, quarter_poly = false, quarter_apply = false;   // fine bf16 launches that run as 64 x 64 blocks
 };
 
 // Launch group: all matrices of one chunk.  Each product is one launch per level: the coarse launch (matrix-core
 // paths only) runs 256 x 256 tiles over the part of every output that whole such tiles cover plus 512 x 128 tiles
 // over the 128-wide column strip an odd multiple of 128 leaves; the fine launch (128 x 128 bf16, 64 x 64 fp32) takes
-// what remains, so that nothing is padded beyond the fine tile.
+// what remains, so that nothing is padded beyond the fine tile.  A product whose coarse launch would leave much of the
+// chip idle has no coarse launch: all its tiles are fine.
 struct Group {
   int n_prob = 0;
   std::vector<int> members;                       // problem index -> matrix index in the caller's list

@@ -1,0 +1,65 @@
+"""The planner gives a product 256-, 128- or 64-wide tiles by how much work a launch holds.  Every tile adds an output
+element's products in the same order, so in plain bf16 a matrix must come out with the same bits whichever tiles computed
+it: alone (64-wide), in a short list (128-wide) and in a list long enough for 256-wide tiles and strips.  With several
+planes an element of a symmetric product and its mirror image add the plane pairs in different orders (fp32 rounding,
+about 1e-7 of A per product), and the tile decides which of the two is kept: there the results agree to a tenth of the
+path's own bar."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2502_16982_amd import binding, workloads  # noqa: E402
+from tests import gpu_util as U  # noqa: E402
+from tests.test_gpu_parity import assert_records  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    binding.lib()
+    return torch.device("cuda:0")
+
+
+def coarse_tiles(shapes, ns):
+    p = binding.param_array(shapes, [1] * len(shapes), [1] * len(shapes))
+    ctx = binding.muon_plan_only(p, len(shapes), binding.NS_DTYPES[ns], binding.muon_workspace_bytes(p, len(shapes), binding.NS_DTYPES[ns]))
+    try:
+        return [len(binding.muon_plan_tiles(ctx, 0, product, 1)) for product in ("gram", "apply")]
+    finally:
+        binding.muon_destroy(ctx)
+
+
+@pytest.mark.parametrize("ns", ["bf16", "bf16x2", "bf16x3"])
+@pytest.mark.parametrize("shape,short,long", [((640, 1408), 12, 130), ((1408, 640), 12, 130), ((1024, 1024), 10, 60)])
+def test_same_bits_from_every_tile(dev, ns, shape, short, long):
+    wl = workloads.custom("routes", [shape] * long, ns_dtype=ns, seed_base=310)
+    first = workloads.make_matrix(wl, 0, dev)
+    hp = binding.default_hparams(lr=0.02, weight_decay=0.1)
+    results = []
+    for n in (1, short, long):
+        tensors = [tuple(t.clone() for t in first) for _ in range(n)]
+        st = binding.MuonStepper(tensors, ns_dtype=ns)
+        st.step(hp)
+        torch.cuda.synchronize()
+        # the same matrix everywhere in the list: first, last and one in the middle
+        for i in {0, n // 2, n - 1}:
+            results.append((st.read_update(i), tensors[i][0], tensors[i][2]))
+        st.close()
+    assert coarse_tiles([shape], ns) == [0, 0] and min(coarse_tiles([shape] * long, ns)) > 0
+    for o, w, m in results[1:]:
+        assert torch.equal(m, results[0][2])
+        if ns == "bf16":
+            assert torch.equal(o, results[0][0]) and torch.equal(w, results[0][1])
+        else:
+            assert U.rel_fro(U.to64(o), U.to64(results[0][0])) <= 0.1 * U.TOL_SPLIT_FRO[ns]
+
+
+@pytest.mark.parametrize("ns,tol", [("bf16", U.TOL_BF16_FRO), ("bf16x2", U.TOL_SPLIT_FRO["bf16x2"]), ("bf16x3", U.TOL_SPLIT_FRO["bf16x3"])])
+def test_64_wide_tiles_at_their_edges(dev, ns, tol):
+    """K of one, two, three and many pairs of slabs, both orientations, one padded row or column short of a tile."""
+    shapes = [(128, 128), (65, 127), (129, 256), (256, 129), (127, 384), (128, 1024), (1024, 128), (320, 577)]
+    wl = workloads.custom("edges64_" + ns, shapes, ns_dtype=ns, seed_base=320)
+    assert coarse_tiles(shapes, ns) == [0, 0]
+    assert_records(U.run_and_compare(wl, dev, steps=2, want_rms=True), tol)

@@ -86,3 +86,11 @@ def test_a_loosened_wait_in_the_generated_code_is_caught(gemm_asm):
             break
     res = hz.check_file_text("\n".join(lines))
     assert any(v for v in res.values())
+
+
+def test_generated_code_of_the_64_wide_tile_waits_for_every_lds_read_it_uses(gemm_asm):
+    kernels = {k: v for k, v in hz.split_kernels(gemm_asm).items() if "ns_tile64_gemm_bf16" in k}
+    assert len(kernels) == 6                     # {k-contiguous, K-major} x {1, 2, 3} planes
+    for name, lines in kernels.items():
+        assert any("ds_read_b128" in t for _, t in lines)
+        assert hz.check_kernel(lines) == [], name
