@@ -32,6 +32,7 @@
 //    coalesced stores; the second orientation comes from a 2-MFMA transpose per 32x32 tile.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <type_traits>
 
 #include "muon_launch.h"
@@ -1124,22 +1125,6 @@ constexpr size_t kLds256 = TileCfg<256, 256>::lds_bytes(2);
 constexpr size_t kLds512 = TileCfg<512, 128>::lds_bytes(2);
 constexpr int kMaxPlanes = 3;
 
-// A table entry through whole-dword loads, so that they are scalar loads: the sub-dword fields would otherwise come
-// through a vector load, and the wait for it is a wait for every store of the block's previous tile as well.
-__device__ __forceinline__ GemmTile load_tile(const GemmTile* __restrict__ tiles, int t) {
-  static_assert(sizeof(GemmTile) == 12, "three dwords");
-  const uint32_t* w = reinterpret_cast<const uint32_t*>(tiles) + 3 * (size_t)t;
-  const uint32_t w0 = w[0], w1 = w[1], w2 = w[2];
-  GemmTile r;
-  r.prob = (int32_t)w0;
-  r.r0 = (uint16_t)(w1 & 0xffffu);
-  r.c0 = (uint16_t)(w1 >> 16);
-  r.shape = (uint8_t)(w2 & 0xffu);
-  r.flags = (uint8_t)((w2 >> 8) & 0xffu);
-  r.pad_ = 0;
-  return r;
-}
-
 template <bool LKM, int PL>
 __global__ __launch_bounds__(256, 2) void ns_gemm_bf16_fine_kernel(const GemmProblem* __restrict__ probs,
                                                                     const GemmTile* __restrict__ tiles, float beta_acc,
@@ -1211,7 +1196,7 @@ hipError_t setup_pair() {
 template <bool LKM, int PL>
 void launch_one(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc,
                 float beta_e, int alpha_idx, float diag_add, hipStream_t s) {
-  if (!coarse && (flags & kGemmTile64))
+  if (!coarse && (flags & kGemmQuarters))
     ns_tile64_gemm_bf16_kernel<LKM, PL><<<(n_tiles + 7) / 8 * 32, 256, kLdsRing64, s>>>(probs, tiles, n_tiles, beta_acc, beta_e,
                                                                                        alpha_idx, diag_add);
   else if (!coarse)
@@ -1232,12 +1217,18 @@ hipError_t gemm_setup() {
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   g_coarse_grid = cus > 0 ? cus : 256;
+  // the kernels' attributes stay set: once per device is enough (two threads that get here together set them twice)
+  static std::atomic<uint64_t> done{0};
+  const uint64_t bit = dev < 64 ? uint64_t{1} << dev : 0;
+  if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
   e = setup_pair<false, 1>();
   if (e == hipSuccess) e = setup_pair<true, 1>();
   if (e == hipSuccess) e = setup_pair<false, 2>();
   if (e == hipSuccess) e = setup_pair<true, 2>();
   if (e == hipSuccess) e = setup_pair<false, 3>();
   if (e == hipSuccess) e = setup_pair<true, 3>();
+  if (e == hipSuccess) e = gemm_f32_setup();
+  if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
   return e;
 }
 

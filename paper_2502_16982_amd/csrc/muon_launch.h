@@ -6,6 +6,22 @@
 
 namespace muon {
 
+// A table entry through whole-dword loads, so that they are scalar loads: the sub-dword fields would otherwise come
+// through a vector load, and the wait for it is a wait for every store of the block's previous tile as well.
+__device__ __forceinline__ GemmTile load_tile(const GemmTile* __restrict__ tiles, int t) {
+  static_assert(sizeof(GemmTile) == 12, "three dwords");
+  const uint32_t* w = reinterpret_cast<const uint32_t*>(tiles) + 3 * (size_t)t;
+  const uint32_t w0 = w[0], w1 = w[1], w2 = w[2];
+  GemmTile r;
+  r.prob = (int32_t)w0;
+  r.r0 = (uint16_t)(w1 & 0xffffu);
+  r.c0 = (uint16_t)(w1 >> 16);
+  r.shape = (uint8_t)(w2 & 0xffu);
+  r.flags = (uint8_t)((w2 >> 8) & 0xffu);
+  r.pad_ = 0;
+  return r;
+}
+
 // One-time per-process kernel attribute setup (large dynamic LDS).  Returns a hipError_t.
 hipError_t gemm_setup();
 // Blocks of a persistent coarse GEMM launch = compute units of the device gemm_setup ran on (0 before it).
@@ -26,14 +42,15 @@ hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, 
 // allocation).  kGemmPersistent: one block per compute unit works through the table with stride gridDim (for launches
 // whose tiles run K loops of nearly the same length, which the planner balances statically; with a wide spread of K
 // the hardware's dynamic block dispatch does better).
-// kGemmTile64 (coarse = 0): every 128 x 128 entry of the table runs as four blocks of 64 x 64.
+// kGemmQuarters (coarse = 0): every entry of the table runs as four blocks, one per quarter of it.
 // l_kmajor: every problem of the launch stores its L operand K-major (element (i, k) at L[k * ldl + i]).
 // planes: 1 = plain bf16; 2 or 3 = every matrix is a sum of that many bf16 planes (GemmProblem::*_plane strides).
-constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmTile64 = 4;
+constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmQuarters = 4;
 hipError_t launch_gemm_bf16(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
                             float beta_acc, float beta_e, int alpha_idx, float diag_add, int l_kmajor, int planes,
                             hipStream_t s);
-hipError_t launch_gemm_f32(const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
+hipError_t gemm_f32_setup();
+hipError_t launch_gemm_f32(int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
                            float beta_acc, float beta_e, int alpha_idx, hipStream_t s);
 
 // a8: W <- W - lr*(scale*O + wd*W); also leaves per-tile sums of O^2 in the partials.

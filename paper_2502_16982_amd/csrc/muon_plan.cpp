@@ -202,19 +202,23 @@ size_t deal_tiles(const std::vector<int>& order, const std::vector<std::vector<G
 bool few_coarse_sym(size_t tiles, int64_t longest_k) { return tiles < 112 || (tiles < 256 && longest_k <= 2048); }
 bool few_coarse_apply(size_t tiles) { return tiles <= 128; }
 
-// Whether a fine bf16 launch runs each 128 x 128 entry as four 64 x 64 blocks, which are quicker through one tile (0.35
+// Whether a fine launch runs each entry as four blocks, one per quarter.  bf16: 64 x 64 blocks of a 128 x 128 entry, which are quicker through one tile (0.35
 // against 0.6 us per 64 of K) but need more of the compute unit for the same work: while the launch holds less work
 // than about 176 tiles of its longest K.  Measured, us per launch, 128 / 64: Gram product of 1024^2 (36 tiles) 16.2 / 10.4,
 // four of 1024 x 4096 (144) 42 / 39, four of 2048 x 1408 (264) 31 / 34; apply product of 1024^2 (64) 14.6 / 9.9, of
 // 32 of 256 x 384 (192) 8.4 / 8.0, of four of 1024^2 (256) 16.3 / 18.2.
-bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k) {
+// fp32 launches run their 64 x 64 entries as four blocks of 32 x 32 up to about 320 entries.  Measured, whole / quarters:
+// Gram product of 1024^2 (136) 26 / 21.5, of 64 of 128 x 256 (192) 11.9 / 11.3, of 16 of 512^2 (576) 34.1 / 34.4; apply product
+// of 1024^2 (256) 27.7 / 27.6, of 64 of 128 x 256 (512) 13.6 / 17.7.
+constexpr int kFewFine = 176, kFewF32 = 320;
+bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int few) {
   int64_t longest = 0, total = 0;
   for (size_t i = 0; i < tiles.size(); ++i)
     if (!tiles[i].empty()) {
       longest = std::max(longest, k[i]);
       total += k[i] * (int64_t)tiles[i].size();
     }
-  return total <= 176 * longest;
+  return total <= few * longest;
 }
 
 void plan_matrices(const muon_param* p, int n, int ns_dtype, std::vector<MatPlan>& out, size_t& total_partials) {
@@ -604,10 +608,11 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         }
         TileSet& ts = level ? g.coarse : g.fine;
         ts.strips = strips;
-        if (level == 0 && mc) {
-          ts.quarter_sym = runs_in_quarters(sym, w_n);
-          ts.quarter_poly = runs_in_quarters(sym, w_m);
-          ts.quarter_apply = runs_in_quarters(app, w_m);
+        if (level == 0) {
+          const int few = mc ? kFewFine : kFewF32;
+          ts.quarter_sym = runs_in_quarters(sym, w_n, few);
+          ts.quarter_poly = runs_in_quarters(sym, w_m, few);
+          ts.quarter_apply = runs_in_quarters(app, w_m, few);
         }
         ts.persistent_n = steady_n;
         ts.persistent_m = steady_m;

@@ -34,7 +34,7 @@ struct TileSet {
   // the K loops of the launch's tiles are of nearly the same length (Gram product: n_pad; the other two: m_pad), so
   // the launch runs persistent blocks that take the planner's static assignment of tiles
   bool persistent_n = false, persistent_m = false;
-  bool quarter_sym = false, quarter_poly = false, quarter_apply = false;   // fine bf16 launches that run as 64 x 64 blocks
+  bool quarter_sym = false, quarter_poly = false, quarter_apply = false;   // fine launches that run as one block per quarter of an entry
 };
 
 // Launch group: all matrices of one chunk.  Each product is one launch per level: the coarse launch (matrix-core

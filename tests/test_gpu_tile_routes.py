@@ -63,3 +63,15 @@ def test_64_wide_tiles_at_their_edges(dev, ns, tol):
     wl = workloads.custom("edges64_" + ns, shapes, ns_dtype=ns, seed_base=320)
     assert coarse_tiles(shapes, ns) == [0, 0]
     assert_records(U.run_and_compare(wl, dev, steps=2, want_rms=True), tol)
+
+
+@pytest.mark.parametrize("copies", [1, 40])
+def test_f32_products_whole_and_in_quarters(dev, copies):
+    """fp32 path: K of two 32-wide slabs (two of a block's four waves have none) up to several rounds of the ring, ragged
+    edges, both orientations; alone every launch runs in quarters, in 40 copies the longer ones run whole.  Bar: a tenth
+    of the path's (a dot product of K <= 1024 fp32 terms is good to about 1e-6; five iterations amplify that by < 5)."""
+    shapes = [(64, 64), (1, 65), (63, 130), (130, 63), (100, 320), (320, 257), (384, 1000)]
+    wl = workloads.custom("f32_routes", shapes * copies, w_dtype=torch.float32, g_dtype=torch.float32, ns_dtype="f32",
+                          w_std=1.0, g_std=1.0, seed_base=330)
+    n = len(wl.shapes)
+    assert_records(U.run_and_compare(wl, dev, check=list(range(n - len(shapes), n)), steps=2, want_rms=True), 0.1 * U.TOL_F32_FRO)
