@@ -21,7 +21,6 @@ __device__ __forceinline__ u16 f32_to_bf16(float f) {
   return (u16)(u >> 16);
 }
 
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
@@ -41,95 +40,64 @@ __device__ __forceinline__ float block_sum_256(float v, float* red /* >= 4 float
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-template <typename T>
-__device__ __forceinline__ void load16(const T* p, float* out);
-template <>
-__device__ __forceinline__ void load16<float>(const float* p, float* out) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float4 v = reinterpret_cast<const float4*>(p)[i];
-    out[4 * i + 0] = v.x; out[4 * i + 1] = v.y; out[4 * i + 2] = v.z; out[4 * i + 3] = v.w;
-  }
-}
-template <>
-__device__ __forceinline__ void load16<u16>(const u16* p, float* out) {
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const uint4 v = reinterpret_cast<const uint4*>(p)[i];
-    const unsigned w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      out[8 * i + 2 * j] = __uint_as_float(w[j] << 16);
-      out[8 * i + 2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
-    }
-  }
-}
+// Accesses go through the global address space (pointers that come out of a table would otherwise be accessed as
+// `flat`).  Those to the caller's matrices are wide at any alignment of the element: rows start anywhere, and global
+// memory takes such accesses (the vector types only tell the compiler), so odd widths and odd buffers keep the wide path.
+#define MUON_GLOBAL __attribute__((address_space(1)))
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int u32x4_any __attribute__((ext_vector_type(4), aligned(2)));
+typedef unsigned int u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
 
-template <typename T>
-__device__ __forceinline__ void store16(T* p, const float* in);
-template <>
-__device__ __forceinline__ void store16<float>(float* p, const float* in) {
+// 4 consecutive elements
+__device__ __forceinline__ void load4(const float* p, float* out) {
+  const f32x4_any v = *(const MUON_GLOBAL f32x4_any*)p;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-    reinterpret_cast<float4*>(p)[i] = make_float4(in[4 * i], in[4 * i + 1], in[4 * i + 2], in[4 * i + 3]);
+  for (int i = 0; i < 4; ++i) out[i] = v[i];
 }
-template <>
-__device__ __forceinline__ void store16<u16>(u16* p, const float* in) {
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-    reinterpret_cast<uint4*>(p)[i] = make_uint4(pack2(in[8 * i], in[8 * i + 1]), pack2(in[8 * i + 2], in[8 * i + 3]),
-                                                pack2(in[8 * i + 4], in[8 * i + 5]), pack2(in[8 * i + 6], in[8 * i + 7]));
+__device__ __forceinline__ void load4(const u16* p, float* out) {
+  const u32x2_any v = *(const MUON_GLOBAL u32x2_any*)p;
+  out[0] = __uint_as_float(v.x << 16);
+  out[1] = __uint_as_float(v.x & 0xffff0000u);
+  out[2] = __uint_as_float(v.y << 16);
+  out[3] = __uint_as_float(v.y & 0xffff0000u);
+}
+__device__ __forceinline__ void store4(float* p, const float* in) { *(MUON_GLOBAL f32x4_any*)p = f32x4_any{in[0], in[1], in[2], in[3]}; }
+__device__ __forceinline__ void store4(u16* p, const float* in) {
+  *(MUON_GLOBAL u32x2_any*)p = u32x2_any{pack2(in[0], in[1]), pack2(in[2], in[3])};
 }
 
 template <typename T>
 __device__ __forceinline__ float load1(const T* p);
 template <>
-__device__ __forceinline__ float load1<float>(const float* p) { return *p; }
+__device__ __forceinline__ float load1<float>(const float* p) { return *(const MUON_GLOBAL float*)p; }
 template <>
-__device__ __forceinline__ float load1<u16>(const u16* p) { return bf16_to_f32(*p); }
+__device__ __forceinline__ float load1<u16>(const u16* p) { return bf16_to_f32(*(const MUON_GLOBAL u16*)p); }
 template <typename T>
 __device__ __forceinline__ void store1(T* p, float v);
 template <>
-__device__ __forceinline__ void store1<float>(float* p, float v) { *p = v; }
+__device__ __forceinline__ void store1<float>(float* p, float v) { *(MUON_GLOBAL float*)p = v; }
 template <>
-__device__ __forceinline__ void store1<u16>(u16* p, float v) { *p = f32_to_bf16(v); }
-
-__device__ __forceinline__ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+__device__ __forceinline__ void store1<u16>(u16* p, float v) { *(MUON_GLOBAL u16*)p = f32_to_bf16(v); }
 
 // Newton-Schulz storage with PL planes (PL = 1: one array of XT; PL > 1, XT = bf16: the value is the sum of PL bf16
 // arrays `plane` elements apart, array q holding what the arrays before it left of the fp32 value after rounding).
 template <typename XT, int PL>
-__device__ __forceinline__ void ns_store16(XT* p, size_t plane, const float* in) {
+__device__ __forceinline__ void ns_store4(XT* p, size_t plane, const float* in) {
   if constexpr (PL == 1) {
-    store16<XT>(p, in);
+    store4(p, in);
   } else {
-    float rest[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) rest[i] = in[i];
+    float rest[4] = {in[0], in[1], in[2], in[3]};
 #pragma unroll
     for (int q = 0; q < PL; ++q) {
-      store16<XT>(p + q * plane, rest);
+      store4(p + q * plane, rest);
       if (q + 1 < PL) {
 #pragma unroll
-        for (int i = 0; i < 16; i += 2) {
+        for (int i = 0; i < 4; i += 2) {
           const unsigned w = pack2(rest[i], rest[i + 1]);
           rest[i] -= __uint_as_float(w << 16);              // exact: the rounding error of an fp32 value is an fp32 value
           rest[i + 1] -= __uint_as_float(w & 0xffff0000u);
         }
       }
-    }
-  }
-}
-template <typename XT, int PL>
-__device__ __forceinline__ void ns_load16(const XT* p, size_t plane, float* out) {
-  load16<XT>(p + (PL - 1) * plane, out);
-  if constexpr (PL > 1) {
-#pragma unroll
-    for (int q = PL - 2; q >= 0; --q) {        // smallest plane first
-      float v[16];
-      load16<XT>(p + q * plane, v);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) out[i] += v[i];
     }
   }
 }
@@ -144,50 +112,63 @@ __device__ __forceinline__ float ns_load1(const XT* p, size_t plane) {
 }
 
 // ------------------------------------------------------------------------------------------------------
-// a1 + a2 (first stage) + a3.  Thread t of a block owns row t/4 and 16 consecutive columns of a 64x64 tile
-// in U's orientation.  GT: gradient element type; XT: Newton-Schulz element type.
+// a1 + a2 (first stage) + a3.  Thread t of a block owns columns 4 (t % 16) .. + 3 of rows t / 16 + 16 j, j = 0..3, of a
+// 64x64 tile in U's orientation: the 16 lanes that share a row cover whole lines with every access.  GT: gradient element
+// type; XT: Newton-Schulz element type.
 // Writes: M (guarded), the tile of U into the buffer of the same orientation, the transposed tile (through
 // LDS) into the buffer of the other orientation, both zero-filled outside A x B, and one partial sum of U^2.
+// Bound by memory on long lists (4 of 4096^2: 152 -> 136 us, 5.9 TB/s of its 12 B per element, when the lanes of a row took
+// 16 consecutive elements each), by the latency of one chain of loads on short ones.  Rows of any width take the wide path:
+// 50 of 2047 x 1401 3074 -> 404 us, six matrices of odd widths 106 -> 32 us, against scalar accesses whose loads waited
+// for the stores before them.  Non-temporal hints: -4 % on aligned rows, +40 % on odd ones, not used.
 // ------------------------------------------------------------------------------------------------------
 template <typename GT, typename XT, int PL>
 __device__ __forceinline__ void momentum_tile(const MatDesc& d, const MatPtrs& pt, int tr, int tc, float mu, int nesterov,
                                               bool both, float (*lds)[kEwTile + 1], float* red) {
   const int tid = threadIdx.x;
-  const int r = tr * kEwTile + (tid >> 2);
-  const int c0 = tc * kEwTile + (tid & 3) * 16;
+  const int lr = tid >> 4, lc = (tid & 15) * 4;
+  const int r0 = tr * kEwTile + lr, c0 = tc * kEwTile + lc;
   const int A = d.rows, B = d.cols;
   const GT* g = static_cast<const GT*>(pt.g);
   float* m = pt.m;
 
-  float u[16];
+  float u[4][4], mv[4][4], gv[4][4];
   float ss = 0.f;
-  const bool row_ok = r < A;
-  const size_t base = (size_t)r * (size_t)B + (size_t)c0;
-  const bool fast = row_ok && (c0 + 16 <= B) && ((B & 7) == 0) && aligned16(m) && aligned16(g);
-  if (fast) {
-    float mv[16], gv[16];
-    load16<float>(m + base, mv);
-    load16<GT>(g + base, gv);
+  const bool wide = c0 + 4 <= B;
+  // all loads are issued before the first store
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const float mn = fmaf(mu, mv[i], gv[i]);
-      mv[i] = mn;
-      u[i] = nesterov ? fmaf(mu, mn, gv[i]) : mn;
-      ss = fmaf(u[i], u[i], ss);
-    }
-    store16<float>(m + base, mv);
-  } else {
+  for (int j = 0; j < 4; ++j) {
+    const int r = r0 + 16 * j;
+    const size_t base = (size_t)r * (size_t)B + (size_t)c0;
+    if (wide && r < A) {
+      load4(m + base, mv[j]);
+      load4(g + base, gv[j]);
+    } else {                                     // the right edge, or beyond the matrix
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      float ui = 0.f;
-      if (row_ok && c0 + i < B) {
-        const float gi = load1<GT>(g + base + i);
-        const float mn = fmaf(mu, m[base + i], gi);
-        m[base + i] = mn;
-        ui = nesterov ? fmaf(mu, mn, gi) : mn;
+      for (int i = 0; i < 4; ++i) {
+        const bool in = r < A && c0 + i < B;
+        mv[j][i] = in ? load1<float>(m + base + i) : 0.f;
+        gv[j][i] = in ? load1<GT>(g + base + i) : 0.f;
       }
-      u[i] = ui;
-      ss = fmaf(ui, ui, ss);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int r = r0 + 16 * j;
+    const size_t base = (size_t)r * (size_t)B + (size_t)c0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float mn = fmaf(mu, mv[j][i], gv[j][i]);
+      mv[j][i] = mn;
+      u[j][i] = nesterov ? fmaf(mu, mn, gv[j][i]) : mn;
+      ss = fmaf(u[j][i], u[j][i], ss);
+    }
+    if (wide && r < A) {
+      store4(m + base, mv[j]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (r < A && c0 + i < B) store1<float>(m + base + i, mv[j][i]);
     }
   }
 
@@ -199,24 +180,45 @@ __device__ __forceinline__ void momentum_tile(const MatDesc& d, const MatPtrs& p
   const int pitch_flip = d.transposed ? d.np : d.mp;
 
   const bool write_same = both || !d.transposed, write_flip = both || d.transposed;
-  if (write_same) ns_store16<XT, PL>(same + (size_t)r * pitch_same + c0, (size_t)d.x_plane, u);
+  if (write_same) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) ns_store4<XT, PL>(same + (size_t)(r0 + 16 * j) * pitch_same + c0, (size_t)d.x_plane, u[j]);
+  }
 
   // the transposed tile goes through LDS; skipped (block-uniformly) where only the untransposed layout is wanted
-  const int lr_ = tid >> 2, lc0 = (tid & 3) * 16;
   if (write_flip) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) lds[lc0 + i][lr_] = u[i];
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) lds[lc + i][lr + 16 * j] = u[j][i];
   }
   const float total = block_sum_256(ss, red);   // contains the barrier that publishes the LDS tile
   if (write_flip) {
-    float t[16];
-    const int fc = tid >> 2, fr0 = (tid & 3) * 16;   // row of U^T (= column of U), 16 consecutive columns of U^T
 #pragma unroll
-    for (int i = 0; i < 16; ++i) t[i] = lds[fc][fr0 + i];
-    ns_store16<XT, PL>(flip + (size_t)(tc * kEwTile + fc) * pitch_flip + tr * kEwTile + fr0, (size_t)d.x_plane, t);
+    for (int j = 0; j < 4; ++j) {
+      const int fc = lr + 16 * j;                // row of U^T (= column of U), 4 consecutive columns of U^T
+      float t[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t[i] = lds[fc][lc + i];
+      ns_store4<XT, PL>(flip + (size_t)(tc * kEwTile + fc) * pitch_flip + tr * kEwTile + lc, (size_t)d.x_plane, t);
+    }
   }
 
   if (tid == 0) d.partials[tr * d.ew_tiles_c + tc] = total;
+}
+
+// A block's work item through whole-dword loads, so that they are scalar loads (uniform address).
+__device__ __forceinline__ EwTile load_item(const EwTile* __restrict__ tiles) {
+  static_assert(sizeof(EwTile) == 12, "three dwords");
+  const uint32_t* w = reinterpret_cast<const uint32_t*>(tiles) + 3 * (size_t)blockIdx.x;
+  const uint32_t w0 = w[0], w1 = w[1], w2 = w[2];
+  EwTile t;
+  t.mat = (int32_t)w0;
+  t.tr = (int16_t)(w1 & 0xffffu);
+  t.tc = (int16_t)(w1 >> 16);
+  t.count = (int16_t)(w2 & 0xffffu);
+  t.pad_ = 0;
+  return t;
 }
 
 template <typename XT, int PL>
@@ -226,8 +228,8 @@ __global__ __launch_bounds__(256) void momentum_norm_cast_kernel(const MatDesc* 
                                                                   int nesterov, int both) {
   __shared__ float lds[kEwTile][kEwTile + 1];
   __shared__ float red[4];
-  const EwTile t = tiles[blockIdx.x];
-  const MatDesc d = mats[t.mat];
+  const EwTile t = load_item(tiles);
+  const MatDesc& d = mats[t.mat];       // read in place (uniform address: scalar loads); see o_source
   const MatPtrs pt = ptrs[t.mat];
   for (int k = 0; k < t.count; ++k) {
     if (k) __syncthreads();     // the LDS tile and the reduction scratch are reused
@@ -275,51 +277,40 @@ __device__ __forceinline__ const void* o_source(const MatDesc& d, int o_sel) {
   return (o_sel & 2) ? d.Xt[0] : d.X;
 }
 
-// 8 consecutive elements: one 16-byte access for bf16, two for fp32
-template <typename T>
-__device__ __forceinline__ void load8(const T* p, float* out);
-template <>
-__device__ __forceinline__ void load8<float>(const float* p, float* out) {
+// 8 consecutive elements at element alignment: one 16-byte access for bf16, two for fp32.  Streaming hint on bf16: every
+// element of the update is touched once; without it the L2 refetched a third of the lines (measured: 1.20 GB fetched for
+// 0.81 GB of W and O on the 4096-wide block, 0.89 GB with the hint).
+__device__ __forceinline__ void load8(const float* p, float* out) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const float4 v = reinterpret_cast<const float4*>(p)[i];
+    const f32x4_any v = ((const MUON_GLOBAL f32x4_any*)p)[i];
     out[4 * i + 0] = v.x; out[4 * i + 1] = v.y; out[4 * i + 2] = v.z; out[4 * i + 3] = v.w;
   }
 }
-template <>
-__device__ __forceinline__ void load8<u16>(const u16* p, float* out) {
-  // streaming hint: every element of the update is touched once; without it the L2 refetched a third of the lines
-  // (measured: 1.20 GB fetched for 0.81 GB of W and O on the 4096-wide block, 0.89 GB with the hint)
-  const u32x4_t vv = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
-  const uint4 v = make_uint4(vv.x, vv.y, vv.z, vv.w);
-  const unsigned w[4] = {v.x, v.y, v.z, v.w};
+__device__ __forceinline__ void load8(const u16* p, float* out) {
+  const u32x4_any v = __builtin_nontemporal_load((const MUON_GLOBAL u32x4_any*)p);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    out[2 * j] = __uint_as_float(w[j] << 16);
-    out[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u);
+    out[2 * j] = __uint_as_float(v[j] << 16);
+    out[2 * j + 1] = __uint_as_float(v[j] & 0xffff0000u);
   }
 }
-template <typename T>
-__device__ __forceinline__ void store8(T* p, const float* in);
-template <>
-__device__ __forceinline__ void store8<float>(float* p, const float* in) {
+__device__ __forceinline__ void store8(float* p, const float* in) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-    reinterpret_cast<float4*>(p)[i] = make_float4(in[4 * i], in[4 * i + 1], in[4 * i + 2], in[4 * i + 3]);
+  for (int i = 0; i < 2; ++i) ((MUON_GLOBAL f32x4_any*)p)[i] = f32x4_any{in[4 * i], in[4 * i + 1], in[4 * i + 2], in[4 * i + 3]};
 }
-template <>
-__device__ __forceinline__ void store8<u16>(u16* p, const float* in) {
-  const u32x4_t vv = {pack2(in[0], in[1]), pack2(in[2], in[3]), pack2(in[4], in[5]), pack2(in[6], in[7])};
-  __builtin_nontemporal_store(vv, reinterpret_cast<u32x4_t*>(p));
+__device__ __forceinline__ void store8(u16* p, const float* in) {
+  const u32x4_any v = {pack2(in[0], in[1]), pack2(in[2], in[3]), pack2(in[4], in[5]), pack2(in[6], in[7])};
+  __builtin_nontemporal_store(v, (MUON_GLOBAL u32x4_any*)p);
 }
 template <typename XT, int PL>
 __device__ __forceinline__ void ns_load8(const XT* p, size_t plane, float* out) {
-  load8<XT>(p + (PL - 1) * plane, out);
+  load8(p + (PL - 1) * plane, out);
   if constexpr (PL > 1) {
 #pragma unroll
     for (int q = PL - 2; q >= 0; --q) {        // smallest plane first
       float v[8];
-      load8<XT>(p + q * plane, v);
+      load8(p + q * plane, v);
 #pragma unroll
       for (int i = 0; i < 8; ++i) out[i] += v[i];
     }
@@ -341,15 +332,15 @@ __device__ __forceinline__ void apply_tile(const MatDesc& d, const MatPtrs& pt, 
   const size_t plane = (size_t)d.x_plane;
   const int r0 = tr * kEwTile + (tid >> 3), r1 = r0 + 32;
   float ss = 0.f;
-  const bool wide = (c0 + 8 <= B) && ((B & 7) == 0) && (!UPDATE || aligned16(w));
+  const bool wide = c0 + 8 <= B;
   if (wide && r1 < A) {
     // both rows at once: all loads are issued before the first store
     float ov[2][8], wv[2][8];
     ns_load8<XT, PL>(o + (size_t)r0 * pitch + c0, plane, ov[0]);
     ns_load8<XT, PL>(o + (size_t)r1 * pitch + c0, plane, ov[1]);
     if (UPDATE) {
-      load8<WT>(w + (size_t)r0 * (size_t)B + c0, wv[0]);
-      load8<WT>(w + (size_t)r1 * (size_t)B + c0, wv[1]);
+      load8(w + (size_t)r0 * (size_t)B + c0, wv[0]);
+      load8(w + (size_t)r1 * (size_t)B + c0, wv[1]);
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -362,38 +353,30 @@ __device__ __forceinline__ void apply_tile(const MatDesc& d, const MatPtrs& pt, 
         }
       }
     if (UPDATE) {
-      store8<WT>(w + (size_t)r0 * (size_t)B + c0, wv[0]);
-      store8<WT>(w + (size_t)r1 * (size_t)B + c0, wv[1]);
+      store8(w + (size_t)r0 * (size_t)B + c0, wv[0]);
+      store8(w + (size_t)r1 * (size_t)B + c0, wv[1]);
     }
-  } else {
+  } else if (c0 < B) {
+    // the matrix's right and bottom edges.  O is padded to whole tiles with zeros, so it is read wide and adds nothing
+    // beyond the matrix; the elements of W are all loaded before the first one is stored.
+    float ov[2][8], wv[2][8];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int r = u ? r1 : r0;
-      if (r >= A || c0 >= B) continue;
-      const size_t base = (size_t)r * (size_t)B + (size_t)c0;
-      const XT* op = o + (size_t)r * pitch + c0;
-      if (wide) {
-        float ov[8], wv[8];
-        ns_load8<XT, PL>(op, plane, ov);
-        if (UPDATE) load8<WT>(w + base, wv);
+      ns_load8<XT, PL>(o + (size_t)r * pitch + c0, plane, ov[u]);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          ss = fmaf(ov[i], ov[i], ss);
-          if (UPDATE) {
-            const float t = fmaf(wd, wv[i], scale * ov[i]);
-            wv[i] = fmaf(-lr, t, wv[i]);
-          }
-        }
-        if (UPDATE) store8<WT>(w + base, wv);
-      } else {
-        for (int i = 0; i < 8 && c0 + i < B; ++i) {
-          const float ov = ns_load1<XT, PL>(op + i, plane);
-          ss = fmaf(ov, ov, ss);
-          if (UPDATE) {
-            const float wv = load1<WT>(w + base + i);
-            const float t = fmaf(wd, wv, scale * ov);
-            store1<WT>(w + base + i, fmaf(-lr, t, wv));
-          }
+      for (int i = 0; i < 8; ++i) wv[u][i] = UPDATE && r < A && c0 + i < B ? load1<WT>(w + (size_t)r * (size_t)B + c0 + i) : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = u ? r1 : r0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const bool in = r < A && c0 + i < B;
+        ss = in ? fmaf(ov[u][i], ov[u][i], ss) : ss;
+        if (UPDATE && in) {
+          const float t = fmaf(wd, wv[u][i], scale * ov[u][i]);
+          store1<WT>(w + (size_t)r * (size_t)B + c0 + i, fmaf(-lr, t, wv[u][i]));
         }
       }
     }
@@ -408,8 +391,8 @@ __global__ __launch_bounds__(256) void apply_update_kernel(const MatDesc* __rest
                                                             float rms_scale, int scale_mode, float sqrt_hidden, int o_sel,
                                                             int use_s) {
   __shared__ float red[4];
-  const EwTile t = tiles[blockIdx.x];
-  const MatDesc& d = mats[t.mat];     // read in place (uniform address: scalar loads); see o_source
+  const EwTile t = load_item(tiles);
+  const MatDesc& d = mats[t.mat];       // read in place (uniform address: scalar loads); see o_source
   const MatPtrs pt = ptrs[t.mat];
   // factor that multiplies the stored O: the three variants of section 3.1 (Eq. 5-7)
   float scale;
@@ -433,8 +416,8 @@ template <typename XT, int PL>
 __global__ __launch_bounds__(256) void update_sumsq_kernel(const MatDesc* __restrict__ mats, const EwTile* __restrict__ tiles,
                                                             int o_sel) {
   __shared__ float red[4];
-  const EwTile t = tiles[blockIdx.x];
-  const MatDesc& d = mats[t.mat];     // read in place (uniform address: scalar loads); see o_source
+  const EwTile t = load_item(tiles);
+  const MatDesc& d = mats[t.mat];       // read in place (uniform address: scalar loads); see o_source
   const MatPtrs none{nullptr, nullptr, nullptr};
   for (int k = 0; k < t.count; ++k) {
     if (k) __syncthreads();

@@ -193,6 +193,12 @@ size_t deal_tiles(const std::vector<int>& order, const std::vector<std::vector<G
   return o;
 }
 
+// Tiles per work item of the elementwise passes: one after the other in a block, each pays the latency of a chain of
+// loads, so a list is given at least 2048 blocks (eight per compute unit, all resident) before they take more.  Measured, us
+// with runs of 4 / by this rule: momentum pass of four of 512^2 10.8 / 7.2, of 1000 x 3001 37 / 14 (with the wide accesses at
+// odd widths); long lists are within 3 % of runs of one, whose table would be four times as long.
+int ew_run(size_t tiles) { return (int)std::min<size_t>((size_t)kEwRun, std::max<size_t>(1, tiles / 2048)); }
+
 // Whether a product goes to the fine launch altogether: its coarse tiles (256 x 256, one block per compute unit) are so
 // few that they leave much of the chip idle.  Measured, us per launch, coarse / fine (128 x 128, or their quarters):
 //   Gram and polynomial: 2048^2 (36 tiles) 45 / 24, 3584^2 (105) 69 / 56, 4096^2 (136) 83 / 102; with a short K the line
@@ -424,14 +430,17 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
     ch.n_ew_tiles = 0;
     {
       EwTile* t = reinterpret_cast<EwTile*>(img.data() + cursor);
+      size_t all = 0;
+      for (int i = ch.first; i < ch.first + ch.count; ++i) all += (size_t)plan.mats[i].ew_tr * plan.mats[i].ew_tc;
+      const int run = ew_run(all);
       for (int i = ch.first; i < ch.first + ch.count; ++i) {
         const MatPlan& q = plan.mats[i];
         for (int r = 0; r < q.ew_tr; ++r)
-          for (int c = 0; c < q.ew_tc; c += kEwRun) {
+          for (int c = 0; c < q.ew_tc; c += run) {
             t[ch.n_ew_tiles].mat = i;
             t[ch.n_ew_tiles].tr = (int16_t)r;
             t[ch.n_ew_tiles].tc = (int16_t)c;
-            t[ch.n_ew_tiles].count = (int16_t)std::min(kEwRun, q.ew_tc - c);
+            t[ch.n_ew_tiles].count = (int16_t)std::min(run, q.ew_tc - c);
             t[ch.n_ew_tiles].pad_ = 0;
             ch.n_ew_tiles++;
           }

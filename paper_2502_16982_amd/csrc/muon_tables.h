@@ -42,7 +42,7 @@ struct MatPtrs {
 };
 
 // One work item of an elementwise pass: `count` consecutive 64x64 tiles of one tile row.
-constexpr int kEwRun = 4;          // tiles per work item (amortises the table look-ups of a block)
+constexpr int kEwRun = 4;          // most tiles per work item (amortises the table look-ups of a block)
 struct EwTile {
   int32_t mat;        // absolute matrix index (into MatDesc / MatPtrs)
   int16_t tr, tc;     // tile row / first tile column in U's (= W's) orientation

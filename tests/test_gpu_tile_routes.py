@@ -75,3 +75,34 @@ def test_f32_products_whole_and_in_quarters(dev, copies):
                           w_std=1.0, g_std=1.0, seed_base=330)
     n = len(wl.shapes)
     assert_records(U.run_and_compare(wl, dev, check=list(range(n - len(shapes), n)), steps=2, want_rms=True), 0.1 * U.TOL_F32_FRO)
+
+
+@pytest.mark.parametrize("dtypes", [(torch.bfloat16, torch.bfloat16), (torch.float32, torch.bfloat16), (torch.bfloat16, torch.float32)])
+def test_elementwise_passes_at_odd_widths_and_addresses(dev, dtypes):
+    """Widths around the 4- and 8-element pieces and the 64-wide tile, buffers that start one element off every wider
+    alignment, in guarded memory: M and W agree with the oracle and nothing outside the matrices changes."""
+    shapes = [(1, 1), (3, 5), (65, 63), (64, 65), (130, 7), (33, 257), (100, 1001)]
+    wl = workloads.custom("odd", shapes, w_dtype=dtypes[0], g_dtype=dtypes[1], seed_base=340)
+    hp, d = U.hp_from(wl.hyper)
+    tensors, flats = [], []
+    for i, (a, b) in enumerate(shapes):
+        views = []
+        for t in workloads.make_matrix(wl, i, dev):
+            flat = torch.full((a * b + 66,), 7.0, dtype=t.dtype, device=dev)
+            flat[33:33 + a * b] = t.reshape(-1)
+            flats.append((flat, a * b))
+            views.append(flat[33:33 + a * b].view(a, b))
+        tensors.append(tuple(views))
+    host = [tuple(U.to64(t) for t in trip) for trip in tensors]
+    st = binding.MuonStepper(tensors)
+    st.step(hp)
+    torch.cuda.synchronize()
+    for i, (w0, g0, m0) in enumerate(host):
+        _, m_ref, _ = U.oracle_step(w0, g0, m0, d)
+        assert U.momentum_error(U.to64(tensors[i][2]), m_ref, m0, g0, d["momentum"]) <= U.TOL_ELEM
+        rec = U.check_weight_update(tensors[i][0], w0, U.to64(st.read_update(i)), d)
+        assert rec.get("max_rel", 0.0) <= U.TOL_ELEM and rec.get("max_excess", 0.0) <= 1.0, (shapes[i], rec)
+        assert torch.equal(tensors[i][1].double().cpu(), torch.from_numpy(g0))
+    for flat, n in flats:
+        assert (flat[:33] == 7).all() and (flat[33 + n:] == 7).all()
+    st.close()
