@@ -74,7 +74,7 @@ hipError_t launch_read_update(const MatDesc* mats, int mat, int o_sel, int use_s
                               int dst_dtype, hipStream_t s);
 
 // AdamW (non-matrix parameters): up to kAdamwSlots tensors per launch, passed by value in the kernel arguments.
-constexpr int kAdamwSlots = 24;
+constexpr int kAdamwSlots = 64;   // 3.3 KB of kernel arguments
 struct AdamwBatch {
   void* p[kAdamwSlots];
   const void* g[kAdamwSlots];

@@ -100,3 +100,36 @@ def test_adamw_degenerate_and_errors(dev):
     arr[0].numel = 0
     assert L.muon_adamw_step(arr, 1, C.byref(ok), None) == -1
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("sizes", [(1, 5, 1023, 1024, 1025, 4099), (50_000_003,), tuple(3 + 401 * i for i in range(130))])
+def test_adamw_odd_addresses_and_streaming_launch(dev, sizes):
+    """Remainders of the 4-element piece and the 1024-element span in buffers that start one element off every wider
+    alignment, and a tensor large enough (more than 1 GiB of traffic) for the launch with the non-temporal hint, and
+    more tensors than two launches hold; the elements around the tensors stay as they are."""
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(7)
+    flats, tensors = [], []
+    for n in sizes:
+        views = []
+        for dt, std in ((torch.bfloat16, 0.5), (torch.bfloat16, 1e-2), (torch.float32, 1e-3), (torch.float32, 1e-3)):
+            flat = torch.empty(n + 66, device=dev).normal_(0, std, generator=gen)
+            flat = (flat.square() if len(views) == 3 else flat).to(dt)
+            flat[:33], flat[33 + n:] = 3.0, 3.0
+            flats.append((flat, n))
+            views.append(flat[33:33 + n])
+        tensors.append(tuple(views))
+    before = [tuple(t.double() for t in quad) for quad in tensors]
+    hp = dict(lr=3e-3, weight_decay=0.1, beta1=0.9, beta2=0.95, eps=1e-8)
+    binding.muon_adamw_step(tensors, step=5, stream_ptr=torch.cuda.current_stream(dev).cuda_stream, **hp)
+    torch.cuda.synchronize()
+    for (p, g, m, v), (p0, g0, m0, v0) in zip(tensors, before):
+        mr, vr = 0.9 * m0 + 0.1 * g0, 0.95 * v0 + 0.05 * g0 * g0
+        upd = (mr / (1 - 0.9 ** 5)) / ((vr / (1 - 0.95 ** 5)).sqrt() + hp["eps"])
+        pr = p0 - hp["lr"] * (upd + hp["weight_decay"] * p0)
+        assert ((m.double() - mr).abs() <= U.TOL_ELEM * (0.9 * m0.abs() + 0.1 * g0.abs())).all()
+        assert ((v.double() - vr).abs() <= U.TOL_ELEM * vr).all()
+        # one bf16 rounding of an fp32 value whose terms are good to a few 2^-24
+        assert ((p.double() - pr).abs() <= 2.0 ** -8 * pr.abs() + 1e-6 * (p0.abs() + hp["lr"] * upd.abs())).all()
+    for flat, n in flats:
+        assert (flat[:33] == 3).all() and (flat[33 + n:] == 3).all()
