@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 from typing import Iterable, List, Optional, Sequence
 
 MUON_F32, MUON_BF16 = 0, 1
@@ -138,13 +139,19 @@ def muon_probe_mfma_rate(random_operands: bool = True, iters: int = 40000) -> di
     return {"tflops": tf.value, "clock_mhz": mhz.value}
 
 
+_DTYPE_CODES: dict = {}
+
+
 def dtype_code(torch_dtype) -> int:
-    import torch
-    if torch_dtype == torch.float32:
-        return MUON_F32
-    if torch_dtype == torch.bfloat16:
-        return MUON_BF16
-    raise MuonError(-2, f"dtype {torch_dtype}")
+    try:
+        return _DTYPE_CODES[torch_dtype]
+    except KeyError:
+        pass
+    import torch                         # at first use only: the host-only functions work without torch
+    _DTYPE_CODES.update({torch.float32: MUON_F32, torch.bfloat16: MUON_BF16})
+    if torch_dtype not in _DTYPE_CODES:
+        raise MuonError(-2, f"dtype {torch_dtype}")
+    return _DTYPE_CODES[torch_dtype]
 
 
 def default_hparams(**overrides) -> muon_hparams:
@@ -261,22 +268,28 @@ def muon_profile_read(ctx, reset: bool = False) -> dict:
     return {name: (float(ms[i]), int(cnt[i])) for i, name in enumerate(PROF_NAMES)}
 
 
+_ADAMW_RECORD = struct.Struct("@PPPPqii")      # the layout of muon_adamw_param
+assert _ADAMW_RECORD.size == C.sizeof(muon_adamw_param)
+
+
 def muon_adamw_step(tensors, *, lr: float, weight_decay: float, beta1: float = 0.9, beta2: float = 0.95,
                     eps: float = 1e-8, step: int = 1, stream_ptr: int = 0) -> None:
     """tensors: iterable of (p, g, m, v) torch tensors of one size each (any shape, contiguous)."""
     tensors = [tuple(t) for t in tensors]
     arr = (muon_adamw_param * max(len(tensors), 1))()
+    offset, size, pack = 0, _ADAMW_RECORD.size, _ADAMW_RECORD.pack_into
+    # one packed record per tensor: with a list of small tensors this loop, not the device, bounds the call (25 tensors:
+    # 45 us with an attribute assignment per field and an import per dtype, 34 us like this, 4 us of it on the device)
     for i, (p, g, m, v) in enumerate(tensors):
         if not (p.is_contiguous() and g.is_contiguous() and m.is_contiguous() and v.is_contiguous()):
             raise MuonError(-1, f"tensor {i}: buffers must be contiguous")
-        if not (p.numel() == g.numel() == m.numel() == v.numel()):
+        n = p.numel()
+        if not (n == g.numel() == m.numel() == v.numel()):
             raise MuonError(-1, f"tensor {i}: p, g, m, v must have one size")
-        if dtype_code(m.dtype) != MUON_F32 or dtype_code(v.dtype) != MUON_F32:
+        if dtype_code(m.dtype) or dtype_code(v.dtype):           # MUON_F32 is 0
             raise MuonError(-2, f"tensor {i}: moments must be fp32")
-        a = arr[i]
-        a.p, a.g, a.m, a.v = p.data_ptr(), g.data_ptr(), m.data_ptr(), v.data_ptr()
-        a.numel = p.numel()
-        a.p_dtype, a.g_dtype = dtype_code(p.dtype), dtype_code(g.dtype)
+        pack(arr, offset, p.data_ptr(), g.data_ptr(), m.data_ptr(), v.data_ptr(), n, dtype_code(p.dtype), dtype_code(g.dtype))
+        offset += size
     hp = muon_adamw_hparams(lr, weight_decay, beta1, beta2, eps, step)
     _check(lib().muon_adamw_step(arr, len(tensors), C.byref(hp), C.c_void_p(stream_ptr)), "muon_adamw_step")
 
