@@ -205,8 +205,14 @@ int ew_run(size_t tiles) { return (int)std::min<size_t>((size_t)kEwRun, std::max
 //   lies at one full round of coarse tiles: 16 of 1024^2 (160) 35 / 33, 12 of 2048 x 1408 (216) 68 / 67 and 56 / 51,
 //   84 of 1024^2 (840) 141 / 143.
 //   Apply: 2048^2 (64) 44 / 26, two of 1024 x 4096 (128) 31 / 24, 3072^2 (144) 63 / 78, four of 1024 x 4096 (256) 38 / 41.
-bool few_coarse_sym(size_t tiles, int64_t longest_k) { return tiles < 112 || (tiles < 256 && longest_k <= 2048); }
-bool few_coarse_apply(size_t tiles) { return tiles <= 128; }
+// With several planes the coarse tiles' epilogue spills (about 50 us a tile, against 10 in plain bf16), and long K loops
+// are what pays for it: two planes, coarse / fine: Gram product of 48 of 1024^2 274 / 216, 24 of 1024 x 4096 439 / 397, 16 of
+// 2048^2 541 / 464, 4096^2 277 / 290; apply product of 48 of 1024^2 406 / 362, 24 of 1024 x 4096 761 / 689, 4 of 2048^2 210 / 212,
+// 16 of 2048^2 825 / 854, 4096^2 355 / 398; three planes: Gram of 16 of 2048^2 988 / 944, apply 1590 / 1732.
+bool few_coarse_sym(size_t tiles, int64_t longest_k, int64_t largest_m, int planes) {
+  return tiles < 112 || (tiles < 256 && longest_k <= 2048) || (planes > 1 && largest_m < 3072);
+}
+bool few_coarse_apply(size_t tiles, int64_t largest_m, int planes) { return tiles <= 128 || (planes > 1 && largest_m <= 1536); }
 
 // Whether a fine launch runs each entry as four blocks, one per quarter.  bf16: 64 x 64 blocks of a 128 x 128 entry, which are quicker through one tile (0.35
 // against 0.6 us per 64 of K) but need more of the compute unit for the same work: while the launch holds less work
@@ -559,7 +565,9 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         coarse_sym += cm * (cm + 1) / 2 + (odd_m && q.mp >= strip_h ? (size_t)((q.mp + strip_h - 1) / strip_h) : 0);
         coarse_app += cm * cn + (odd_m && q.np >= strip_h ? (size_t)((q.np + strip_h - 1) / strip_h) : 0);
       }
-      const bool few_sym = few_coarse_sym(coarse_sym, *std::max_element(w_n.begin(), w_n.end())), few_app = few_coarse_apply(coarse_app);
+      const int64_t largest_m = *std::max_element(w_m.begin(), w_m.end());
+      const bool few_sym = few_coarse_sym(coarse_sym, *std::max_element(w_n.begin(), w_n.end()), largest_m, (int)planes);
+      const bool few_app = few_coarse_apply(coarse_app, largest_m, (int)planes);
       std::vector<std::vector<GemmTile>> moved_sym(np_), moved_app(np_);   // coarse tiles handed to the fine level
       for (int level = 1; level >= 0; --level) {
         if (level == 1 && !mc) continue;
@@ -628,7 +636,6 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         ts.sym = take(n_sym * sizeof(GemmTile));
         ts.poly = take(n_sym * sizeof(GemmTile));
         ts.apply = take(n_app * sizeof(GemmTile));
-        ts.apply_last = take(n_app * sizeof(GemmTile));
         // The two symmetric products run the same tiles but not the same K (n for the Gram product, m for the
         // polynomial), so each gets its own table: dealt longest K first and weighted by its own K, and with the costs
         // evened out over a die's blocks where its launch is persistent (where the hardware hands out the blocks the
@@ -637,7 +644,9 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         ts.n_sym = (int)deal_tiles(by_n, sym, sym_cuts, w_n, reinterpret_cast<GemmTile*>(img.data() + ts.sym), steady_n ? slots : 0, level == 0);
         ts.n_poly = (int)deal_tiles(by_m, sym, sym_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.poly), steady_m ? slots : 0, level == 0);
         ts.n_apply = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply), steady_m ? slots : 0, level == 0);
-        ts.n_apply_last = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply_last), steady_m ? slots : 0, level == 0);
+// the last apply product runs the same tiles (only its outputs differ)
+        ts.apply_last = ts.apply;
+        ts.n_apply_last = ts.n_apply;
       }
       ch.groups.push_back(g);
     }

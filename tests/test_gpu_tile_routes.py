@@ -1,6 +1,6 @@
 """The planner gives a product 256-, 128- or 64-wide tiles by how much work a launch holds.  Every tile adds an output
 element's products in the same order, so in plain bf16 a matrix must come out with the same bits whichever tiles computed
-it: alone (64-wide), in a short list (128-wide) and in a list long enough for 256-wide tiles and strips.  With several
+it: alone (64-wide), in a short list (128-wide) and in a list long enough for 256-wide tiles and strips (plain bf16 only at these sides).  With several
 planes an element of a symmetric product and its mirror image add the plane pairs in different orders (fp32 rounding,
 about 1e-7 of A per product), and the tile decides which of the two is kept: there the results agree to a tenth of the
 path's own bar."""
@@ -47,7 +47,7 @@ def test_same_bits_from_every_tile(dev, ns, shape, short, long):
         for i in {0, n // 2, n - 1}:
             results.append((st.read_update(i), tensors[i][0], tensors[i][2]))
         st.close()
-    assert coarse_tiles([shape], ns) == [0, 0] and min(coarse_tiles([shape] * long, ns)) > 0
+    assert coarse_tiles([shape], ns) == [0, 0] and (min(coarse_tiles([shape] * long, ns)) > 0) == (ns == "bf16")
     for o, w, m in results[1:]:
         assert torch.equal(m, results[0][2])
         if ns == "bf16":
@@ -106,3 +106,14 @@ def test_elementwise_passes_at_odd_widths_and_addresses(dev, dtypes):
     for flat, n in flats:
         assert (flat[:33] == 7).all() and (flat[33 + n:] == 7).all()
     st.close()
+
+
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("ns", ["bf16x2", "bf16x3"])
+def test_planes_in_coarse_tiles_and_strips(dev, ns):
+    """With several planes only large matrices get 256-wide tiles and, where the side is an odd multiple of 128, 512 x 128
+    strips; one of the two is iterated on its transpose."""
+    shapes = [(3200, 3328), (3328, 3200)]
+    assert min(coarse_tiles(shapes, ns)) > 0
+    wl = workloads.custom("strips_" + ns, shapes, ns_dtype=ns, seed_base=350)
+    assert_records(U.run_and_compare(wl, dev), U.TOL_SPLIT_FRO[ns])
