@@ -20,6 +20,7 @@ namespace {
 
 constexpr int kRing64 = 3;
 constexpr size_t kLdsRing64 = (size_t)kRing64 * 128 * ROWB;
+constexpr size_t kLdsFold64 = 256 * sizeof(double);       // scratch behind the ring for the folded norm
 
 // Fragments of one k-step of a wave, read by assembly (in front of an LDS read of its own the compiler puts a wait for
 // all vector memory, the slabs in flight included).  The transposing read of the K-major operand delivers two halves.
@@ -54,7 +55,7 @@ __device__ __forceinline__ void land64(Frag64<LKM>& f) {
 // The tile at (row0, col0); `diagonal`: it lies on the diagonal of a symmetric product (its own mirror image).
 template <bool LKM, int PL>
 __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem,
-                                                 float beta_acc, float beta_e, int alpha_idx, float diag_add) {
+                                                 float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add) {
   constexpr int NW = 4, BT = 64, NST = kRing64, NLOAD = 4;      // waves, tile side, stages, 1 KB requests per wave and slab
   constexpr int STAGE_B = 2 * BT * ROWB, KSTEPS = BK / 16, NSEG = seg_count(PL);
   static_assert(NST >= 3 && NLOAD * (NST - 1) < 64 && ROWB == 2 * BT, "ring shape");
@@ -173,6 +174,20 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
   static_assert(NST == 3, "the slabs written out below: extents are padded to 128, so KT is even");
   request_slab(0);
   request_slab(1);
+  float alpha = 1.f;
+  if (!LKM && alpha_idx == kAlphaFromPartials) {
+    // first Gram product: the norm, from the partial sums (K-major launches are never first)
+    float s, s2;
+    norm_scalars(block_sum_f64(static_cast<const float*>(p.E), p.lde, reinterpret_cast<double*>(smem + kLdsRing64)), eps, &s, &s2);
+    if (row0 == 0 && col0 == 0 && tid == 0) {
+      float* scal = const_cast<float*>(p.scal);
+      scal[0] = s;
+      scal[1] = s2;
+    }
+    alpha = s2;
+  } else if (alpha_idx >= 0) {
+    alpha = p.scal[alpha_idx];
+  }
   if (KT == 2) {                                 // K = 128, one plane: all of it is on its way
     wait_vmcnt<NLOAD>();
     __builtin_amdgcn_s_barrier();
@@ -196,7 +211,6 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
   __syncthreads();                               // every wave has read the last slab: the LDS is free for the images
 
   // ---- epilogue: val = alpha * (beta_acc * acc + beta_e * E) (+ the diagonal constant), in the large tiles' order ----
-  const float alpha = alpha_idx >= 0 ? p.scal[alpha_idx] : 1.f;
   const float ab_acc = alpha * beta_acc, ab_e = alpha * beta_e;
   u16* C = static_cast<u16*>(p.C);
   u16* Ct = static_cast<u16*>(p.Ct);

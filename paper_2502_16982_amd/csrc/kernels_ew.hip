@@ -222,15 +222,9 @@ __device__ __forceinline__ EwTile load_item(const EwTile* __restrict__ tiles) {
 }
 
 template <typename XT, int PL>
-__global__ __launch_bounds__(256) void momentum_norm_cast_kernel(const MatDesc* __restrict__ mats,
-                                                                  const MatPtrs* __restrict__ ptrs,
-                                                                  const EwTile* __restrict__ tiles, float mu,
-                                                                  int nesterov, int both) {
+__device__ __forceinline__ void momentum_item(const MatDesc& d, const MatPtrs& pt, const EwTile& t, float mu, int nesterov, int both) {
   __shared__ float lds[kEwTile][kEwTile + 1];
   __shared__ float red[4];
-  const EwTile t = load_item(tiles);
-  const MatDesc& d = mats[t.mat];       // read in place (uniform address: scalar loads); see o_source
-  const MatPtrs pt = ptrs[t.mat];
   for (int k = 0; k < t.count; ++k) {
     if (k) __syncthreads();     // the LDS tile and the reduction scratch are reused
     if (d.g_dtype == kDtypeBF16)
@@ -240,26 +234,43 @@ __global__ __launch_bounds__(256) void momentum_norm_cast_kernel(const MatDesc* 
   }
 }
 
+template <typename XT, int PL>
+__global__ __launch_bounds__(256) void momentum_norm_cast_kernel(const MatDesc* __restrict__ mats,
+                                                                  const MatPtrs* __restrict__ ptrs,
+                                                                  const EwTile* __restrict__ tiles, float mu,
+                                                                  int nesterov, int both) {
+  const EwTile t = load_item(tiles);
+  const MatDesc& d = mats[t.mat];     // read in place (uniform address: scalar loads); see o_source
+  const MatPtrs pt = ptrs[t.mat];
+  momentum_item<XT, PL>(d, pt, t, mu, nesterov, both);
+}
+
+// The same with the step's pointers as a kernel argument; a matrix's first block leaves them in the table for the passes
+// behind this one (a launch of its own for the table cost 3 us).
+template <typename XT, int PL>
+__global__ __launch_bounds__(256) void momentum_norm_cast_pack_kernel(const MatDesc* __restrict__ mats, PtrPack pack,
+                                                                       MatPtrs* __restrict__ ptrs,
+                                                                       const EwTile* __restrict__ tiles, float mu,
+                                                                       int nesterov, int both) {
+  const EwTile t = load_item(tiles);
+  const MatDesc& d = mats[t.mat];
+  const MatPtrs pt = pack.p[t.mat];
+  if (t.tr == 0 && t.tc == 0 && threadIdx.x == 0) ptrs[t.mat] = pt;
+  momentum_item<XT, PL>(d, pt, t, mu, nesterov, both);
+}
+
 // ------------------------------------------------------------------------------------------------------
 // a2 second stage: one block per matrix sums its partials in a fixed order, in double.
 // ------------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void norm_finalize_kernel(const MatDesc* __restrict__ mats, int first_mat, double eps) {
   __shared__ double red[256];
-  const MatDesc d = mats[first_mat + blockIdx.x];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < d.n_part; i += 256) acc += (double)d.partials[i];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
+  const MatDesc& d = mats[first_mat + blockIdx.x];
+  const double sum = block_sum_f64(d.partials, d.n_part, red);
   if (threadIdx.x == 0) {
-    const double inv = 1.0 / (sqrt(red[0]) + eps);
-    // an all-zero U with eps = 0 would give inf; X is all zero then, and 0 * inf must not appear
-    const float s = (red[0] > 0.0 || eps > 0.0) ? (float)inv : 0.f;
+    float s, s2;
+    norm_scalars(sum, eps, &s, &s2);
     d.scal[0] = s;
-    d.scal[1] = (red[0] > 0.0 || eps > 0.0) ? (float)(inv * inv) : 0.f;
+    d.scal[1] = s2;
   }
 }
 
@@ -429,17 +440,10 @@ __global__ __launch_bounds__(256) void update_sumsq_kernel(const MatDesc* __rest
 __global__ __launch_bounds__(256) void update_rms_kernel(const MatDesc* __restrict__ mats, int first_mat, int use_s,
                                                           int to_scal, float* __restrict__ out) {
   __shared__ double red[256];
-  const MatDesc d = mats[first_mat + blockIdx.x];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < d.n_part; i += 256) acc += (double)d.partials[i];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
-  }
+  const MatDesc& d = mats[first_mat + blockIdx.x];
+  const double sum = block_sum_f64(d.partials, d.n_part, red);
   if (threadIdx.x == 0) {
-    double rms = sqrt(red[0] / ((double)d.rows * (double)d.cols));
+    double rms = sqrt(sum / ((double)d.rows * (double)d.cols));
     if (to_scal) {
       d.scal[2] = rms > 0.0 ? (float)(1.0 / rms) : 0.f;
     } else {
@@ -475,12 +479,19 @@ __global__ __launch_bounds__(256) void read_update_kernel(const MatDesc* __restr
     default: return hipErrorInvalidValue;                \
   }
 
-hipError_t launch_momentum_norm_cast(const MatDesc* mats, const MatPtrs* ptrs, const EwTile* tiles, int n_tiles, float mu,
-                                     int nesterov, int both_layouts, int ns_dtype, hipStream_t s) {
+hipError_t launch_momentum_norm_cast(const MatDesc* mats, MatPtrs* ptrs, const PtrPack* pack, const EwTile* tiles, int n_tiles,
+                                     float mu, int nesterov, int both_layouts, int ns_dtype, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-#define MUON_CALL(XT, PL) momentum_norm_cast_kernel<XT, PL><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, mu, nesterov, both_layouts)
-  MUON_NS_DISPATCH(ns_dtype, MUON_CALL)
+  if (pack) {
+#define MUON_CALL(XT, PL) \
+  momentum_norm_cast_pack_kernel<XT, PL><<<n_tiles, 256, 0, s>>>(mats, *pack, ptrs, tiles, mu, nesterov, both_layouts)
+    MUON_NS_DISPATCH(ns_dtype, MUON_CALL)
 #undef MUON_CALL
+  } else {
+#define MUON_CALL(XT, PL) momentum_norm_cast_kernel<XT, PL><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, mu, nesterov, both_layouts)
+    MUON_NS_DISPATCH(ns_dtype, MUON_CALL)
+#undef MUON_CALL
+  }
   return hipGetLastError();
 }
 

@@ -1141,7 +1141,7 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_bf16_fine_kernel(const GemmPro
 template <bool LKM, int PL>
 __global__ __launch_bounds__(256, 3) void ns_tile64_gemm_bf16_kernel(const GemmProblem* __restrict__ probs,
                                                                    const GemmTile* __restrict__ tiles, int n_tiles, float beta_acc,
-                                                                   float beta_e, int alpha_idx, float diag_add) {
+                                                                   float beta_e, int alpha_idx, double eps, float diag_add) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int t = (int)(blockIdx.x >> 5) * 8 + (int)(blockIdx.x & 7), quarter = (int)(blockIdx.x >> 3) & 3;
   if (t >= n_tiles) return;
@@ -1150,7 +1150,7 @@ __global__ __launch_bounds__(256, 3) void ns_tile64_gemm_bf16_kernel(const GemmP
   if (on_diag && quarter == 2) return;           // below the diagonal: the mirror image of quarter 1
   const GemmProblem p = probs[tile.prob];
   gemm_tile64_body<LKM, PL>(p, tile.r0 * kTileUnit + 64 * (quarter >> 1), tile.c0 * kTileUnit + 64 * (quarter & 1),
-                            on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, diag_add);
+                            on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps, diag_add);
 }
 
 // Block b works through table entries b, b + gridDim.x, ...  Launched with one block per tile, or persistent: one
@@ -1187,7 +1187,7 @@ hipError_t setup_pair() {
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds128);
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_tile64_gemm_bf16_kernel<LKM, PL>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsRing64);
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsRing64 + kLdsFold64));
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_bf16_kernel<LKM, PL>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds512);
@@ -1195,10 +1195,11 @@ hipError_t setup_pair() {
 
 template <bool LKM, int PL>
 void launch_one(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc,
-                float beta_e, int alpha_idx, float diag_add, hipStream_t s) {
+                float beta_e, int alpha_idx, double eps, float diag_add, hipStream_t s) {
   if (!coarse && (flags & kGemmQuarters))
-    ns_tile64_gemm_bf16_kernel<LKM, PL><<<(n_tiles + 7) / 8 * 32, 256, kLdsRing64, s>>>(probs, tiles, n_tiles, beta_acc, beta_e,
-                                                                                       alpha_idx, diag_add);
+    ns_tile64_gemm_bf16_kernel<LKM, PL><<<(n_tiles + 7) / 8 * 32, 256,
+                                          kLdsRing64 + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(
+        probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, diag_add);
   else if (!coarse)
     ns_gemm_bf16_fine_kernel<LKM, PL><<<n_tiles, 256, kLds128, s>>>(probs, tiles, beta_acc, beta_e, alpha_idx, diag_add);
   else
@@ -1233,11 +1234,12 @@ hipError_t gemm_setup() {
 }
 
 hipError_t launch_gemm_bf16(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc,
-                            float beta_e, int alpha_idx, float diag_add, int l_kmajor, int planes, hipStream_t s) {
+                            float beta_e, int alpha_idx, double eps, float diag_add, int l_kmajor, int planes, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
   if (planes < 1 || planes > kMaxPlanes) return hipErrorInvalidValue;
+  if (alpha_idx == kAlphaFromPartials && (coarse || l_kmajor || !(flags & kGemmQuarters))) return hipErrorInvalidValue;
 #define MUON_GEMM_CASE(K, P)                                                                                     \
-  if ((l_kmajor != 0) == K && planes == P) launch_one<K, P>(coarse, flags, probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, diag_add, s)
+  if ((l_kmajor != 0) == K && planes == P) launch_one<K, P>(coarse, flags, probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, diag_add, s)
   MUON_GEMM_CASE(false, 1);
   MUON_GEMM_CASE(true, 1);
   MUON_GEMM_CASE(false, 2);

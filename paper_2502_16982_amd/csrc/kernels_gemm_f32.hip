@@ -57,12 +57,13 @@ __device__ __forceinline__ void land_half(HalfSlab& f) {
 // two slabs per wave's own ring leave room for two blocks of quarters on a compute unit (three: 1024^2 -> 408 instead of 346 us)
 constexpr int ring_of(bool quarters) { return quarters ? 2 : 3; }
 constexpr size_t stage_bytes(bool quarters) { return quarters ? 4 * 64 * ROWF : 128 * ROWF; }
+constexpr size_t kLdsFold = 256 * sizeof(double);            // scratch behind the rings for the folded norm
 constexpr size_t lds_bytes(bool quarters) { return ring_of(quarters) * stage_bytes(quarters); }
 
 template <bool Q>
 __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* __restrict__ probs,
                                                               const GemmTile* __restrict__ tiles, int n_tiles, float beta_acc,
-                                                              float beta_e, int alpha_idx) {
+                                                              float beta_e, int alpha_idx, double eps) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NST = ring_of(Q), NLOAD = Q ? 8 : 4;            // stages, 1 KB requests per wave and slab
   constexpr int ROWS = Q ? 32 : 64;                             // rows of each operand in a stage
@@ -139,10 +140,24 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  if (n > 0) {
 #pragma unroll
-    for (int s = 0; s < NST; ++s)
-      if (s < n) request(s, s);
+  for (int s = 0; s < NST; ++s)
+    if (s < n) request(s, s);
+  float alpha = 1.f;
+  if (Q && alpha_idx == kAlphaFromPartials) {
+    // first Gram product: the norm, from the partial sums
+    float s, s2;
+    norm_scalars(block_sum_f64(static_cast<const float*>(p.E), p.lde, reinterpret_cast<double*>(smem + lds_bytes(true))), eps, &s, &s2);
+    if (row0 == 0 && col0 == 0 && tid == 0) {
+      float* scal = const_cast<float*>(p.scal);
+      scal[0] = s;
+      scal[1] = s2;
+    }
+    alpha = s2;
+  } else if (alpha_idx >= 0) {
+    alpha = p.scal[alpha_idx];
+  }
+  if (n > 0) {
     if (!Q && n >= 3) wait_vmcnt<2 * NLOAD>();
     else if (n >= 2) wait_vmcnt<NLOAD>();
     else wait_vmcnt<0>();
@@ -185,7 +200,6 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
   // ---- epilogue.  A lane holds column fr, rows 8 q + 4 h + e of its wave's 32 x 32 tile: it goes to LDS as image
   // [column][row].  Quarters: the four waves' partial tiles are added up, one float4 per thread; whole: each wave reads
   // its own tile back.  Et is the addend stored transposed, so that it is read and Ct written along rows of the image.
-  const float alpha = alpha_idx >= 0 ? p.scal[alpha_idx] : 1.f;
   const float* Et = static_cast<const float*>(p.Et);
   float* C = static_cast<float*>(p.C);
   float* Ct = static_cast<float*>(p.Ct);
@@ -249,19 +263,21 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
 
 hipError_t gemm_f32_setup() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_f32_kernel<true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(true));
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_bytes(true) + kLdsFold));
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_f32_kernel<false>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(false));
 }
 
 hipError_t launch_gemm_f32(int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc, float beta_e,
-                           int alpha_idx, hipStream_t s) {
+                           int alpha_idx, double eps, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
+  if (alpha_idx == kAlphaFromPartials && !(flags & kGemmQuarters)) return hipErrorInvalidValue;
   if (flags & kGemmQuarters)
-    ns_gemm_f32_kernel<true><<<(n_tiles + 7) / 8 * 32, 256, lds_bytes(true), s>>>(probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx);
+    ns_gemm_f32_kernel<true><<<(n_tiles + 7) / 8 * 32, 256, lds_bytes(true) + (alpha_idx == kAlphaFromPartials ? kLdsFold : 0), s>>>(
+        probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps);
   else
-    ns_gemm_f32_kernel<false><<<n_tiles, 256, lds_bytes(false), s>>>(probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx);
+    ns_gemm_f32_kernel<false><<<n_tiles, 256, lds_bytes(false), s>>>(probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps);
   return hipGetLastError();
 }
 

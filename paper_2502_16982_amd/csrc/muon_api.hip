@@ -178,8 +178,9 @@ int check_step_args(const muon_ctx* ctx, const muon_param* params, int32_t n, co
   return MUON_OK;
 }
 
-// Enqueues every kernel of one step on stream s (the pointer table is already on its way on the same stream).
-int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* update_rms_out) {
+// Enqueues every kernel of one step on stream s.  The pointer table is already on its way on the same stream, or (pack, plans
+// of one chunk) the first pass takes the pointers as an argument and fills it.
+int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* update_rms_out, const PtrPack* pack = nullptr) {
   const int N = hp->ns_steps;
   const int use_s = N == 0;
   const bool mc = on_matrix_cores(ctx->ns_dtype);   // bf16 or split-bf16: the MFMA kernels and their one-layout plan
@@ -191,9 +192,10 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
   for (size_t ci = 0; ci < ctx->plan.chunks.size(); ++ci) {
     const Chunk& ch = ctx->plan.chunks[ci];
     const EwTile* ew = reinterpret_cast<const EwTile*>(ctx->ws + ch.ew_tiles_off);
-    MUON_TIMED(MUON_PROF_MOMENTUM, launch_momentum_norm_cast(ctx->d_mats, ctx->d_ptrs, ew, ch.n_ew_tiles, (float)hp->momentum,
+    MUON_TIMED(MUON_PROF_MOMENTUM, launch_momentum_norm_cast(ctx->d_mats, ctx->d_ptrs, pack, ew, ch.n_ew_tiles, (float)hp->momentum,
                                                              hp->nesterov != 0, (!mc || N == 0) ? 1 : 0, ctx->ns_dtype, s));
-    MUON_TIMED(MUON_PROF_NORM, launch_norm_finalize(ctx->d_mats, ch.first, ch.count, hp->eps, s));
+    const bool fold = ch.fold_norm && N > 0;
+    if (!fold) MUON_TIMED(MUON_PROF_NORM, launch_norm_finalize(ctx->d_mats, ch.first, ch.count, hp->eps, s));
     for (int it = 0; it < N; ++it) {
       const int first = it == 0, last = it == N - 1, par = it & 1;
       const double* sch = hp->coeff_schedule ? hp->coeff_schedule + 3 * it : nullptr;
@@ -207,17 +209,18 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
           if (ts.n_sym == 0) continue;
           if (mc)
             MUON_TIMED(MUON_PROF_GRAM, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_n ? kGemmPersistent : 0) | (ts.quarter_sym ? kGemmQuarters : 0), P(g.prob_gram[par]), T(ts.sym), ts.n_sym, 1.f, 0.f,
-                                                        first ? 1 : -1, 0.f, 0, planes, s));
+                                                        first ? (fold ? kAlphaFromPartials : 1) : -1, hp->eps, 0.f, 0, planes, s));
           else
-            MUON_TIMED(MUON_PROF_GRAM, launch_gemm_f32(ts.quarter_sym ? kGemmQuarters : 0, P(g.prob_gram[par]), T(ts.sym), ts.n_sym, 1.f, 0.f, first ? 1 : -1, s));
+            MUON_TIMED(MUON_PROF_GRAM, launch_gemm_f32(ts.quarter_sym ? kGemmQuarters : 0, P(g.prob_gram[par]), T(ts.sym), ts.n_sym, 1.f, 0.f,
+                                                       first ? (fold ? kAlphaFromPartials : 1) : -1, hp->eps, s));
         }
         for (int level = 1; level >= 0; --level) {
           const TileSet& ts = level ? g.coarse : g.fine;
           if (ts.n_poly == 0) continue;
           if (mc)
-            MUON_TIMED(MUON_PROF_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | (ts.quarter_poly ? kGemmQuarters : 0), P(g.prob_poly), T(ts.poly), ts.n_poly, c, b, -1, a, 0, planes, s));
+            MUON_TIMED(MUON_PROF_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | (ts.quarter_poly ? kGemmQuarters : 0), P(g.prob_poly), T(ts.poly), ts.n_poly, c, b, -1, 0.0, a, 0, planes, s));
           else
-            MUON_TIMED(MUON_PROF_POLY, launch_gemm_f32(ts.quarter_poly ? kGemmQuarters : 0, P(g.prob_poly), T(ts.poly), ts.n_poly, c, b, -1, s));
+            MUON_TIMED(MUON_PROF_POLY, launch_gemm_f32(ts.quarter_poly ? kGemmQuarters : 0, P(g.prob_poly), T(ts.poly), ts.n_poly, c, b, -1, 0.0, s));
         }
         for (int level = 1; level >= 0; --level) {
           const TileSet& ts = level ? g.coarse : g.fine;
@@ -226,10 +229,10 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
           if (n_app == 0) continue;
           if (mc)
             MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | (ts.quarter_apply ? kGemmQuarters : 0), P(g.prob_apply[par * 2 + last]), T(t_app),
-                                                              n_app, 1.f, a, first ? 0 : -1, 0.f, 1, planes, s));
+                                                              n_app, 1.f, a, first ? 0 : -1, 0.0, 0.f, 1, planes, s));
           else
             MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_f32(ts.quarter_apply ? kGemmQuarters : 0, P(g.prob_apply[par * 2 + last]), T(t_app), n_app, 1.f, a,
-                                                             first ? 0 : -1, s));
+                                                             first ? 0 : -1, 0.0, s));
         }
       }
     }
@@ -358,20 +361,13 @@ int muon_step(muon_ctx* ctx, const muon_param* params, int32_t n, const muon_hpa
 namespace {
 
 constexpr int kStaticMaxDevices = 64;
-struct PtrPack {                     // the per-step pointers of muon_step_static travel as a kernel argument
-  MatPtrs p[MUON_STATIC_MAX_MATRICES];
-};
+static_assert(kPackSlots == MUON_STATIC_MAX_MATRICES, "the per-step pointers of muon_step_static travel as a kernel argument");
 struct StaticSlot {
   unsigned char* ptr = nullptr;      // device address of `scratch` on this device (hipGetSymbolAddress)
   muon_ctx* ctx = nullptr;           // plan and tables of the shape list of the last call on this device
   std::vector<muon_param> key;       // that shape list (rows, cols, dtypes)
 };
 StaticSlot g_static[kStaticMaxDevices];
-
-__global__ void set_ptrs_kernel(PtrPack pack, MatPtrs* __restrict__ dst, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = pack.p[i];
-}
 
 int step_static_impl(const muon_param* params, int32_t n, int32_t ns_dtype, const muon_hparams* hp, void* hip_stream,
                      float* update_rms_out) {
@@ -440,9 +436,7 @@ int step_static_impl(const muon_param* params, int32_t n, int32_t ns_dtype, cons
   if (st != MUON_OK) return st;
   PtrPack pack{};
   for (int i = 0; i < n; ++i) pack.p[i] = MatPtrs{params[i].w, params[i].g, params[i].m};
-  set_ptrs_kernel<<<1, MUON_STATIC_MAX_MATRICES, 0, s>>>(pack, ctx->d_ptrs, n);
-  MUON_HIP(hipGetLastError());
-  return enqueue_step(ctx, hp, s, update_rms_out);
+  return enqueue_step(ctx, hp, s, update_rms_out, &pack);
 }
 
 }  // namespace

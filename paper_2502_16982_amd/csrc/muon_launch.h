@@ -22,6 +22,28 @@ __device__ __forceinline__ GemmTile load_tile(const GemmTile* __restrict__ tiles
   return r;
 }
 
+// Sum of n floats in double by the 256 threads of a block, in the order of the norm's own kernel, returned to every lane
+// (red: 256 doubles of LDS).  Contains one barrier.
+__device__ __forceinline__ double block_sum_f64(const float* __restrict__ v, int n, double* red) {
+  double acc = 0.0;
+  for (int i = threadIdx.x; i < n; i += 256) acc += (double)v[i];
+  red[threadIdx.x] = acc;
+  __syncthreads();
+  const int l = threadIdx.x & 63;
+  double t = (red[l] + red[l + 128]) + (red[l + 64] + red[l + 192]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+  return t;
+}
+// a2: 1/(sqrt(sum) + eps) and its square from the sum of squares of U.  An all-zero U with eps = 0 would give inf; X is all
+// zero then, and 0 * inf must not appear.
+__device__ __forceinline__ void norm_scalars(double sum, double eps, float* s, float* s2) {
+  const double inv = 1.0 / (sqrt(sum) + eps);
+  const bool ok = sum > 0.0 || eps > 0.0;
+  *s = ok ? (float)inv : 0.f;
+  *s2 = ok ? (float)(inv * inv) : 0.f;
+}
+
 // One-time per-process kernel attribute setup (large dynamic LDS).  Returns a hipError_t.
 hipError_t gemm_setup();
 // Blocks of a persistent coarse GEMM launch = compute units of the device gemm_setup ran on (0 before it).
@@ -29,13 +51,20 @@ int gemm_coarse_blocks();
 
 // a1-a3: momentum, sum of squares, cast + orient.  both_layouts != 0: U goes to X and Xt[0] (one holds U, the other
 // U^T); 0: only X (the orientation with rows <= cols) is written.  One block per EwTile.
-hipError_t launch_momentum_norm_cast(const MatDesc* mats, const MatPtrs* ptrs, const EwTile* tiles, int n_tiles,
+// pack != null: the pointers come as a kernel argument and the pass leaves them in `ptrs` for the kernels behind it.
+constexpr int kPackSlots = 64;
+struct PtrPack {
+  MatPtrs p[kPackSlots];
+};
+hipError_t launch_momentum_norm_cast(const MatDesc* mats, MatPtrs* ptrs, const PtrPack* pack, const EwTile* tiles, int n_tiles,
                                      float mu, int nesterov, int both_layouts, int ns_dtype, hipStream_t s);
 
 // a2 second stage: fixed-order sum of the partials of each matrix, s = 1/(sqrt(sum)+eps).
 hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, double eps, hipStream_t s);
 
-// a4-a6: grouped NT GEMM with fused epilogue.  alpha_idx: -1 none, 0 -> scal[0], 1 -> scal[1].  diag_add: constant
+// a4-a6: grouped NT GEMM with fused epilogue.  alpha_idx: -1 none, 0 -> scal[0], 1 -> scal[1], kAlphaFromPartials (first
+// Gram product, kGemmQuarters launches only) -> what scal[1] has to be, from the partial sums of squares and eps; the block
+// of the first tile leaves scal[0] and scal[1] behind.  diag_add: constant
 // added to the diagonal of the outputs of problems that ask for it (GemmProblem::diag_add), bf16 kernel only.
 // coarse: 0 = every tile of the table is 128 x 128 (two blocks per compute unit); 1 = the table mixes 256 x 256 and,
 // with kGemmStrips in `flags`, 512 x 128 tiles (one block per compute unit; the flag selects the larger LDS
@@ -45,13 +74,14 @@ hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, 
 // kGemmQuarters (coarse = 0): every entry of the table runs as four blocks, one per quarter of it.
 // l_kmajor: every problem of the launch stores its L operand K-major (element (i, k) at L[k * ldl + i]).
 // planes: 1 = plain bf16; 2 or 3 = every matrix is a sum of that many bf16 planes (GemmProblem::*_plane strides).
+constexpr int kAlphaFromPartials = 2;
 constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmQuarters = 4;
 hipError_t launch_gemm_bf16(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
-                            float beta_acc, float beta_e, int alpha_idx, float diag_add, int l_kmajor, int planes,
+                            float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add, int l_kmajor, int planes,
                             hipStream_t s);
 hipError_t gemm_f32_setup();
 hipError_t launch_gemm_f32(int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
-                           float beta_acc, float beta_e, int alpha_idx, hipStream_t s);
+                           float beta_acc, float beta_e, int alpha_idx, double eps, hipStream_t s);
 
 // a8: W <- W - lr*(scale*O + wd*W); also leaves per-tile sums of O^2 in the partials.
 // o_sel: where O sits in W's orientation: bit 0 picks Xt[0] / Xt[1] for matrices iterated on their transpose, bit 1

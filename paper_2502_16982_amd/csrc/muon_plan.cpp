@@ -222,6 +222,7 @@ bool few_coarse_apply(size_t tiles, int64_t largest_m, int planes) { return tile
 // fp32 launches run their 64 x 64 entries as four blocks of 32 x 32 up to about 320 entries.  Measured, whole / quarters:
 // Gram product of 1024^2 (136) 26 / 21.5, of 64 of 128 x 256 (192) 11.9 / 11.3, of 16 of 512^2 (576) 34.1 / 34.4; apply product
 // of 1024^2 (256) 27.7 / 27.6, of 64 of 128 x 256 (512) 13.6 / 17.7.
+constexpr int kMaxFoldedPartials = 1024;
 constexpr int kFewFine = 176, kFewF32 = 320;
 bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int few) {
   int64_t longest = 0, total = 0;
@@ -483,8 +484,8 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         void* const xbuf[2] = {d.X, mc ? d.Xt[0] : d.X};
         // Gram: A = X X^T
         for (int par = 0; par < 2; ++par) {
-          gp.L = xbuf[par]; gp.R = xbuf[par]; gp.E = nullptr; gp.Et = nullptr; gp.C = d.Ag; gp.Ct = nullptr;
-          gp.K = q.np; gp.ldl = q.np; gp.ldr = q.np; gp.lde = 0; gp.ldet = 0; gp.ldc = q.mp; gp.ldct = q.mp; gp.symmetric = 1;
+          gp.L = xbuf[par]; gp.R = xbuf[par]; gp.E = d.partials; gp.Et = nullptr; gp.C = d.Ag; gp.Ct = nullptr;
+          gp.K = q.np; gp.ldl = q.np; gp.ldr = q.np; gp.lde = d.n_part; gp.ldet = 0; gp.ldc = q.mp; gp.ldct = q.mp; gp.symmetric = 1;
           gp.l_plane = xpl; gp.r_plane = xpl; gp.et_plane = 0; gp.c_plane = apl; gp.ct_plane = apl;
           reinterpret_cast<GemmProblem*>(img.data() + g.prob_gram[par])[k] = gp;
         }
@@ -648,6 +649,11 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         ts.apply_last = ts.apply;
         ts.n_apply_last = ts.n_apply;
       }
+      // Lists short enough for quarter blocks save the norm's own launch (about 4 us): every block adds up its matrix's
+      // partials, at most four per thread, while its first operands are on their way.
+      int most_parts = 0;
+      for (int i = ch.first; i < ch.first + ch.count; ++i) most_parts = std::max(most_parts, h_mats[i].n_part);
+      ch.fold_norm = g.coarse.n_sym == 0 && g.fine.quarter_sym && most_parts <= kMaxFoldedPartials;
       ch.groups.push_back(g);
     }
   }

@@ -53,6 +53,7 @@ struct Chunk {
   int first = 0, count = 0;
   size_t ew_tiles_off = 0;   // byte offset of the EwTile table
   int n_ew_tiles = 0;
+  bool fold_norm = false;    // the blocks of the first Gram launch add up the partial sums of squares themselves
   std::vector<Group> groups;
 };
 

@@ -58,7 +58,8 @@ struct EwTile {
 struct GemmProblem {
   const void* L;      // M x K, leading dimension ldl (K-major launches: element (i, k) at L[k * ldl + i])
   const void* R;      // N x K, leading dimension ldr
-  const void* E;      // M x N addend at the output position (may be null), leading dimension lde
+  const void* E;      // Gram problems: the partial sums of squares of U (float), `lde` of them; otherwise the M x N addend
+                      // at the output position (may be null), leading dimension lde
   const void* Et;     // the same addend stored transposed, N x M, leading dimension ldet (bf16 kernel reads this one)
   void* C;            // M x N output (may be null), leading dimension ldc
   void* Ct;           // N x M transposed output, leading dimension ldct (the bf16 kernel requires it unless symmetric)
