@@ -204,7 +204,8 @@ int ew_run(size_t tiles) { return (int)std::min<size_t>((size_t)kEwRun, std::max
 //   Gram and polynomial: 2048^2 (36 tiles) 45 / 24, 3584^2 (105) 69 / 56, 4096^2 (136) 83 / 102; with a short K the line
 //   lies at one full round of coarse tiles: 16 of 1024^2 (160) 35 / 33, 12 of 2048 x 1408 (216) 68 / 67 and 56 / 51,
 //   84 of 1024^2 (840) 141 / 143.
-//   Apply: 2048^2 (64) 44 / 26, two of 1024 x 4096 (128) 31 / 24, 3072^2 (144) 63 / 78, four of 1024 x 4096 (256) 38 / 41.
+//   Apply: 2048^2 (64) 44 / 26, two of 1024 x 4096 (128) 31 / 24, six ragged ones up to 1000 x 3001 (132, with what the coarse
+//   tiles leave) 38 / 22, 3072^2 (144) 63 / 78, four of 2048 x 1408 (176) 41 / 42, four of 1024 x 4096 (256) 38 / 41.
 // With several planes the coarse tiles' epilogue spills (about 50 us a tile, against 10 in plain bf16), and long K loops
 // are what pays for it: two planes, coarse / fine: Gram product of 48 of 1024^2 274 / 216, 24 of 1024 x 4096 439 / 397, 16 of
 // 2048^2 541 / 464, 4096^2 277 / 290; apply product of 48 of 1024^2 406 / 362, 24 of 1024 x 4096 761 / 689, 4 of 2048^2 210 / 212,
@@ -212,7 +213,9 @@ int ew_run(size_t tiles) { return (int)std::min<size_t>((size_t)kEwRun, std::max
 bool few_coarse_sym(size_t tiles, int64_t longest_k, int64_t largest_m, int planes) {
   return tiles < 112 || (tiles < 256 && longest_k <= 2048) || (planes > 1 && largest_m < 3072);
 }
-bool few_coarse_apply(size_t tiles, int64_t largest_m, int planes) { return tiles <= 128 || (planes > 1 && largest_m <= 1536); }
+bool few_coarse_apply(size_t tiles, int64_t largest_m, int planes) {
+  return tiles <= 128 || (tiles < 176 && largest_m <= 1536) || (planes > 1 && largest_m <= 1536);
+}
 
 // Whether a fine launch runs each entry as four blocks, one per quarter.  bf16: 64 x 64 blocks of a 128 x 128 entry, which are quicker through one tile (0.35
 // against 0.6 us per 64 of K) but need more of the compute unit for the same work: while the launch holds less work
