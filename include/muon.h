@@ -98,7 +98,7 @@ int muon_default_hparams(muon_hparams* hp);
 /*
  * Workspace size for a parameter list.  Only rows/cols/dtypes of `shapes` are read (pointers may be
  * null).  ns_dtype selects the Newton-Schulz arithmetic: MUON_BF16 (bf16 operands, fp32 accumulation;
- * section 2.3 notes bf16 suffices), MUON_F32 (vector ALUs; meant for small matrices), or the split
+ * section 2.3 notes bf16 suffices), MUON_F32 (fp32 matrix instructions; meant for small matrices), or the split
  * forms MUON_BF16X2 / MUON_BF16X3 (fp32-class accuracy on the matrix cores, the "more accurate"
  * direction of section 2.2 at model sizes).  The Newton-Schulz temporaries of all matrices are
  * kept resident when they fit in `max_bytes`; otherwise the list is processed in consecutive chunks
