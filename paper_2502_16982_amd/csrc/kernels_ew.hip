@@ -40,6 +40,48 @@ __device__ __forceinline__ float block_sum_256(float v, float* red /* >= 4 float
   return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// Value of lane S of this lane's group of four.
+template <int S>
+__device__ __forceinline__ float quad_lane(float v) {
+  constexpr int ctrl = S | (S << 2) | (S << 4) | (S << 6);
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true));
+}
+
+// Sum of squares of a 64 x 64 tile of which thread t holds columns 4 (t % 16) .. + 3 of rows t / 16 + 16 j, in an order that
+// belongs to the tile and not to this distribution: 16 consecutive columns of a row are one chain of fma; the 64 chains of
+// 16 consecutive rows (chain 4 (r % 16) + c / 16) are added up as a tree (32 apart first, neighbours last); the four
+// results as (0 + 1) + (2 + 3).  The last bits of the norm decide bf16 roundings of everything behind it, so another
+// order would be another result (up to 6e-4 of the updated weights).  A chain passes through the four lanes that hold
+// its columns.  Contains one barrier; the sum is valid in the first wave.
+// Next to sums of each thread's own elements: within the noise in the momentum pass, which is bound by memory.
+__device__ __forceinline__ float tile_sum_squares(const float (&u)[4][4], float* red /* 256 floats of LDS */) {
+  const int tid = threadIdx.x;
+  auto chain = [](float c, const float (&x)[4]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c = fmaf(x[i], x[i], c);
+    return c;
+  };
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    float c = chain(0.f, u[j]);                  // right in the first lane of four, then in the second, ...
+    c = chain(quad_lane<0>(c), u[j]);
+    c = chain(quad_lane<1>(c), u[j]);
+    c = chain(quad_lane<2>(c), u[j]);
+    if ((tid & 3) == 3) red[64 * j + (tid >> 2)] = c;
+  }
+  __syncthreads();
+  float t = 0.f;
+  if (tid < 64) {
+    const float* v = red + 64 * (tid >> 4) + (tid & 15);       // 16 lanes for each group of 64 chains
+    t = (v[0] + v[32]) + (v[16] + v[48]);
+#pragma unroll
+    for (int off = 8; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    t += __shfl_xor(t, 16, 64);
+    t += __shfl_xor(t, 32, 64);
+  }
+  return t;
+}
+
 // Accesses go through the global address space (pointers that come out of a table would otherwise be accessed as
 // `flat`).  Those to the caller's matrices are wide at any alignment of the element: rows start anywhere, and global
 // memory takes such accesses (the vector types only tell the compiler), so odd widths and odd buffers keep the wide path.
@@ -133,7 +175,6 @@ __device__ __forceinline__ void momentum_tile(const MatDesc& d, const MatPtrs& p
   float* m = pt.m;
 
   float u[4][4], mv[4][4], gv[4][4];
-  float ss = 0.f;
   const bool wide = c0 + 4 <= B;
   // all loads are issued before the first store
 #pragma unroll
@@ -161,7 +202,6 @@ __device__ __forceinline__ void momentum_tile(const MatDesc& d, const MatPtrs& p
       const float mn = fmaf(mu, mv[j][i], gv[j][i]);
       mv[j][i] = mn;
       u[j][i] = nesterov ? fmaf(mu, mn, gv[j][i]) : mn;
-      ss = fmaf(u[j][i], u[j][i], ss);
     }
     if (wide && r < A) {
       store4(m + base, mv[j]);
@@ -192,7 +232,7 @@ __device__ __forceinline__ void momentum_tile(const MatDesc& d, const MatPtrs& p
 #pragma unroll
       for (int i = 0; i < 4; ++i) lds[lc + i][lr + 16 * j] = u[j][i];
   }
-  const float total = block_sum_256(ss, red);   // contains the barrier that publishes the LDS tile
+  const float total = tile_sum_squares(u, red);   // contains the barrier that publishes the LDS tile
   if (write_flip) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -224,7 +264,7 @@ __device__ __forceinline__ EwTile load_item(const EwTile* __restrict__ tiles) {
 template <typename XT, int PL>
 __device__ __forceinline__ void momentum_item(const MatDesc& d, const MatPtrs& pt, const EwTile& t, float mu, int nesterov, int both) {
   __shared__ float lds[kEwTile][kEwTile + 1];
-  __shared__ float red[4];
+  __shared__ float red[256];
   for (int k = 0; k < t.count; ++k) {
     if (k) __syncthreads();     // the LDS tile and the reduction scratch are reused
     if (d.g_dtype == kDtypeBF16)
