@@ -232,7 +232,7 @@ int muon_profile_read(muon_ctx* ctx, double* ms_out, int64_t* launches_out, int 
  *   p = p - lr * ( m/(1-beta1^t) / (sqrt(v/(1-beta2^t)) + eps) + weight_decay * p ).
  * Tensors are flat arrays of `numel` elements (any shape); p and g may be fp32 or bf16, the moments m and v
  * are fp32 and updated in place.  Stateless: needs no context and no workspace (pointers travel in kernel
- * arguments, 64 tensors per launch).  Asynchronous on hip_stream.  `step` is t, counted from 1.
+ * arguments, 64 tensors or 2^34 - 1024 elements per launch; larger tensors are split over launches).  Asynchronous on hip_stream.  `step` is t, counted from 1.
  */
 typedef struct {
   void* p;            /* device; parameter, dtype p_dtype; updated in place   */

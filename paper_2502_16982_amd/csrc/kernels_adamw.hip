@@ -1,7 +1,7 @@
 // AdamW for the parameters that stay off Muon (RMSNorm gains, LM head, embeddings; section 2.2 of the paper), sharing
 // lr and weight decay with it.  HBM-bound elementwise kernel: one launch covers up to kAdamwSlots tensors, whose
 // pointers and sizes travel in the kernel arguments (no device table, no workspace); each block owns one
-// 1024-element span of one tensor.  fp32 math, moments in fp32, one rounding to the parameter's dtype.
+// 1024-element span (kAdamwSpan) of one tensor.  fp32 math, moments in fp32, one rounding to the parameter's dtype.
 // Bound by memory: 22 (bf16) or 28 bytes per element.  Four elements per thread, their loads all issued before the first
 // store; a launch that moves more than the memory-side cache can carry over carries the non-temporal hint.  Measured, TB/s,
 // spans of 4096 loaded and stored piece by piece / these / these with the hint: 134 M elements bf16 5.2 / 5.4 / 5.8, 67 M
@@ -17,7 +17,6 @@ typedef unsigned short u16;
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
-constexpr int kSpan = 1024;   // elements per block (4 per thread)
 // launches that move at least this many bytes use the non-temporal hint (the memory-side cache holds 256 MB)
 constexpr long long kStreamBytes = 1ll << 30;
 
@@ -112,7 +111,7 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamwBatch batch, AdamwScala
 #pragma unroll
   for (int step = kAdamwSlots / 2; step > 0; step /= 2)
     if (t + step < batch.n && (int)blockIdx.x >= batch.block_start[t + step]) t += step;
-  const long long begin = (long long)((int)blockIdx.x - batch.block_start[t]) * kSpan;
+  const long long begin = (long long)((int)blockIdx.x - batch.block_start[t]) * kAdamwSpan;
   const long long numel = batch.numel[t];
   float* m = batch.m[t];
   float* v = batch.v[t];
@@ -127,8 +126,6 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamwBatch batch, AdamwScala
 }
 
 }  // namespace
-
-long long adamw_blocks_for(long long numel) { return (numel + kSpan - 1) / kSpan; }
 
 hipError_t launch_adamw(const AdamwBatch& batch, int n_blocks, float lr, float wd, float beta1, float beta2, float eps,
                         float inv_bc1, float inv_bc2, hipStream_t s) {

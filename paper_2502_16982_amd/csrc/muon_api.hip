@@ -516,31 +516,17 @@ int muon_adamw_step(const muon_adamw_param* params, int32_t n, const muon_adamw_
     if ((reinterpret_cast<uintptr_t>(q.p) & pa) || (reinterpret_cast<uintptr_t>(q.g) & ga) ||
         (reinterpret_cast<uintptr_t>(q.m) & 3u) || (reinterpret_cast<uintptr_t>(q.v) & 3u))
       return MUON_E_MISALIGNED;
-    if (adamw_blocks_for(q.numel) > (1ll << 30)) return MUON_E_INVALID_ARG;
+    if (q.numel > kAdamwMaxNumel) return MUON_E_INVALID_ARG;
   }
   // bias corrections in double, handed to the kernel as reciprocals
   const float inv_bc1 = (float)(1.0 / (1.0 - std::pow(hp->beta1, (double)hp->step)));
   const float inv_bc2 = (float)(1.0 / (1.0 - std::pow(hp->beta2, (double)hp->step)));
   hipStream_t s = static_cast<hipStream_t>(hip_stream);
-  for (int first = 0; first < n;) {
-    AdamwBatch b{};
-    long long blocks = 0;
-    int k = 0;
-    while (first + k < n && k < kAdamwSlots && blocks + adamw_blocks_for(params[first + k].numel) <= (1ll << 30)) {
-      const muon_adamw_param& q = params[first + k];
-      b.p[k] = q.p; b.g[k] = q.g; b.m[k] = q.m; b.v[k] = q.v;
-      b.numel[k] = q.numel;
-      b.p_dtype[k] = q.p_dtype; b.g_dtype[k] = q.g_dtype;
-      b.block_start[k] = (int)blocks;
-      blocks += adamw_blocks_for(q.numel);
-      ++k;
-    }
-    b.block_start[k] = (int)blocks;
-    b.n = k;
-    MUON_HIP(launch_adamw(b, (int)blocks, (float)hp->lr, (float)hp->weight_decay, (float)hp->beta1, (float)hp->beta2,
-                          (float)hp->eps, inv_bc1, inv_bc2, s));
-    first += k;
-  }
+  AdamwBatch b{};
+  AdamwCursor at;
+  while (const int blocks = adamw_next_batch(params, n, at, b))
+    MUON_HIP(launch_adamw(b, blocks, (float)hp->lr, (float)hp->weight_decay, (float)hp->beta1, (float)hp->beta2, (float)hp->eps,
+                          inv_bc1, inv_bc2, s));
   return MUON_OK;
 }
 
