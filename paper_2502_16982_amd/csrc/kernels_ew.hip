@@ -47,6 +47,12 @@ __device__ __forceinline__ float quad_lane(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true));
 }
 
+// Value of the lane N places on, around this lane's group of sixteen.
+template <int N>
+__device__ __forceinline__ float row_rotate(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x120 + N, 0xf, 0xf, true));
+}
+
 // Sum of squares of a 64 x 64 tile of which thread t holds columns 4 (t % 16) .. + 3 of rows t / 16 + 16 j, in an order that
 // belongs to the tile and not to this distribution: 16 consecutive columns of a row are one chain of fma; the 64 chains of
 // 16 consecutive rows (chain 4 (r % 16) + c / 16) are added up as a tree (32 apart first, neighbours last); the four
@@ -74,10 +80,12 @@ __device__ __forceinline__ float tile_sum_squares(const float (&u)[4][4], float*
   if (tid < 64) {
     const float* v = red + 64 * (tid >> 4) + (tid & 15);       // 16 lanes for each group of 64 chains
     t = (v[0] + v[32]) + (v[16] + v[48]);
-#pragma unroll
-    for (int off = 8; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
-    t += __shfl_xor(t, 16, 64);
-    t += __shfl_xor(t, 32, 64);
+    t += row_rotate<8>(t);                       // t repeats every 8 lanes now, then every 4, ...: a rotation is the exchange
+    t += row_rotate<4>(t);
+    t += row_rotate<2>(t);
+    t += row_rotate<1>(t);
+    auto lane = [&](int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), l)); };
+    t = (lane(0) + lane(16)) + (lane(32) + lane(48));
   }
   return t;
 }
