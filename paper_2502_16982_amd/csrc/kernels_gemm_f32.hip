@@ -60,7 +60,7 @@ constexpr size_t stage_bytes(bool quarters) { return quarters ? 4 * 64 * ROWF : 
 constexpr size_t kLdsFold = 256 * sizeof(double);            // scratch behind the rings for the folded norm
 constexpr size_t lds_bytes(bool quarters) { return ring_of(quarters) * stage_bytes(quarters); }
 
-template <bool Q>
+template <bool Q, bool LONG>
 __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* __restrict__ probs,
                                                               const GemmTile* __restrict__ tiles, int n_tiles, float beta_acc,
                                                               float beta_e, int alpha_idx, double eps) {
@@ -118,25 +118,35 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
     const unsigned c0 = (unsigned)(((4 * which + fh) ^ fkey) * 16), c1 = (unsigned)(((4 * which + 2 + fh) ^ fkey) * 16);
     read_half(half[which], s + a_base + c0, s + a_base + c1, s + b_base + c0, s + b_base + c1);
   };
-  // Two-level accumulation: acc takes at most kFlush slabs (1024 terms) before it is added to `total`, so the rounding
-  // error of a dot product grows with K / 1024 + 1024 terms instead of K (a single fp32 accumulator over 2^20 squares
-  // drifts by 4e-4 relative).  Two accumulators take turns, so that no MFMA waits for the one before it.
-  constexpr int kFlush = 32;
-  f32x16 acc[2], total;
+  // The order of a dot product's terms belongs to K alone, so that a matrix gets the same bits from whole entries and from
+  // quarters, i.e. in any list: slab i goes to partial sum i % 4 (a quarter's wave holds one of the four, a whole entry's
+  // wave all of them), and the result is (0 + 1) + (2 + 3).  LONG (K > 4096): an accumulator takes at most kFlush slabs
+  // (1024 terms) before it is added to its total, so the rounding error of a dot product grows with K / 4096 + 1024 terms
+  // instead of K / 4 (a single fp32 accumulator over 2^20 squares drifts by 4e-4 relative); below that a total would
+  // receive one addend, so there is none.  One accumulator per partial sum: MFMAs that wait for one another cost nothing
+  // beside the other waves' (16 of 512^2 553 -> 557 us, 4 of 512^2 232 -> 227, 128 x 256 65.1 -> 64.3, against two that
+  // took turns in an order of each form's own); two per partial sum spill in the whole form (602 us).
+  constexpr int kFlush = 32, NP = Q ? 1 : 4;
+  f32x16 acc[NP], total[NP];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[0][v] = acc[1][v] = total[v] = 0.f;
+  for (int c = 0; c < NP; ++c)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[c][v] = total[c][v] = 0.f;
   auto flush = [&]() {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      total[v] += acc[0][v] + acc[1][v];
-      acc[0][v] = acc[1][v] = 0.f;
-    }
+    for (int c = 0; c < NP; ++c)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        total[c][v] += acc[c][v];
+        acc[c][v] = 0.f;
+      }
   };
-  auto mma = [&](const HalfSlab& f) {
+  auto mma = [&](const HalfSlab& f, auto c_tag) {
+    constexpr int c = decltype(c_tag)::value;
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[kk][e], f.b[kk][e], acc[e & 1], 0, 0, 0);
+      for (int e = 0; e < 4; ++e) acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[kk][e], f.b[kk][e], acc[c], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
 
@@ -163,11 +173,13 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
     else wait_vmcnt<0>();
     if (!Q) __builtin_amdgcn_s_barrier();
     read(0, 0);
-    int stage = 0, since = 0;
-    for (int i = 0; i + 1 < n; ++i) {
-      land_half(half[0]);
+    land_half(half[0]);
+    int stage = 0;
+    // slab i with others behind it, and the last one.  The first half is landed where the slab begins: a read in flight
+    // must not cross a branch, where the compiler may move its registers.
+    auto slab = [&](int i, auto c_tag) {
       read(stage, 1);
-      mma(half[0]);
+      mma(half[0], c_tag);
       land_half(half[1]);
       const int next = stage + 1 == NST ? 0 : stage + 1;
       if (Q) {
@@ -182,20 +194,58 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
         if (i + NST < n) request(i + NST, stage);
       }
       read(next, 0);
-      mma(half[1]);
+      mma(half[1], c_tag);
+      land_half(half[0]);
       stage = next;
-      if (++since == kFlush) {
-        since = 0;
-        flush();
+    };
+    auto last_slab = [&](auto c_tag) {
+      read(stage, 1);
+      mma(half[0], c_tag);
+      land_half(half[1]);
+      mma(half[1], c_tag);
+    };
+    using P0 = std::integral_constant<int, 0>;
+    using P1 = std::integral_constant<int, Q ? 0 : 1>;
+    using P2 = std::integral_constant<int, Q ? 0 : 2>;
+    using P3 = std::integral_constant<int, Q ? 0 : 3>;
+    int i = 0, since = 0;
+    if constexpr (Q) {
+      for (; i + 1 < n; ++i) {
+        slab(i, P0{});
+        if (LONG && ++since == kFlush) {
+          since = 0;
+          flush();
+        }
+      }
+      last_slab(P0{});
+    } else {                                     // n is even
+      for (; i + 4 < n; i += 4) {
+        slab(i, P0{});
+        slab(i + 1, P1{});
+        slab(i + 2, P2{});
+        slab(i + 3, P3{});
+        if (LONG && ++since == kFlush) {
+          since = 0;
+          flush();
+        }
+      }
+      slab(i, P0{});
+      if (n - i == 2) {
+        last_slab(P1{});
+      } else {
+        slab(i + 1, P1{});
+        slab(i + 2, P2{});
+        last_slab(P3{});
       }
     }
-    land_half(half[0]);
-    read(stage, 1);
-    mma(half[0]);
-    land_half(half[1]);
-    mma(half[1]);
   }
-  flush();
+  if constexpr (LONG) flush();
+  f32x16 sum = LONG ? total[0] : acc[0];         // quarters: this wave's partial sum, added to the others' below
+  if constexpr (!Q) {
+    const f32x16 *const t = LONG ? total : acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sum[v] = (t[0][v] + t[1][v]) + (t[2][v] + t[3][v]);
+  }
 
   // ---- epilogue.  A lane holds column fr, rows 8 q + 4 h + e of its wave's 32 x 32 tile: it goes to LDS as image
   // [column][row].  Quarters: the four waves' partial tiles are added up, one float4 per thread; whole: each wave reads
@@ -212,7 +262,7 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
   float* const img = reinterpret_cast<float*>(smem) + wave * 32 * kImgPitch;
 #pragma unroll
   for (int q = 0; q < 4; ++q)
-    *reinterpret_cast<f32x4*>(img + fr * kImgPitch + 8 * q + 4 * fh) = f32x4{total[4 * q], total[4 * q + 1], total[4 * q + 2], total[4 * q + 3]};
+    *reinterpret_cast<f32x4*>(img + fr * kImgPitch + 8 * q + 4 * fh) = f32x4{sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
   __syncthreads();
   constexpr int NV = Q ? 1 : 4;                  // float4s per thread
   const int sub_r = Q ? 0 : (wave >> 1) * 32, sub_c = Q ? 0 : (wave & 1) * 32;
@@ -259,25 +309,38 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
   }
 }
 
+template <bool LONG>
+hipError_t setup_f32() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_f32_kernel<true, LONG>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_bytes(true) + kLdsFold));
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_f32_kernel<false, LONG>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(false));
+}
+
+template <bool LONG>
+void launch_f32(int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc, float beta_e, int alpha_idx,
+                double eps, hipStream_t s) {
+  if (flags & kGemmQuarters)
+    ns_gemm_f32_kernel<true, LONG><<<(n_tiles + 7) / 8 * 32, 256, lds_bytes(true) + (alpha_idx == kAlphaFromPartials ? kLdsFold : 0), s>>>(
+        probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps);
+  else
+    ns_gemm_f32_kernel<false, LONG><<<n_tiles, 256, lds_bytes(false), s>>>(probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps);
+}
+
 }  // namespace
 
 hipError_t gemm_f32_setup() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_f32_kernel<true>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_bytes(true) + kLdsFold));
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_f32_kernel<false>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(false));
+  const hipError_t e = setup_f32<false>();
+  return e != hipSuccess ? e : setup_f32<true>();
 }
 
 hipError_t launch_gemm_f32(int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc, float beta_e,
                            int alpha_idx, double eps, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
   if (alpha_idx == kAlphaFromPartials && !(flags & kGemmQuarters)) return hipErrorInvalidValue;
-  if (flags & kGemmQuarters)
-    ns_gemm_f32_kernel<true><<<(n_tiles + 7) / 8 * 32, 256, lds_bytes(true) + (alpha_idx == kAlphaFromPartials ? kLdsFold : 0), s>>>(
-        probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps);
-  else
-    ns_gemm_f32_kernel<false><<<n_tiles, 256, lds_bytes(false), s>>>(probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps);
+  if (flags & kGemmLongK) launch_f32<true>(flags, probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, s);
+  else launch_f32<false>(flags, probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, s);
   return hipGetLastError();
 }
 

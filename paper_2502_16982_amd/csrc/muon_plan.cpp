@@ -635,6 +635,8 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
           ts.quarter_poly = runs_in_quarters(sym, w_m, few);
           ts.quarter_apply = runs_in_quarters(app, w_m, few);
         }
+        ts.long_n = !mc && hi_n > kF32LongK;
+        ts.long_m = !mc && hi_m > kF32LongK;
         ts.persistent_n = steady_n;
         ts.persistent_m = steady_m;
         ts.sym = take(n_sym * sizeof(GemmTile));

@@ -34,6 +34,7 @@ struct TileSet {
   // the K loops of the launch's tiles are of nearly the same length (Gram product: n_pad; the other two: m_pad), so
   // the launch runs persistent blocks that take the planner's static assignment of tiles
   bool persistent_n = false, persistent_m = false;
+  bool long_n = false, long_m = false;    // fp32: some K (Gram product: n_pad; the other two: m_pad) is over kF32LongK
   bool quarter_sym = false, quarter_poly = false, quarter_apply = false;   // fine launches that run as one block per quarter of an entry
 };
 

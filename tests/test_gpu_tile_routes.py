@@ -22,13 +22,18 @@ def dev():
     return torch.device("cuda:0")
 
 
-def coarse_tiles(shapes, ns):
+def table_sizes(shapes, ns, level):
+    """Entries of the Gram, polynomial and apply tables of a list that is planned whole."""
     p = binding.param_array(shapes, [1] * len(shapes), [1] * len(shapes))
     ctx = binding.muon_plan_only(p, len(shapes), binding.NS_DTYPES[ns], binding.muon_workspace_bytes(p, len(shapes), binding.NS_DTYPES[ns]))
     try:
-        return [len(binding.muon_plan_tiles(ctx, 0, product, 1)) for product in ("gram", "apply")]
+        return [len(binding.muon_plan_tiles(ctx, 0, product, level)) for product in ("gram", "poly", "apply")]
     finally:
         binding.muon_destroy(ctx)
+
+
+def coarse_tiles(shapes, ns):
+    return table_sizes(shapes, ns, 1)[::2]
 
 
 @pytest.mark.parametrize("ns", ["bf16", "bf16x2", "bf16x3"])
@@ -75,6 +80,30 @@ def test_f32_products_whole_and_in_quarters(dev, copies):
                           w_std=1.0, g_std=1.0, seed_base=330)
     n = len(wl.shapes)
     assert_records(U.run_and_compare(wl, dev, check=list(range(n - len(shapes), n)), steps=2, want_rms=True), 0.1 * U.TOL_F32_FRO)
+
+
+@pytest.mark.parametrize("shape,long", [((100, 320), 120), ((384, 1000), 30), ((520, 130), 70), ((130, 4300), 60)])
+def test_f32_bits_do_not_depend_on_the_list(dev, shape, long):
+    """fp32 path: the order of a dot product's terms belongs to K alone.  A matrix comes out with the same bits alone (quarters),
+    in a list long enough for whole entries, beside a matrix whose K is over 4096 (accumulators with a second level; the last
+    shape needs them itself), and in a workspace that holds a part of the list."""
+    wl = workloads.custom("f32_lists", [shape], w_dtype=torch.float32, g_dtype=torch.float32, ns_dtype="f32", seed_base=335)
+    first = workloads.make_matrix(wl, 0, dev)
+    far = (torch.randn(40, 5000, device=dev), torch.randn(40, 5000, device=dev), torch.zeros(40, 5000, device=dev))
+    hp = binding.default_hparams(lr=0.02, weight_decay=0.1)
+    assert min(table_sizes([shape] * long, "f32", 0)) > 320         # more than a launch that runs in quarters holds
+    results = []
+    for n, extra, parts in ((1, 0, 1), (1, 1, 1), (long, 0, 1), (long, 1, 1), (long, 0, 5)):
+        tensors = [tuple(t.clone() for t in first) for _ in range(n)] + [tuple(t.clone() for t in far)] * extra
+        whole = binding.MuonStepper(tensors, ns_dtype="f32").workspace_bytes
+        st = binding.MuonStepper(tensors, ns_dtype="f32", max_workspace_bytes=0 if parts == 1 else whole // parts)
+        assert (binding.muon_plan_chunks(st.ctx) > 1) == (parts > 1)
+        st.step(hp)
+        torch.cuda.synchronize()
+        results += [(n, extra, parts, i, tensors[i][0], tensors[i][2]) for i in {0, n // 2, n - 1}]
+        st.close()
+    for n, extra, parts, i, w, m in results[1:]:
+        assert torch.equal(m, results[0][5]) and torch.equal(w, results[0][4]), (n, extra, parts, i)
 
 
 @pytest.mark.parametrize("dtypes", [(torch.bfloat16, torch.bfloat16), (torch.float32, torch.bfloat16), (torch.bfloat16, torch.float32)])
