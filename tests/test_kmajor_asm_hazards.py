@@ -1,6 +1,6 @@
-"""The K-major GEMM path reads its LDS fragments from inline assembly with hand-placed waits.  The source ties each
-result to the wait that covers it; this test compiles the kernel file to gfx950 assembly (no GPU needed) and checks the
-generated code itself: no instruction touches the destination of an LDS read that no `s_waitcnt lgkmcnt` has retired
+"""The GEMM kernels read LDS fragments from inline assembly with hand-placed waits (the K-major path, the 64-wide tile and the
+fp32 products).  The source ties each result to the wait that covers it; this test compiles the kernel files to gfx950
+assembly (no GPU needed) and checks the generated code itself: no instruction touches the destination of an LDS read that no `s_waitcnt lgkmcnt` has retired
 yet, on any path through any of the kernels.  Planted mistakes show that the checker sees one when it is there."""
 import os
 import re
@@ -56,14 +56,22 @@ kern:
     assert hz.check_file_text(with_smem) == {"kern": []}
 
 
-@pytest.fixture(scope="module")
-def gemm_asm(tmp_path_factory):
-    out = tmp_path_factory.mktemp("asm") / "kernels_gemm_bf16.s"
-    cmd = [build.hipcc_path(), *build.HIPCC_FLAGS, "-S", "--cuda-device-only",
-           os.path.join(build.CSRC, "kernels_gemm_bf16.hip"), "-o", str(out)]
+def compile_to_asm(tmp_path_factory, source):
+    out = tmp_path_factory.mktemp("asm") / (source + ".s")
+    cmd = [build.hipcc_path(), *build.HIPCC_FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", str(out)]
     proc = subprocess.run(cmd, capture_output=True, text=True, cwd=str(out.parent))
     assert proc.returncode == 0, proc.stderr[-2000:]
     return out.read_text()
+
+
+@pytest.fixture(scope="module")
+def gemm_asm(tmp_path_factory):
+    return compile_to_asm(tmp_path_factory, "kernels_gemm_bf16.hip")
+
+
+@pytest.fixture(scope="module")
+def gemm_f32_asm(tmp_path_factory):
+    return compile_to_asm(tmp_path_factory, "kernels_gemm_f32.hip")
 
 
 def test_generated_gemm_code_waits_for_every_lds_read_it_uses(gemm_asm):
@@ -93,4 +101,15 @@ def test_generated_code_of_the_64_wide_tile_waits_for_every_lds_read_it_uses(gem
     assert len(kernels) == 6                     # {k-contiguous, K-major} x {1, 2, 3} planes
     for name, lines in kernels.items():
         assert any("ds_read_b128" in t for _, t in lines)
+        assert hz.check_kernel(lines) == [], name
+
+
+def test_generated_code_of_the_fp32_products_waits_for_every_lds_read_it_uses(gemm_f32_asm):
+    """Its fragments are read while others are multiplied, also at the end of a slab for the next one: a read that crosses a
+    branch in flight can have its registers copied before it has landed."""
+    kernels = {k: v for k, v in hz.split_kernels(gemm_f32_asm).items() if "ns_gemm_f32" in k}
+    assert len(kernels) == 4                     # {whole entries, quarters} x {short, long K}
+    for name, lines in kernels.items():
+        assert sum("ds_read_b128" in t for _, t in lines) >= 8
+        assert not any("scratch_" in t for _, t in lines), name          # no spills
         assert hz.check_kernel(lines) == [], name
