@@ -199,22 +199,65 @@ size_t deal_tiles(const std::vector<int>& order, const std::vector<std::vector<G
 // odd widths); long lists are within 3 % of runs of one, whose table would be four times as long.
 int ew_run(size_t tiles) { return (int)std::min<size_t>((size_t)kEwRun, std::max<size_t>(1, tiles / 2048)); }
 
-// Whether a product goes to the fine launch altogether: its coarse tiles (256 x 256, one block per compute unit) are so
-// few that they leave much of the chip idle.  Measured, us per launch, coarse / fine (128 x 128, or their quarters):
-//   Gram and polynomial: 2048^2 (36 tiles) 45 / 24, 3584^2 (105) 69 / 56, 4096^2 (136) 83 / 102; with a short K the line
-//   lies at one full round of coarse tiles: 16 of 1024^2 (160) 35 / 33, 12 of 2048 x 1408 (216) 68 / 67 and 56 / 51,
-//   84 of 1024^2 (840) 141 / 143.
-//   Apply: 2048^2 (64) 44 / 26, two of 1024 x 4096 (128) 31 / 24, six ragged ones up to 1000 x 3001 (132, with what the coarse
-//   tiles leave) 38 / 22, 3072^2 (144) 63 / 78, four of 2048 x 1408 (176) 41 / 42, four of 1024 x 4096 (256) 38 / 41.
-// With several planes the coarse tiles' epilogue spills (about 50 us a tile, against 10 in plain bf16), and long K loops
-// are what pays for it: two planes, coarse / fine: Gram product of 48 of 1024^2 274 / 216, 24 of 1024 x 4096 439 / 397, 16 of
-// 2048^2 541 / 464, 4096^2 277 / 290; apply product of 48 of 1024^2 406 / 362, 24 of 1024 x 4096 761 / 689, 4 of 2048^2 210 / 212,
-// 16 of 2048^2 825 / 854, 4096^2 355 / 398; three planes: Gram of 16 of 2048^2 988 / 944, apply 1590 / 1732.
-bool few_coarse_sym(size_t tiles, int64_t longest_k, int64_t largest_m, int planes) {
-  return tiles < 112 || (tiles < 256 && longest_k <= 2048) || (planes > 1 && largest_m < 3072);
+// The coarse tiles (256 x 256, strips among them) a product's outputs hold, and what their matrices are like on average,
+// each tile counted once: sides and area.
+struct CoarseLoad {
+  size_t tiles = 0;
+  double m = 0.0, n = 0.0, area = 0.0;
+  void add(size_t t, double rows, double cols) {
+    if (t == 0) return;
+    tiles += t;
+    const double w = (double)t / (double)tiles;
+    m += w * (rows - m);
+    n += w * (cols - n);
+    area += w * (rows * cols - area);
+  }
+  // share of the blocks that have a tile, over the rounds of `blocks` tiles
+  double fill(int blocks) const {
+    const size_t b = (size_t)std::max(blocks, 1);
+    return (double)tiles / (double)((tiles + b - 1) / b * b);
+  }
+};
+
+// Whether a product goes to the fine launch altogether: its coarse tiles (one block per compute unit, `blocks` at a time)
+// are too few, or cannot pay for their epilogue.  Averages over the tiles, not extremes of the list: one large or long
+// matrix more does not move all the others.  Measured, us per launch, coarse / fine (128 x 128, or their quarters).
+// Plain bf16, Gram and polynomial: 2048^2 (36 tiles) 45 / 24, 3584^2 (105) 69 / 56, 4096^2 (136) 83 / 102.  Up to one full round
+// small matrices stay fine a little longer: 16 of 1024^2 (160) 35 / 33 and 39 / 34, 25 of 1024^2 (250) 46 / 43 and 49 / 43,
+// 12 of 2048 x 1408 (216) 68 / 67 and 56 / 51; but 8 of 2048 x 1536 (168) 53 / 56 and 48 / 46, 4 of 2048^2 (144) 50 / 56 and
+// 53 / 58, 7 of 2048^2 (252) 67 / 73 and 70 / 75.
+// With several planes the coarse epilogue spills (about 50 us a tile at two planes, 70 at three, against 10 in plain
+// bf16), and what pays for it are long K loops of large matrices in well-filled rounds.  Gram and polynomial together,
+// two planes: 48 of 1024^2 553 / 437, 24 of 1024 x 4096 608 / 514, 25 of 1024 x 8192 992 / 963, 7 of 2048^2 443 / 405, 8 of 2560^2
+// 1003 / 941, 7 of 2688 x 3200 1093 / 1042, 6 of 1536 x 8192 (126 tiles) 734 / 483, 4 of 2048 x 4096 471 / 442, 7 598 / 607 (the line
+// errs); 12 of 1536 x 6144 780 / 797, 12 of 1536 x 8192 929 / 990, 4 of 2048 x 8192 732 / 786, 7 923 / 1026, 16 2321 / 2413, 4 of
+// 2560 x 5120 674 / 714, 4 of 2560 x 10240 1084 / 1224, 4096^2 531 / 571.  Three planes: 48 of 1024^2 959 / 822, 24 of 1024 x 4096
+// 1118 / 1032, 6 of 2304^2 (270 tiles) 1112 / 1171 (errs); 14 of 2048^2 (504: two full rounds) 1630 / 1667, 25 of 1024 x 8192
+// 1901 / 1939, 12 of 1536 x 6144 1511 / 1629, 7 of 2048 x 4096 1132 / 1250, 4 of 2560^2 895 / 974.  A round that is little more than
+// half full is not worth it below m = 3072: 4 of 2816 x 11008 (264) 1481 / 1415 and 3009 / 2967.
+// 48 of 1024^2 beside one 3072^2: 1438 / 1118 and 2858 / 2350.
+bool few_coarse_sym(const CoarseLoad& c, int planes, int blocks) {
+  if (c.tiles < 112) return true;
+  if (planes == 1) return c.tiles < 256 && c.n <= 2048 && c.area <= 3.0 * (1 << 20);
+  if (c.m >= 3072) return false;
+  const double fill = c.fill(blocks);
+  if (planes == 3 && fill >= 0.9 && c.m >= 2048) return false;
+  return fill < 0.55 || fill * c.area < (planes == 2 ? 8.5 : 5.0) * (1 << 20);
 }
-bool few_coarse_apply(size_t tiles, int64_t largest_m, int planes) {
-  return tiles <= 128 || (tiles < 176 && largest_m <= 1536) || (planes > 1 && largest_m <= 1536);
+// Apply product, plain bf16: 2048^2 (64 tiles) 44 / 26, two of 1024 x 4096 (128: a full round of fine tiles) 31 / 24, 8 of 1024^2 (128)
+// 31 / 23, 4 of 512 x 4096 23 / 16; with a short K (m) a little beyond it: 5 of 256 x 8192 (160) 21 / 15, 5 of 512 x 4096 (160)
+// 23 / 20, 3 of 640 x 5120 (150) 27 / 24, 4 of 768 x 3072 (144) 27 / 26, 10 of 1024^2 (160) 31 / 32, 4 of 1000 x 2500 (160) 31 / 31; but
+// 3 of 1280 x 2560 (150) 36 / 38, 4 of 1536^2 (144) 39 / 43, 3072^2 (144) 63 / 78, four of 1024 x 4096 (256) 38 / 41.
+// Two planes: 48 of 1024^2 397 / 356, 24 of 1024 x 4096 741 / 674, 12 of 1536^2 320 / 296, 16 of 2048 x 1408 462 / 414, 8 of
+// 1280 x 10240 910 / 873, 4 of 2048^2 203 / 202, 16 of 2048 x 8192 3115 / 3318, 4096^2 340 / 381; three planes: 24 of 1024 x 4096
+// 1428 / 1327, 24 of 1536^2 1259 / 1134, 7 of 2048^2 728 / 771, 4 of 2560^2 872 / 936.
+// At m = 1536 the largest are even in full rounds (two planes: 12 of 1536 x 6144 1129 / 1109, of 1536 x 8192 1445 / 1435; three: 2231 / 2254 and
+// 2858 / 2899), but the other launches of the step are quicker beside coarse ones, which draw less power: 12 of 1536 x 8192
+// 12.75 -> 12.6 ms and 25.2 -> 24.3 ms (6 of them, rounds 90 % full: 756 / 708, 1465 / 1436), 12 of 1536 x 6144 with three planes 19.7 -> 19.2 ms.
+bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
+  if (c.tiles <= 128 || (c.tiles < 176 && c.m <= 1024)) return true;
+  if (planes == 1 || c.m > 1536) return false;
+  return c.m <= 1280 || c.area < (planes == 2 ? 10.0 : 8.0) * (1 << 20) || c.fill(blocks) < 0.95;
 }
 
 // Whether a fine launch runs each entry as four blocks, one per quarter.  bf16: 64 x 64 blocks of a 128 x 128 entry, which are quicker through one tile (0.35
@@ -560,18 +603,17 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         lo_m = std::min(lo_m, w_m[k]); hi_m = std::max(hi_m, w_m[k]);
       }
       const bool steady_n = 2 * hi_n <= 3 * lo_n, steady_m = 2 * hi_m <= 3 * lo_m;
-      size_t coarse_sym = 0, coarse_app = 0;
+      CoarseLoad coarse_sym, coarse_app;
       for (size_t k = 0; mc && k < np_; ++k) {
         const MatPlan& q = plan.mats[members[k]];
         const size_t cm = (size_t)(q.mp / kCoarse), cn = (size_t)(q.np / kCoarse);
         const int strip_h = kShapeRows[kShape512x128];
         const bool odd_m = (q.mp % kCoarse) != 0;
-        coarse_sym += cm * (cm + 1) / 2 + (odd_m && q.mp >= strip_h ? (size_t)((q.mp + strip_h - 1) / strip_h) : 0);
-        coarse_app += cm * cn + (odd_m && q.np >= strip_h ? (size_t)((q.np + strip_h - 1) / strip_h) : 0);
+        coarse_sym.add(cm * (cm + 1) / 2 + (odd_m && q.mp >= strip_h ? (size_t)((q.mp + strip_h - 1) / strip_h) : 0), q.mp, q.np);
+        coarse_app.add(cm * cn + (odd_m && q.np >= strip_h ? (size_t)((q.np + strip_h - 1) / strip_h) : 0), q.mp, q.np);
       }
-      const int64_t largest_m = *std::max_element(w_m.begin(), w_m.end());
-      const bool few_sym = few_coarse_sym(coarse_sym, *std::max_element(w_n.begin(), w_n.end()), largest_m, (int)planes);
-      const bool few_app = few_coarse_apply(coarse_app, largest_m, (int)planes);
+      const bool few_sym = few_coarse_sym(coarse_sym, (int)planes, plan.coarse_blocks);
+      const bool few_app = few_coarse_apply(coarse_app, (int)planes, plan.coarse_blocks);
       std::vector<std::vector<GemmTile>> moved_sym(np_), moved_app(np_);   // coarse tiles handed to the fine level
       for (int level = 1; level >= 0; --level) {
         if (level == 1 && !mc) continue;

@@ -268,3 +268,51 @@ def test_tiles_that_run_together_on_a_die_share_operand_panels(shape, product):
             assert len({t[1] for t in first}) + len({t[2] for t in first}) == 12
     finally:
         binding.lib().muon_destroy(ctx)
+
+
+def coarse_counts(shapes, ns):
+    ctx, _ = plan(shapes, ns)
+    try:
+        return tuple(len(binding.muon_plan_tiles(ctx, 0, product, 1)) for product in ("gram", "apply"))
+    finally:
+        binding.lib().muon_destroy(ctx)
+
+
+@pytest.mark.parametrize("ns,shapes,gram,apply", [
+    # plain bf16: below one full round of coarse tiles only small matrices are quicker in fine tiles
+    (binding.MUON_BF16, [(1024, 1024)] * 16, False, True),
+    (binding.MUON_BF16, [(2048, 2048)] * 4, True, True),
+    (binding.MUON_BF16, [(1536, 2048)] * 8, False, True),
+    (binding.MUON_BF16, [(1792, 2048)] * 6, True, True),
+    (binding.MUON_BF16, [(1536, 1536)] * 4, False, True),
+    (binding.MUON_BF16, [(1280, 2560)] * 3, False, True),
+    (binding.MUON_BF16, [(256, 8192)] * 5, False, False),
+    # planes: long K loops of large matrices in well-filled rounds pay for the coarse epilogue
+    (binding.MUON_BF16X2, [(1024, 1024)] * 48, False, False),
+    (binding.MUON_BF16X2, [(1024, 4096)] * 24, False, False),
+    (binding.MUON_BF16X2, [(1536, 8192)] * 6, False, False),
+    (binding.MUON_BF16X2, [(1536, 8192)] * 12, True, True),
+    (binding.MUON_BF16X2, [(1280, 10240)] * 8, False, False),
+    (binding.MUON_BF16X2, [(1536, 6144)] * 12, True, False),
+    (binding.MUON_BF16X2, [(2048, 2048)] * 7, False, True),
+    (binding.MUON_BF16X2, [(2688, 3200)] * 7, False, True),
+    (binding.MUON_BF16X2, [(2048, 8192)] * 4, True, True),
+    (binding.MUON_BF16X2, [(2560, 10240)] * 4, True, True),
+    (binding.MUON_BF16X2, [(2816, 11008)] * 4, False, True),
+    (binding.MUON_BF16X2, [(4096, 4096)], True, True),
+    (binding.MUON_BF16X3, [(2048, 2048)] * 7, True, True),
+    (binding.MUON_BF16X3, [(2048, 4096)] * 7, True, True),
+    (binding.MUON_BF16X3, [(2560, 2560)] * 4, True, True),
+    (binding.MUON_BF16X3, [(1024, 4096)] * 24, False, False),
+])
+def test_coarse_tiles_where_they_were_measured_to_be_quicker(ns, shapes, gram, apply):
+    assert tuple(c > 0 for c in coarse_counts(shapes, ns)) == (gram, apply)
+
+
+def test_one_more_matrix_does_not_move_all_the_others():
+    """The choice between the launches goes by what the coarse tiles are like on average, not by the list's extremes."""
+    for ns in (binding.MUON_BF16X2, binding.MUON_BF16X3):
+        assert coarse_counts([(1024, 1024)] * 48, ns) == (0, 0)
+        assert coarse_counts([(1024, 1024)] * 48 + [(3072, 3072)], ns) == (0, 0)
+    assert coarse_counts([(1024, 1024)] * 16, binding.MUON_BF16) == (0, 256)
+    assert coarse_counts([(1024, 1024)] * 16 + [(16, 2100)], binding.MUON_BF16)[0] == 0
