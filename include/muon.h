@@ -171,8 +171,9 @@ int muon_debug_read_update(muon_ctx* ctx, int32_t index, void* dst, int32_t dst_
 
 /*
  * Plan introspection (host only, no device work): writes up to `cap` int64 values describing matrix
- * `index`: {m, n, transposed, m_pad, n_pad, chunk, tile_m, tile_n}.  Returns the number written or
- * a negative status.
+ * `index`: {m, n, transposed, m_pad, n_pad, chunk, tile_m, tile_n}; tile_n is the side of the fine tile, tile_m
+ * 256 where the plan computes some of the matrix's products in coarse tiles and tile_n where it does not.
+ * Returns the number written or a negative status.
  */
 int muon_plan_describe(const muon_ctx* ctx, int32_t index, int64_t* out, int32_t cap);
 

@@ -460,8 +460,7 @@ int muon_debug_read_update(muon_ctx* ctx, int32_t index, void* dst, int32_t dst_
 int muon_plan_describe(const muon_ctx* ctx, int32_t index, int64_t* out, int32_t cap) {
   if (!ctx || !out || index < 0 || index >= ctx->n || cap < 0) return MUON_E_INVALID_ARG;
   const MatPlan& q = ctx->plan.mats[index];
-  const int coarse = on_matrix_cores(ctx->ns_dtype) && q.mp >= kCoarse ? kCoarse : q.tile;
-  const int64_t v[8] = {q.m, q.n, q.transposed, q.mp, q.np, q.chunk, coarse, q.tile};
+  const int64_t v[8] = {q.m, q.n, q.transposed, q.mp, q.np, q.chunk, q.coarse ? kCoarse : q.tile, q.tile};
   const int k = std::min<int>(cap, 8);
   for (int i = 0; i < k; ++i) out[i] = v[i];
   return k;

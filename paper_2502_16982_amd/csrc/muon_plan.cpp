@@ -304,6 +304,7 @@ void plan_matrices(const muon_param* p, int n, int ns_dtype, std::vector<MatPlan
     q.part_off = total_partials;
     total_partials += (size_t)q.ew_tr * q.ew_tc;
     q.chunk = 0;
+    q.coarse = false;
   }
 }
 
@@ -668,6 +669,7 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         for (size_t k = 0; k < np_; ++k) {
           n_sym += sym[k].size();
           n_app += app[k].size();
+          if (level == 1) plan.mats[members[k]].coarse = !sym[k].empty() || !app[k].empty();
         }
         TileSet& ts = level ? g.coarse : g.fine;
         ts.strips = strips;

@@ -21,6 +21,7 @@ struct MatPlan {
   int w_dtype, g_dtype;
   int tile;         // fine GEMM block tile = padding granule, in elements
   int chunk;
+  bool coarse;      // some of its outputs are computed in coarse tiles
   int ew_tr, ew_tc; // 64x64 tiles in U's orientation (padded)
   size_t ns_bytes;  // X + Xt[0] (+ Xt[1], see x_buffers) + Ag + Bp
   size_t part_off;  // first partial (floats)

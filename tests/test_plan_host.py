@@ -152,6 +152,20 @@ def test_orientation_padding_and_tile_sizes():
         binding.lib().muon_destroy(ctx)
 
 
+def test_described_tile_is_one_the_plan_uses():
+    for shapes, ns in (([(1024, 1024)], binding.MUON_BF16), ([(4096, 4096), (100, 130), (384, 640)], binding.MUON_BF16),
+                       ([(1024, 1024)] * 48, binding.MUON_BF16X2), ([(512, 512)], binding.MUON_F32)):
+        ctx, _ = plan(shapes, ns)
+        try:
+            for i in range(len(shapes)):
+                used = {t[3] for product in ("gram", "poly", "apply") for level in (0, 1)
+                        for t in binding.muon_plan_tiles(ctx, 0, product, level) if t[0] == i}
+                d = binding.muon_plan_describe(ctx, i)
+                assert d["tile_m"] == (256 if used & {256, 512} else d["tile_n"]), (shapes, i, used)
+        finally:
+            binding.lib().muon_destroy(ctx)
+
+
 def test_chunked_plan_keeps_each_matrix_in_one_chunk():
     shapes = [(256, 384)] * 5 + [(384, 256)] * 3
     n = len(shapes)
