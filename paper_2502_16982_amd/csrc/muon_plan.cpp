@@ -396,7 +396,9 @@ int plan_workspace_bytes(const muon_param* shapes, int32_t n, int32_t ns_dtype, 
 int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype, uintptr_t ws_base, size_t workspace_bytes) {
   int st = validate_shapes(shapes, n, ns_dtype);
   if (st != MUON_OK) return st;
+  const int coarse_blocks = plan.coarse_blocks;
   plan = Plan{};
+  plan.coarse_blocks = coarse_blocks;
   plan.n = n;
   plan.ns_dtype = ns_dtype;
   size_t total_partials = 0;

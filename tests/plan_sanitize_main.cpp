@@ -192,6 +192,19 @@ int main() {
       CHECK(plan_build(small, p.data(), n, ns, uintptr_t{1} << 40, least - 4096) == MUON_E_WORKSPACE_TOO_SMALL);
     }
   }
+  // the planner works for the number of compute units it is given: 360 Gram tiles leave 8 over on 32 units, which go to
+  // the fine launch, and 104 on 256, too many to move
+  for (int blocks : {32, 256}) {
+    const std::vector<muon_param> p = params_of(Shapes(10, {2048, 2048}));
+    size_t bytes = 0;
+    CHECK(plan_workspace_bytes(p.data(), 10, MUON_BF16, 0, &bytes) == MUON_OK);
+    Plan plan;
+    plan.coarse_blocks = blocks;
+    CHECK(plan_build(plan, p.data(), 10, MUON_BF16, uintptr_t{1} << 40, bytes) == MUON_OK);
+    CHECK(plan.coarse_blocks == blocks);
+    const int sym = plan.chunks[0].groups[0].coarse.n_sym;        // 360 of them
+    CHECK(sym == (blocks == 32 ? 352 : 360));
+  }
   // rejected inputs
   {
     Plan plan;
