@@ -215,7 +215,7 @@ int muon_plan_tiles(const muon_ctx* ctx, int32_t chunk, int32_t product, int32_t
  */
 enum {
   MUON_PROF_MOMENTUM = 0,   /* momentum + sum of squares + cast/orient        */
-  MUON_PROF_NORM = 1,       /* norm finalisation                              */
+  MUON_PROF_NORM = 1,       /* norm finalisation; no launch of its own for short lists, whose first Gram launch does it */
   MUON_PROF_GRAM = 2,       /* A = X X^T                                      */
   MUON_PROF_POLY = 3,       /* B = b A + c A A                                */
   MUON_PROF_APPLY_POLY = 4, /* X = a X + B X                                  */

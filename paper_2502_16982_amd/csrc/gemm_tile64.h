@@ -178,7 +178,7 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
   if (!LKM && alpha_idx == kAlphaFromPartials) {
     // first Gram product: the norm, from the partial sums (K-major launches are never first)
     float s, s2;
-    norm_scalars(block_sum_f64(static_cast<const float*>(p.E), p.lde, reinterpret_cast<double*>(smem + kLdsRing64)), eps, &s, &s2);
+    norm_scalars(block_sum_f64(p.partials, p.n_part, reinterpret_cast<double*>(smem + kLdsRing64)), eps, &s, &s2);
     if (row0 == 0 && col0 == 0 && tid == 0) {
       float* scal = const_cast<float*>(p.scal);
       scal[0] = s;

@@ -1,6 +1,6 @@
 // fp32 Newton-Schulz products for gfx950 (Eq. 2 of the paper), used when the caller asks for fp32 iteration
 // arithmetic: grouped "NT" GEMM  C[i][j] = sum_k L[i][k] * R[j][k]  with the same problem/tile tables and
-// fused epilogue  val = alpha * (beta_acc * acc + beta_e * E[i][j])  as the bf16 MFMA kernel.
+// fused epilogue  val = alpha * (beta_acc * acc + beta_e * Et[j][i])  as the bf16 MFMA kernel.
 //
 // The products run on v_mfma_f32_32x32x2_f32 (fp32 operands, fp32 accumulation; twice the rate of unpacked fp32 FMAs,
 // and a fragment read from LDS feeds 32 multiply-adds instead of 4).  Operands come through the LDS-DMA path into a ring
@@ -157,7 +157,7 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
   if (Q && alpha_idx == kAlphaFromPartials) {
     // first Gram product: the norm, from the partial sums
     float s, s2;
-    norm_scalars(block_sum_f64(static_cast<const float*>(p.E), p.lde, reinterpret_cast<double*>(smem + lds_bytes(true))), eps, &s, &s2);
+    norm_scalars(block_sum_f64(p.partials, p.n_part, reinterpret_cast<double*>(smem + lds_bytes(true))), eps, &s, &s2);
     if (row0 == 0 && col0 == 0 && tid == 0) {
       float* scal = const_cast<float*>(p.scal);
       scal[0] = s;

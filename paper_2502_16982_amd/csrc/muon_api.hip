@@ -224,14 +224,12 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
         }
         for (int level = 1; level >= 0; --level) {
           const TileSet& ts = level ? g.coarse : g.fine;
-          const size_t t_app = last ? ts.apply_last : ts.apply;
-          const int n_app = last ? ts.n_apply_last : ts.n_apply;
-          if (n_app == 0) continue;
+          if (ts.n_apply == 0) continue;
           if (mc)
-            MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | (ts.quarter_apply ? kGemmQuarters : 0), P(g.prob_apply[par * 2 + last]), T(t_app),
-                                                              n_app, 1.f, a, first ? 0 : -1, 0.0, 0.f, 1, planes, s));
+            MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | (ts.quarter_apply ? kGemmQuarters : 0), P(g.prob_apply[par * 2 + last]), T(ts.apply),
+                                                              ts.n_apply, 1.f, a, first ? 0 : -1, 0.0, 0.f, 1, planes, s));
           else
-            MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_f32((ts.quarter_apply ? kGemmQuarters : 0) | (ts.long_m ? kGemmLongK : 0), P(g.prob_apply[par * 2 + last]), T(t_app), n_app, 1.f, a,
+            MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_f32((ts.quarter_apply ? kGemmQuarters : 0) | (ts.long_m ? kGemmLongK : 0), P(g.prob_apply[par * 2 + last]), T(ts.apply), ts.n_apply, 1.f, a,
                                                              first ? 0 : -1, 0.0, s));
         }
       }

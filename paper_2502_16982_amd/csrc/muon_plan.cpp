@@ -260,15 +260,14 @@ bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
   return c.m <= 1280 || c.area < (planes == 2 ? 10.0 : 8.0) * (1 << 20) || c.fill(blocks) < 0.95;
 }
 
-// Whether a fine launch runs each entry as four blocks, one per quarter.  bf16: 64 x 64 blocks of a 128 x 128 entry, which are quicker through one tile (0.35
-// against 0.6 us per 64 of K) but need more of the compute unit for the same work: while the launch holds less work
-// than about 176 tiles of its longest K.  Measured, us per launch, 128 / 64: Gram product of 1024^2 (36 tiles) 16.2 / 10.4,
+// Whether a fine launch runs each entry as four blocks, one per quarter.  bf16: 64 x 64 blocks of a 128 x 128 entry, which
+// are quicker through one tile (0.35 against 0.6 us per 64 of K) but need more of the compute unit for the same work: while
+// the launch holds less work than about 176 tiles of its longest K.  Measured, us per launch, 128 / 64: Gram product of 1024^2 (36 tiles) 16.2 / 10.4,
 // four of 1024 x 4096 (144) 42 / 39, four of 2048 x 1408 (264) 31 / 34; apply product of 1024^2 (64) 14.6 / 9.9, of
 // 32 of 256 x 384 (192) 8.4 / 8.0, of four of 1024^2 (256) 16.3 / 18.2.
 // fp32 launches run their 64 x 64 entries as four blocks of 32 x 32 up to about 320 entries.  Measured, whole / quarters:
 // Gram product of 1024^2 (136) 26 / 21.5, of 64 of 128 x 256 (192) 11.9 / 11.3, of 16 of 512^2 (576) 34.1 / 34.4; apply product
 // of 1024^2 (256) 27.7 / 27.6, of 64 of 128 x 256 (512) 13.6 / 17.7.
-constexpr int kMaxFoldedPartials = 1024;
 constexpr int kFewFine = 176, kFewF32 = 320;
 bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int few) {
   int64_t longest = 0, total = 0;
@@ -313,7 +312,8 @@ struct TableLayout {
   size_t mats, ptrs, scal, partials, ew_tiles, gemm, total;
 };
 
-// No tile shape is smaller than the fine tile, so the fine-tile counts bound the table sizes.
+// No tile shape is smaller than the fine tile, so the fine-tile counts bound the table sizes.  (An upper bound: there is one
+// apply table, not two, but callers' workspaces are sized by this.)
 size_t gemm_tables_bytes_for(const MatPlan& q) {
   const int tm = q.mp / q.tile, tn = q.np / q.tile;
   const size_t sym = (size_t)tm * (tm + 1) / 2 + 1, app = (size_t)tm * tn + 1;
@@ -533,14 +533,15 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         void* const xbuf[2] = {d.X, mc ? d.Xt[0] : d.X};
         // Gram: A = X X^T
         for (int par = 0; par < 2; ++par) {
-          gp.L = xbuf[par]; gp.R = xbuf[par]; gp.E = d.partials; gp.Et = nullptr; gp.C = d.Ag; gp.Ct = nullptr;
-          gp.K = q.np; gp.ldl = q.np; gp.ldr = q.np; gp.lde = d.n_part; gp.ldet = 0; gp.ldc = q.mp; gp.ldct = q.mp; gp.symmetric = 1;
+          gp.L = xbuf[par]; gp.R = xbuf[par]; gp.partials = d.partials; gp.Et = nullptr; gp.C = d.Ag; gp.Ct = nullptr;
+          gp.K = q.np; gp.ldl = q.np; gp.ldr = q.np; gp.n_part = d.n_part; gp.ldet = 0; gp.ldc = q.mp; gp.ldct = q.mp; gp.symmetric = 1;
           gp.l_plane = xpl; gp.r_plane = xpl; gp.et_plane = 0; gp.c_plane = apl; gp.ct_plane = apl;
           reinterpret_cast<GemmProblem*>(img.data() + g.prob_gram[par])[k] = gp;
         }
         // polynomial: B = b A + c A A  (A is symmetric, so it is its own transposed addend)
-        gp.L = d.Ag; gp.R = d.Ag; gp.E = d.Ag; gp.Et = d.Ag; gp.C = d.Bp; gp.Ct = nullptr;
-        gp.K = q.mp; gp.ldl = q.mp; gp.ldr = q.mp; gp.lde = q.mp; gp.ldet = q.mp; gp.ldc = q.mp; gp.ldct = q.mp; gp.symmetric = 1;
+        gp.partials = nullptr; gp.n_part = 0;
+        gp.L = d.Ag; gp.R = d.Ag; gp.Et = d.Ag; gp.C = d.Bp; gp.Ct = nullptr;
+        gp.K = q.mp; gp.ldl = q.mp; gp.ldr = q.mp; gp.ldet = q.mp; gp.ldc = q.mp; gp.ldct = q.mp; gp.symmetric = 1;
         gp.l_plane = apl; gp.r_plane = apl; gp.et_plane = apl; gp.c_plane = apl; gp.ct_plane = apl;
         gp.diag_add = folds_identity(q, ns_dtype) ? 1 : 0;
         reinterpret_cast<GemmProblem*>(img.data() + g.prob_poly)[k] = gp;
@@ -554,7 +555,6 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
               // Only the last iteration of a matrix iterated on its transpose needs T as it is (O in W's
               // orientation), through the kernel's other output, into Xt[1].
               gp.L = xbuf[par]; gp.R = d.Bp; gp.K = q.mp; gp.ldl = q.np; gp.ldr = q.mp;
-              gp.E = nullptr; gp.lde = 0;
               gp.Et = folds_identity(q, ns_dtype) ? nullptr : xbuf[par]; gp.ldet = q.np;
               gp.C = nullptr; gp.ldc = 0; gp.Ct = xbuf[par ^ 1]; gp.ldct = q.np;
               if (last && q.transposed) { gp.C = d.Xt[1]; gp.ldc = q.mp; gp.Ct = nullptr; gp.ldct = 0; }
@@ -562,8 +562,8 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
             } else {
               // apply, fp32: X' = a X + B X, reading X^T from Xt[p], writing X in place and X'^T to Xt[p^1]; the last
               // iteration writes only the layout W needs.
-              gp.L = d.Bp; gp.R = d.Xt[par]; gp.E = d.X; gp.Et = d.Xt[par]; gp.C = d.X; gp.Ct = d.Xt[par ^ 1];
-              gp.K = q.mp; gp.ldl = q.mp; gp.ldr = q.mp; gp.lde = q.np; gp.ldet = q.mp; gp.ldc = q.np; gp.ldct = q.mp;
+              gp.L = d.Bp; gp.R = d.Xt[par]; gp.Et = d.Xt[par]; gp.C = d.X; gp.Ct = d.Xt[par ^ 1];
+              gp.K = q.mp; gp.ldl = q.mp; gp.ldr = q.mp; gp.ldet = q.mp; gp.ldc = q.np; gp.ldct = q.mp;
               if (last) {
                 if (q.transposed) gp.C = nullptr;
                 else gp.Ct = nullptr;
@@ -687,7 +687,7 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         ts.persistent_m = steady_m;
         ts.sym = take(n_sym * sizeof(GemmTile));
         ts.poly = take(n_sym * sizeof(GemmTile));
-        ts.apply = take(n_app * sizeof(GemmTile));
+        ts.apply = take(n_app * sizeof(GemmTile));      // the last iteration runs the same tiles: only its outputs differ
         // The two symmetric products run the same tiles but not the same K (n for the Gram product, m for the
         // polynomial), so each gets its own table: dealt longest K first and weighted by its own K, and with the costs
         // evened out over a die's blocks where its launch is persistent (where the hardware hands out the blocks the
@@ -696,12 +696,10 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         ts.n_sym = (int)deal_tiles(by_n, sym, sym_cuts, w_n, reinterpret_cast<GemmTile*>(img.data() + ts.sym), steady_n ? slots : 0, level == 0);
         ts.n_poly = (int)deal_tiles(by_m, sym, sym_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.poly), steady_m ? slots : 0, level == 0);
         ts.n_apply = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply), steady_m ? slots : 0, level == 0);
-// the last apply product runs the same tiles (only its outputs differ)
-        ts.apply_last = ts.apply;
-        ts.n_apply_last = ts.n_apply;
       }
       // Lists short enough for quarter blocks save the norm's own launch (about 4 us): every block adds up its matrix's
       // partials, at most four per thread, while its first operands are on their way.
+      constexpr int kMaxFoldedPartials = 1024;
       int most_parts = 0;
       for (int i = ch.first; i < ch.first + ch.count; ++i) most_parts = std::max(most_parts, h_mats[i].n_part);
       ch.fold_norm = g.coarse.n_sym == 0 && g.fine.quarter_sym && most_parts <= kMaxFoldedPartials;
@@ -721,8 +719,8 @@ int64_t plan_tiles(const Plan& plan, int chunk, int product, int level, int32_t*
   const bool mc = on_matrix_cores(plan.ns_dtype);
   for (const Group& g : plan.chunks[chunk].groups) {
     const TileSet& ts = level ? g.coarse : g.fine;
-    const size_t off = product == 0 ? ts.sym : product == 1 ? ts.poly : product == 2 ? ts.apply : ts.apply_last;
-    const int count = product == 0 ? ts.n_sym : product == 1 ? ts.n_poly : product == 2 ? ts.n_apply : ts.n_apply_last;
+    const size_t off = product == 0 ? ts.sym : product == 1 ? ts.poly : ts.apply;
+    const int count = product == 0 ? ts.n_sym : product == 1 ? ts.n_poly : ts.n_apply;
     const GemmTile* t = reinterpret_cast<const GemmTile*>(plan.image.data() + off);
     for (int i = 0; i < count; ++i, ++total) {
       if (total >= cap_records) continue;

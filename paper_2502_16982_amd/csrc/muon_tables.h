@@ -51,21 +51,20 @@ struct EwTile {
 };
 
 // One product  C[i][j] = sum_k L[i][k] * R[j][k]  ("NT": both operands contiguous along k),
-// followed by  val = alpha * (beta_acc * acc + beta_e * E[i][j]) (+ d on the matrix diagonal when diag_add is set;
+// followed by  val = alpha * (beta_acc * acc + beta_e * Et[j][i]) (+ d on the matrix diagonal when diag_add is set;
 // d is a launch argument)  and stores of C and/or its transpose.
 // The bf16 kernel writes Ct straight from the accumulator layout and C through one extra MFMA transpose,
 // so single-output problems are posed with Ct as the output.
 struct GemmProblem {
   const void* L;      // M x K, leading dimension ldl (K-major launches: element (i, k) at L[k * ldl + i])
   const void* R;      // N x K, leading dimension ldr
-  const void* E;      // Gram problems: the partial sums of squares of U (float), `lde` of them; otherwise the M x N addend
-                      // at the output position (may be null), leading dimension lde
-  const void* Et;     // the same addend stored transposed, N x M, leading dimension ldet (bf16 kernel reads this one)
+  const float* partials;  // Gram problems: the n_part partial sums of squares of U
+  const void* Et;     // addend stored transposed, N x M (may be null), leading dimension ldet
   void* C;            // M x N output (may be null), leading dimension ldc
   void* Ct;           // N x M transposed output, leading dimension ldct (the bf16 kernel requires it unless symmetric)
   const float* scal;  // per-matrix scalars (alpha source)
   int32_t K;
-  int32_t ldl, ldr, lde, ldet, ldc, ldct;
+  int32_t ldl, ldr, n_part, ldet, ldc, ldct;
   int32_t symmetric;  // output is symmetric: off-diagonal tiles are also stored mirrored into C
   int32_t diag_add;   // square output only: add the launch's diagonal constant to C[i][i] before rounding
   // split-bf16 launches (every matrix = sum of several bf16 planes): elements from one plane to the next

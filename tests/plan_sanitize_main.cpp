@@ -80,14 +80,15 @@ static void walk(const Plan& plan, uintptr_t base, size_t ws_bytes) {
       for (int v = 0; v < 4; ++v) CHECK(g.prob_apply[v] + pb <= img_bytes);
       for (int level = 0; level < 2; ++level) {
         const TileSet& ts = level ? g.coarse : g.fine;
-        const size_t offs[3] = {ts.sym, ts.apply, ts.apply_last};
-        const int counts[3] = {ts.n_sym, ts.n_apply, ts.n_apply_last};
-        for (int w = 0; w < 3; ++w) {
-          CHECK(offs[w] + sizeof(GemmTile) * (size_t)counts[w] <= img_bytes);
-          const GemmTile* tiles = reinterpret_cast<const GemmTile*>(img + offs[w]);
+        const size_t offs[3] = {ts.sym, ts.apply, ts.poly};
+        const int counts[3] = {ts.n_sym, ts.n_apply, ts.n_poly};
+        for (int v = 0; v < 3; ++v) {
+          const int w = v == 1 ? 1 : 0;          // Gram and polynomial: symmetric outputs
+          CHECK(offs[v] + sizeof(GemmTile) * (size_t)counts[v] <= img_bytes);
+          const GemmTile* tiles = reinterpret_cast<const GemmTile*>(img + offs[v]);
           // per problem: every cell of the output covered
           std::vector<std::vector<unsigned char>> cover(g.n_prob);
-          for (int t = 0; t < counts[w]; ++t) {
+          for (int t = 0; t < counts[v]; ++t) {
             const GemmTile& gt = tiles[t];
             CHECK(gt.prob >= 0 && gt.prob < g.n_prob);
             if (gt.prob < 0 || gt.prob >= g.n_prob) continue;
