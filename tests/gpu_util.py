@@ -40,6 +40,22 @@ def oracle_step(w0, g0, m0, d):
                          hidden_size=d.get("hidden_size") or None, schedule=d.get("coeff_schedule"))
 
 
+def table_sizes(shapes, ns: str, level: int) -> list:
+    """Entries of the Gram, polynomial and apply tables of a list that is planned whole (level 1: coarse launch)."""
+    p = binding.param_array(shapes, [1] * len(shapes), [1] * len(shapes))
+    need = binding.muon_workspace_bytes(p, len(shapes), binding.NS_DTYPES[ns])
+    ctx = binding.muon_plan_only(p, len(shapes), binding.NS_DTYPES[ns], need)
+    try:
+        return [len(binding.muon_plan_tiles(ctx, 0, product, level)) for product in ("gram", "poly", "apply")]
+    finally:
+        binding.muon_destroy(ctx)
+
+
+def coarse_tiles(shapes, ns: str) -> list:
+    """Coarse tiles of the Gram and the apply product."""
+    return table_sizes(shapes, ns, 1)[::2]
+
+
 def rel_fro(x: np.ndarray, ref: np.ndarray) -> float:
     den = np.linalg.norm(ref)
     return float(np.linalg.norm(x - ref) / den) if den > 0 else float(np.linalg.norm(x))

@@ -7,16 +7,19 @@ import pytest
 import torch
 
 from paper_2502_16982_amd import binding, workloads
-from tests.gpu_util import hp_from
+from tests.gpu_util import coarse_tiles, hp_from
 
 pytestmark = pytest.mark.gpu
 
 CASES = {
     "bf16_mixed": dict(shapes=[(128, 256), (384, 256), (200, 136), (256, 640)], ns_dtype="bf16",
                        w_dtype=torch.bfloat16, g_dtype=torch.bfloat16),
-    # two bf16 planes; the 256 x 256 instantiations of this path use per-lane scratch memory in their epilogue
     "bf16x2_mixed": dict(shapes=[(512, 640), (384, 256), (200, 136)], ns_dtype="bf16x2",
                          w_dtype=torch.bfloat16, g_dtype=torch.bfloat16),
+    # two bf16 planes in 256-wide tiles and strips, whose instantiations use per-lane scratch memory in their epilogue,
+    # with a matrix in the fine launch beside them
+    "bf16x2_coarse": dict(shapes=[(3200, 3328), (200, 136), (3328, 3200)], ns_dtype="bf16x2",
+                          w_dtype=torch.bfloat16, g_dtype=torch.bfloat16),
     "f32_single": dict(shapes=[(128, 256)], ns_dtype="f32", w_dtype=torch.float32, g_dtype=torch.float32),
 }
 
@@ -25,6 +28,8 @@ CASES = {
 def test_captured_step_replays_like_eager_steps(case):
     dev = torch.device("cuda:0")
     cfg = CASES[case]
+    if cfg["ns_dtype"] != "f32":
+        assert (min(coarse_tiles(cfg["shapes"], cfg["ns_dtype"])) > 0) == case.endswith("coarse")
     wl = workloads.custom(case, cfg["shapes"], w_dtype=cfg["w_dtype"], g_dtype=cfg["g_dtype"], ns_dtype=cfg["ns_dtype"],
                           seed_base=4200)
     tensors = workloads.make_all(wl, dev)

@@ -75,10 +75,13 @@ def test_bf16_fp32_buffers_and_plain_momentum(dev):
     assert_records(U.run_and_compare(wl, dev, steps=3, hp_over={"nesterov": 0}), U.TOL_BF16_FRO)
 
 
-def test_bf16_large_tile_shapes(dev):
-    # multiples of 256 with m >= 1024 take the 256x256 block tile
-    wl = workloads.custom("tile256", [(1024, 1024), (1024, 1536), (1280, 1024)], seed_base=23)
-    recs = U.run_and_compare(wl, dev, steps=2)
+@pytest.mark.parametrize("copies", [1, 9])
+def test_bf16_large_tile_shapes(dev, copies):
+    """Sides that 256 x 256 tiles cover: three matrices alone run in smaller tiles, a list of them in the large ones."""
+    shapes = [(1024, 1024), (1024, 1536), (1280, 1024)] * copies
+    assert (min(U.coarse_tiles(shapes, "bf16")) > 0) == (copies > 1)
+    wl = workloads.custom("tile256", shapes, seed_base=23)
+    recs = U.run_and_compare(wl, dev, check=range(len(shapes) - 3, len(shapes)), steps=2)
     assert_records(recs, U.TOL_BF16_FRO)
 
 
@@ -188,11 +191,19 @@ def test_split_ragged_shapes(dev, ns):
 
 
 @pytest.mark.parametrize("ns", SPLIT)
+@pytest.mark.timeout(600)
 def test_split_large_tiles_and_strips(dev, ns):
-    # 256x256 tiles, 256-tiles plus 128-wide strips (m = 384, 640), both orientations, fp32 and bf16 buffers
-    wl = workloads.custom("tiles_" + ns, [(1024, 1024), (1024, 1536), (1280, 1024), (384, 640), (640, 1152)], ns_dtype=ns,
-                          seed_base=52)
+    # sides that are even and odd multiples of 128, both orientations, fp32 and bf16 buffers: up to here planes stay in
+    # 128-wide tiles
+    shapes = [(1024, 1024), (1024, 1536), (1280, 1024), (384, 640), (640, 1152)]
+    assert U.coarse_tiles(shapes, ns) == [0, 0]
+    wl = workloads.custom("tiles_" + ns, shapes, ns_dtype=ns, seed_base=52)
     assert_records(U.run_and_compare(wl, dev, steps=2), U.TOL_SPLIT_FRO[ns])
+    # 256-wide tiles and 512 x 128 strips, and a small matrix in the fine launch beside them
+    shapes = [(3200, 3200), (200, 333), (3328, 3200)]
+    assert min(U.coarse_tiles(shapes, ns)) > 0
+    wl = workloads.custom("large_" + ns, shapes, ns_dtype=ns, seed_base=59)
+    assert_records(U.run_and_compare(wl, dev, check=[1, 2]), U.TOL_SPLIT_FRO[ns])
     wl = workloads.custom("tiles32_" + ns, [(300, 500), (512, 256)], w_dtype=torch.float32, g_dtype=torch.float32, ns_dtype=ns,
                           w_std=1.0, g_std=1.0, seed_base=53)
     assert_records(U.run_and_compare(wl, dev, steps=3, hp_over={"nesterov": 0}), U.TOL_SPLIT_FRO[ns])

@@ -1,7 +1,7 @@
 """The planner gives a product 256-, 128- or 64-wide tiles by how much work a launch holds.  Every tile adds an output
 element's products in the same order, so in plain bf16 a matrix must come out with the same bits whichever tiles computed
-it: alone (64-wide), in a short list (128-wide) and in a list long enough for 256-wide tiles and strips (plain bf16 only at these sides).  With several
-planes an element of a symmetric product and its mirror image add the plane pairs in different orders (fp32 rounding,
+it: alone (64-wide), in a short list (128-wide) and in a list long enough for 256-wide tiles and strips (plain bf16 only at
+these sides).  With several planes an element of a symmetric product and its mirror image add the plane pairs in different orders (fp32 rounding,
 about 1e-7 of A per product), and the tile decides which of the two is kept: there the results agree to a tenth of the
 path's own bar."""
 import pytest
@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 
 from paper_2502_16982_amd import binding, workloads  # noqa: E402
 from tests import gpu_util as U  # noqa: E402
+from tests.gpu_util import coarse_tiles, table_sizes  # noqa: E402
 from tests.test_gpu_parity import assert_records  # noqa: E402
 
 
@@ -20,20 +21,6 @@ def dev():
         pytest.skip("no GPU")
     binding.lib()
     return torch.device("cuda:0")
-
-
-def table_sizes(shapes, ns, level):
-    """Entries of the Gram, polynomial and apply tables of a list that is planned whole."""
-    p = binding.param_array(shapes, [1] * len(shapes), [1] * len(shapes))
-    ctx = binding.muon_plan_only(p, len(shapes), binding.NS_DTYPES[ns], binding.muon_workspace_bytes(p, len(shapes), binding.NS_DTYPES[ns]))
-    try:
-        return [len(binding.muon_plan_tiles(ctx, 0, product, level)) for product in ("gram", "poly", "apply")]
-    finally:
-        binding.muon_destroy(ctx)
-
-
-def coarse_tiles(shapes, ns):
-    return table_sizes(shapes, ns, 1)[::2]
 
 
 @pytest.mark.parametrize("ns", ["bf16", "bf16x2", "bf16x3"])
@@ -110,7 +97,7 @@ def test_f32_bits_do_not_depend_on_the_list(dev, shape, long):
 def test_elementwise_passes_at_odd_widths_and_addresses(dev, dtypes):
     """Widths around the 4- and 8-element pieces and the 64-wide tile, buffers that start one element off every wider
     alignment, in guarded memory: M and W agree with the oracle and nothing outside the matrices changes."""
-    shapes = [(1, 1), (3, 5), (65, 63), (64, 65), (130, 7), (33, 257), (100, 1001)]
+    shapes = [(1, 1), (3, 5), (65, 63), (64, 65), (130, 7), (33, 257), (100, 1001), (16, 320), (97, 64), (31, 72)]
     wl = workloads.custom("odd", shapes, w_dtype=dtypes[0], g_dtype=dtypes[1], seed_base=340)
     hp, d = U.hp_from(wl.hyper)
     tensors, flats = [], []
@@ -146,3 +133,13 @@ def test_planes_in_coarse_tiles_and_strips(dev, ns):
     assert min(coarse_tiles(shapes, ns)) > 0
     wl = workloads.custom("strips_" + ns, shapes, ns_dtype=ns, seed_base=350)
     assert_records(U.run_and_compare(wl, dev), U.TOL_SPLIT_FRO[ns])
+
+
+@pytest.mark.timeout(600)
+def test_planes_in_both_launches_of_a_product(dev):
+    """Two planes, 2 x 136 symmetric tiles of one K: 256 stay in the persistent coarse launch, the last 16, all of the second
+    matrix, go to the fine launch as four 128 x 128 tiles each."""
+    shapes = [(4096, 4096)] * 2
+    assert table_sizes(shapes, "bf16x2", 1) == [256, 256, 512] and table_sizes(shapes, "bf16x2", 0) == [64, 64, 0]
+    wl = workloads.custom("planes_tail", shapes, ns_dtype="bf16x2", seed_base=355)
+    assert_records(U.run_and_compare(wl, dev, check=[1]), U.TOL_SPLIT_FRO["bf16x2"])

@@ -119,6 +119,27 @@ def test_random_shape_lists_are_covered_in_every_chunking(seed):
             binding.lib().muon_destroy(ctx)
 
 
+@pytest.mark.parametrize("seed", range(6))
+def test_random_lists_of_large_matrices_with_planes_are_covered(seed):
+    """Several planes get coarse tiles, strips and moved tails only where matrices are large: sides up to 5000, one list in
+    three of one shape (persistent launches, whose last round moves)."""
+    rng = np.random.RandomState(2000 + seed)
+    def dim():
+        return int([rng.randint(3072, 5000), 128 * rng.randint(24, 40), 256 * rng.randint(12, 20)][rng.randint(3)])
+    shapes = [(dim(), dim())] * int(rng.randint(2, 5)) if seed % 3 == 0 else \
+        [(dim(), dim()) for _ in range(int(rng.randint(2, 4)))] + [(int(rng.randint(1, 1000)), int(rng.randint(1, 1000)))]
+    ns = [binding.MUON_BF16X2, binding.MUON_BF16X3][seed % 2]
+    n = len(shapes)
+    p = binding.param_array(shapes, [1] * n, [1] * n)
+    full = binding.muon_workspace_bytes(p, n, ns, 0)
+    ctx = binding.muon_plan_only(p, n, ns, full)
+    try:
+        assert len(binding.muon_plan_tiles(ctx, 0, "gram", 1)) > 0 and len(binding.muon_plan_tiles(ctx, 0, "apply", 1)) > 0
+        assert_full_coverage(ctx, shapes, ns, "planes%d" % seed)
+    finally:
+        binding.lib().muon_destroy(ctx)
+
+
 def test_orientation_padding_and_tile_sizes():
     shapes = [(2048, 1408), (1408, 2048), (100, 130), (4096, 4096), (384, 640)]
     ctx, _ = plan(shapes, binding.MUON_BF16)
