@@ -338,7 +338,10 @@ __device__ __forceinline__ const void* o_source(const MatDesc& d, int o_sel) {
 
 // 8 consecutive elements at element alignment: one 16-byte access for bf16, two for fp32.  Streaming hint on bf16: every
 // element of the update is touched once; without it the L2 refetched a third of the lines (measured: 1.20 GB fetched for
-// 0.81 GB of W and O on the 4096-wide block, 0.89 GB with the hint).
+// 0.81 GB of W and O on the 4096-wide block, 0.89 GB with the hint).  The hint leaves more of the caches to the next step's
+// momentum pass (50 of 2048 x 1408: update 164 us with it, 160 without, momentum 319 and 343), and it costs where rows do
+// not end on whole lines: 50 of 2047 x 1401 383 / 194 us (momentum 404 / 427), of 2048 x 1400 345 / 188; kept there all the
+// same, one kernel for all widths.
 __device__ __forceinline__ void load8(const float* p, float* out) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
