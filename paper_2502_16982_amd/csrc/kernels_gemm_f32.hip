@@ -11,9 +11,10 @@
 //  * quarters: an entry is four blocks of 32 x 32 whose four waves take every fourth slab each, from a ring of their own
 //              (no barrier before the partial results are added up).  For launches with few entries: four times as many
 //              blocks and a K loop a quarter as long, at twice the operand traffic.
-// Measured, us per step of one matrix (four of them), a 64 x 64 tile of FMAs without prefetch / whole / quarters:
-// 128 x 256 244 / 125 / 78, 512 x 512 555 / 241 / 124 (575 / 257 / 241), 1024 x 1024 1016 / 390 / 346 (1694 / 982 / 989:
-// apply product 129 / 78 / 91 us = 110 TFLOP/s of the 157 the fp32 matrix instructions can do).
+// Measured, us per step of one matrix (four of them) when the two forms came in, a 64 x 64 tile of FMAs without prefetch /
+// whole / quarters: 128 x 256 244 / 125 / 78, 512 x 512 555 / 241 / 124 (575 / 257 / 241), 1024 x 1024 1016 / 390 / 346
+// (1694 / 982 / 989).  Now 128 x 256 64 (with the elementwise passes and the norm of today), 512 x 512 110 (224), 1024 x 1024 329
+// (972: apply product 78 us = 110 TFLOP/s of the 157 the fp32 matrix instructions can do).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -121,12 +122,13 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
   // The order of a dot product's terms belongs to K alone, so that a matrix gets the same bits from whole entries and from
   // quarters, i.e. in any list: slab i goes to partial sum i % 4 (a quarter's wave holds one of the four, a whole entry's
   // wave all of them), and the result is (0 + 1) + (2 + 3).  LONG (K > 4096): an accumulator takes at most kFlush slabs
-  // (1024 terms) before it is added to its total, so the rounding error of a dot product grows with K / 4096 + 1024 terms
-  // instead of K / 4 (a single fp32 accumulator over 2^20 squares drifts by 4e-4 relative); below that a total would
-  // receive one addend, so there is none.  One accumulator per partial sum: MFMAs that wait for one another cost nothing
-  // beside the other waves' (16 of 512^2 553 -> 557 us, 4 of 512^2 232 -> 227, 128 x 256 65.1 -> 64.3, against two that
-  // took turns in an order of each form's own); two per partial sum spill in the whole form (602 us).
-  constexpr int kFlush = 32, NP = Q ? 1 : 4;
+  // (512 terms) before it is added to its total, so the rounding error of a dot product grows with K / 2048 + 512 terms
+  // instead of K / 4 (a single fp32 accumulator over 2^20 squares drifts by 4e-4 relative).
+  // One accumulator per partial sum: MFMAs that wait for one another cost little beside the other waves' (16 of 512^2
+  // 550 -> 556 us, 4 of 512^2 229 -> 224, 128 x 256 65.0 -> 64.2, against two that took turns in an order of each form's own);
+  // two per partial sum spill in the whole form (602 us).  Chains that start at zero every slab, or every fourth, are more
+  // exact beyond K = 512 (O of 1024^2 1.4e-6 -> 0.6e-6 and 1.0e-6) and cost 5 and 2 to 5 %.
+  constexpr int kFlush = 16, NP = Q ? 1 : 4;
   f32x16 acc[NP], total[NP];
 #pragma unroll
   for (int c = 0; c < NP; ++c)

@@ -81,7 +81,7 @@ enum GemmShape : int { kShape128 = 0, kShape256 = 1, kShape512x128 = 2, kShape25
 constexpr int kShapeRows[kNumShapes] = {128, 256, 512, 256};
 constexpr int kShapeCols[kNumShapes] = {128, 256, 128, 256};
 constexpr int kF32Tile = 64;       // block tile of the fp32 Newton-Schulz GEMM
-constexpr int kF32LongK = 4096;    // longest K whose four partial sums hold at most 1024 terms each
+constexpr int kF32LongK = 4096;    // longest K whose four partial sums (of at most 1024 terms) are one accumulator each
 constexpr int kTileDiagonal = 1;   // GemmTile::flags: tile on the diagonal of a symmetric product: it is its own mirror
                                    // image, so only one of the two stores is made
 struct GemmTile {
