@@ -59,7 +59,7 @@ __device__ __forceinline__ float row_rotate(float v) {
 // results as (0 + 1) + (2 + 3).  The last bits of the norm decide bf16 roundings of everything behind it, so another
 // order would be another result (up to 6e-4 of the updated weights).  A chain passes through the four lanes that hold
 // its columns.  Contains one barrier; the sum is valid in the first wave.
-// Next to sums of each thread's own elements: within the noise in the momentum pass, which is bound by memory.
+// Against sums of each thread's own elements: 0.2 us on a launch of a few blocks, nothing on long lists, which memory bounds.
 __device__ __forceinline__ float tile_sum_squares(const float (&u)[4][4], float* red /* 256 floats of LDS */) {
   const int tid = threadIdx.x;
   auto chain = [](float c, const float (&x)[4]) {

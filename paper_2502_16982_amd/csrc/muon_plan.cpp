@@ -217,6 +217,8 @@ struct CoarseLoad {
     const size_t b = (size_t)std::max(blocks, 1);
     return (double)tiles / (double)((tiles + b - 1) / b * b);
   }
+  // tiles for every 256 blocks (the numbers below were measured on 256 compute units)
+  size_t per_256(int blocks) const { return tiles * 256 / (size_t)std::max(blocks, 1); }
 };
 
 // Whether a product goes to the fine launch altogether: its coarse tiles (one block per compute unit, `blocks` at a time)
@@ -237,8 +239,8 @@ struct CoarseLoad {
 // half full is not worth it below m = 3072: 4 of 2816 x 11008 (264) 1481 / 1415 and 3009 / 2967.
 // 48 of 1024^2 beside one 3072^2: 1438 / 1118 and 2858 / 2350.
 bool few_coarse_sym(const CoarseLoad& c, int planes, int blocks) {
-  if (c.tiles < 112) return true;
-  if (planes == 1) return c.tiles < 256 && c.n <= 2048 && c.area <= 3.0 * (1 << 20);
+  if (c.per_256(blocks) < 112) return true;
+  if (planes == 1) return c.per_256(blocks) < 256 && c.n <= 2048 && c.area <= 3.0 * (1 << 20);
   if (c.m >= 3072) return false;
   const double fill = c.fill(blocks);
   if (planes == 3 && fill >= 0.9 && c.m >= 2048) return false;
@@ -255,7 +257,7 @@ bool few_coarse_sym(const CoarseLoad& c, int planes, int blocks) {
 // 2858 / 2899), but the other launches of the step are quicker beside coarse ones, which draw less power: 12 of 1536 x 8192
 // 12.75 -> 12.6 ms and 25.2 -> 24.3 ms (6 of them, rounds 90 % full: 756 / 708, 1465 / 1436), 12 of 1536 x 6144 with three planes 19.7 -> 19.2 ms.
 bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
-  if (c.tiles <= 128 || (c.tiles < 176 && c.m <= 1024)) return true;
+  if (c.per_256(blocks) <= 128 || (c.per_256(blocks) < 176 && c.m <= 1024)) return true;
   if (planes == 1 || c.m > 1536) return false;
   return c.m <= 1280 || c.area < (planes == 2 ? 10.0 : 8.0) * (1 << 20) || c.fill(blocks) < 0.95;
 }
