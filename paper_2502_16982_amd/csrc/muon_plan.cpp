@@ -203,7 +203,7 @@ int ew_run(size_t tiles) { return (int)std::min<size_t>((size_t)kEwRun, std::max
 // each tile counted once: sides and area.
 struct CoarseLoad {
   size_t tiles = 0;
-  double m = 0.0, n = 0.0, area = 0.0;
+  double m = 0.0, n = 0.0, area = 0.0, mm = 0.0, nn = 0.0;     // mm, nn: averages of the squares
   void add(size_t t, double rows, double cols) {
     if (t == 0) return;
     tiles += t;
@@ -211,7 +211,13 @@ struct CoarseLoad {
     m += w * (rows - m);
     n += w * (cols - n);
     area += w * (rows * cols - area);
+    mm += w * (rows * rows - mm);
+    nn += w * (cols * cols - nn);
   }
+  // standard deviation over a fifth of the average: about where the longest K is 1.5 times the shortest
+  bool mixed_m() const { return mm - m * m > 0.04 * m * m; }
+  bool mixed_n() const { return nn - n * n > 0.04 * n * n; }
+  bool one_m() const { return mm - m * m < 0.0025 * m * m; }
   // share of the blocks that have a tile, over the rounds of `blocks` tiles
   double fill(int blocks) const {
     const size_t b = (size_t)std::max(blocks, 1);
@@ -224,38 +230,45 @@ struct CoarseLoad {
 // Whether a product goes to the fine launch altogether: its coarse tiles (one block per compute unit, `blocks` at a time)
 // are too few, or cannot pay for their epilogue.  Averages over the tiles, not extremes of the list: one large or long
 // matrix more does not move all the others.  Measured, us per launch, coarse / fine (128 x 128, or their quarters).
-// Plain bf16, Gram and polynomial: 2048^2 (36 tiles) 45 / 24, 3584^2 (105) 69 / 56, 4096^2 (136) 83 / 102.  Up to one full round
-// small matrices stay fine a little longer: 16 of 1024^2 (160) 35 / 33 and 39 / 34, 25 of 1024^2 (250) 46 / 43 and 49 / 43,
-// 12 of 2048 x 1408 (216) 68 / 67 and 56 / 51; but 8 of 2048 x 1536 (168) 53 / 56 and 48 / 46, 4 of 2048^2 (144) 50 / 56 and
-// 53 / 58, 7 of 2048^2 (252) 67 / 73 and 70 / 75.
-// With several planes the coarse epilogue spills (about 50 us a tile at two planes, 70 at three, against 10 in plain
-// bf16), and what pays for it are long K loops of large matrices in well-filled rounds.  Gram and polynomial together,
-// two planes: 48 of 1024^2 553 / 437, 24 of 1024 x 4096 608 / 514, 25 of 1024 x 8192 992 / 963, 7 of 2048^2 443 / 405, 8 of 2560^2
-// 1003 / 941, 7 of 2688 x 3200 1093 / 1042, 6 of 1536 x 8192 (126 tiles) 734 / 483, 4 of 2048 x 4096 471 / 442, 7 598 / 607 (the line
-// errs); 12 of 1536 x 6144 780 / 797, 12 of 1536 x 8192 929 / 990, 4 of 2048 x 8192 732 / 786, 7 923 / 1026, 16 2321 / 2413, 4 of
-// 2560 x 5120 674 / 714, 4 of 2560 x 10240 1084 / 1224, 4096^2 531 / 571.  Three planes: 48 of 1024^2 959 / 822, 24 of 1024 x 4096
-// 1118 / 1032, 6 of 2304^2 (270 tiles) 1112 / 1171 (errs); 14 of 2048^2 (504: two full rounds) 1630 / 1667, 25 of 1024 x 8192
-// 1901 / 1939, 12 of 1536 x 6144 1511 / 1629, 7 of 2048 x 4096 1132 / 1250, 4 of 2560^2 895 / 974.  A round that is little more than
-// half full is not worth it below m = 3072: 4 of 2816 x 11008 (264) 1481 / 1415 and 3009 / 2967.
-// 48 of 1024^2 beside one 3072^2: 1438 / 1118 and 2858 / 2350.
+// Plain bf16, Gram and polynomial: 2048^2 (36 tiles) 45 / 24, 3584^2 (105) 69 / 56, 4096^2 (136) 83 / 102.  Up to one full
+// round small matrices stay fine a little longer: 16 of 1024^2 (160) 35 / 33 and 39 / 34, 25 of 1024^2 (250) 46 / 43 and 49
+// / 43, 12 of 2048 x 1408 (216) 68 / 67 and 56 / 51; but 8 of 2048 x 1536 (168) 53 / 56 and 48 / 46, 4 of 2048^2 (144) 50 /
+// 56 and 53 / 58, 7 of 2048^2 (252) 67 / 73 and 70 / 75.
+// With several planes the coarse epilogue spills (about 50 us a tile at two planes, 70 at three, against 10 in plain bf16),
+// and what pays for it are long K loops of large matrices in well-filled rounds.  Gram and polynomial together, two planes:
+// 48 of 1024^2 553 / 437, 24 of 1024 x 4096 608 / 514, 25 of 1024 x 8192 992 / 963, 7 of 2048^2 443 / 405, 8 of 2560^2 1003
+// / 941, 7 of 2688 x 3200 1093 / 1042, 6 of 1536 x 8192 (126 tiles) 734 / 483, 4 of 2048 x 4096 471 / 442, 7 598 / 607 (the
+// line errs); 11 of 2304 x 3840 1206 / 1261, 12 of 1536 x 6144 780 / 797, 12 of 1536 x 8192 929 / 990, 4 of 2048 x 8192 732
+// / 786, 7 923 / 1026, 16 2321 / 2413, 4 of 2560 x 5120 674 / 714, 4 of 2560 x 10240 1084 / 1224, 4096^2 531 / 571.  Three
+// planes: 48 of 1024^2 959 / 822, 24 of 1024 x 4096 1118 / 1032, 6 of 2304^2 (270 tiles) 1112 / 1171 (errs); 14 of 2048^2
+// (504: two full rounds) 1630 / 1667, 25 of 1024 x 8192 1901 / 1939, 12 of 1536 x 6144 1511 / 1629, 7 of 2048 x 4096 1132 /
+// 1250, 4 of 2560^2 895 / 974.  A round that is little more than half full is not worth it below m = 3072: 4 of 2816 x
+// 11008 (264) 1481 / 1415 and 3009 / 2967.
+// Lists that mix K (or m) lose more of their coarse rounds: 7 of 2048 x 8192 and 4 of 1024^2 1559 / 1033 and 3212 / 2132, 3
+// of 2048 x 2816 and of 2944 x 8832 1386 / 1216 and 2762 / 2498, 12 of 1536 x 8192 and of 1536 x 2048 1784 / 1337 and 3529
+// / 2768, 48 of 1024^2 beside one 3072^2 1438 / 1118 and 2858 / 2350; three planes of one large m are the exception: 4 of
+// 2560 x 10240 and of 2560^2 1609 / 1610 and 3179 / 3369, 3 of 2816 x 8192 and 4 of 2816^2 1452 / 1441 and 2865 / 3044.
 bool few_coarse_sym(const CoarseLoad& c, int planes, int blocks) {
   if (c.per_256(blocks) < 112) return true;
   if (planes == 1) return c.per_256(blocks) < 256 && c.n <= 2048 && c.area <= 3.0 * (1 << 20);
   if (c.m >= 3072) return false;
   const double fill = c.fill(blocks);
+  if (c.mixed_m() || (c.mixed_n() && !(planes == 3 && c.m >= 2560 && c.one_m()))) return true;
   if (planes == 3 && fill >= 0.9 && c.m >= 2048) return false;
-  return fill < 0.55 || fill * c.area < (planes == 2 ? 8.5 : 5.0) * (1 << 20);
+  return fill < 0.55 || fill * c.area < (planes == 2 ? 8.0 : 5.0) * (1 << 20);
 }
-// Apply product, plain bf16: 2048^2 (64 tiles) 44 / 26, two of 1024 x 4096 (128: a full round of fine tiles) 31 / 24, 8 of 1024^2 (128)
-// 31 / 23, 4 of 512 x 4096 23 / 16; with a short K (m) a little beyond it: 5 of 256 x 8192 (160) 21 / 15, 5 of 512 x 4096 (160)
-// 23 / 20, 3 of 640 x 5120 (150) 27 / 24, 4 of 768 x 3072 (144) 27 / 26, 10 of 1024^2 (160) 31 / 32, 4 of 1000 x 2500 (160) 31 / 31; but
-// 3 of 1280 x 2560 (150) 36 / 38, 4 of 1536^2 (144) 39 / 43, 3072^2 (144) 63 / 78, four of 1024 x 4096 (256) 38 / 41.
-// Two planes: 48 of 1024^2 397 / 356, 24 of 1024 x 4096 741 / 674, 12 of 1536^2 320 / 296, 16 of 2048 x 1408 462 / 414, 8 of
-// 1280 x 10240 910 / 873, 4 of 2048^2 203 / 202, 16 of 2048 x 8192 3115 / 3318, 4096^2 340 / 381; three planes: 24 of 1024 x 4096
-// 1428 / 1327, 24 of 1536^2 1259 / 1134, 7 of 2048^2 728 / 771, 4 of 2560^2 872 / 936.
-// At m = 1536 the largest are even in full rounds (two planes: 12 of 1536 x 6144 1129 / 1109, of 1536 x 8192 1445 / 1435; three: 2231 / 2254 and
-// 2858 / 2899), but the other launches of the step are quicker beside coarse ones, which draw less power: 12 of 1536 x 8192
-// 12.75 -> 12.6 ms and 25.2 -> 24.3 ms (6 of them, rounds 90 % full: 756 / 708, 1465 / 1436), 12 of 1536 x 6144 with three planes 19.7 -> 19.2 ms.
+// Apply product, plain bf16: 2048^2 (64 tiles) 44 / 26, two of 1024 x 4096 (128: a full round of fine tiles) 31 / 24, 8 of
+// 1024^2 (128) 31 / 23, 4 of 512 x 4096 23 / 16; with a short K (m) a little beyond it: 5 of 256 x 8192 (160) 21 / 15, 5 of
+// 512 x 4096 (160) 23 / 20, 3 of 640 x 5120 (150) 27 / 24, 4 of 768 x 3072 (144) 27 / 26, 10 of 1024^2 (160) 31 / 32, 4 of
+// 1000 x 2500 (160) 31 / 31; but 3 of 1280 x 2560 (150) 36 / 38, 4 of 1536^2 (144) 39 / 43, 3072^2 (144) 63 / 78, four of
+// 1024 x 4096 (256) 38 / 41.
+// Two planes: 48 of 1024^2 397 / 356, 24 of 1024 x 4096 741 / 674, 12 of 1536^2 320 / 296, 16 of 2048 x 1408 462 / 414, 8
+// of 1280 x 10240 910 / 873, 4 of 2048^2 203 / 202, 16 of 2048 x 8192 3115 / 3318, 4096^2 340 / 381; three planes: 24 of
+// 1024 x 4096 1428 / 1327, 24 of 1536^2 1259 / 1134, 7 of 2048^2 728 / 771, 4 of 2560^2 872 / 936.
+// At m = 1536 the largest are even in full rounds (two planes: 12 of 1536 x 6144 1129 / 1109, of 1536 x 8192 1445 / 1435;
+// three: 2231 / 2254 and 2858 / 2899), but the other launches of the step are quicker beside coarse ones, which draw less
+// power: 12 of 1536 x 8192 12.75 -> 12.6 ms and 25.2 -> 24.3 ms (6 of them, rounds 90 % full: 756 / 708, 1465 / 1436), 12
+// of 1536 x 6144 with three planes 19.7 -> 19.2 ms.
 bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
   if (c.per_256(blocks) <= 128 || (c.per_256(blocks) < 176 && c.m <= 1024)) return true;
   if (planes == 1 || c.m > 1536) return false;
@@ -264,8 +277,8 @@ bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
 
 // Whether a fine launch runs each entry as four blocks, one per quarter.  bf16: 64 x 64 blocks of a 128 x 128 entry, which
 // are quicker through one tile (0.35 against 0.6 us per 64 of K) but need more of the compute unit for the same work: while
-// the launch holds less work than about 176 tiles of its longest K.  Measured, us per launch, 128 / 64: Gram product of 1024^2 (36 tiles) 16.2 / 10.4,
-// four of 1024 x 4096 (144) 42 / 39, four of 2048 x 1408 (264) 31 / 34; apply product of 1024^2 (64) 14.6 / 9.9, of
+// the launch holds less work than about 176 tiles of its longest K.  Measured, us per launch, 128 / 64: Gram product of
+// 1024^2 (36 tiles) 16.2 / 10.4, four of 1024 x 4096 (144) 42 / 39, four of 2048 x 1408 (264) 31 / 34; apply product of 1024^2 (64) 14.6 / 9.9, of
 // 32 of 256 x 384 (192) 8.4 / 8.0, of four of 1024^2 (256) 16.3 / 18.2.
 // fp32 launches run their 64 x 64 entries as four blocks of 32 x 32 up to about 320 entries.  Measured, whole / quarters:
 // Gram product of 1024^2 (136) 26 / 21.5, of 64 of 128 x 256 (192) 11.9 / 11.3, of 16 of 512^2 (576) 34.1 / 34.4; apply product

@@ -339,6 +339,13 @@ def coarse_counts(shapes, ns):
     (binding.MUON_BF16X3, [(2048, 4096)] * 7, True, True),
     (binding.MUON_BF16X3, [(2560, 2560)] * 4, True, True),
     (binding.MUON_BF16X3, [(1024, 4096)] * 24, False, False),
+    # lists that mix K, and one that only has a small matrix beside the large ones
+    (binding.MUON_BF16X2, [(2048, 2816)] * 3 + [(2944, 8832)] * 3, False, True),
+    (binding.MUON_BF16X3, [(2048, 8192)] * 7 + [(1024, 1024)] * 4, False, True),
+    (binding.MUON_BF16X3, [(2560, 10240)] * 4 + [(2560, 2560)] * 4, True, True),
+    (binding.MUON_BF16X3, [(2048, 2816)] * 3 + [(2944, 8832)] * 3, False, True),
+    (binding.MUON_BF16X2, [(2048, 8192)] * 4 + [(256, 256)], True, True),
+    (binding.MUON_BF16X2, [(2304, 3840)] * 11, True, True),
 ])
 def test_coarse_tiles_where_they_were_measured_to_be_quicker(ns, shapes, gram, apply):
     assert tuple(c > 0 for c in coarse_counts(shapes, ns)) == (gram, apply)
