@@ -278,11 +278,11 @@ bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
 // Whether a fine launch runs each entry as four blocks, one per quarter.  bf16: 64 x 64 blocks of a 128 x 128 entry, which
 // are quicker through one tile (0.35 against 0.6 us per 64 of K) but need more of the compute unit for the same work: while
 // the launch holds less work than about 176 tiles of its longest K.  Measured, us per launch, 128 / 64: Gram product of
-// 1024^2 (36 tiles) 16.2 / 10.4, four of 1024 x 4096 (144) 42 / 39, four of 2048 x 1408 (264) 31 / 34; apply product of 1024^2 (64) 14.6 / 9.9, of
-// 32 of 256 x 384 (192) 8.4 / 8.0, of four of 1024^2 (256) 16.3 / 18.2.
+// 1024^2 (36 tiles) 16.2 / 10.4, four of 1024 x 4096 (144) 42 / 39, four of 2048 x 1408 (264) 31 / 34; apply product of
+// 1024^2 (64) 14.6 / 9.9, of 32 of 256 x 384 (192) 8.4 / 8.0, of four of 1024^2 (256) 16.3 / 18.2.
 // fp32 launches run their 64 x 64 entries as four blocks of 32 x 32 up to about 320 entries.  Measured, whole / quarters:
-// Gram product of 1024^2 (136) 26 / 21.5, of 64 of 128 x 256 (192) 11.9 / 11.3, of 16 of 512^2 (576) 34.1 / 34.4; apply product
-// of 1024^2 (256) 27.7 / 27.6, of 64 of 128 x 256 (512) 13.6 / 17.7.
+// Gram product of 1024^2 (136) 26 / 21.5, of 64 of 128 x 256 (192) 11.9 / 11.3, of 16 of 512^2 (576) 34.1 / 34.4; apply
+// product of 1024^2 (256) 27.7 / 27.6, of 64 of 128 x 256 (512) 13.6 / 17.7.
 constexpr int kFewFine = 176, kFewF32 = 320;
 bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int few) {
   int64_t longest = 0, total = 0;
