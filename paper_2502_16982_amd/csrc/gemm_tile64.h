@@ -1,5 +1,5 @@
 // 64 x 64 output tile of a bf16 Newton-Schulz product, for launches that hold few tiles (device code; the products, the
-// operand layouts and the split-plane arithmetic are described in kernels_gemm_bf16.hip, which includes this file).
+// operand layouts are described in kernels_gemm_bf16.hip, which includes this file; split operands: gemm_planes.h).
 //
 // What bounds such a launch is not the matrix cores but latency: the first operands come from the memory-side cache
 // (about 2 us after the block starts), a block's K loop is a serial chain of slabs, and most compute units hold one
@@ -10,8 +10,7 @@
 // Addresses, swizzles and the order in which an output element's products are added are those of the large tiles: in
 // plain bf16 an element comes out with the same bits whichever tile computes it.
 // Measured (us per launch, 256-wide tiles of one block per compute unit / 128-wide tiles / these): Gram product of
-// 4 x 1024^2 and 3 x 1024 x 4096 75 / 43 / 34; products of nine matrices of 200 x 333 to 512 x 768 22 / 9 / 6; Gram
-// product of 4 x 512^2 and 3 x 512 x 1536 with three planes 230 / 87 / 53.  Rings of 2, 4 and 8 slabs took 1.17, 0.98 to
+// 4 x 1024^2 and 3 x 1024 x 4096 75 / 43 / 34; products of nine matrices of 200 x 333 to 512 x 768 22 / 9 / 6.  Rings of 2, 4 and 8 slabs took 1.17, 0.98 to
 // 1.07 and 1.1 to 1.4 times as long over whole steps.
 #pragma once
 
@@ -53,11 +52,11 @@ __device__ __forceinline__ void land64(Frag64<LKM>& f) {
 }
 
 // The tile at (row0, col0); `diagonal`: it lies on the diagonal of a symmetric product (its own mirror image).
-template <bool LKM, int PL>
+template <bool LKM>
 __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem,
                                                  float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add) {
   constexpr int NW = 4, BT = 64, NST = kRing64, NLOAD = 4;      // waves, tile side, stages, 1 KB requests per wave and slab
-  constexpr int STAGE_B = 2 * BT * ROWB, KSTEPS = BK / 16, NSEG = seg_count(PL);
+  constexpr int STAGE_B = 2 * BT * ROWB, KSTEPS = BK / 16;
   static_assert(NST >= 3 && NLOAD * (NST - 1) < 64 && ROWB == 2 * BT, "ring shape");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -76,26 +75,14 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
   const u16* rsrc = static_cast<const u16*>(p.R) + (size_t)(col0 + dma_row) * p.ldr + dma_chunk * 8;
   const size_t lstep = (size_t)(8 * NW) * p.ldl, rstep = (size_t)(8 * NW) * p.ldr;
   const size_t lslab = LKM ? (size_t)BK * p.ldl : (size_t)BK;
-  const int KT1 = p.K / BK, KT = NSEG * KT1;
+  const int KT = p.K / BK;
   auto request_one = [&](int kt, int stage, auto n_tag) {
     constexpr int n = decltype(n_tag)::value;
     unsigned char* base = smem + stage * STAGE_B + wave * 1024;
-    int seg = 0, kl = kt, lpl = seg_plane(PL, 0, 0), rpl = seg_plane(PL, 0, 1);
-    if constexpr (PL > 1) {
-#pragma unroll
-      for (int sgm = 1; sgm < NSEG; ++sgm)
-        if (kt >= sgm * KT1) { seg = sgm; kl = kt - sgm * KT1; }
-#pragma unroll
-      for (int sgm = 1; sgm < NSEG; ++sgm)
-        if (seg == sgm) { lpl = seg_plane(PL, sgm, 0); rpl = seg_plane(PL, sgm, 1); }
-    }
-    if constexpr (n < 2) {
-      const size_t off = (size_t)kl * lslab + (PL > 1 ? (size_t)lpl * (size_t)p.l_plane : 0);
-      __builtin_amdgcn_global_load_lds((gptr)(lsrc + n * lstep + off), (lptr)(base + n * NW * 1024), 16, 0, 0);
-    } else {
-      const size_t off = (size_t)kl * BK + (PL > 1 ? (size_t)rpl * (size_t)p.r_plane : 0);
-      __builtin_amdgcn_global_load_lds((gptr)(rsrc + (n - 2) * rstep + off), (lptr)(base + BT * ROWB + (n - 2) * NW * 1024), 16, 0, 0);
-    }
+    if constexpr (n < 2)
+      __builtin_amdgcn_global_load_lds((gptr)(lsrc + n * lstep + (size_t)kt * lslab), (lptr)(base + n * NW * 1024), 16, 0, 0);
+    else
+      __builtin_amdgcn_global_load_lds((gptr)(rsrc + (n - 2) * rstep + (size_t)kt * BK), (lptr)(base + BT * ROWB + (n - 2) * NW * 1024), 16, 0, 0);
   };
 
   // ---- fragment reads (lane addressing as in the large tiles) ----
@@ -153,18 +140,16 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
     ++kt;
   };
 
-  // ---- the addend: this lane's pieces of its MFMA tile, 8 contiguous bytes each of the transposed addend.  Plain bf16
-  // requests them ahead of the first slab; being older than every slab they are never counted in a wait for one.
+  // ---- the addend: this lane's pieces of its MFMA tile, 8 contiguous bytes each of the transposed addend, requested ahead of
+  // the first slab; being older than every slab they are never counted in a wait for one.
   const u16* Et = static_cast<const u16*>(p.Et);
   const bool has_e = Et != nullptr;
   u32x2 ev[4];
-  auto load_e = [&](int plane) {
+  if (has_e) {
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      ev[q] = *reinterpret_cast<const u32x2*>(Et + (PL > 1 ? (size_t)plane * (size_t)p.et_plane : 0) +
-                                              (size_t)(col0 + wn * 32 + fr) * p.ldet + row0 + wm * 32 + 8 * q + 4 * fh);
-  };
-  if (PL == 1 && has_e) load_e(0);
+      ev[q] = *reinterpret_cast<const u32x2*>(Et + (size_t)(col0 + wn * 32 + fr) * p.ldet + row0 + wm * 32 + 8 * q + 4 * fh);
+  }
 
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
@@ -188,7 +173,7 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
   } else if (alpha_idx >= 0) {
     alpha = p.scal[alpha_idx];
   }
-  if (KT == 2) {                                 // K = 128, one plane: all of it is on its way
+  if (KT == 2) {                                 // K = 128: all of it is on its way
     wait_vmcnt<NLOAD>();
     __builtin_amdgcn_s_barrier();
     read_slab(0, I0{});
@@ -220,7 +205,9 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
     ldct = p.ldc;
     if (diagonal) C = nullptr;
   }
-  auto add_e = [&]() {
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] *= ab_acc;
+  if (has_e) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       acc[4 * q + 0] = fmaf(ab_e, __uint_as_float(ev[q].x << 16), acc[4 * q + 0]);
@@ -228,25 +215,13 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
       acc[4 * q + 2] = fmaf(ab_e, __uint_as_float(ev[q].y << 16), acc[4 * q + 2]);
       acc[4 * q + 3] = fmaf(ab_e, __uint_as_float(ev[q].y & 0xffff0000u), acc[4 * q + 3]);
     }
-  };
-#pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] *= ab_acc;
-  if (PL == 1 && has_e) add_e();                 // plain bf16: addend, then diagonal; planes: the reverse
+  }
   if (p.diag_add != 0 && row0 + wm * 32 == col0 + wn * 32) {     // wave-uniform
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] += (fr == 8 * (v >> 2) + 4 * fh + (v & 3)) ? diag_add : 0.f;
   }
-  if constexpr (PL > 1) {
-    if (has_e) {
-#pragma unroll 1
-      for (int q = 0; q < PL; ++q) {
-        load_e(q);
-        add_e();
-      }
-    }
-  }
 
-  // ---- results leave plane by plane through swizzled LDS images of 64 rows x 128 B (chunk of row r at position
+  // ---- results leave through swizzled LDS images of 64 rows x 128 B (chunk of row r at position
   // chunk ^ (r / 2) % 8), 16 bytes per lane ----
   auto slot = [&](int row, int chunk) -> u32x2* {
     return reinterpret_cast<u32x2*>(smem + row * ROWB + ((chunk ^ ((row >> 1) & 7)) * 16) + fh * 8);
@@ -273,42 +248,30 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
     const f32x2 v = {x, y};
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
   };
+  u32x2 pk[4];
 #pragma unroll
-  for (int plane = 0; plane < PL; ++plane) {
-    u32x2 pk[4];
+  for (int q = 0; q < 4; ++q) pk[q] = u32x2{pack2f(acc[4 * q], acc[4 * q + 1]), pack2f(acc[4 * q + 2], acc[4 * q + 3])};
+  if (Ct) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      pk[q] = u32x2{pack2f(acc[4 * q], acc[4 * q + 1]), pack2f(acc[4 * q + 2], acc[4 * q + 3])};
-      if (plane + 1 < PL) {                      // what this plane leaves of the value (exact)
-        acc[4 * q + 0] -= __uint_as_float(pk[q].x << 16);
-        acc[4 * q + 1] -= __uint_as_float(pk[q].x & 0xffff0000u);
-        acc[4 * q + 2] -= __uint_as_float(pk[q].y << 16);
-        acc[4 * q + 3] -= __uint_as_float(pk[q].y & 0xffff0000u);
-      }
+    for (int q = 0; q < 4; ++q) *slot(wn * 32 + fr, 4 * wm + q) = pk[q];
+    __syncthreads();
+    store_image(Ct, ldct, col0, row0);
+  }
+  if (C) {
+    if (Ct) __syncthreads();
+    f32x16 d;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) d[v] = 0.f;
+#pragma unroll
+    for (int sx = 0; sx < 2; ++sx) {
+      const u32x4 raw = {pk[2 * sx].x, pk[2 * sx].y, pk[2 * sx + 1].x, pk[2 * sx + 1].y};
+      d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, raw), sel[sx], d, 0, 0, 0);
     }
-    if (Ct) {
-      if (plane) __syncthreads();                // the previous plane's image has been read out
 #pragma unroll
-      for (int q = 0; q < 4; ++q) *slot(wn * 32 + fr, 4 * wm + q) = pk[q];
-      __syncthreads();
-      store_image(Ct + (PL > 1 ? (size_t)plane * (size_t)(p.symmetric ? p.c_plane : p.ct_plane) : 0), ldct, col0, row0);
-    }
-    if (C) {
-      if (plane || Ct) __syncthreads();
-      f32x16 d;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) d[v] = 0.f;
-#pragma unroll
-      for (int sx = 0; sx < 2; ++sx) {
-        const u32x4 raw = {pk[2 * sx].x, pk[2 * sx].y, pk[2 * sx + 1].x, pk[2 * sx + 1].y};
-        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, raw), sel[sx], d, 0, 0, 0);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q)
-        *slot(wm * 32 + fr, 4 * wn + q) = u32x2{pack2f(d[4 * q], d[4 * q + 1]), pack2f(d[4 * q + 2], d[4 * q + 3])};
-      __syncthreads();
-      store_image(C + (PL > 1 ? (size_t)plane * (size_t)p.c_plane : 0), p.ldc, row0, col0);
-    }
+    for (int q = 0; q < 4; ++q)
+      *slot(wm * 32 + fr, 4 * wn + q) = u32x2{pack2f(d[4 * q], d[4 * q + 1]), pack2f(d[4 * q + 2], d[4 * q + 3])};
+    __syncthreads();
+    store_image(C, p.ldc, row0, col0);
   }
 }
 

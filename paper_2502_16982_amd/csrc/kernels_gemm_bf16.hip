@@ -9,9 +9,10 @@
 //     apply      T  = X'^T = X^T B'        L = X read K-major, R = B'  (stores T^T = X' row-major; T itself only
 //                                                                       where O is wanted transposed)
 // Operands are zero-padded to whole tiles by the producer, so the kernel has no edge handling.
-// The same kernel also runs the split-bf16 forms (template parameter PL, see seg_count below): every matrix a sum of
-// 2 or 3 bf16 planes, each product one K loop over the plane pairs that matter, the epilogue splitting the fp32
-// result into planes again.
+// Split operands: every matrix is the sum of PL = 2 or 3 bf16 arrays ("planes", plane q at element offset q * plane stride
+// from the base pointer), each holding what the planes before it left of the fp32 value after rounding to bf16, i.e. about
+// 2^-8 of its predecessor.  A product of two such sums is taken over the plane pairs (i, j) with i + j < PL - the pairs left
+// out are below 2^(-8 PL) of the result - and its fp32 result is split into planes again (gemm_planes.h).
 //
 // Design for CDNA4:
 //  * v_mfma_f32_32x32x16_bf16 (the 16x16x32 form runs at half the rate on this chip), wave tile = FM x FN
@@ -121,31 +122,15 @@ __device__ __forceinline__ void tie_regs(u32x4 (&b)[4]) {
 }
 __device__ __forceinline__ void tie_regs(u32x4 (&b)[2]) { asm volatile("" : "+v"(b[0]), "+v"(b[1]) : : "memory"); }
 
-// Split operands (PL > 1 planes): every matrix is the sum of PL bf16 arrays ("planes", plane q at element offset
-// q * plane stride from the base pointer), each holding what the planes before it left of the fp32 value after
-// rounding to bf16, i.e. about 2^-8 of its predecessor.  A product of two such sums is taken over the plane pairs
-// (i, j) with i + j < PL - the pairs left out are below 2^(-8 PL) of the result - as ONE K loop over
-// PL (PL + 1) / 2 segments that all accumulate into the same fp32 registers, smallest terms first.
-constexpr int seg_count(int pl) { return pl * (pl + 1) / 2; }
-// plane of the L (which = 0) or R (which = 1) operand in segment s: pairs by decreasing i + j, then decreasing i
-constexpr int seg_plane(int pl, int s, int which) {
-  int n = 0;
-  for (int total = pl - 1; total >= 0; --total)
-    for (int i = total; i >= 0; --i, ++n)
-      if (n == s) return which == 0 ? i : total - i;
-  return 0;
-}
-
 // LKM: the L operand is stored K-major (element (i, k) at L[k * ldl + i], i.e. the product is L^T-by-R^T of two
 // row-major arrays); its MFMA fragments then come from LDS through the transposing read ds_read_b64_tr_b16.
-// PL: number of bf16 planes per matrix (1: plain bf16).
 __device__ __forceinline__ int thread_index(int wave_id) {
   unsigned zero = 0;
   asm volatile("" : "+v"(zero));                 // opaque, so that the lane count below is redone where it is used
   return (wave_id << 6) | (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
 }
 
-template <int BM, int BN, int WM_, int WN_, int NSTAGE, bool LKM, int PL>
+template <int BM, int BN, int WM_, int WN_, int NSTAGE, bool LKM>
 __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmTile& tile, unsigned char* smem, float beta_acc,
                                                float beta_e, int alpha_idx, float diag_add, int wave_id) {
   constexpr int NW = WM_ * WN_, NT = NW * 64;
@@ -155,7 +140,6 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
   constexpr int NLOAD = LI + RI;
   constexpr int STAGE_B = (BM + BN) * ROWB;        // bytes per stage
   constexpr int KSTEPS = BK / 16;                  // MFMA k-steps per slab
-  constexpr int NSEG = seg_count(PL);              // K-loop segments (plane pairs)
   static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0 && WTM % 32 == 0 && WTN % 32 == 0, "tile shape");
   static_assert(NW % 2 == 0 && NSTAGE == 2 && NLOAD < 32, "pipeline shape");
   static_assert(4 * FM == WTM / 8 && (WTM / 8 & (WTM / 8 - 1)) == 0 && BM / 8 >= 16, "slot addressing: 4i+q and wm*WTM/8 use disjoint bits");
@@ -190,27 +174,11 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
   const u16* rsrc = static_cast<const u16*>(p.R) + (size_t)(col0 + dma_row) * p.ldr + dma_chunk * 8;
   const size_t lstep = (size_t)(LKM ? NW * RPK : 8 * NW) * p.ldl, rstep = (size_t)(8 * NW) * p.ldr;
   const size_t lslab = LKM ? (size_t)BK * p.ldl : (size_t)BK;      // elements from one K slab of L to the next
-  const int KT1 = p.K / BK;                        // slabs per segment
   // requests DMA instructions [first, first + count) of slab kt (instructions 0..LI-1 fetch L rows, the rest R rows)
   auto request_part = [&](int kt, int stage, auto first_tag, auto count_tag) {
     constexpr int FIRST = decltype(first_tag)::value, COUNT = decltype(count_tag)::value;
     unsigned char* base = smem + stage * STAGE_B + wave * 1024;
-    size_t loff, roff;                             // element offsets of slab kt in L and R (wave-uniform)
-    if constexpr (PL == 1) {
-      loff = (size_t)kt * lslab;
-      roff = (size_t)kt * BK;
-    } else {
-      int seg = 0, kl = kt;
-#pragma unroll
-      for (int sgm = 1; sgm < NSEG; ++sgm)
-        if (kt >= sgm * KT1) { seg = sgm; kl = kt - sgm * KT1; }
-      int lpl = seg_plane(PL, 0, 0), rpl = seg_plane(PL, 0, 1);
-#pragma unroll
-      for (int sgm = 1; sgm < NSEG; ++sgm)
-        if (seg == sgm) { lpl = seg_plane(PL, sgm, 0); rpl = seg_plane(PL, sgm, 1); }
-      loff = (size_t)kl * lslab + (size_t)lpl * (size_t)p.l_plane;
-      roff = (size_t)kl * BK + (size_t)rpl * (size_t)p.r_plane;
-    }
+    const size_t loff = (size_t)kt * lslab, roff = (size_t)kt * BK;       // slab kt in L and R (wave-uniform)
 #pragma unroll
     for (int n = FIRST; n < FIRST + COUNT; ++n) {
       if (n < LI)
@@ -330,7 +298,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
   //      wait: my reads of stage `cur` and my requests of slab kt+1 have completed; barrier
   //   C  MFMAs of k-steps 1, 2          | the requests of slab kt+2, into stage `cur`
   //                                     | fragment reads of k-step 0 of slab kt+1
-  const int KT = NSEG * KT1;
+  const int KT = p.K / BK;
   request_part(0, 0, Zero{}, AllN{});
   if (KT > 1) request_part(1, 1, Zero{}, AllN{});
   wait_vmcnt<0>();
@@ -368,18 +336,17 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
   constexpr int CNT0 = IPS < TI ? IPS : TI, CNT1 = TI - CNT0 < IPS ? TI - CNT0 : IPS;   // instructions per region
   // instruction i of the part of the image that overlays pipeline stage `region` (the last region may hold fewer
   // instructions than a stage has room for)
-  auto et_request_one = [&](int region, int i, int plane = 0) {
+  auto et_request_one = [&](int region, int i) {
     if (i >= (region == 0 ? CNT0 : CNT1)) return;
     const int idx0 = region * IPS * NW + wave;
     const int c = idx0 * RPI_T + lane / CPT + i * NW * RPI_T;
     const u16* src = Et + (size_t)(col0 + c) * p.ldet + row0;
-    if constexpr (PL > 1) src += (size_t)plane * (size_t)p.et_plane;
     const int chunk = (lane % CPT) ^ (c & KEYMASK);
     __builtin_amdgcn_global_load_lds((gptr)(src + chunk * 8), (lptr)(smem + idx0 * 1024 + i * NW * 1024), 16, 0, 0);
   };
-  auto et_request = [&](int region, int plane = 0) {
+  auto et_request = [&](int region) {
 #pragma unroll
-    for (int i = 0; i < CNT0; ++i) et_request_one(region, i, plane);
+    for (int i = 0; i < CNT0; ++i) et_request_one(region, i);
   };
 
   int cur = 0;
@@ -457,7 +424,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
     // C: 2 MT MFMAs; among them, evenly, the NLOAD requests of slab kt+2, the NR reads of k-step 0 of slab kt+1 and, in
     // the last iteration, the part of the addend image that overlays the stage no longer in use
     constexpr int NC = (KSTEPS - 2) * MT;
-    constexpr bool EARLY_ET = PL == 1 && !REFILL && !SYNC;
+    constexpr bool EARLY_ET = !REFILL && !SYNC;
     const bool early_et = EARLY_ET && Et != nullptr;
     static_for<0, NC>([&](auto t_tag) {
       constexpr int t = decltype(t_tag)::value;
@@ -511,12 +478,10 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
     ldct = p.ldc;
     if (tile.flags & kTileDiagonal) C = nullptr;
   }
-  if constexpr (PL == 1) {
   if (Et) {
     et_request(cur ^ 1);        // `cur` was flipped after the last iteration: cur^1 is the stage that iteration still read
     wait_vmcnt<0>();
     __syncthreads();
-  }
   }
 
   // Each lane's slot for (MFMA tile i, j; quarter q): image row c = wn*WTN + 32j + r, logical chunk
@@ -571,7 +536,6 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  if constexpr (PL == 1) {
   if (Et) combine(std::true_type{}); else combine(std::false_type{});
   if (Ct) {
     __syncthreads();
@@ -658,181 +622,6 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
         *(gvec_ptr)(dst[i % PERIOD] + (size_t)(i / PERIOD) * dstep) = v[u];
       }
       __builtin_amdgcn_sched_barrier(0);
-    }
-  }
-  } else {
-    // ---- split operands: val = alpha * (beta_acc * acc + beta_e * sum_q E_q) (+ diagonal constant) is formed in
-    // the accumulator registers in fp32; plane q of the outputs is bf16(val_q) with val_0 = val and
-    // val_{q+1} = val_q - bf16(val_q) (exact in fp32).  Every plane takes the same route through the LDS images
-    // as the single plane of the plain path; nothing is overlapped here - three to six times the matrix-core work
-    // stands against this epilogue.
-    const size_t ctpl = (size_t)(p.symmetric ? p.c_plane : p.ct_plane), cpl = (size_t)p.c_plane;
-    auto pack4 = [](float x0, float x1, float x2, float x3) -> u32x2 {
-      const f32x2 lo = {x0, x1}, hi = {x2, x3};
-      u32x2 w;
-      w.x = __builtin_bit_cast(unsigned, __builtin_convertvector(lo, bf16x2));
-      w.y = __builtin_bit_cast(unsigned, __builtin_convertvector(hi, bf16x2));
-      return w;
-    };
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] *= ab_acc;
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-        if (diag_shift == 32 * (j - i)) {        // wave-uniform
-#pragma unroll
-          for (int v = 0; v < 16; ++v) acc[i][j][v] += (fr == 8 * (v >> 2) + 4 * fh + (v & 3)) ? diag_add : 0.f;
-        }
-    if (Et) {
-#pragma unroll 1
-      for (int q = 0; q < PL; ++q) {
-        if (q) __syncthreads();                  // every lane has taken its pieces of the previous plane's image
-        et_request(0, q);
-        et_request(1, q);
-        wait_vmcnt<0>();
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-              const u32x2 e2 = *reinterpret_cast<const u32x2*>(slot_of(i, j, qq));
-              acc[i][j][4 * qq + 0] = fmaf(ab_e, __uint_as_float(e2.x << 16), acc[i][j][4 * qq + 0]);
-              acc[i][j][4 * qq + 1] = fmaf(ab_e, __uint_as_float(e2.x & 0xffff0000u), acc[i][j][4 * qq + 1]);
-              acc[i][j][4 * qq + 2] = fmaf(ab_e, __uint_as_float(e2.y << 16), acc[i][j][4 * qq + 2]);
-              acc[i][j][4 * qq + 3] = fmaf(ab_e, __uint_as_float(e2.y & 0xffff0000u), acc[i][j][4 * qq + 3]);
-              if (qq == 3) __builtin_amdgcn_sched_barrier(0);   // one MFMA tile at a time: keeps the register count down
-            }
-      }
-    }
-    // store-out of the transposed image [BN][BM] and of the row-major image [BM][BN]: 16 bytes per lane, coalesced
-    constexpr int SBT = TI < 8 ? TI : 8;
-    constexpr int CSTEP = NW * RPI_T, PERIOD_T = (KEYMASK + 1) / CSTEP > 0 ? (KEYMASK + 1) / CSTEP : 1;
-    auto store_ct = [&](u16* base) {
-      const int c_first = wave * RPI_T + lane / CPT;
-      u16* dst[PERIOD_T];
-#pragma unroll
-      for (int k = 0; k < PERIOD_T; ++k) {
-        const int c = c_first + k * CSTEP;
-        dst[k] = base + (size_t)(col0 + c) * ldct + row0 + ((lane % CPT) ^ (c & KEYMASK)) * 8;
-      }
-      const size_t dstep = (size_t)(CSTEP * PERIOD_T) * ldct;
-#pragma unroll
-      for (int i0 = 0; i0 < TI; i0 += SBT) {
-        u32x4 v[SBT];
-#pragma unroll
-        for (int u = 0; u < SBT; ++u) v[u] = *reinterpret_cast<const u32x4*>(smem + ((i0 + u) * NW + wave) * 1024 + lane * 16);
-#pragma unroll
-        for (int u = 0; u < SBT; ++u) {
-          const int i = i0 + u;
-          *(gvec_ptr)(dst[i % PERIOD_T] + (size_t)(i / PERIOD_T) * dstep) = v[u];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    constexpr int CPR = BN / 8, RPI_C = 64 / CPR, CI = BM / RPI_C / NW;
-    constexpr int SBC = CI < 8 ? CI : 8;
-    constexpr int RSTEP = NW * RPI_C, PERIOD_C = CPR / RSTEP > 0 ? CPR / RSTEP : 1;
-    auto store_c = [&](u16* base) {
-      const int r_first = wave * RPI_C + lane / CPR;
-      u16* dst[PERIOD_C];
-#pragma unroll
-      for (int k = 0; k < PERIOD_C; ++k) {
-        const int r = r_first + k * RSTEP;
-        dst[k] = base + (size_t)(row0 + r) * p.ldc + col0 + ((lane % CPR) ^ (r & (CPR - 1))) * 8;
-      }
-      const size_t dstep = (size_t)(RSTEP * PERIOD_C) * p.ldc;
-#pragma unroll
-      for (int i0 = 0; i0 < CI; i0 += SBC) {
-        u32x4 v[SBC];
-#pragma unroll
-        for (int u = 0; u < SBC; ++u) v[u] = *reinterpret_cast<const u32x4*>(smem + ((i0 + u) * NW + wave) * 1024 + lane * 16);
-#pragma unroll
-        for (int u = 0; u < SBC; ++u) {
-          const int i = i0 + u;
-          *(gvec_ptr)(dst[i % PERIOD_C] + (size_t)(i / PERIOD_C) * dstep) = v[u];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    bf16x8 sel[2];                               // 0/1 selector of the MFMA transpose (see the plain path)
-#pragma unroll
-    for (int sx = 0; sx < 2; ++sx)
-#pragma unroll
-      for (int t = 0; t < 8; ++t) {
-        const int row = 16 * sx + 4 * fh + (t < 4 ? t : 4 + t);
-        sel[sx][t] = (__bf16)(fr == row ? 1.0f : 0.0f);
-      }
-    // all planes at once, MFMA tile by MFMA tile: the fp32 values leave the accumulator registers for good
-    u32x2 pkq[PL][FM][FN][4];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-#pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-          float x0 = acc[i][j][4 * qq], x1 = acc[i][j][4 * qq + 1], x2 = acc[i][j][4 * qq + 2], x3 = acc[i][j][4 * qq + 3];
-#pragma unroll
-          for (int q = 0; q < PL; ++q) {
-            const u32x2 w = pack4(x0, x1, x2, x3);
-            pkq[q][i][j][qq] = w;
-            if (q + 1 < PL) {                    // what this plane left of the value
-              x0 -= __uint_as_float(w.x << 16);
-              x1 -= __uint_as_float(w.x & 0xffff0000u);
-              x2 -= __uint_as_float(w.y << 16);
-              x3 -= __uint_as_float(w.y & 0xffff0000u);
-            }
-          }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-    for (int q = 0; q < PL; ++q) {
-      if (Ct) {
-        __syncthreads();                         // the image is free (addend consumed / previous plane stored)
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) *reinterpret_cast<u32x2*>(slot_of(i, j, qq)) = pkq[q][i][j][qq];
-        __syncthreads();
-        store_ct(Ct + (size_t)q * ctpl);
-      }
-      if (C) {
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) {
-            f32x16 d;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) d[v] = 0.f;
-#pragma unroll
-            for (int sx = 0; sx < 2; ++sx) {
-              const u32x4 raw = {pkq[q][i][j][2 * sx].x, pkq[q][i][j][2 * sx].y, pkq[q][i][j][2 * sx + 1].x, pkq[q][i][j][2 * sx + 1].y};
-              d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, raw), sel[sx], d, 0, 0, 0);
-            }
-            const int r = wm * WTM + i * 32 + fr;
-#pragma unroll
-            for (int qq = 0; qq < 4; ++qq) {
-              const int lchunk = (wn * WTN + j * 32) / 8 + qq;
-              *reinterpret_cast<u32x2*>(smem + r * (BN * 2) + ((lchunk ^ (r & (CPR - 1))) * 16) + fh * 8) =
-                  pack4(d[4 * qq], d[4 * qq + 1], d[4 * qq + 2], d[4 * qq + 3]);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        __syncthreads();
-        store_c(C + (size_t)q * cpl);
-      }
     }
   }
 }
@@ -1110,6 +899,7 @@ __device__ __forceinline__ void diag_tile_body(const GemmProblem& p, const GemmT
 }  // namespace
 }  // namespace muon
 
+#include "gemm_planes.h"
 #include "gemm_tile64.h"
 
 namespace muon {
@@ -1121,25 +911,30 @@ namespace {
 // 128 x 128 tile, so they share register budget, MFMA schedule and per-wave LDS traffic, and a launch mixes them freely:
 // the strips fill compute units next to the 256-tiles of the same product instead of running as a launch of their own.
 constexpr size_t kLds128 = TileCfg<128, 128>::lds_bytes(2);
+constexpr size_t lds_fine(int planes) { return planes > 1 ? planes_lds(128, planes) : kLds128; }
 constexpr size_t kLds256 = TileCfg<256, 256>::lds_bytes(2);
 constexpr size_t kLds512 = TileCfg<512, 128>::lds_bytes(2);
 constexpr int kMaxPlanes = 3;
 
 template <bool LKM, int PL>
-__global__ __launch_bounds__(256, 2) void ns_gemm_bf16_fine_kernel(const GemmProblem* __restrict__ probs,
+__global__ __launch_bounds__(256, PL == 3 ? 1 : 2) void ns_gemm_bf16_fine_kernel(const GemmProblem* __restrict__ probs,
                                                                     const GemmTile* __restrict__ tiles, float beta_acc,
                                                                     float beta_e, int alpha_idx, float diag_add) {
   extern __shared__ __align__(16) unsigned char smem[];
   const GemmTile tile = load_tile(tiles, blockIdx.x);
   const GemmProblem p = probs[tile.prob];
-  gemm_tile_body<128, 128, 2, 2, 2, LKM, PL>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add,
-                                             __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  if constexpr (PL > 1)
+    planes_tile<128, LKM, PL>(p, tile.r0 * kTileUnit, tile.c0 * kTileUnit, (tile.flags & kTileDiagonal) != 0, smem, beta_acc, beta_e,
+                              alpha_idx, 0.0);
+  else
+    gemm_tile_body<128, 128, 2, 2, 2, LKM>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add,
+                                               __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
 }
 
 // Each 128 x 128 table entry as four blocks of 64 x 64.  Block b: entry 8 (b / 32) + b % 8, so that an entry's quarters
 // run on the die its entry is dealt to; quarter (b / 8) % 4.
 template <bool LKM, int PL>
-__global__ __launch_bounds__(256, 3) void ns_tile64_gemm_bf16_kernel(const GemmProblem* __restrict__ probs,
+__global__ __launch_bounds__(256, PL == 3 ? 2 : 3) void ns_tile64_gemm_bf16_kernel(const GemmProblem* __restrict__ probs,
                                                                    const GemmTile* __restrict__ tiles, int n_tiles, float beta_acc,
                                                                    float beta_e, int alpha_idx, double eps, float diag_add) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1149,8 +944,9 @@ __global__ __launch_bounds__(256, 3) void ns_tile64_gemm_bf16_kernel(const GemmP
   const bool on_diag = (tile.flags & kTileDiagonal) != 0;
   if (on_diag && quarter == 2) return;           // below the diagonal: the mirror image of quarter 1
   const GemmProblem p = probs[tile.prob];
-  gemm_tile64_body<LKM, PL>(p, tile.r0 * kTileUnit + 64 * (quarter >> 1), tile.c0 * kTileUnit + 64 * (quarter & 1),
-                            on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps, diag_add);
+  const int row0 = tile.r0 * kTileUnit + 64 * (quarter >> 1), col0 = tile.c0 * kTileUnit + 64 * (quarter & 1);
+  if constexpr (PL > 1) planes_tile<64, LKM, PL>(p, row0, col0, on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps);
+  else gemm_tile64_body<LKM>(p, row0, col0, on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps, diag_add);
 }
 
 // Block b works through table entries b, b + gridDim.x, ...  Launched with one block per tile, or persistent: one
@@ -1158,24 +954,37 @@ __global__ __launch_bounds__(256, 3) void ns_tile64_gemm_bf16_kernel(const GemmP
 // goes on to its next tile neither waits for its stores to drain nor is re-dispatched, and its next tile's first
 // operand requests overlap both (measured +2 % on the MoE bank; with tiles of mixed K the static dealing loses that
 // again, so such launches stay one block per tile).
+// With several planes every entry is four blocks of 128 x 128 on the entry's die: a 256-wide tile has no registers for the
+// planes' fragments (gemm_planes.h holds both sides' times).
 template <bool LKM, int PL>
-__global__ __launch_bounds__(256, 1) void ns_gemm_bf16_kernel(const GemmProblem* __restrict__ probs,
+__global__ __launch_bounds__(256, PL == 2 ? 2 : 1) void ns_gemm_bf16_kernel(const GemmProblem* __restrict__ probs,
                                                                const GemmTile* __restrict__ tiles, int n_tiles, float beta_acc,
                                                                float beta_e, int alpha_idx, float diag_add) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+  if constexpr (PL > 1) {
+    const int t = (int)(blockIdx.x >> 5) * 8 + (int)(blockIdx.x & 7), quarter = (int)(blockIdx.x >> 3) & 3;
+    if (t >= n_tiles) return;
     const GemmTile tile = load_tile(tiles, t);
+    const bool strip = tile.shape == kShape512x128;
     const GemmProblem p = probs[tile.prob];
-    const int shape = __builtin_amdgcn_readfirstlane(tile.shape);
-    if (shape == kShape512x128) {
-      gemm_tile_body<512, 128, 4, 1, 2, LKM, PL>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id);
-    } else if (!LKM && PL == 1 && shape == kShape256Diag) {
-      if constexpr (!LKM && PL == 1) diag_tile_body(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id);
-    } else {
-      gemm_tile_body<256, 256, 2, 2, 2, LKM, PL>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id);
+    const int row0 = tile.r0 * kTileUnit + 128 * (strip ? quarter : quarter >> 1), col0 = tile.c0 * kTileUnit + 128 * (strip ? 0 : quarter & 1);
+    if (p.symmetric && row0 > col0) return;      // below the diagonal: a mirror image
+    planes_tile<128, LKM, PL>(p, row0, col0, p.symmetric && row0 == col0, smem, beta_acc, beta_e, alpha_idx, 0.0);
+  } else {
+    const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
+      const GemmTile tile = load_tile(tiles, t);
+      const GemmProblem p = probs[tile.prob];
+      const int shape = __builtin_amdgcn_readfirstlane(tile.shape);
+      if (shape == kShape512x128) {
+        gemm_tile_body<512, 128, 4, 1, 2, LKM>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id);
+      } else if (!LKM && shape == kShape256Diag) {
+        if constexpr (!LKM) diag_tile_body(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id);
+      } else {
+        gemm_tile_body<256, 256, 2, 2, 2, LKM>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id);
+      }
+      __syncthreads();        // every wave has read its part of the LDS images: the next tile may overwrite them
     }
-    __syncthreads();        // every wave has read its part of the LDS images: the next tile may overwrite them
   }
 }
 
@@ -1184,13 +993,13 @@ int g_coarse_grid = 0;      // blocks of a coarse launch: one per compute unit (
 template <bool LKM, int PL>
 hipError_t setup_pair() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_bf16_fine_kernel<LKM, PL>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds128);
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_fine(PL));
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_tile64_gemm_bf16_kernel<LKM, PL>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsRing64 + kLdsFold64));
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_bf16_kernel<LKM, PL>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds512);
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(PL > 1 ? lds_fine(PL) : kLds512));
 }
 
 template <bool LKM, int PL>
@@ -1201,10 +1010,10 @@ void launch_one(int coarse, int flags, const GemmProblem* probs, const GemmTile*
                                           kLdsRing64 + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(
         probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, diag_add);
   else if (!coarse)
-    ns_gemm_bf16_fine_kernel<LKM, PL><<<n_tiles, 256, kLds128, s>>>(probs, tiles, beta_acc, beta_e, alpha_idx, diag_add);
+    ns_gemm_bf16_fine_kernel<LKM, PL><<<n_tiles, 256, lds_fine(PL), s>>>(probs, tiles, beta_acc, beta_e, alpha_idx, diag_add);
   else
-    ns_gemm_bf16_kernel<LKM, PL><<<(flags & kGemmPersistent) && n_tiles > g_coarse_grid ? g_coarse_grid : n_tiles, 256,
-                                   (flags & kGemmStrips) ? kLds512 : kLds256, s>>>(
+    ns_gemm_bf16_kernel<LKM, PL><<<PL > 1 ? (n_tiles + 7) / 8 * 32 : (flags & kGemmPersistent) && n_tiles > g_coarse_grid ? g_coarse_grid : n_tiles,
+                                   256, PL > 1 ? lds_fine(PL) : (flags & kGemmStrips) ? kLds512 : kLds256, s>>>(
         probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, diag_add);
 }
 

@@ -75,7 +75,8 @@ hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, 
 // kGemmQuarters (coarse = 0): every entry of the table runs as four blocks, one per quarter of it.
 // kGemmLongK (fp32): needed where a problem of the launch has K > kF32LongK.
 // l_kmajor: every problem of the launch stores its L operand K-major (element (i, k) at L[k * ldl + i]).
-// planes: 1 = plain bf16; 2 or 3 = every matrix is a sum of that many bf16 planes (GemmProblem::*_plane strides).
+// planes: 1 = plain bf16; 2 or 3 = every matrix is a sum of that many bf16 planes (GemmProblem::*_plane strides); entries of a
+// coarse table then run as four 128 x 128 blocks each.
 constexpr int kAlphaFromPartials = 2;
 constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmQuarters = 4, kGemmLongK = 8;
 hipError_t launch_gemm_bf16(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,

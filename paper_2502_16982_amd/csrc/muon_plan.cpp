@@ -234,8 +234,9 @@ struct CoarseLoad {
 // round small matrices stay fine a little longer: 16 of 1024^2 (160) 35 / 33 and 39 / 34, 25 of 1024^2 (250) 46 / 43 and 49
 // / 43, 12 of 2048 x 1408 (216) 68 / 67 and 56 / 51; but 8 of 2048 x 1536 (168) 53 / 56 and 48 / 46, 4 of 2048^2 (144) 50 /
 // 56 and 53 / 58, 7 of 2048^2 (252) 67 / 73 and 70 / 75.
-// With several planes the coarse epilogue spills (about 50 us a tile at two planes, 70 at three, against 10 in plain bf16),
-// and what pays for it are long K loops of large matrices in well-filled rounds.  Gram and polynomial together, two planes:
+// With several planes both launches run 128 x 128 tiles (gemm_planes.h), and all that is left of the choice is the order of
+// the tiles and which die they run on.  Its line stems from 256-wide tiles whose epilogue spilled (about 50 us a tile at two
+// planes, 70 at three), which paid only with long K loops of large matrices in well-filled rounds.  As measured then: Gram and polynomial together, two planes:
 // 48 of 1024^2 553 / 437, 24 of 1024 x 4096 608 / 514, 25 of 1024 x 8192 992 / 963, 7 of 2048^2 443 / 405, 8 of 2560^2 1003
 // / 941, 7 of 2688 x 3200 1093 / 1042, 6 of 1536 x 8192 (126 tiles) 734 / 483, 4 of 2048 x 4096 471 / 442, 7 598 / 607 (the
 // line errs); 11 of 2304 x 3840 1206 / 1261, 12 of 1536 x 6144 780 / 797, 12 of 1536 x 8192 929 / 990, 4 of 2048 x 8192 732
@@ -262,7 +263,7 @@ bool few_coarse_sym(const CoarseLoad& c, int planes, int blocks) {
 // 512 x 4096 (160) 23 / 20, 3 of 640 x 5120 (150) 27 / 24, 4 of 768 x 3072 (144) 27 / 26, 10 of 1024^2 (160) 31 / 32, 4 of
 // 1000 x 2500 (160) 31 / 31; but 3 of 1280 x 2560 (150) 36 / 38, 4 of 1536^2 (144) 39 / 43, 3072^2 (144) 63 / 78, four of
 // 1024 x 4096 (256) 38 / 41.
-// Two planes: 48 of 1024^2 397 / 356, 24 of 1024 x 4096 741 / 674, 12 of 1536^2 320 / 296, 16 of 2048 x 1408 462 / 414, 8
+// Several planes, as above: two planes 48 of 1024^2 397 / 356, 24 of 1024 x 4096 741 / 674, 12 of 1536^2 320 / 296, 16 of 2048 x 1408 462 / 414, 8
 // of 1280 x 10240 910 / 873, 4 of 2048^2 203 / 202, 16 of 2048 x 8192 3115 / 3318, 4096^2 340 / 381; three planes: 24 of
 // 1024 x 4096 1428 / 1327, 24 of 1536^2 1259 / 1134, 7 of 2048^2 728 / 771, 4 of 2560^2 872 / 936.
 // At m = 1536 the largest are even in full rounds (two planes: 12 of 1536 x 6144 1129 / 1109, of 1536 x 8192 1445 / 1435;

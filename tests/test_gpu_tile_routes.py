@@ -57,6 +57,19 @@ def test_64_wide_tiles_at_their_edges(dev, ns, tol):
     assert_records(U.run_and_compare(wl, dev, steps=2, want_rms=True), tol)
 
 
+@pytest.mark.parametrize("ns", ["bf16x2", "bf16x3"])
+def test_planes_in_128_wide_tiles_at_their_edges(dev, ns):
+    """More entries than a launch in quarters holds.  K of one and of several pairs of pieces (the loop not run, run once, run
+    several times), both orientations, one padded row or column short of a tile."""
+    shapes = [(128, 128), (127, 384), (384, 129), (257, 640)]
+    copies = 60
+    sizes = table_sizes(shapes * copies, ns, 0)
+    assert min(sizes) > 400 and coarse_tiles(shapes * copies, ns) == [0, 0]
+    wl = workloads.custom("edges128_" + ns, shapes * copies, ns_dtype=ns, seed_base=325)
+    n = len(wl.shapes)
+    assert_records(U.run_and_compare(wl, dev, check=list(range(4)) + list(range(n - 4, n)), steps=2, want_rms=True), U.TOL_SPLIT_FRO[ns])
+
+
 @pytest.mark.parametrize("copies", [1, 40])
 def test_f32_products_whole_and_in_quarters(dev, copies):
     """fp32 path: K of two 32-wide slabs (two of a block's four waves have none) up to several rounds of the ring, ragged
