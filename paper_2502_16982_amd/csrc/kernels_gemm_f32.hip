@@ -61,8 +61,15 @@ constexpr size_t stage_bytes(bool quarters) { return quarters ? 4 * 64 * ROWF : 
 constexpr size_t kLdsFold = 256 * sizeof(double);            // scratch behind the rings for the folded norm
 constexpr size_t lds_bytes(bool quarters) { return ring_of(quarters) * stage_bytes(quarters); }
 
+// Barrier for what is in LDS: unlike __syncthreads it does not wait for loads from memory that are on their way.
+__device__ __forceinline__ void meet() {
+  asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" : : : "memory");
+}
+
 template <bool Q, bool LONG>
-__global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* __restrict__ probs,
+__global__ __launch_bounds__(256, Q || LONG ? 2 : 3) void ns_gemm_f32_kernel(const GemmProblem* __restrict__ probs,
                                                               const GemmTile* __restrict__ tiles, int n_tiles, float beta_acc,
                                                               float beta_e, int alpha_idx, double eps) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -252,7 +259,6 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
   // ---- epilogue.  A lane holds column fr, rows 8 q + 4 h + e of its wave's 32 x 32 tile: it goes to LDS as image
   // [column][row].  Quarters: the four waves' partial tiles are added up, one float4 per thread; whole: each wave reads
   // its own tile back.  Et is the addend stored transposed, so that it is read and Ct written along rows of the image.
-  const float* Et = static_cast<const float*>(p.Et);
   float* C = static_cast<float*>(p.C);
   float* Ct = static_cast<float*>(p.Ct);
   int ldct = p.ldct;
@@ -260,14 +266,27 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
     Ct = on_diag && (!Q || quarter != 1) ? nullptr : C;
     ldct = p.ldc;
   }
-  __syncthreads();                               // every wave is done with the ring
+  // The addend, this thread's float4s of the transposed tile: whole entries ask for it before the block meets and the tile
+  // passes through the LDS (-1 to -2 % of a step); in quarters, one float4 behind a longer sum, that place gains nothing.
+  constexpr int NV = Q ? 1 : 4;                  // float4s per thread
+  const float* Et = static_cast<const float*>(p.Et);
+  const int sub_r = Q ? 0 : (wave >> 1) * 32, sub_c = Q ? 0 : (wave & 1) * 32;
+  f32x4 ev[NV];
+  auto load_e = [&](int u) {
+    const int c = Q ? tid >> 3 : (lane >> 3) + 8 * u, r4 = 4 * (lane & 7);
+    ev[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (Et) ev[u] = *reinterpret_cast<const f32x4*>(Et + (size_t)(col0 + sub_c + c) * p.ldet + row0 + sub_r + r4);
+  };
+  if constexpr (!Q) {
+#pragma unroll
+    for (int u = 0; u < NV; ++u) load_e(u);
+  }
+  meet();                                        // every wave is done with the ring
   float* const img = reinterpret_cast<float*>(smem) + wave * 32 * kImgPitch;
 #pragma unroll
   for (int q = 0; q < 4; ++q)
     *reinterpret_cast<f32x4*>(img + fr * kImgPitch + 8 * q + 4 * fh) = f32x4{sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
-  __syncthreads();
-  constexpr int NV = Q ? 1 : 4;                  // float4s per thread
-  const int sub_r = Q ? 0 : (wave >> 1) * 32, sub_c = Q ? 0 : (wave & 1) * 32;
+  meet();
   f32x4 val[NV];
 #pragma unroll
   for (int u = 0; u < NV; ++u) {
@@ -282,12 +301,11 @@ __global__ __launch_bounds__(256, 2) void ns_gemm_f32_kernel(const GemmProblem* 
     } else {
       x = *reinterpret_cast<const f32x4*>(img + c * kImgPitch + r4);
     }
-    f32x4 ev = {0.f, 0.f, 0.f, 0.f};
-    if (Et) ev = *reinterpret_cast<const f32x4*>(Et + (size_t)(col0 + sub_c + c) * p.ldet + row0 + sub_r + r4);
+    if constexpr (Q) load_e(u);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       float y = beta_acc * x[e];
-      if (Et) y = fmaf(beta_e, ev[e], y);
+      if (Et) y = fmaf(beta_e, ev[u][e], y);
       val[u][e] = alpha * y;
     }
     if (Ct) *reinterpret_cast<f32x4*>(Ct + (size_t)(col0 + sub_c + c) * ldct + row0 + sub_r + r4) = val[u];

@@ -281,18 +281,27 @@ bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
 // the launch holds less work than about 176 tiles of its longest K.  Measured, us per launch, 128 / 64: Gram product of
 // 1024^2 (36 tiles) 16.2 / 10.4, four of 1024 x 4096 (144) 42 / 39, four of 2048 x 1408 (264) 31 / 34; apply product of
 // 1024^2 (64) 14.6 / 9.9, of 32 of 256 x 384 (192) 8.4 / 8.0, of four of 1024^2 (256) 16.3 / 18.2.
-// fp32 launches run their 64 x 64 entries as four blocks of 32 x 32 up to about 320 entries.  Measured, whole / quarters:
-// Gram product of 1024^2 (136) 26 / 21.5, of 64 of 128 x 256 (192) 11.9 / 11.3, of 16 of 512^2 (576) 34.1 / 34.4; apply
-// product of 1024^2 (256) 27.7 / 27.6, of 64 of 128 x 256 (512) 13.6 / 17.7.
-constexpr int kFewFine = 176, kFewF32 = 320;
-bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int few) {
-  int64_t longest = 0, total = 0;
+// fp32 launches run their 64 x 64 entries as four blocks of 32 x 32 up to about 180 entries' work, and again where there is a
+// little more than one entry for each of `blocks` compute units, so that whole entries would need a second round for a few.
+// Measured, us per step, quarters / whole for the launches of that many entries: 144 (products of 4 of 512^2) 207 / 221, 180 (5)
+// 242 / 261, 196 (apply product of 896^2) 245 / 236, 200 (2 of 640^2) 204 / 195, 216 (6 of 512^2) 278 / 260, 252 (7) 286 / 262,
+// 256 (apply products of 1024^2, of 4 of 512^2) 327 / 314, 215 / 207, 288 (8 of 512^2) 315 / 351; earlier, us per launch, apply
+// product of 64 of 128 x 256 (512) 17.7 / 13.6, Gram product of 16 of 512^2 (576) 34.4 / 34.1.
+constexpr int kFewFine = 176, kFewF32 = 180, kLittleOverF32 = 64;
+// a launch's work in entries of its longest K
+int64_t entries_of_work(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k) {
+  int64_t longest = 1, total = 0;
   for (size_t i = 0; i < tiles.size(); ++i)
     if (!tiles[i].empty()) {
       longest = std::max(longest, k[i]);
       total += k[i] * (int64_t)tiles[i].size();
     }
-  return total <= few * longest;
+  return (total + longest - 1) / longest;
+}
+bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, bool mc, int blocks) {
+  const int64_t entries = entries_of_work(tiles, k);
+  if (mc) return entries <= kFewFine;
+  return entries <= kFewF32 || (entries > blocks && entries <= blocks + kLittleOverF32);
 }
 
 void plan_matrices(const muon_param* p, int n, int ns_dtype, std::vector<MatPlan>& out, size_t& total_partials) {
@@ -692,10 +701,9 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         TileSet& ts = level ? g.coarse : g.fine;
         ts.strips = strips;
         if (level == 0) {
-          const int few = mc ? kFewFine : kFewF32;
-          ts.quarter_sym = runs_in_quarters(sym, w_n, few);
-          ts.quarter_poly = runs_in_quarters(sym, w_m, few);
-          ts.quarter_apply = runs_in_quarters(app, w_m, few);
+          ts.quarter_sym = runs_in_quarters(sym, w_n, mc, plan.coarse_blocks);
+          ts.quarter_poly = runs_in_quarters(sym, w_m, mc, plan.coarse_blocks);
+          ts.quarter_apply = runs_in_quarters(app, w_m, mc, plan.coarse_blocks);
         }
         ts.long_n = !mc && hi_n > kF32LongK;
         ts.long_m = !mc && hi_m > kF32LongK;
