@@ -11,6 +11,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 OBJ_DIR = os.path.join(PKG_DIR, "_build")
 LIB_NAME = "libmuon_hip.so"
 LIB_PATH = os.path.join(PKG_DIR, LIB_NAME)
+MARSHAL_PATH = os.path.join(PKG_DIR, "_adamw_marshal.so")
 # the planner is plain C++ (it also builds with g++ alone, see tests/test_plan_sanitized.py); the rest is HIP
 SOURCES = ("muon_api.hip", "muon_plan.cpp", "kernels_ew.hip", "kernels_gemm_bf16.hip", "kernels_gemm_f32.hip",
            "kernels_adamw.hip", "probe_mfma.hip")
@@ -33,6 +34,18 @@ def hipcc_path() -> str:
     raise RuntimeError("hipcc not found: the Muon HIP library cannot be built")
 
 
+def marshal_command(out):
+    """The compiler line of the extension that marshals AdamW's tensors (host code only; torch's headers and libraries)."""
+    import sysconfig
+    import torch
+    from torch.utils import cpp_extension
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    include = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            *(f"-isystem{d}" for d in include), os.path.join(CSRC, "adamw_marshal.cpp"), "-o", out, f"-L{PKG_DIR}",
+            f"-l:{LIB_NAME}", f"-L{lib_dir}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+
+
 def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
@@ -51,6 +64,8 @@ def build_library(verbose: bool = False, extra_flags=()) -> str:
         list(pool.map(lambda c: _run(c, verbose), cmds))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH + ".tmp"], verbose)
     os.replace(LIB_PATH + ".tmp", LIB_PATH)
+    _run(marshal_command(MARSHAL_PATH + ".tmp"), verbose)
+    os.replace(MARSHAL_PATH + ".tmp", MARSHAL_PATH)
     return LIB_PATH
 
 

@@ -133,3 +133,20 @@ def test_adamw_odd_addresses_and_streaming_launch(dev, sizes):
         assert ((p.double() - pr).abs() <= 2.0 ** -8 * pr.abs() + 1e-6 * (p0.abs() + hp["lr"] * upd.abs())).all()
     for flat, n in flats:
         assert (flat[:33] == 3).all() and (flat[33 + n:] == 3).all()
+
+
+def test_adamw_marshalled_either_way_gives_the_same_bits(dev, monkeypatch):
+    """The extension that reads the tensors and the loop that does without it hand the library the same records."""
+    assert binding._marshal()
+    sizes = [1, 77, 4097, 1024]
+    runs = []
+    for native in (True, False):
+        if not native:
+            monkeypatch.setattr(binding, "_MARSHAL", False)
+        tensors = make(sizes, torch.bfloat16, torch.float32, dev, 3) + make(sizes, torch.float32, torch.bfloat16, dev, 4)
+        for step in (1, 2):
+            binding.muon_adamw_step(tensors, lr=3e-3, weight_decay=0.1, step=step,
+                                    stream_ptr=torch.cuda.current_stream(dev).cuda_stream)
+        torch.cuda.synchronize()
+        runs.append(tensors)
+    assert all(torch.equal(a, b) for x, y in zip(*runs) for a, b in zip(x, y))
