@@ -1,24 +1,28 @@
-// 64 x 64 output tile of a bf16 Newton-Schulz product, for launches that hold few tiles (device code; the products, the
-// operand layouts are described in kernels_gemm_bf16.hip, which includes this file; split operands: gemm_planes.h).
+// 64 x 64 output tile of a bf16 Newton-Schulz product, for launches that hold few tiles, and 32 x 32 tile of one wave for
+// those that hold the fewest (device code; the products and the operand layouts are described in kernels_gemm_bf16.hip, which
+// includes this file; split operands: gemm_planes.h).
 //
 // What bounds such a launch is not the matrix cores but latency: the first operands come from the memory-side cache
 // (about 2 us after the block starts), a block's K loop is a serial chain of slabs, and most compute units hold one
-// block or none.  So the tile is small - four waves with one 32 x 32 MFMA tile each - and the LDS is a ring of kRing64
+// block or none.  So the tile is small - four waves with one 32 x 32 MFMA tile each - and the LDS is a ring of NST
 // slabs of 16 KB that are requested as early as a stage is free and waited for with a partial s_waitcnt vmcnt: only the
-// first slab's latency is seen, and three blocks fit a compute unit.  The fragments of the next slab are read while this
-// one is multiplied; one barrier per slab.
+// first slab's latency is seen.  The fragments of the next slab are read while this one is multiplied; one barrier per slab.
+// A ring of three fits a compute unit three times; alone a block waits for its slabs then (0.35 us each: two slabs' time
+// is a trip to the memory-side cache), with a ring of four 0.3 us.  One wave by itself (NW = 1) has no barriers, half
+// the LDS traffic per slab and a ring of six 8 KB slabs.  muon_plan.cpp holds the line between the three, with their times.
 // Addresses, swizzles and the order in which an output element's products are added are those of the large tiles: in
 // plain bf16 an element comes out with the same bits whichever tile computes it.
 // Measured (us per launch, 256-wide tiles of one block per compute unit / 128-wide tiles / these): Gram product of
-// 4 x 1024^2 and 3 x 1024 x 4096 75 / 43 / 34; products of nine matrices of 200 x 333 to 512 x 768 22 / 9 / 6.  Rings of 2, 4 and 8 slabs took 1.17, 0.98 to
-// 1.07 and 1.1 to 1.4 times as long over whole steps.
+// 4 x 1024^2 and 3 x 1024 x 4096 75 / 43 / 34; products of nine matrices of 200 x 333 to 512 x 768 22 / 9 / 6.  Rings of 6 and
+// 8 slabs gain no more on lone blocks and cost 5 to 10 % of a step where several blocks could share a compute unit.
 #pragma once
 
 namespace muon {
 namespace {
 
-constexpr int kRing64 = 3;
-constexpr size_t kLdsRing64 = (size_t)kRing64 * 128 * ROWB;
+constexpr int kRing64 = 3, kRing64Few = 4, kRing32 = 6;
+constexpr size_t lds_ring64(int stages) { return (size_t)stages * 128 * ROWB; }
+constexpr size_t kLdsRing32 = (size_t)kRing32 * 64 * ROWB;
 constexpr size_t kLdsFold64 = 256 * sizeof(double);       // scratch behind the ring for the folded norm
 
 // Fragments of one k-step of a wave, read by assembly (in front of an LDS read of its own the compiler puts a wait for
@@ -28,11 +32,11 @@ struct Frag64 {
   u32x4 a, b;
   u32x2 h0, h1;
 };
-template <bool LKM>
+template <bool LKM, int HALF>     // HALF: bytes from the first half's k-rows to the second's
 __device__ __forceinline__ void read64(Frag64<LKM>& f, unsigned a_addr, unsigned b_addr) {
   if constexpr (LKM) {
     asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(f.h0) : "v"(a_addr) : "memory");
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.h1) : "v"(a_addr), "n"(4 * ROWB) : "memory");
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.h1) : "v"(a_addr), "n"(HALF) : "memory");
   } else {
     asm volatile("ds_read_b128 %0, %1" : "=v"(f.a) : "v"(a_addr) : "memory");
   }
@@ -52,37 +56,44 @@ __device__ __forceinline__ void land64(Frag64<LKM>& f) {
 }
 
 // The tile at (row0, col0); `diagonal`: it lies on the diagonal of a symmetric product (its own mirror image).
-template <bool LKM>
+template <bool LKM, int NW, int NST>
 __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem,
                                                  float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add) {
-  constexpr int NW = 4, BT = 64, NST = kRing64, NLOAD = 4;      // waves, tile side, stages, 1 KB requests per wave and slab
+  static_assert(NW == 4 || NW == 1, "a wave owns a 32 x 32 tile");
+  constexpr int BT = NW == 4 ? 64 : 32;                         // tile side
+  constexpr int LREQ = BT / 8 / NW, NLOAD = 2 * LREQ;           // 1 KB requests per wave and slab: L, both
   constexpr int STAGE_B = 2 * BT * ROWB, KSTEPS = BK / 16;
-  static_assert(NST >= 3 && NLOAD * (NST - 1) < 64 && ROWB == 2 * BT, "ring shape");
+  static_assert(NST >= 2 && NLOAD * (NST - 1) < 64, "ring shape");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
+  const int wm = NW == 4 ? wave >> 1 : 0, wn = NW == 4 ? wave & 1 : 0;
   const int fr = lane & 31, fh = lane >> 5;
 
-  // ---- requests: a wave instruction fills 8 LDS rows of 128 B (L rows, or k-rows of the K-major L: a slab is 64 x 64
-  // either way).  Row R keeps its 16-byte chunks XOR-swizzled: by (R / 2) % 8, and a k-row by 4 ((R / 2) % 2), which
-  // spreads the four k-rows one transposing read touches over the banks.
+  // ---- requests: a wave instruction fills 8 LDS rows of 128 B (L rows or R rows), which keep their 16-byte chunks
+  // XOR-swizzled by (row / 2) % 8; or, of the K-major L, 1 KB of 64 k-rows of 2 BT bytes, whose chunks are moved by
+  // 4 ((row / 2) % 2) where rows are 128 B (it spreads the four k-rows one transposing read touches over the banks; four rows
+  // of 64 B do not meet).
+  constexpr int CPRK = BT / 8, RPK = 64 / CPRK;
   const int dma_row = wave * 8 + (lane >> 3);
-  const int dma_chunk = (lane & 7) ^ ((dma_row >> 1) & 7);
-  const int km_chunk = (lane & 7) ^ (4 * ((dma_row >> 1) & 1));
-  const u16* lsrc = LKM ? static_cast<const u16*>(p.L) + (size_t)dma_row * p.ldl + row0 + km_chunk * 8
+  const int dma_chunk = (lane & 7) ^ ((dma_row >> 1) & 7);      // of request 0; one wave: odd requests start 8 rows on, key + 4
+  const int km_row = wave * RPK + lane / CPRK;
+  const int km_chunk = (lane % CPRK) ^ (NW == 4 ? 4 * ((km_row >> 1) & 1) : 0);
+  const u16* lsrc = LKM ? static_cast<const u16*>(p.L) + (size_t)km_row * p.ldl + row0 + km_chunk * 8
                         : static_cast<const u16*>(p.L) + (size_t)(row0 + dma_row) * p.ldl + dma_chunk * 8;
   const u16* rsrc = static_cast<const u16*>(p.R) + (size_t)(col0 + dma_row) * p.ldr + dma_chunk * 8;
-  const size_t lstep = (size_t)(8 * NW) * p.ldl, rstep = (size_t)(8 * NW) * p.ldr;
+  const int odd = NW == 4 ? 0 : (dma_chunk ^ 4) * 8 - dma_chunk * 8;
+  const size_t lstep = (size_t)(LKM ? NW * RPK : 8 * NW) * p.ldl, rstep = (size_t)(8 * NW) * p.ldr;
   const size_t lslab = LKM ? (size_t)BK * p.ldl : (size_t)BK;
   const int KT = p.K / BK;
   auto request_one = [&](int kt, int stage, auto n_tag) {
     constexpr int n = decltype(n_tag)::value;
     unsigned char* base = smem + stage * STAGE_B + wave * 1024;
-    if constexpr (n < 2)
-      __builtin_amdgcn_global_load_lds((gptr)(lsrc + n * lstep + (size_t)kt * lslab), (lptr)(base + n * NW * 1024), 16, 0, 0);
+    if constexpr (n < LREQ)
+      __builtin_amdgcn_global_load_lds((gptr)(lsrc + n * lstep + (size_t)kt * lslab + (!LKM && n % 2 ? odd : 0)), (lptr)(base + n * NW * 1024), 16, 0, 0);
     else
-      __builtin_amdgcn_global_load_lds((gptr)(rsrc + (n - 2) * rstep + (size_t)kt * BK), (lptr)(base + BT * ROWB + (n - 2) * NW * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gptr)(rsrc + (n - LREQ) * rstep + (size_t)kt * BK + ((n - LREQ) % 2 ? odd : 0)),
+                                       (lptr)(base + BT * ROWB + (n - LREQ) * NW * 1024), 16, 0, 0);
   };
 
   // ---- fragment reads (lane addressing as in the large tiles) ----
@@ -90,8 +101,8 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
   const unsigned lds0 = (unsigned)(size_t)(lptr)smem;
   const unsigned a_base = (unsigned)((wm * 32 + fr) * ROWB), b_base = (unsigned)(BT * ROWB + (wn * 32 + fr) * ROWB);
   const int l16 = lane & 15, grp = lane >> 4, r4 = l16 >> 2;
-  const unsigned a_km = (unsigned)((8 * (grp >> 1) + r4) * ROWB + (((4 * wm) ^ (4 * ((r4 >> 1) & 1))) + 2 * (grp & 1) + ((l16 & 3) >> 1)) * 16 +
-                                   (l16 & 1) * 8);
+  const unsigned a_km = (unsigned)((8 * (grp >> 1) + r4) * (2 * BT) +
+                                   (((4 * wm) ^ (NW == 4 ? 4 * ((r4 >> 1) & 1) : 0)) + 2 * (grp & 1) + ((l16 & 3) >> 1)) * 16 + (l16 & 1) * 8);
   Frag64<LKM> fg[2][KSTEPS];                     // fragments of two slabs: one multiplied, one being read
   auto read_slab = [&](int stage, auto set_tag) {
     constexpr int set = decltype(set_tag)::value;
@@ -99,7 +110,7 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
     static_for<0, KSTEPS>([&](auto kk_tag) {
       constexpr int kk = decltype(kk_tag)::value;
       const unsigned chunk = (unsigned)(((2 * kk + fh) ^ fkey) * 16);
-      read64(fg[set][kk], LKM ? sa + (unsigned)(16 * kk * ROWB) + a_km : sa + a_base + chunk, sa + b_base + chunk);
+      read64<LKM, 4 * 2 * BT>(fg[set][kk], LKM ? sa + (unsigned)(16 * kk * 2 * BT) + a_km : sa + a_base + chunk, sa + b_base + chunk);
     });
   };
   f32x16 acc;
@@ -134,7 +145,8 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
       }
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, fg[set][kk].b), acc, 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (REFILL) request_one(kt + NST, stage, kk_tag);
+      if constexpr (REFILL)
+        static_for<kk * NLOAD / KSTEPS, (kk + 1) * NLOAD / KSTEPS>([&](auto n_tag) { request_one(kt + NST, stage, n_tag); });
     });
     stage = next;
     ++kt;
@@ -156,14 +168,19 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
   using T_ = std::true_type;
   using F_ = std::false_type;
   auto request_slab = [&](int s) { static_for<0, NLOAD>([&](auto n_tag) { request_one(s, s, n_tag); }); };
-  static_assert(NST == 3, "the slabs written out below: extents are padded to 128, so KT is even");
+  // (extents are padded to 128, so KT is even)
   request_slab(0);
   request_slab(1);
+  if constexpr (NST % 2 == 0)
+    static_for<2, NST>([&](auto s_tag) {
+      if (decltype(s_tag)::value < KT) request_slab(decltype(s_tag)::value);
+    });
   float alpha = 1.f;
   if (!LKM && alpha_idx == kAlphaFromPartials) {
     // first Gram product: the norm, from the partial sums (K-major launches are never first)
     float s, s2;
-    norm_scalars(block_sum_f64(p.partials, p.n_part, reinterpret_cast<double*>(smem + kLdsRing64)), eps, &s, &s2);
+    if constexpr (NW == 4) norm_scalars(block_sum_f64(p.partials, p.n_part, reinterpret_cast<double*>(smem + lds_ring64(NST))), eps, &s, &s2);
+    else norm_scalars(wave_sum_f64(p.partials, p.n_part), eps, &s, &s2);
     if (row0 == 0 && col0 == 0 && tid == 0) {
       float* scal = const_cast<float*>(p.scal);
       scal[0] = s;
@@ -173,25 +190,45 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
   } else if (alpha_idx >= 0) {
     alpha = p.scal[alpha_idx];
   }
-  if (KT == 2) {                                 // K = 128: all of it is on its way
-    wait_vmcnt<NLOAD>();
+  if constexpr (NST == 3) {
+    if (KT == 2) {                               // K = 128: all of it is on its way
+      wait_vmcnt<NLOAD>();
+      __builtin_amdgcn_s_barrier();
+      read_slab(0, I0{});
+      slab(I0{}, T_{}, F_{}, I0{});
+      slab(I1{}, F_{}, F_{}, I0{});
+    } else {
+      request_slab(2);
+      wait_vmcnt<2 * NLOAD>();
+      __builtin_amdgcn_s_barrier();
+      read_slab(0, I1{});
+      slab(I1{}, T_{}, T_{}, I1{});
+      while (kt + NST < KT) {
+        slab(I0{}, T_{}, T_{}, I1{});
+        slab(I1{}, T_{}, T_{}, I1{});
+      }
+      slab(I0{}, T_{}, F_{}, I1{});
+      slab(I1{}, T_{}, F_{}, I0{});
+      slab(I0{}, F_{}, F_{}, I0{});
+    }
+  } else {
+    static_assert(NST == 4 || NST == 6, "every shorter K has its wait");
+    if (KT >= NST) wait_vmcnt<NLOAD * (NST - 1)>();
+    else if (KT == 4) wait_vmcnt<NLOAD * 3>();
+    else wait_vmcnt<NLOAD>();
     __builtin_amdgcn_s_barrier();
     read_slab(0, I0{});
-    slab(I0{}, T_{}, F_{}, I0{});
-    slab(I1{}, F_{}, F_{}, I0{});
-  } else {                                       // KT is even
-    request_slab(2);
-    wait_vmcnt<2 * NLOAD>();
-    __builtin_amdgcn_s_barrier();
-    read_slab(0, I1{});
-    slab(I1{}, T_{}, T_{}, I1{});
     while (kt + NST < KT) {
-      slab(I0{}, T_{}, T_{}, I1{});
-      slab(I1{}, T_{}, T_{}, I1{});
+      slab(I0{}, T_{}, T_{}, std::integral_constant<int, NST - 2>{});
+      slab(I1{}, T_{}, T_{}, std::integral_constant<int, NST - 2>{});
     }
-    slab(I0{}, T_{}, F_{}, I1{});
-    slab(I1{}, T_{}, F_{}, I0{});
-    slab(I0{}, F_{}, F_{}, I0{});
+    static_for<0, NST / 2>([&](auto h_tag) {
+      constexpr int left = NST - 1 - 2 * decltype(h_tag)::value;               // slabs behind this one
+      if (left == 1 || KT > left) {
+        slab(I0{}, T_{}, F_{}, std::integral_constant<int, left - 1>{});
+        slab(I1{}, std::integral_constant<bool, (left > 1)>{}, F_{}, std::integral_constant<int, (left > 1 ? left - 2 : 0)>{});
+      }
+    });
   }
   __syncthreads();                               // every wave has read the last slab: the LDS is free for the images
 
@@ -223,17 +260,19 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
 
   // ---- results leave through swizzled LDS images of 64 rows x 128 B (chunk of row r at position
   // chunk ^ (r / 2) % 8), 16 bytes per lane ----
+  constexpr int CPT = BT / 8, RPI = 64 / CPT, NIMG = BT / RPI / NW;     // chunks per row, rows and instructions per wave
+  auto key = [](int row) { return NW == 4 ? (row >> 1) & 7 : (row >> 2) & 3; };
   auto slot = [&](int row, int chunk) -> u32x2* {
-    return reinterpret_cast<u32x2*>(smem + row * ROWB + ((chunk ^ ((row >> 1) & 7)) * 16) + fh * 8);
+    return reinterpret_cast<u32x2*>(smem + row * (2 * BT) + ((chunk ^ key(row)) * 16) + fh * 8);
   };
   auto store_image = [&](u16* dst, int ld, int first_row, int first_col) {
-    u32x4 v[2];
+    u32x4 v[NIMG];
 #pragma unroll
-    for (int n = 0; n < 2; ++n) v[n] = *reinterpret_cast<const u32x4*>(smem + (n * NW + wave) * 1024 + lane * 16);
+    for (int n = 0; n < NIMG; ++n) v[n] = *reinterpret_cast<const u32x4*>(smem + (n * NW + wave) * 1024 + lane * 16);
 #pragma unroll
-    for (int n = 0; n < 2; ++n) {
-      const int r = n * 8 * NW + dma_row;
-      *(gvec_ptr)(dst + (size_t)(first_row + r) * ld + first_col + dma_chunk * 8) = v[n];
+    for (int n = 0; n < NIMG; ++n) {
+      const int r = (n * NW + wave) * RPI + lane / CPT;
+      *(gvec_ptr)(dst + (size_t)(first_row + r) * ld + first_col + ((lane % CPT) ^ key(r)) * 8) = v[n];
     }
   };
   bf16x8 sel[2];                                 // 0/1 selector of the MFMA transpose

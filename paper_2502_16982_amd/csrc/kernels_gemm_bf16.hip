@@ -946,7 +946,39 @@ __global__ __launch_bounds__(256, PL == 3 ? 2 : 3) void ns_tile64_gemm_bf16_kern
   const GemmProblem p = probs[tile.prob];
   const int row0 = tile.r0 * kTileUnit + 64 * (quarter >> 1), col0 = tile.c0 * kTileUnit + 64 * (quarter & 1);
   if constexpr (PL > 1) planes_tile<64, LKM, PL>(p, row0, col0, on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps);
-  else gemm_tile64_body<LKM>(p, row0, col0, on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps, diag_add);
+  else gemm_tile64_body<LKM, 4, kRing64>(p, row0, col0, on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps, diag_add);
+}
+
+// The same with a longer ring: two blocks fit a compute unit instead of three.
+template <bool LKM>
+__global__ __launch_bounds__(256, 2) void ns_ring4_gemm_bf16_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
+                                                                    int n_tiles, float beta_acc, float beta_e, int alpha_idx, double eps,
+                                                                    float diag_add) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int t = (int)(blockIdx.x >> 5) * 8 + (int)(blockIdx.x & 7), quarter = (int)(blockIdx.x >> 3) & 3;
+  if (t >= n_tiles) return;
+  const GemmTile tile = load_tile(tiles, t);
+  const bool on_diag = (tile.flags & kTileDiagonal) != 0;
+  if (on_diag && quarter == 2) return;
+  const GemmProblem p = probs[tile.prob];
+  gemm_tile64_body<LKM, 4, kRing64Few>(p, tile.r0 * kTileUnit + 64 * (quarter >> 1), tile.c0 * kTileUnit + 64 * (quarter & 1),
+                                       on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps, diag_add);
+}
+
+// Each entry as sixteen blocks of one wave and 32 x 32.  Block b: entry 8 (b / 128) + b % 8, sixteenth (b / 8) % 16.
+template <bool LKM>
+__global__ __launch_bounds__(64) void ns_tile32_gemm_bf16_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
+                                                                 int n_tiles, float beta_acc, float beta_e, int alpha_idx, double eps,
+                                                                 float diag_add) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int t = (int)(blockIdx.x >> 7) * 8 + (int)(blockIdx.x & 7), part = (int)(blockIdx.x >> 3) & 15;
+  if (t >= n_tiles) return;
+  const GemmTile tile = load_tile(tiles, t);
+  const bool on_diag = (tile.flags & kTileDiagonal) != 0;
+  if (on_diag && (part >> 2) > (part & 3)) return;   // below the diagonal: a mirror image
+  const GemmProblem p = probs[tile.prob];
+  gemm_tile64_body<LKM, 1, kRing32>(p, tile.r0 * kTileUnit + 32 * (part >> 2), tile.c0 * kTileUnit + 32 * (part & 3),
+                           on_diag && (part >> 2) == (part & 3), smem, beta_acc, beta_e, alpha_idx, eps, diag_add);
 }
 
 // Block b works through table entries b, b + gridDim.x, ...  Launched with one block per tile, or persistent: one
@@ -996,7 +1028,10 @@ hipError_t setup_pair() {
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_fine(PL));
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_tile64_gemm_bf16_kernel<LKM, PL>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsRing64 + kLdsFold64));
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_ring64(kRing64) + kLdsFold64));
+  if (e == hipSuccess && PL == 1)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_ring4_gemm_bf16_kernel<LKM>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_ring64(kRing64Few) + kLdsFold64));
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_bf16_kernel<LKM, PL>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)(PL > 1 ? lds_fine(PL) : kLds512));
@@ -1005,9 +1040,16 @@ hipError_t setup_pair() {
 template <bool LKM, int PL>
 void launch_one(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc,
                 float beta_e, int alpha_idx, double eps, float diag_add, hipStream_t s) {
-  if (!coarse && (flags & kGemmQuarters))
+  if (PL == 1 && !coarse && (flags & kGemmSixteenths))
+    ns_tile32_gemm_bf16_kernel<LKM><<<(n_tiles + 7) / 8 * 128, 64, kLdsRing32, s>>>(probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx,
+                                                                                    eps, diag_add);
+  else if (PL == 1 && !coarse && (flags & kGemmFewQuarters))
+    ns_ring4_gemm_bf16_kernel<LKM><<<(n_tiles + 7) / 8 * 32, 256,
+                                     lds_ring64(kRing64Few) + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(
+        probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, diag_add);
+  else if (!coarse && (flags & kGemmQuarters))
     ns_tile64_gemm_bf16_kernel<LKM, PL><<<(n_tiles + 7) / 8 * 32, 256,
-                                          kLdsRing64 + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(
+                                          lds_ring64(kRing64) + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(
         probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, diag_add);
   else if (!coarse)
     ns_gemm_bf16_fine_kernel<LKM, PL><<<n_tiles, 256, lds_fine(PL), s>>>(probs, tiles, beta_acc, beta_e, alpha_idx, diag_add);

@@ -178,6 +178,10 @@ int check_step_args(const muon_ctx* ctx, const muon_param* params, int32_t n, co
   return MUON_OK;
 }
 
+int quarter_flags(bool quarters, int few) {
+  return quarters ? kGemmQuarters | (few == 2 ? kGemmSixteenths : few == 1 ? kGemmFewQuarters : 0) : 0;
+}
+
 // Enqueues every kernel of one step on stream s.  The pointer table is already on its way on the same stream, or (pack, plans
 // of one chunk) the first pass takes the pointers as an argument and fills it.
 int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* update_rms_out, const PtrPack* pack = nullptr) {
@@ -208,7 +212,7 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
           const TileSet& ts = level ? g.coarse : g.fine;
           if (ts.n_sym == 0) continue;
           if (mc)
-            MUON_TIMED(MUON_PROF_GRAM, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_n ? kGemmPersistent : 0) | (ts.quarter_sym ? kGemmQuarters : 0), P(g.prob_gram[par]), T(ts.sym), ts.n_sym, 1.f, 0.f,
+            MUON_TIMED(MUON_PROF_GRAM, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_n ? kGemmPersistent : 0) | quarter_flags(ts.quarter_sym, ts.few_sym), P(g.prob_gram[par]), T(ts.sym), ts.n_sym, 1.f, 0.f,
                                                         first ? (fold ? kAlphaFromPartials : 1) : -1, hp->eps, 0.f, 0, planes, s));
           else
             MUON_TIMED(MUON_PROF_GRAM, launch_gemm_f32((ts.quarter_sym ? kGemmQuarters : 0) | (ts.long_n ? kGemmLongK : 0), P(g.prob_gram[par]), T(ts.sym), ts.n_sym, 1.f, 0.f,
@@ -218,7 +222,7 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
           const TileSet& ts = level ? g.coarse : g.fine;
           if (ts.n_poly == 0) continue;
           if (mc)
-            MUON_TIMED(MUON_PROF_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | (ts.quarter_poly ? kGemmQuarters : 0), P(g.prob_poly), T(ts.poly), ts.n_poly, c, b, -1, 0.0, a, 0, planes, s));
+            MUON_TIMED(MUON_PROF_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | quarter_flags(ts.quarter_poly, ts.few_poly), P(g.prob_poly), T(ts.poly), ts.n_poly, c, b, -1, 0.0, a, 0, planes, s));
           else
             MUON_TIMED(MUON_PROF_POLY, launch_gemm_f32((ts.quarter_poly ? kGemmQuarters : 0) | (ts.long_m ? kGemmLongK : 0), P(g.prob_poly), T(ts.poly), ts.n_poly, c, b, -1, 0.0, s));
         }
@@ -226,7 +230,7 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
           const TileSet& ts = level ? g.coarse : g.fine;
           if (ts.n_apply == 0) continue;
           if (mc)
-            MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | (ts.quarter_apply ? kGemmQuarters : 0), P(g.prob_apply[par * 2 + last]), T(ts.apply),
+            MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | quarter_flags(ts.quarter_apply, ts.few_apply), P(g.prob_apply[par * 2 + last]), T(ts.apply),
                                                               ts.n_apply, 1.f, a, first ? 0 : -1, 0.0, 0.f, 1, planes, s));
           else
             MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_f32((ts.quarter_apply ? kGemmQuarters : 0) | (ts.long_m ? kGemmLongK : 0), P(g.prob_apply[par * 2 + last]), T(ts.apply), ts.n_apply, 1.f, a,

@@ -36,6 +36,20 @@ __device__ __forceinline__ double block_sum_f64(const float* __restrict__ v, int
   for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
   return t;
 }
+// The same sum in the same order by one wave.
+__device__ __forceinline__ double wave_sum_f64(const float* __restrict__ v, int n) {
+  const int l = threadIdx.x & 63;
+  double acc[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    acc[q] = 0.0;
+    for (int i = l + 64 * q; i < n; i += 256) acc[q] += (double)v[i];
+  }
+  double t = (acc[0] + acc[2]) + (acc[1] + acc[3]);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+  return t;
+}
 // a2: 1/(sqrt(sum) + eps) and its square from the sum of squares of U.  An all-zero U with eps = 0 would give inf; X is all
 // zero then, and 0 * inf must not appear.
 __device__ __forceinline__ void norm_scalars(double sum, double eps, float* s, float* s2) {
@@ -72,13 +86,14 @@ hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, 
 // allocation).  kGemmPersistent: one block per compute unit works through the table with stride gridDim (for launches
 // whose tiles run K loops of nearly the same length, which the planner balances statically; with a wide spread of K
 // the hardware's dynamic block dispatch does better).
-// kGemmQuarters (coarse = 0): every entry of the table runs as four blocks, one per quarter of it.
+// kGemmQuarters (coarse = 0): every entry of the table runs as four blocks, one per quarter of it.  kGemmFewQuarters (plain
+// bf16, with kGemmQuarters): with a longer ring; kGemmSixteenths (plain bf16, with kGemmQuarters): as sixteen blocks of one wave.
 // kGemmLongK (fp32): needed where a problem of the launch has K > kF32LongK.
 // l_kmajor: every problem of the launch stores its L operand K-major (element (i, k) at L[k * ldl + i]).
 // planes: 1 = plain bf16; 2 or 3 = every matrix is a sum of that many bf16 planes (GemmProblem::*_plane strides); entries of a
 // coarse table then run as four 128 x 128 blocks each.
 constexpr int kAlphaFromPartials = 2;
-constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmQuarters = 4, kGemmLongK = 8;
+constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmQuarters = 4, kGemmLongK = 8, kGemmSixteenths = 16, kGemmFewQuarters = 32;
 hipError_t launch_gemm_bf16(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
                             float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add, int l_kmajor, int planes,
                             hipStream_t s);

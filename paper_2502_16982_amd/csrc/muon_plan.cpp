@@ -304,6 +304,27 @@ bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std
   return entries <= kFewF32 || (entries > blocks && entries <= blocks + kLittleOverF32);
 }
 
+// Plain bf16, launches in quarters that leave most compute units with one block or none: 2 = each 32 x 32 as one wave of its
+// own (shortest chain of slabs; twice the operand traffic), 1 = 64 x 64 blocks with a ring of four slabs (two blocks on a
+// compute unit instead of three), 0 = with a ring of three.  Measured, us per step, 0 / 1 / 2: 256^2 (3 and 4 entries) 57.2 /
+// 56.4 / 50.7, 512^2 (10, 16) 77.3 / 73.6 / 66.9, 63 x 4097 (1, 33) 134 / 115 / 113, 2 of 512^2 (20, 32) 81.0 / 77.5 / 74.8, 9
+// of 200 x 333 (27, 54) 72.0 / 70.8 / 68.5; longer K from 24 entries on: 1024 x 4096 (36) 218 / 193 / 208, 1000 x 3001 (36) 197
+// / 178 / 185; 512^2 x 6 (60) 96.2 / 95.3; 1536^2 (78) 215 / 218, 10 of 512^2 (100) 119 / 121, 3 of 1024^2 (108) 172 / 176, 14 of
+// 512^2 (140) 147 / 157; a Gram launch of 128 entries with the work of 60, six matrices of K up to 4224: 318 / 308.
+constexpr size_t kFewest = 24, kFewestShort = 36, kFewEntries = 128;
+constexpr int64_t kShortK = 1024, kFewWork = 64;
+int few_blocks(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k) {
+  size_t n = 0;
+  int64_t longest = 0;
+  for (size_t i = 0; i < tiles.size(); ++i)
+    if (!tiles[i].empty()) {
+      n += tiles[i].size();
+      longest = std::max(longest, k[i]);
+    }
+  if (n <= kFewest || (n <= kFewestShort && longest <= kShortK)) return 2;
+  return n <= kFewEntries && entries_of_work(tiles, k) <= kFewWork ? 1 : 0;
+}
+
 void plan_matrices(const muon_param* p, int n, int ns_dtype, std::vector<MatPlan>& out, size_t& total_partials) {
   out.resize(n);
   total_partials = 0;
@@ -704,6 +725,11 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
           ts.quarter_sym = runs_in_quarters(sym, w_n, mc, plan.coarse_blocks);
           ts.quarter_poly = runs_in_quarters(sym, w_m, mc, plan.coarse_blocks);
           ts.quarter_apply = runs_in_quarters(app, w_m, mc, plan.coarse_blocks);
+          if (ns_dtype == MUON_BF16) {
+            ts.few_sym = few_blocks(sym, w_n);
+            ts.few_poly = few_blocks(sym, w_m);
+            ts.few_apply = few_blocks(app, w_m);
+          }
         }
         ts.long_n = !mc && hi_n > kF32LongK;
         ts.long_m = !mc && hi_m > kF32LongK;

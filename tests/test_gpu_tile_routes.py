@@ -57,6 +57,28 @@ def test_64_wide_tiles_at_their_edges(dev, ns, tol):
     assert_records(U.run_and_compare(wl, dev, steps=2, want_rms=True), tol)
 
 
+@pytest.mark.parametrize("shape,longer", [((100, 130), 6), ((128, 256), 3), ((256, 300), 6), ((384, 200), 9), ((130, 520), 4), ((40, 900), 26), ((300, 1100), 7)])
+def test_same_bits_from_waves_and_both_rings(dev, shape, longer):
+    """Plain bf16: alone a matrix of these sizes runs as one wave per 32 x 32; in a list of some tens of entries, then of hundreds, as
+    64-wide blocks with a ring of four slabs, then of three, or in 128-wide tiles.  K of 2, 4, 6 and more slabs; the norm
+    added up by one wave, by a block, and by its own launch."""
+    wl = workloads.custom("waves", [shape], seed_base=345)
+    first = workloads.make_matrix(wl, 0, dev)
+    hp = binding.default_hparams(lr=0.02, weight_decay=0.1)
+    results = []
+    for n in (1, longer, 60, 400):
+        tensors = [tuple(t.clone() for t in first) for _ in range(n)]
+        st = binding.MuonStepper(tensors)
+        for _ in range(2):
+            st.step(hp)
+        torch.cuda.synchronize()
+        results += [(n, i, st.read_update(i), tensors[i][0], tensors[i][2]) for i in {0, n // 2, n - 1}]
+        st.close()
+    assert max(table_sizes([shape], "bf16", 0)) <= 36
+    for n, i, o, w, m in results[1:]:
+        assert torch.equal(o, results[0][2]) and torch.equal(w, results[0][3]) and torch.equal(m, results[0][4]), (n, i)
+
+
 @pytest.mark.parametrize("ns", ["bf16x2", "bf16x3"])
 def test_planes_in_128_wide_tiles_at_their_edges(dev, ns):
     """More entries than a launch in quarters holds.  K of one and of several pairs of pieces (the loop not run, run once, run
