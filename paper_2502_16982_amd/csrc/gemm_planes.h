@@ -11,7 +11,9 @@
 // in a loop over pairs, the whole rate of a compute unit, 85 and 64 B here.
 // The LDS is a ring of NST units, requested as early as a stage is free and waited for with a partial s_waitcnt vmcnt; the
 // next unit's fragments are read while this one is multiplied; one barrier per unit.  The addend's planes come through the
-// same ring behind the last unit.  BT = 128: with two planes two blocks on a compute unit (ring of 2, 250 registers; one
+// same ring behind the last unit.  BT = 64: three stages, or four where a launch leaves a block alone on its compute unit: one
+// more unit in flight (two planes: 512^2 118 -> 109 us, 1024 x 4096 397 -> 362, 5 of 40 x 3800 222 -> 189; three: 156 -> 145, 579
+// -> 545, 307 -> 265), but fewer blocks on a compute unit (10 of 512^2 208 -> 214 and 292 -> 296).  BT = 128: with two planes two blocks on a compute unit (ring of 2, 250 registers; one
 // block with a ring of 4 is 2 % faster on 4096^2 and 8 to 20 % slower on lists of 512^2 to 1024 x 4096), with three planes one.
 // Rounding.  Three planes: the leading pair has two accumulators, of even and odd pieces, and the other pairs a third, so the
 // small terms are not rounded at the size of the sum (error of O against 64 bits: 1024 x 4096 1.38e-6 -> 0.97e-6, 100 x 300
@@ -29,7 +31,8 @@ namespace muon {
 namespace {
 
 constexpr int planes_ring(int bt, int pl) { return bt == 64 ? 3 : pl == 2 ? 2 : 4; }
-constexpr size_t planes_lds(int bt, int pl) { return (size_t)planes_ring(bt, pl) * 2 * (size_t)bt * ROWB; }
+constexpr int kPlanesRingFew = 4;                // BT = 64 where a block has a compute unit to itself
+constexpr size_t planes_lds(int bt, int stages) { return (size_t)stages * 2 * (size_t)bt * ROWB; }
 
 // Fragments of one k-step of one plane, read by assembly (see gemm_tile64.h).
 template <int F, bool LKM>
@@ -55,10 +58,10 @@ __device__ __forceinline__ void tie_planes(PlaneFrag<F, LKM>& f) {
 }
 
 // ADD: the product has an addend.  The tile at (row0, col0); `diagonal`: it lies on the diagonal of a symmetric product (its own mirror image).
-template <int BT, bool LKM, int PL, bool ADD>
+template <int BT, int NST, bool LKM, int PL, bool ADD>
 __device__ __forceinline__ void gemm_planes_body(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem,
                                                  float beta_acc, float beta_e, int alpha_idx, double eps) {
-  constexpr int NW = 4, F = BT / 64, WT = BT / 2, NST = planes_ring(BT, PL);
+  constexpr int NW = 4, F = BT / 64, WT = BT / 2;
   constexpr int LREQ = BT / 32, NLOAD = 2 * LREQ;               // 1 KB requests per wave and unit: L, both
   constexpr bool SPLIT = PL == 3, ALL11 = PL == 3 || (!LKM && ADD);
   constexpr int UNIT_B = 2 * BT * ROWB, KSTEPS = BK / 16, NACC = SPLIT ? 3 : 1;
@@ -221,7 +224,7 @@ __device__ __forceinline__ void gemm_planes_body(const GemmProblem& p, int row0,
   if (BT == 64 && !LKM && alpha_idx == kAlphaFromPartials) {
     // first Gram product: the norm, from the partial sums (K-major launches are never first)
     float s, s2;
-    norm_scalars(block_sum_f64(p.partials, p.n_part, reinterpret_cast<double*>(smem + planes_lds(BT, PL))), eps, &s, &s2);
+    norm_scalars(block_sum_f64(p.partials, p.n_part, reinterpret_cast<double*>(smem + planes_lds(BT, NST))), eps, &s, &s2);
     if (row0 == 0 && col0 == 0 && tid == 0) {
       float* scal = const_cast<float*>(p.scal);
       scal[0] = s;
@@ -360,11 +363,11 @@ __device__ __forceinline__ void gemm_planes_body(const GemmProblem& p, int row0,
 }
 
 // (the apply product, K-major, always has an addend: with planes the a X term is not folded into the polynomial)
-template <int BT, bool LKM, int PL>
+template <int BT, int NST, bool LKM, int PL>
 __device__ __forceinline__ void planes_tile(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem,
                                             float beta_acc, float beta_e, int alpha_idx, double eps) {
-  if (LKM || p.Et) gemm_planes_body<BT, LKM, PL, true>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps);
-  else gemm_planes_body<BT, LKM, PL, false>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps);
+  if (LKM || p.Et) gemm_planes_body<BT, NST, LKM, PL, true>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps);
+  else gemm_planes_body<BT, NST, LKM, PL, false>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps);
 }
 
 }  // namespace

@@ -911,7 +911,9 @@ namespace {
 // 128 x 128 tile, so they share register budget, MFMA schedule and per-wave LDS traffic, and a launch mixes them freely:
 // the strips fill compute units next to the 256-tiles of the same product instead of running as a launch of their own.
 constexpr size_t kLds128 = TileCfg<128, 128>::lds_bytes(2);
-constexpr size_t lds_fine(int planes) { return planes > 1 ? planes_lds(128, planes) : kLds128; }
+constexpr size_t lds_quarters(int planes) { return planes > 1 ? planes_lds(64, planes_ring(64, planes)) : lds_ring64(kRing64); }
+constexpr size_t lds_few_quarters(int planes) { return planes > 1 ? planes_lds(64, kPlanesRingFew) : lds_ring64(kRing64Few); }
+constexpr size_t lds_fine(int planes) { return planes > 1 ? planes_lds(128, planes_ring(128, planes)) : kLds128; }
 constexpr size_t kLds256 = TileCfg<256, 256>::lds_bytes(2);
 constexpr size_t kLds512 = TileCfg<512, 128>::lds_bytes(2);
 constexpr int kMaxPlanes = 3;
@@ -924,7 +926,7 @@ __global__ __launch_bounds__(256, PL == 3 ? 1 : 2) void ns_gemm_bf16_fine_kernel
   const GemmTile tile = load_tile(tiles, blockIdx.x);
   const GemmProblem p = probs[tile.prob];
   if constexpr (PL > 1)
-    planes_tile<128, LKM, PL>(p, tile.r0 * kTileUnit, tile.c0 * kTileUnit, (tile.flags & kTileDiagonal) != 0, smem, beta_acc, beta_e,
+    planes_tile<128, planes_ring(128, PL), LKM, PL>(p, tile.r0 * kTileUnit, tile.c0 * kTileUnit, (tile.flags & kTileDiagonal) != 0, smem, beta_acc, beta_e,
                               alpha_idx, 0.0);
   else
     gemm_tile_body<128, 128, 2, 2, 2, LKM>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add,
@@ -945,12 +947,12 @@ __global__ __launch_bounds__(256, PL == 3 ? 2 : 3) void ns_tile64_gemm_bf16_kern
   if (on_diag && quarter == 2) return;           // below the diagonal: the mirror image of quarter 1
   const GemmProblem p = probs[tile.prob];
   const int row0 = tile.r0 * kTileUnit + 64 * (quarter >> 1), col0 = tile.c0 * kTileUnit + 64 * (quarter & 1);
-  if constexpr (PL > 1) planes_tile<64, LKM, PL>(p, row0, col0, on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps);
+  if constexpr (PL > 1) planes_tile<64, planes_ring(64, PL), LKM, PL>(p, row0, col0, on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps);
   else gemm_tile64_body<LKM, 4, kRing64>(p, row0, col0, on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps, diag_add);
 }
 
-// The same with a longer ring: two blocks fit a compute unit instead of three.
-template <bool LKM>
+// The same with a ring of four stages: two blocks fit a compute unit instead of three.
+template <bool LKM, int PL>
 __global__ __launch_bounds__(256, 2) void ns_ring4_gemm_bf16_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
                                                                     int n_tiles, float beta_acc, float beta_e, int alpha_idx, double eps,
                                                                     float diag_add) {
@@ -961,8 +963,9 @@ __global__ __launch_bounds__(256, 2) void ns_ring4_gemm_bf16_kernel(const GemmPr
   const bool on_diag = (tile.flags & kTileDiagonal) != 0;
   if (on_diag && quarter == 2) return;
   const GemmProblem p = probs[tile.prob];
-  gemm_tile64_body<LKM, 4, kRing64Few>(p, tile.r0 * kTileUnit + 64 * (quarter >> 1), tile.c0 * kTileUnit + 64 * (quarter & 1),
-                                       on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps, diag_add);
+  const int row0 = tile.r0 * kTileUnit + 64 * (quarter >> 1), col0 = tile.c0 * kTileUnit + 64 * (quarter & 1);
+  if constexpr (PL > 1) planes_tile<64, kPlanesRingFew, LKM, PL>(p, row0, col0, on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps);
+  else gemm_tile64_body<LKM, 4, kRing64Few>(p, row0, col0, on_diag && quarter != 1, smem, beta_acc, beta_e, alpha_idx, eps, diag_add);
 }
 
 // Each entry as sixteen blocks of one wave and 32 x 32.  Block b: entry 8 (b / 128) + b % 8, sixteenth (b / 8) % 16.
@@ -1001,7 +1004,7 @@ __global__ __launch_bounds__(256, PL == 2 ? 2 : 1) void ns_gemm_bf16_kernel(cons
     const GemmProblem p = probs[tile.prob];
     const int row0 = tile.r0 * kTileUnit + 128 * (strip ? quarter : quarter >> 1), col0 = tile.c0 * kTileUnit + 128 * (strip ? 0 : quarter & 1);
     if (p.symmetric && row0 > col0) return;      // below the diagonal: a mirror image
-    planes_tile<128, LKM, PL>(p, row0, col0, p.symmetric && row0 == col0, smem, beta_acc, beta_e, alpha_idx, 0.0);
+    planes_tile<128, planes_ring(128, PL), LKM, PL>(p, row0, col0, p.symmetric && row0 == col0, smem, beta_acc, beta_e, alpha_idx, 0.0);
   } else {
     const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
@@ -1028,10 +1031,10 @@ hipError_t setup_pair() {
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_fine(PL));
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_tile64_gemm_bf16_kernel<LKM, PL>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_ring64(kRing64) + kLdsFold64));
-  if (e == hipSuccess && PL == 1)
-    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_ring4_gemm_bf16_kernel<LKM>),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_ring64(kRing64Few) + kLdsFold64));
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_quarters(PL) + kLdsFold64));
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_ring4_gemm_bf16_kernel<LKM, PL>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_few_quarters(PL) + kLdsFold64));
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_bf16_kernel<LKM, PL>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)(PL > 1 ? lds_fine(PL) : kLds512));
@@ -1043,13 +1046,13 @@ void launch_one(int coarse, int flags, const GemmProblem* probs, const GemmTile*
   if (PL == 1 && !coarse && (flags & kGemmSixteenths))
     ns_tile32_gemm_bf16_kernel<LKM><<<(n_tiles + 7) / 8 * 128, 64, kLdsRing32, s>>>(probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx,
                                                                                     eps, diag_add);
-  else if (PL == 1 && !coarse && (flags & kGemmFewQuarters))
-    ns_ring4_gemm_bf16_kernel<LKM><<<(n_tiles + 7) / 8 * 32, 256,
-                                     lds_ring64(kRing64Few) + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(
+  else if (!coarse && (flags & kGemmFewQuarters))
+    ns_ring4_gemm_bf16_kernel<LKM, PL><<<(n_tiles + 7) / 8 * 32, 256,
+                                         lds_few_quarters(PL) + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(
         probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, diag_add);
   else if (!coarse && (flags & kGemmQuarters))
     ns_tile64_gemm_bf16_kernel<LKM, PL><<<(n_tiles + 7) / 8 * 32, 256,
-                                          lds_ring64(kRing64) + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(
+                                          lds_quarters(PL) + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(
         probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, diag_add);
   else if (!coarse)
     ns_gemm_bf16_fine_kernel<LKM, PL><<<n_tiles, 256, lds_fine(PL), s>>>(probs, tiles, beta_acc, beta_e, alpha_idx, diag_add);

@@ -86,8 +86,8 @@ hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, 
 // allocation).  kGemmPersistent: one block per compute unit works through the table with stride gridDim (for launches
 // whose tiles run K loops of nearly the same length, which the planner balances statically; with a wide spread of K
 // the hardware's dynamic block dispatch does better).
-// kGemmQuarters (coarse = 0): every entry of the table runs as four blocks, one per quarter of it.  kGemmFewQuarters (plain
-// bf16, with kGemmQuarters): with a longer ring; kGemmSixteenths (plain bf16, with kGemmQuarters): as sixteen blocks of one wave.
+// kGemmQuarters (coarse = 0): every entry of the table runs as four blocks, one per quarter of it.  kGemmFewQuarters
+// (with kGemmQuarters): with a longer ring; kGemmSixteenths (plain bf16, with kGemmQuarters): as sixteen blocks of one wave.
 // kGemmLongK (fp32): needed where a problem of the launch has K > kF32LongK.
 // l_kmajor: every problem of the launch stores its L operand K-major (element (i, k) at L[k * ldl + i]).
 // planes: 1 = plain bf16; 2 or 3 = every matrix is a sum of that many bf16 planes (GemmProblem::*_plane strides); entries of a

@@ -288,6 +288,13 @@ bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
 // 256 (apply products of 1024^2, of 4 of 512^2) 327 / 314, 215 / 207, 288 (8 of 512^2) 315 / 351; earlier, us per launch, apply
 // product of 64 of 128 x 256 (512) 17.7 / 13.6, Gram product of 16 of 512^2 (576) 34.4 / 34.1.
 constexpr int kFewFine = 176, kFewF32 = 180, kLittleOverF32 = 64;
+// Two planes: up to 185 entries' work, with a short K up to 400; three planes, whose 128-wide tiles have a compute unit to
+// themselves: up to 200, and where they would leave the last of several rounds of `blocks` tiles less than 0.85 full on average.  us per
+// step, 128 / 64: two planes 12 of 640 x 1408 (180) 591 / 551, 60 of 256 x 384 (180, 360) 266 / 247, 100 of 128 x 300 (100,
+// 300) 160 / 154, but 20 of 512^2 (200) 343 / 359; three planes 60 of 256 x 384 442 / 386, 100 of 128 x 300 268 / 224, 20 of
+// 512^2 (200, 320) 557 / 497, 10 of 1024^2 (360, 640) 1552 / 1432, but apply products of 208 entries (ten iterations of
+// seven matrices) 677 / 695, 240 (40 of 256 x 384) 262 / 277, 256 (4 of 1024^2) 633 / 650, 896 (14 of 1024^2) 1939 / 2012.
+constexpr int kFewFine2 = 185, kFewFine2Short = 400, kShortKPlanes = 384, kFewFine3 = 200, kMostFine3 = 1024;
 // a launch's work in entries of its longest K
 int64_t entries_of_work(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k) {
   int64_t longest = 1, total = 0;
@@ -298,22 +305,33 @@ int64_t entries_of_work(const std::vector<std::vector<GemmTile>>& tiles, const s
     }
   return (total + longest - 1) / longest;
 }
-bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, bool mc, int blocks) {
+bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, bool mc, int planes, int blocks) {
   const int64_t entries = entries_of_work(tiles, k);
+  int64_t longest = 0;
+  for (size_t i = 0; i < tiles.size(); ++i)
+    if (!tiles[i].empty()) longest = std::max(longest, k[i]);
+  if (mc && planes == 2) return entries <= kFewFine2 || (longest <= kShortKPlanes && entries <= kFewFine2Short);
+  if (mc && planes == 3) {
+    if (entries <= kFewFine3) return true;
+    const int64_t b = std::max(blocks, 1), rounds = (entries + b - 1) / b;
+    return rounds > 1 && entries <= kMostFine3 && 100 * entries < 85 * rounds * b;
+  }
   if (mc) return entries <= kFewFine;
   return entries <= kFewF32 || (entries > blocks && entries <= blocks + kLittleOverF32);
 }
 
-// Plain bf16, launches in quarters that leave most compute units with one block or none: 2 = each 32 x 32 as one wave of its
+// Launches in quarters that leave most compute units with one block or none: 2 = each 32 x 32 as one wave of its
 // own (shortest chain of slabs; twice the operand traffic), 1 = 64 x 64 blocks with a ring of four slabs (two blocks on a
 // compute unit instead of three), 0 = with a ring of three.  Measured, us per step, 0 / 1 / 2: 256^2 (3 and 4 entries) 57.2 /
 // 56.4 / 50.7, 512^2 (10, 16) 77.3 / 73.6 / 66.9, 63 x 4097 (1, 33) 134 / 115 / 113, 2 of 512^2 (20, 32) 81.0 / 77.5 / 74.8, 9
 // of 200 x 333 (27, 54) 72.0 / 70.8 / 68.5; longer K from 24 entries on: 1024 x 4096 (36) 218 / 193 / 208, 1000 x 3001 (36) 197
 // / 178 / 185; 512^2 x 6 (60) 96.2 / 95.3; 1536^2 (78) 215 / 218, 10 of 512^2 (100) 119 / 121, 3 of 1024^2 (108) 172 / 176, 14 of
 // 512^2 (140) 147 / 157; a Gram launch of 128 entries with the work of 60, six matrices of K up to 4224: 318 / 308.
-constexpr size_t kFewest = 24, kFewestShort = 36, kFewEntries = 128;
+// Several planes know 0 and 1 (gemm_planes.h holds the times): 512^2 x 4 (40 and 64 entries) 132 / 130 and 169 / 161, ten
+// iterations of seven matrices (70 and 208) 674 / 685.
+constexpr size_t kFewest = 24, kFewestShort = 36, kFewEntries = 128, kFewPlanes = 64;
 constexpr int64_t kShortK = 1024, kFewWork = 64;
-int few_blocks(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k) {
+int few_blocks(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int planes) {
   size_t n = 0;
   int64_t longest = 0;
   for (size_t i = 0; i < tiles.size(); ++i)
@@ -321,6 +339,7 @@ int few_blocks(const std::vector<std::vector<GemmTile>>& tiles, const std::vecto
       n += tiles[i].size();
       longest = std::max(longest, k[i]);
     }
+  if (planes > 1) return n <= kFewPlanes ? 1 : 0;
   if (n <= kFewest || (n <= kFewestShort && longest <= kShortK)) return 2;
   return n <= kFewEntries && entries_of_work(tiles, k) <= kFewWork ? 1 : 0;
 }
@@ -722,13 +741,13 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         TileSet& ts = level ? g.coarse : g.fine;
         ts.strips = strips;
         if (level == 0) {
-          ts.quarter_sym = runs_in_quarters(sym, w_n, mc, plan.coarse_blocks);
-          ts.quarter_poly = runs_in_quarters(sym, w_m, mc, plan.coarse_blocks);
-          ts.quarter_apply = runs_in_quarters(app, w_m, mc, plan.coarse_blocks);
-          if (ns_dtype == MUON_BF16) {
-            ts.few_sym = few_blocks(sym, w_n);
-            ts.few_poly = few_blocks(sym, w_m);
-            ts.few_apply = few_blocks(app, w_m);
+          ts.quarter_sym = runs_in_quarters(sym, w_n, mc, (int)planes, plan.coarse_blocks);
+          ts.quarter_poly = runs_in_quarters(sym, w_m, mc, (int)planes, plan.coarse_blocks);
+          ts.quarter_apply = runs_in_quarters(app, w_m, mc, (int)planes, plan.coarse_blocks);
+          if (mc) {
+            ts.few_sym = few_blocks(sym, w_n, (int)planes);
+            ts.few_poly = few_blocks(sym, w_m, (int)planes);
+            ts.few_apply = few_blocks(app, w_m, (int)planes);
           }
         }
         ts.long_n = !mc && hi_n > kF32LongK;

@@ -37,7 +37,7 @@ struct TileSet {
   bool persistent_n = false, persistent_m = false;
   bool long_n = false, long_m = false;    // fp32: some K (Gram product: n_pad; the other two: m_pad) is over kF32LongK
   bool quarter_sym = false, quarter_poly = false, quarter_apply = false;   // fine launches that run as one block per quarter of an entry
-  int few_sym = 0, few_poly = 0, few_apply = 0;   // plain bf16, quarters: 1 with the longer ring, 2 as one wave per 32 x 32
+  int few_sym = 0, few_poly = 0, few_apply = 0;   // quarters on the matrix cores: 1 with the longer ring, 2 (plain bf16) as one wave per 32 x 32
 };
 
 // Launch group: all matrices of one chunk.  Each product is one launch per level: the coarse launch (matrix-core

@@ -106,7 +106,7 @@ def test_generated_code_of_the_64_wide_tile_waits_for_every_lds_read_it_uses(gem
 
 def test_generated_code_of_lone_waves_and_of_the_longer_ring_waits_for_every_lds_read_it_uses(gemm_asm):
     kernels = {k: v for k, v in hz.split_kernels(gemm_asm).items() if "ns_tile32_gemm_bf16" in k or "ns_ring4_gemm_bf16" in k}
-    assert len(kernels) == 4                     # each {k-contiguous, K-major}
+    assert len(kernels) == 8                     # each {k-contiguous, K-major}, the ring x {1, 2, 3} planes
     for name, lines in kernels.items():
         assert any("ds_read_b128" in t for _, t in lines)
         assert not any("scratch_" in t for _, t in lines), name          # no spills
