@@ -339,9 +339,10 @@ __device__ __forceinline__ const void* o_source(const MatDesc& d, int o_sel) {
 // 8 consecutive elements at element alignment: one 16-byte access for bf16, two for fp32.  Streaming hint on bf16: every
 // element of the update is touched once; without it the L2 refetched a third of the lines (measured: 1.20 GB fetched for
 // 0.81 GB of W and O on the 4096-wide block, 0.89 GB with the hint).  The hint leaves more of the caches to the next step's
-// momentum pass (50 of 2048 x 1408: update 164 us with it, 160 without, momentum 319 and 343), and it costs where rows do
-// not end on whole lines: 50 of 2047 x 1401 383 / 194 us (momentum 404 / 427), of 2048 x 1400 345 / 188; kept there all the
-// same, one kernel for all widths.
+// momentum pass (50 of 2048 x 1408: update 164 us with it, 160 without, momentum 319 and 343).  Long lists whose
+// rows do not end on whole lines take W without it (STREAM = false): a line written in two pieces leaves the caches between
+// them.  Step of 50 of 2047 x 1401 4881 us with the hint on W, 4700 without, of 2048 x 1400 4806 / 4676.
+template <bool STREAM = true>
 __device__ __forceinline__ void load8(const float* p, float* out) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -349,21 +350,27 @@ __device__ __forceinline__ void load8(const float* p, float* out) {
     out[4 * i + 0] = v.x; out[4 * i + 1] = v.y; out[4 * i + 2] = v.z; out[4 * i + 3] = v.w;
   }
 }
+template <bool STREAM = true>
 __device__ __forceinline__ void load8(const u16* p, float* out) {
-  const u32x4_any v = __builtin_nontemporal_load((const MUON_GLOBAL u32x4_any*)p);
+  u32x4_any v;
+  if constexpr (STREAM) v = __builtin_nontemporal_load((const MUON_GLOBAL u32x4_any*)p);
+  else v = *(const MUON_GLOBAL u32x4_any*)p;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     out[2 * j] = __uint_as_float(v[j] << 16);
     out[2 * j + 1] = __uint_as_float(v[j] & 0xffff0000u);
   }
 }
+template <bool STREAM>
 __device__ __forceinline__ void store8(float* p, const float* in) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) ((MUON_GLOBAL f32x4_any*)p)[i] = f32x4_any{in[4 * i], in[4 * i + 1], in[4 * i + 2], in[4 * i + 3]};
 }
+template <bool STREAM>
 __device__ __forceinline__ void store8(u16* p, const float* in) {
   const u32x4_any v = {pack2(in[0], in[1]), pack2(in[2], in[3]), pack2(in[4], in[5]), pack2(in[6], in[7])};
-  __builtin_nontemporal_store(v, (MUON_GLOBAL u32x4_any*)p);
+  if constexpr (STREAM) __builtin_nontemporal_store(v, (MUON_GLOBAL u32x4_any*)p);
+  else *(MUON_GLOBAL u32x4_any*)p = v;
 }
 template <typename XT, int PL>
 __device__ __forceinline__ void ns_load8(const XT* p, size_t plane, float* out) {
@@ -382,7 +389,7 @@ __device__ __forceinline__ void ns_load8(const XT* p, size_t plane, float* out) 
 // One 64x64 tile of the update.  Thread t owns 8 consecutive columns, (t % 8) * 8 .., of rows t / 8 and t / 8 + 32:
 // the 8 lanes that share a row cover one whole 128-byte line of a bf16 array with every load or store instruction
 // (a thread that owned 16 consecutive elements wrote every line in two instructions of scattered 16-byte pieces).
-template <typename WT, typename XT, int PL, bool UPDATE>
+template <typename WT, typename XT, int PL, bool UPDATE, bool STREAM>
 __device__ __forceinline__ void apply_tile(const MatDesc& d, const MatPtrs& pt, int tr, int tc, float lr, float wd,
                                            float scale, int o_sel, float* red) {
   const int tid = threadIdx.x;
@@ -401,8 +408,8 @@ __device__ __forceinline__ void apply_tile(const MatDesc& d, const MatPtrs& pt, 
     ns_load8<XT, PL>(o + (size_t)r0 * pitch + c0, plane, ov[0]);
     ns_load8<XT, PL>(o + (size_t)r1 * pitch + c0, plane, ov[1]);
     if (UPDATE) {
-      load8(w + (size_t)r0 * (size_t)B + c0, wv[0]);
-      load8(w + (size_t)r1 * (size_t)B + c0, wv[1]);
+      load8<STREAM>(w + (size_t)r0 * (size_t)B + c0, wv[0]);
+      load8<STREAM>(w + (size_t)r1 * (size_t)B + c0, wv[1]);
     }
 #pragma unroll
     for (int u = 0; u < 2; ++u)
@@ -415,8 +422,8 @@ __device__ __forceinline__ void apply_tile(const MatDesc& d, const MatPtrs& pt, 
         }
       }
     if (UPDATE) {
-      store8(w + (size_t)r0 * (size_t)B + c0, wv[0]);
-      store8(w + (size_t)r1 * (size_t)B + c0, wv[1]);
+      store8<STREAM>(w + (size_t)r0 * (size_t)B + c0, wv[0]);
+      store8<STREAM>(w + (size_t)r1 * (size_t)B + c0, wv[1]);
     }
   } else if (c0 < B) {
     // the matrix's bottom rows, which stay wide, and its right edge.  O's columns are padded to whole tiles, so it is read
@@ -429,7 +436,7 @@ __device__ __forceinline__ void apply_tile(const MatDesc& d, const MatPtrs& pt, 
       if (r >= A) continue;
       ns_load8<XT, PL>(o + (size_t)r * pitch + c0, plane, ov[u]);
       if (UPDATE && wide) {
-        load8(w + (size_t)r * (size_t)B + c0, wv[u]);
+        load8<STREAM>(w + (size_t)r * (size_t)B + c0, wv[u]);
       } else {
 #pragma unroll
         for (int i = 0; i < 8; ++i) wv[u][i] = UPDATE && c0 + i < B ? load1<WT>(w + (size_t)r * (size_t)B + c0 + i) : 0.f;
@@ -448,7 +455,7 @@ __device__ __forceinline__ void apply_tile(const MatDesc& d, const MatPtrs& pt, 
         }
       }
       if (UPDATE && wide) {
-        store8(w + (size_t)r * (size_t)B + c0, wv[u]);
+        store8<STREAM>(w + (size_t)r * (size_t)B + c0, wv[u]);
       } else if (UPDATE) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
@@ -460,7 +467,7 @@ __device__ __forceinline__ void apply_tile(const MatDesc& d, const MatPtrs& pt, 
   if (tid == 0) d.partials[tr * d.ew_tiles_c + tc] = total;
 }
 
-template <typename XT, int PL>
+template <typename XT, int PL, bool STREAM>
 __global__ __launch_bounds__(256) void apply_update_kernel(const MatDesc* __restrict__ mats, const MatPtrs* __restrict__ ptrs,
                                                             const EwTile* __restrict__ tiles, float lr, float wd,
                                                             float rms_scale, int scale_mode, float sqrt_hidden, int o_sel,
@@ -480,9 +487,9 @@ __global__ __launch_bounds__(256) void apply_update_kernel(const MatDesc* __rest
   for (int k = 0; k < t.count; ++k) {
     if (k) __syncthreads();     // the reduction scratch is reused
     if (d.w_dtype == kDtypeBF16)
-      apply_tile<u16, XT, PL, true>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
+      apply_tile<u16, XT, PL, true, STREAM>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
     else
-      apply_tile<float, XT, PL, true>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
+      apply_tile<float, XT, PL, true, STREAM>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
   }
 }
 
@@ -496,7 +503,7 @@ __global__ __launch_bounds__(256) void update_sumsq_kernel(const MatDesc* __rest
   const MatPtrs none{nullptr, nullptr, nullptr};
   for (int k = 0; k < t.count; ++k) {
     if (k) __syncthreads();
-    apply_tile<float, XT, PL, false>(d, none, t.tr, t.tc + k, 0.f, 0.f, 0.f, o_sel, red);
+    apply_tile<float, XT, PL, false, true>(d, none, t.tr, t.tc + k, 0.f, 0.f, 0.f, o_sel, red);
   }
 }
 
@@ -566,11 +573,15 @@ hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, 
 }
 
 hipError_t launch_apply_update(const MatDesc* mats, const MatPtrs* ptrs, const EwTile* tiles, int n_tiles, float lr, float wd,
-                               float rms_scale, int scale_mode, float sqrt_hidden, int o_sel, int use_s, int ns_dtype,
-                               hipStream_t s) {
+                               float rms_scale, int scale_mode, float sqrt_hidden, int o_sel, int use_s, int stream_w,
+                               int ns_dtype, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-#define MUON_CALL(XT, PL) \
-  apply_update_kernel<XT, PL><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, lr, wd, rms_scale, scale_mode, sqrt_hidden, o_sel, use_s)
+#define MUON_CALL(XT, PL)                                                                                                          \
+  if (stream_w)                                                                                                                    \
+    apply_update_kernel<XT, PL, true><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, lr, wd, rms_scale, scale_mode, sqrt_hidden, o_sel, \
+                                                              use_s);                                                              \
+  else                                                                                                                             \
+    apply_update_kernel<XT, PL, false><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, lr, wd, rms_scale, scale_mode, sqrt_hidden, o_sel, use_s)
   MUON_NS_DISPATCH(ns_dtype, MUON_CALL)
 #undef MUON_CALL
   return hipGetLastError();

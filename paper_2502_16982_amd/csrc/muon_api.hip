@@ -246,7 +246,7 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
     MUON_TIMED(MUON_PROF_UPDATE, launch_apply_update(ctx->d_mats, ctx->d_ptrs, ew, ch.n_ew_tiles, (float)hp->lr,
                                                      (float)hp->weight_decay, (float)hp->rms_scale, hp->scale_mode,
                                                      (float)std::sqrt(hp->hidden_size > 0.0 ? hp->hidden_size : 0.0), o_sel, use_s,
-                                                     ctx->ns_dtype, s));
+                                                     ch.stream_w, ctx->ns_dtype, s));
     if (update_rms_out) MUON_TIMED(MUON_PROF_RMS, launch_update_rms(ctx->d_mats, ch.first, ch.count, use_s, 0, update_rms_out, s));
   }
   ctx->last_o_sel = o_sel;

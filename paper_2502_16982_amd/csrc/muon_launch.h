@@ -106,9 +106,10 @@ hipError_t launch_gemm_f32(int flags, const GemmProblem* probs, const GemmTile* 
 // picks X (0) or Xt[0] (1) for the others; use_s: multiply O by scal[0] (only when no Newton-Schulz iteration ran).
 // scale_mode: 0 factor = rms_scale*sqrt(max(A,B)); 1 factor = rms_scale*sqrt_hidden; 2 factor = rms_scale*scal[2]
 // (scal[2] = 1/RMS of the stored O, left there by launch_update_rms(..., to_scal = 1)).
+// stream_w: the streaming hint on accesses to bf16 weights (for rows that end on whole lines).
 hipError_t launch_apply_update(const MatDesc* mats, const MatPtrs* ptrs, const EwTile* tiles, int n_tiles,
                                float lr, float wd, float rms_scale, int scale_mode, float sqrt_hidden, int o_sel,
-                               int use_s, int ns_dtype, hipStream_t s);
+                               int use_s, int stream_w, int ns_dtype, hipStream_t s);
 
 // Per-tile sums of O^2 into the partials, without touching W (first pass of the "Update Norm" variant).
 hipError_t launch_update_sumsq(const MatDesc* mats, const EwTile* tiles, int n_tiles, int o_sel, int ns_dtype, hipStream_t s);

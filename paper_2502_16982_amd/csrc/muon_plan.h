@@ -56,6 +56,7 @@ struct Chunk {
   int first = 0, count = 0;
   size_t ew_tiles_off = 0;   // byte offset of the EwTile table
   int n_ew_tiles = 0;
+  bool stream_w = true;      // no long list of bf16 weights whose rows end inside 128-byte lines
   bool fold_norm = false;    // the blocks of the first Gram launch add up the partial sums of squares themselves
   std::vector<Group> groups;
 };

@@ -160,6 +160,13 @@ def test_elementwise_passes_at_odd_widths_and_addresses(dev, dtypes):
 
 
 @pytest.mark.timeout(600)
+def test_update_of_a_long_list_of_odd_widths(dev):
+    """More than 64 M elements of bf16 weights in rows that end inside a 128-byte line: the weight update without its hint."""
+    wl = workloads.custom("long_odd", [(1025, 1025)] * 64 + [(1031, 999)], seed_base=360)
+    assert_records(U.run_and_compare(wl, dev, check=[0, 63, 64]), U.TOL_BF16_FRO)
+
+
+@pytest.mark.timeout(600)
 @pytest.mark.parametrize("ns", ["bf16x2", "bf16x3"])
 def test_planes_in_coarse_tiles_and_strips(dev, ns):
     """With several planes only large matrices get 256-wide tiles and, where the side is an odd multiple of 128, 512 x 128
