@@ -13,8 +13,8 @@
 //              blocks and a K loop a quarter as long, at twice the operand traffic.
 // Measured, us per step of one matrix (four of them) when the two forms came in, a 64 x 64 tile of FMAs without prefetch /
 // whole / quarters: 128 x 256 244 / 125 / 78, 512 x 512 555 / 241 / 124 (575 / 257 / 241), 1024 x 1024 1016 / 390 / 346
-// (1694 / 982 / 989).  Now 128 x 256 64 (with the elementwise passes and the norm of today), 512 x 512 110 (224), 1024 x 1024 329
-// (972: apply product 78 us = 110 TFLOP/s of the 157 the fp32 matrix instructions can do).
+// (1694 / 982 / 989).  Now 128 x 256 59 (with the elementwise passes and the norm of today), 512 x 512 105 (207), 1024 x 1024 313
+// (967: apply product 78 us = 110 TFLOP/s of the 157 the fp32 matrix instructions can do).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
