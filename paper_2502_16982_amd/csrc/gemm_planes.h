@@ -13,18 +13,26 @@
 // next unit's fragments are read while this one is multiplied; one barrier per unit.  The addend's planes come through the
 // same ring behind the last unit.  BT = 64: three stages, or four where a launch leaves a block alone on its compute unit: one
 // more unit in flight (two planes: 512^2 118 -> 109 us, 1024 x 4096 397 -> 362, 5 of 40 x 3800 222 -> 189; three: 156 -> 145, 579
-// -> 545, 307 -> 265), but fewer blocks on a compute unit (10 of 512^2 208 -> 214 and 292 -> 296).  BT = 128: with two planes two blocks on a compute unit (ring of 2, 250 registers; one
-// block with a ring of 4 is 2 % faster on 4096^2 and 8 to 20 % slower on lists of 512^2 to 1024 x 4096), with three planes one.
-// Rounding.  Three planes: the leading pair has two accumulators, of even and odd pieces, and the other pairs a third, so the
-// small terms are not rounded at the size of the sum (error of O against 64 bits: 1024 x 4096 1.38e-6 -> 0.97e-6, 100 x 300
-// 6.4e-7 -> 5.9e-7 against one accumulator that takes the pairs one after the other, smallest first).  Two planes: one
-// accumulator (no registers for more), +0.3 to +1 % of the error; in exchange the polynomial, the smallest of the products,
-// takes the pair (1,1) too, whose 2^-18 is as large as the rounding of the second plane (512^2 2.20e-5 -> 2.13e-5, 1024 x
-// 4096 2.14e-5 -> 1.87e-5; +2 to +5 % time where all matrices are square).
+// -> 545, 307 -> 265), but fewer blocks on a compute unit (10 of 512^2 208 -> 214 and 292 -> 296).  BT = 128: three planes
+// take the registers of a whole compute unit, ring of 4.  Two planes fit two blocks with a ring of 2 (250 registers), or one with a
+// ring of 4 and three accumulators: the symmetric products of large matrices, the coarse tables, run like that, us per launch two
+// blocks / one: Gram 8192^2 1530 / 1450, 2 of 4096 x 11008 1039 / 967, 4 of 2048 x 8192 489 / 429, 3 of 3200^2 272 / 278;
+// everything else runs two (apply product of 12 of 1536 x 8192 1231 / 1399, steps of lists of 512^2 to 1024 x 4096 +8 to +20 %).
+// Rounding.  Three planes, and two with the ring of 4: the leading pair has two accumulators, of even and odd pieces, and the
+// other pairs a third, so the small terms are not rounded at the size of the sum (error of O against 64 bits, three planes:
+// 1024 x 4096 1.38e-6 -> 0.97e-6, 100 x 300 6.4e-7 -> 5.9e-7 against one accumulator that takes the pairs one after the other,
+// smallest first).  Two planes with one accumulator: +0.3 to +1 % of the error.
+// Two planes: the polynomial takes the pair (1,1) too, whose 2^-18 is as large as the rounding of the second plane (512^2
+// 2.20e-5 -> 2.13e-5, 1024 x 4096 2.14e-5 -> 1.87e-5).  All of that comes from the diagonal of A, the part of A A^T's sums that does
+// not average: the coarse tables, where a quarter of the products shows, take the pair only in the pieces of K that hold the tile's
+// own rows or columns.  Error of O before the pair / with it / in own pieces and three accumulators: 4096^2 1.72e-5 / 1.68e-5 /
+// 1.67e-5, 4096 x 11008 2.33e-5 / 1.48e-5 / 1.42e-5, 8192^2 1.67e-5 / 1.63e-5 / 1.60e-5; us per polynomial launch: 8 of 4096^2 1659 /
+// 1899 / 1568, 8192^2 1480 / 1898 / 1458.  (On shorter lists own pieces are 2 to 5 % of a step faster and the error 0.1 to 0.4 %
+// larger: they take the whole pair.)
 // Measured, us per step, with 256- and 128-wide tiles in a loop over pairs / now.  Two planes: 4 of 1024^2 with 3 of 1024 x 4096
-// 1306 / 1066, 48 of 1024^2 4173 / 3717, 4096^2 4505 / 4300, 12 of 1536 x 8192 12599 / 11103, 4 of 4096^2 with 3 of 4096 x
-// 11008 41069 / 41192, 3 of 16 x 2000 206 / 145.  Three planes: 4096^2 8970 / 7052, 24 of 1024 x 4096 12377 / 9707, 30 of 300 x
-// 700 840 / 660, ten iterations of 4 of 512^2, 2 of 512 x 1536 and 1500 x 500 1210 / 673.
+// 1306 / 1066, 48 of 1024^2 4173 / 3717, 12 of 1536 x 8192 12599 / 10800, 3 of 16 x 2000 206 / 145, 7 of 4096^2 27013 / 25770, 4
+// of 4096^2 with 3 of 4096 x 11008 41783 / 39316, 8192^2 28525 / 28525.  Three planes: 4096^2 8970 / 7052, 24 of 1024 x 4096
+// 12377 / 9707, 30 of 300 x 700 840 / 660, ten iterations of 4 of 512^2, 2 of 512 x 1536 and 1500 x 500 1210 / 673.
 #pragma once
 
 namespace muon {
@@ -32,6 +40,7 @@ namespace {
 
 constexpr int planes_ring(int bt, int pl) { return bt == 64 ? 3 : pl == 2 ? 2 : 4; }
 constexpr int kPlanesRingFew = 4;                // BT = 64 where a block has a compute unit to itself
+constexpr int planes_ring_coarse(bool kmajor, int pl) { return pl == 2 && !kmajor ? 4 : planes_ring(128, pl); }
 constexpr size_t planes_lds(int bt, int stages) { return (size_t)stages * 2 * (size_t)bt * ROWB; }
 
 // Fragments of one k-step of one plane, read by assembly (see gemm_tile64.h).
@@ -63,7 +72,8 @@ __device__ __forceinline__ void gemm_planes_body(const GemmProblem& p, int row0,
                                                  float beta_acc, float beta_e, int alpha_idx, double eps) {
   constexpr int NW = 4, F = BT / 64, WT = BT / 2;
   constexpr int LREQ = BT / 32, NLOAD = 2 * LREQ;               // 1 KB requests per wave and unit: L, both
-  constexpr bool SPLIT = PL == 3, ALL11 = PL == 3 || (!LKM && ADD);
+  constexpr bool SPLIT = PL == 3 || (BT == 128 && NST == 4);    // three accumulators
+  constexpr bool OWN11 = PL == 2 && SPLIT && !LKM && ADD, ALL11 = !OWN11 && (PL == 3 || (!LKM && ADD));
   constexpr int UNIT_B = 2 * BT * ROWB, KSTEPS = BK / 16, NACC = SPLIT ? 3 : 1;
   static_assert((BT == 64 || BT == 128) && NST >= PL && NST <= 2 * PL && NLOAD * (NST - 1) < 64, "ring shape");
   const int tid = threadIdx.x;
@@ -158,6 +168,8 @@ __device__ __forceinline__ void gemm_planes_body(const GemmProblem& p, int row0,
     });
   };
 
+  // Pieces of K that hold rows of this tile's own row or column range (the polynomial, whose K runs over the rows of A).
+  auto own = [&](int piece) { return (unsigned)(piece * BK - row0) < (unsigned)BT || (unsigned)(piece * BK - col0) < (unsigned)BT; };
   // Unit (piece, q), whose fragments are on their way; LEFT units follow it (kMany: enough for everything).  Its first k-step
   // is multiplied as soon as its fragments have landed; then one wait and barrier: all of this unit's fragments are in
   // registers, everybody's, and the next unit is in the LDS.  From there on, spread among the MFMAs, the next unit's fragments
@@ -213,6 +225,15 @@ __device__ __forceinline__ void gemm_planes_body(const GemmProblem& p, int row0,
     });
     if constexpr (left > 0 && next_q == 0)
       static_for<NR - RPS, NR>([&](auto n_tag) { read(next, std::integral_constant<int, 0>{}, n_tag); });
+    if constexpr (OWN11 && q == 1)
+      if (own(piece)) {                          // the pair (1,1): its fragments stay until the next unit of this plane
+        static_for<0, KSTEPS * F * F>([&](auto t_tag) {
+          constexpr int t = decltype(t_tag)::value, kk = t / (F * F), i = t / F % F, j = t % F;
+          acc[NACC - 1][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a_frag(fg[q][kk], i), __builtin_bit_cast(bf16x8, fg[q][kk].b[j]),
+                                                                        acc[NACC - 1][i][j], 0, 0, 0);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      }
     stage = next;
   };
 

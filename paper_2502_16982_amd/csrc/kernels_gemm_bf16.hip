@@ -914,6 +914,7 @@ constexpr size_t kLds128 = TileCfg<128, 128>::lds_bytes(2);
 constexpr size_t lds_quarters(int planes) { return planes > 1 ? planes_lds(64, planes_ring(64, planes)) : lds_ring64(kRing64); }
 constexpr size_t lds_few_quarters(int planes) { return planes > 1 ? planes_lds(64, kPlanesRingFew) : lds_ring64(kRing64Few); }
 constexpr size_t lds_fine(int planes) { return planes > 1 ? planes_lds(128, planes_ring(128, planes)) : kLds128; }
+constexpr size_t lds_coarse(bool kmajor, int planes) { return planes_lds(128, planes_ring_coarse(kmajor, planes)); }
 constexpr size_t kLds256 = TileCfg<256, 256>::lds_bytes(2);
 constexpr size_t kLds512 = TileCfg<512, 128>::lds_bytes(2);
 constexpr int kMaxPlanes = 3;
@@ -989,10 +990,10 @@ __global__ __launch_bounds__(64) void ns_tile32_gemm_bf16_kernel(const GemmProbl
 // goes on to its next tile neither waits for its stores to drain nor is re-dispatched, and its next tile's first
 // operand requests overlap both (measured +2 % on the MoE bank; with tiles of mixed K the static dealing loses that
 // again, so such launches stay one block per tile).
-// With several planes every entry is four blocks of 128 x 128 on the entry's die: a 256-wide tile has no registers for the
-// planes' fragments (gemm_planes.h holds both sides' times).
+// With several planes every entry is four blocks of 128 x 128 on the entry's die, none of them persistent: a 256-wide tile has
+// no registers for the planes' fragments (gemm_planes.h holds both sides' times).
 template <bool LKM, int PL>
-__global__ __launch_bounds__(256, PL == 2 ? 2 : 1) void ns_gemm_bf16_kernel(const GemmProblem* __restrict__ probs,
+__global__ __launch_bounds__(256, PL == 2 && LKM ? 2 : 1) void ns_gemm_bf16_kernel(const GemmProblem* __restrict__ probs,
                                                                const GemmTile* __restrict__ tiles, int n_tiles, float beta_acc,
                                                                float beta_e, int alpha_idx, float diag_add) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -1004,7 +1005,7 @@ __global__ __launch_bounds__(256, PL == 2 ? 2 : 1) void ns_gemm_bf16_kernel(cons
     const GemmProblem p = probs[tile.prob];
     const int row0 = tile.r0 * kTileUnit + 128 * (strip ? quarter : quarter >> 1), col0 = tile.c0 * kTileUnit + 128 * (strip ? 0 : quarter & 1);
     if (p.symmetric && row0 > col0) return;      // below the diagonal: a mirror image
-    planes_tile<128, planes_ring(128, PL), LKM, PL>(p, row0, col0, p.symmetric && row0 == col0, smem, beta_acc, beta_e, alpha_idx, 0.0);
+    planes_tile<128, planes_ring_coarse(LKM, PL), LKM, PL>(p, row0, col0, p.symmetric && row0 == col0, smem, beta_acc, beta_e, alpha_idx, 0.0);
   } else {
     const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int t = blockIdx.x; t < n_tiles; t += gridDim.x) {
@@ -1037,7 +1038,7 @@ hipError_t setup_pair() {
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_few_quarters(PL) + kLdsFold64));
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_bf16_kernel<LKM, PL>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(PL > 1 ? lds_fine(PL) : kLds512));
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(PL > 1 ? lds_coarse(LKM, PL) : kLds512));
 }
 
 template <bool LKM, int PL>
@@ -1058,7 +1059,7 @@ void launch_one(int coarse, int flags, const GemmProblem* probs, const GemmTile*
     ns_gemm_bf16_fine_kernel<LKM, PL><<<n_tiles, 256, lds_fine(PL), s>>>(probs, tiles, beta_acc, beta_e, alpha_idx, diag_add);
   else
     ns_gemm_bf16_kernel<LKM, PL><<<PL > 1 ? (n_tiles + 7) / 8 * 32 : (flags & kGemmPersistent) && n_tiles > g_coarse_grid ? g_coarse_grid : n_tiles,
-                                   256, PL > 1 ? lds_fine(PL) : (flags & kGemmStrips) ? kLds512 : kLds256, s>>>(
+                                   256, PL > 1 ? lds_coarse(LKM, PL) : (flags & kGemmStrips) ? kLds512 : kLds256, s>>>(
         probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, diag_add);
 }
 

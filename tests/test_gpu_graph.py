@@ -16,7 +16,7 @@ CASES = {
                        w_dtype=torch.bfloat16, g_dtype=torch.bfloat16),
     "bf16x2_mixed": dict(shapes=[(512, 640), (384, 256), (200, 136)], ns_dtype="bf16x2",
                          w_dtype=torch.bfloat16, g_dtype=torch.bfloat16),
-    # two bf16 planes in 256-wide tiles and strips, whose instantiations use per-lane scratch memory in their epilogue,
+    # two bf16 planes in coarse tables (256- and 512 x 128-wide entries, run as 128 x 128 blocks),
     # with a matrix in the fine launch beside them
     "bf16x2_coarse": dict(shapes=[(3200, 3328), (200, 136), (3328, 3200)], ns_dtype="bf16x2",
                           w_dtype=torch.bfloat16, g_dtype=torch.bfloat16),

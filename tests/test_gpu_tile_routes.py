@@ -185,3 +185,71 @@ def test_planes_in_both_launches_of_a_product(dev):
     assert table_sizes(shapes, "bf16x2", 1) == [256, 256, 512] and table_sizes(shapes, "bf16x2", 0) == [64, 64, 0]
     wl = workloads.custom("planes_tail", shapes, ns_dtype="bf16x2", seed_base=355)
     assert_records(U.run_and_compare(wl, dev, check=[1]), U.TOL_SPLIT_FRO["bf16x2"])
+
+
+def scalar_two_planes(u, pair, steps=5, a=3.4445, b=-4.7750, c=2.0315, eps=1e-7):
+    """What two-plane arithmetic makes of a diagonal matrix: every product of the iteration is a scalar one (float64 vector u of
+    the diagonal; `pair`: with (1,1) in the polynomial)."""
+    def split(x):
+        x = x.float()
+        h = x.bfloat16().float()
+        return h.double(), (x - h).bfloat16().double()
+
+    s = 1.0 / (u.norm() + eps)
+    x = split(u)
+    for it in range(steps):
+        s2, s1 = (s * s, s) if it == 0 else (1.0, 1.0)
+        g = split(s2 * (x[0] * x[0] + 2 * x[0] * x[1]))
+        poly = split(c * (g[0] * g[0] + 2 * g[0] * g[1] + (g[1] * g[1] if pair else 0.0)) + b * (g[0] + g[1]))
+        x = split(s1 * (x[0] * poly[0] + x[0] * poly[1] + x[1] * poly[0] + a * (x[0] + x[1])))
+    return x[0] + x[1]
+
+
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("shape,copies,coarse", [((3200, 3328), 2, True), ((3328, 3200), 2, True), ((1024, 1100), 12, False), ((300, 500), 1, False)])
+def test_two_planes_polynomial_takes_the_last_pair_on_the_diagonal(dev, shape, copies, coarse):
+    """A diagonal matrix runs the scalar iteration on every element: O must be the one with the pair (1,1), whichever tile
+    the polynomial runs in (coarse ones take the pair in their own pieces of K alone).  The library's fp32 norm and products
+    round the second plane of some elements the other way, which is seen as a fifth of the distance to the iteration
+    without the pair; without it the two distances would change places."""
+    assert (coarse_tiles([shape] * copies, "bf16x2")[0] > 0) == coarse
+    m = min(shape)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(5)
+    d = torch.empty(m, device=dev).uniform_(0.7e-3, 1.4e-3, generator=gen)
+    g = torch.zeros(shape, device=dev)
+    g[torch.arange(m), torch.arange(m)] = d
+    tensors = [(torch.zeros(shape, device=dev), g.clone(), torch.zeros(shape, device=dev)) for _ in range(copies)]
+    st = binding.MuonStepper(tensors, ns_dtype="bf16x2")
+    st.step(binding.default_hparams(lr=0.02, weight_decay=0.1, momentum=0.95, nesterov=1, eps=1e-7))
+    o = st.read_update(copies - 1).double()
+    st.close()
+    diag = o[torch.arange(m), torch.arange(m)]
+    assert float((o - torch.zeros_like(o).index_put((torch.arange(m, device=dev),) * 2, diag)).abs().max()) == 0.0
+    u = (torch.tensor(0.95, device=dev) * d + d).double()
+    far = {pair: float(((diag - scalar_two_planes(u, pair)) / diag).square().mean().sqrt()) for pair in (True, False)}
+    print("rms distance from the scalar iteration with / without the pair:", far[True], far[False], flush=True)
+    assert far[True] < 0.5 * far[False]
+
+
+@pytest.mark.timeout(600)
+def test_large_two_plane_polynomial_costs_what_the_gram_product_costs(dev):
+    """Square matrices in coarse tiles: Gram product and polynomial are the same three plane pairs over the same tiles.  The
+    polynomial's addend and its fourth pair in the tile's own pieces (4 of 64 here) are 2 to 6 % more; the pair over the whole of K
+    was 25 %."""
+    shapes = [(4096, 4096)] * 3
+    assert min(coarse_tiles(shapes, "bf16x2")) > 0
+    wl = workloads.custom("poly_cost", shapes, ns_dtype="bf16x2", seed_base=365)
+    st = binding.MuonStepper(workloads.make_all(wl, dev), ns_dtype="bf16x2")
+    hp = binding.default_hparams(lr=0.02, weight_decay=0.1)
+    ratios = []
+    for k in range(6):
+        binding.muon_profile_enable(st.ctx, True)
+        st.step(hp)
+        torch.cuda.synchronize()
+        r = binding.muon_profile_read(st.ctx, reset=True)
+        if k:
+            ratios.append(r["poly"][0] / r["gram"][0])
+    st.close()
+    print("polynomial / Gram product:", sorted(ratios), flush=True)
+    assert sorted(ratios)[2] < 1.15
