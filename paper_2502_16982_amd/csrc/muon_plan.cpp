@@ -288,13 +288,29 @@ bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
 // 256 (apply products of 1024^2, of 4 of 512^2) 327 / 314, 215 / 207, 288 (8 of 512^2) 315 / 351; earlier, us per launch, apply
 // product of 64 of 128 x 256 (512) 17.7 / 13.6, Gram product of 16 of 512^2 (576) 34.4 / 34.1.
 constexpr int kFewFine = 176, kFewF32 = 180, kLittleOverF32 = 64;
-// Two planes: up to 185 entries' work, with a short K up to 400; three planes, whose 128-wide tiles have a compute unit to
-// themselves: up to 200, and where they would leave the last of several rounds of `blocks` tiles less than 0.85 full on average.  us per
-// step, 128 / 64: two planes 12 of 640 x 1408 (180) 591 / 551, 60 of 256 x 384 (180, 360) 266 / 247, 100 of 128 x 300 (100,
-// 300) 160 / 154, but 20 of 512^2 (200) 343 / 359; three planes 60 of 256 x 384 442 / 386, 100 of 128 x 300 268 / 224, 20 of
-// 512^2 (200, 320) 557 / 497, 10 of 1024^2 (360, 640) 1552 / 1432, but apply products of 208 entries (ten iterations of
-// seven matrices) 677 / 695, 240 (40 of 256 x 384) 262 / 277, 256 (4 of 1024^2) 633 / 650, 896 (14 of 1024^2) 1939 / 2012.
-constexpr int kFewFine2 = 185, kFewFine2Short = 400, kShortKPlanes = 384, kFewFine3 = 200, kMostFine3 = 1024;
+// Planes: 64-wide blocks pay while all of them have a place at the same time, three on a compute unit with two planes and two
+// with three, and again where 128-wide ones would leave their last round badly filled, the sooner the shorter K.  us per
+// launch, 128 / 64.  Two planes, up to 192 entries and from 256 to 320 with K up to 2048: 90 entries of K = 256 15.6 /
+// 10.8, 144 of 1024 33.8 / 29.9, 156 of 6144 136 / 123, 180 of 512 19.8 / 19.2, of 4096 126 / 100, 189 of 768 25.9 / 23.2; but 195 of 640
+// 26.7 / 27.2, of 1408 38.9 / 42.2, 200 of 512 20.0 / 22.0, of 2048 52.6 / 56.7, 240 of 256 18.5 / 18.8, of 512 20.8 / 23.5; 260 of 2048
+// 72.5 / 68.1, 288 of 1024 54.1 / 47.4, 300 of 512 34.7 / 29.2, of 1408 56.0 / 50.9, of 2048 82.3 / 81.9, 320 of 512 27.8 / 26.2; but 288
+// of 4096 136 / 143, 312 of 6144 204 / 258; 324 of 768 36.4 / 38.3, 360 of 256 20.7 / 21.4, 384 of 1024 45.9 / 49.3.
+// Three planes: 72 of 256 20.9 / 12.4, 108 of 4096 121 / 88, 120 of 512 26.3 / 20.3, 126 of 3072 97 / 72; 144 of 1024 41.8 / 39.9, 168 of 768
+// 36.2 / 32.7, 190 of 128 17.5 / 15.5, 195 of 384 26.4 / 25.8; but 140 of 4096 131 / 137, 156 of 1536 55.8 / 61.5, 180 of 1024 44.1 /
+// 45.9, 200 of 512 30.7 / 30.3.  Beyond one round, by its fill: 272 of 512 50.5 / 38.3, 600 of 512 (0.78) 78 / 76, 570 of 256 57 / 46, 810 of
+// 128 (0.79) 58 / 43, 420 of 768 (0.82) 74 / 67; 360 of 1024 (0.70) 84 / 77, 576 of 1024 (0.75) 127 / 115; 272 of 2048 (0.53) 135 / 113, 312
+// of 1536 (0.61) 108 / 96; 288 of 4096 (0.56) 256 / 238, 272 of 8192 490 / 474; but 432 of 1024 (0.84) 85 / 90, 840 of 768 (0.82) 136 / 145,
+// 360 of 2048 (0.70) 139 / 145, 420 of 2560 (0.82) 177 / 211, 390 of 6144 (0.76) 407 / 537, 324 of 8192 (0.63) 506 / 578, 300 of 4096 (0.59) 264
+// / 275; 1080 of 1024 (0.84) 204 / 230, 1300 of 512 (0.85) 147 / 166.
+constexpr int64_t kLongKPlanes2 = 2048, kMostFine3 = 1024;
+struct Fine3 {
+  int64_t k;        // longest K
+  int entries;      // of a launch in quarters within one round of 256 compute units
+  int fill;         // per cent of the last round
+};
+constexpr Fine3 kFine3[] = {{768, 200, 85}, {1024, 150, 80}, {2048, 128, 65}, {INT64_MAX, 128, 57}};
+// entries whose 64-wide blocks all have a place at the same time
+int lone_entries(int planes, int blocks) { return planes == 2 ? 3 * blocks / 4 : blocks / 2; }
 // a launch's work in entries of its longest K
 int64_t entries_of_work(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k) {
   int64_t longest = 1, total = 0;
@@ -310,11 +326,15 @@ bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std
   int64_t longest = 0;
   for (size_t i = 0; i < tiles.size(); ++i)
     if (!tiles[i].empty()) longest = std::max(longest, k[i]);
-  if (mc && planes == 2) return entries <= kFewFine2 || (longest <= kShortKPlanes && entries <= kFewFine2Short);
+  const int64_t b = std::max(blocks, 1);
+  if (mc && planes == 2)
+    return entries <= lone_entries(2, blocks) || (entries > b && 4 * entries <= 5 * b && longest <= kLongKPlanes2);
   if (mc && planes == 3) {
-    if (entries <= kFewFine3) return true;
-    const int64_t b = std::max(blocks, 1), rounds = (entries + b - 1) / b;
-    return rounds > 1 && entries <= kMostFine3 && 100 * entries < 85 * rounds * b;
+    const Fine3* f = kFine3;
+    while (longest > f->k) ++f;
+    if (entries <= f->entries * b / 256) return true;
+    const int64_t rounds = (entries + b - 1) / b;
+    return rounds > 1 && entries <= kMostFine3 && 100 * entries < f->fill * rounds * b;
   }
   if (mc) return entries <= kFewFine;
   return entries <= kFewF32 || (entries > blocks && entries <= blocks + kLittleOverF32);
@@ -322,16 +342,20 @@ bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std
 
 // Launches in quarters that leave most compute units with one block or none: 2 = each 32 x 32 as one wave of its
 // own (shortest chain of slabs; twice the operand traffic), 1 = 64 x 64 blocks with a ring of four slabs (two blocks on a
-// compute unit instead of three), 0 = with a ring of three.  Measured, us per step, 0 / 1 / 2: 256^2 (3 and 4 entries) 57.2 /
-// 56.4 / 50.7, 512^2 (10, 16) 77.3 / 73.6 / 66.9, 63 x 4097 (1, 33) 134 / 115 / 113, 2 of 512^2 (20, 32) 81.0 / 77.5 / 74.8, 9
-// of 200 x 333 (27, 54) 72.0 / 70.8 / 68.5; longer K from 24 entries on: 1024 x 4096 (36) 218 / 193 / 208, 1000 x 3001 (36) 197
-// / 178 / 185; 512^2 x 6 (60) 96.2 / 95.3; 1536^2 (78) 215 / 218, 10 of 512^2 (100) 119 / 121, 3 of 1024^2 (108) 172 / 176, 14 of
-// 512^2 (140) 147 / 157; a Gram launch of 128 entries with the work of 60, six matrices of K up to 4224: 318 / 308.
-// Several planes know 0 and 1 (gemm_planes.h holds the times): 512^2 x 4 (40 and 64 entries) 132 / 130 and 169 / 161, ten
-// iterations of seven matrices (70 and 208) 674 / 685.
-constexpr size_t kFewest = 24, kFewestShort = 36, kFewEntries = 128, kFewPlanes = 64;
-constexpr int64_t kShortK = 1024, kFewWork = 64;
-int few_blocks(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int planes) {
+// compute unit instead of three), 0 = with a ring of three.
+// Plain bf16, waves for the fewest entries, with K up to 512 a few more, us per step, 0 / 1 / 2: 256^2 (3 and 4 entries) 58.5 / 57.4 /
+// 51.8, 512^2 (10, 16) 78.0 / 73.4 / 68.3, 2 of 512^2 (20, 32) 81.4 / 78.7 / 77.1, 63 x 4097 (1, 33) 135.7 / 115.4 / 112.9; per launch 27
+// entries of K = 384 6.6 / 6.6 / 6.4, 36 of 1024 9.9 / 9.4 / 9.7, of 4096 21.7 / 18.4 / 21.9, 40 of 512 7.0 / 7.1 / 7.9.
+// The longer ring goes by the work: entries that have a compute unit to themselves, or a few long ones among short ones.  us per launch,
+// 0 / 1: 60 entries of 512 8.3 / 8.0, 63 of 768 9.9 / 9.6; 72 of 1024 11.0 / 11.3, 80 of 512 8.0 / 8.5, 100 8.8 / 9.1, 140 11.3 / 11.9; lists
+// that mix K, work in brackets: 130 (67) 24.4 / 23.3, 133 (66) 25.9 / 22.7, 128 (61) 24.7 / 22.4, 112 (50) 23.0 / 20.6, 100 (62) 95.7 /
+// 72.8, 96 (42) 26.2 / 21.4, 80 (26) 22.1 / 18.5, 45 (14) 36.2 / 26.6.
+// Planes, 0 / 1, two and three: 40 of 512 9.8 / 9.8 and 12.3 / 11.8, 36 of 4096 36.6 / 30.1 and 50.8 / 45.7, 63 of 768 12.8 / 12.2 and 17.1 /
+// 16.8; 70 of 512 12.8 / 12.6 and 17.6 / 18.1, 72 of 1024 17.4 / 17.8 and 25.5 / 26.4, 100 of 512 13.5 / 13.7 and 18.7 / 19.1; mixed 80 (22)
+// 36.6 / 30.9 and 51.6 / 46.3, 66 (40) 37.0 / 33.0 and 52.3 / 48.8, 70 (44) 18.0 / 17.3 and 24.9 / 25.7, 66 (46) 29.0 / 26.8 and 40.4 / 41.9.
+constexpr size_t kFewest = 24, kFewestShort = 36;
+constexpr int64_t kShortK = 512;
+int few_blocks(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int planes, int blocks) {
   size_t n = 0;
   int64_t longest = 0;
   for (size_t i = 0; i < tiles.size(); ++i)
@@ -339,9 +363,10 @@ int few_blocks(const std::vector<std::vector<GemmTile>>& tiles, const std::vecto
       n += tiles[i].size();
       longest = std::max(longest, k[i]);
     }
-  if (planes > 1) return n <= kFewPlanes ? 1 : 0;
-  if (n <= kFewest || (n <= kFewestShort && longest <= kShortK)) return 2;
-  return n <= kFewEntries && entries_of_work(tiles, k) <= kFewWork ? 1 : 0;
+  if (planes == 1 && (n <= kFewest || (n <= kFewestShort && longest <= kShortK))) return 2;
+  const int64_t work = entries_of_work(tiles, k), b = std::max(blocks, 1);
+  if (planes > 1) return 4 * (int64_t)n <= b || 6 * work <= b ? 1 : 0;
+  return 4 * work <= b + b / 16 ? 1 : 0;
 }
 
 void plan_matrices(const muon_param* p, int n, int ns_dtype, std::vector<MatPlan>& out, size_t& total_partials) {
@@ -752,9 +777,9 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
           ts.quarter_poly = runs_in_quarters(sym, w_m, mc, (int)planes, plan.coarse_blocks);
           ts.quarter_apply = runs_in_quarters(app, w_m, mc, (int)planes, plan.coarse_blocks);
           if (mc) {
-            ts.few_sym = few_blocks(sym, w_n, (int)planes);
-            ts.few_poly = few_blocks(sym, w_m, (int)planes);
-            ts.few_apply = few_blocks(app, w_m, (int)planes);
+            ts.few_sym = few_blocks(sym, w_n, (int)planes, plan.coarse_blocks);
+            ts.few_poly = few_blocks(sym, w_m, (int)planes, plan.coarse_blocks);
+            ts.few_apply = few_blocks(app, w_m, (int)planes, plan.coarse_blocks);
           }
         }
         ts.long_n = !mc && hi_n > kF32LongK;

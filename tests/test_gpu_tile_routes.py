@@ -1,4 +1,4 @@
-"""The planner gives a product 256-, 128- or 64-wide tiles by how much work a launch holds.  Every tile adds an output
+"""The planner gives a product 256-, 128-, 64- or 32-wide tiles by how much work a launch holds.  Every tile adds an output
 element's products in the same order, so in plain bf16 a matrix must come out with the same bits whichever tiles computed
 it: alone (64-wide), in a short list (128-wide) and in a list long enough for 256-wide tiles and strips (plain bf16 only at
 these sides).  With several planes an element of a symmetric product and its mirror image add the plane pairs in different orders (fp32 rounding,
@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 from paper_2502_16982_amd import binding, workloads  # noqa: E402
 from tests import gpu_util as U  # noqa: E402
 from tests.gpu_util import coarse_tiles, table_sizes  # noqa: E402
+from tests.plan_routes import fine_forms  # noqa: E402
 from tests.test_gpu_parity import assert_records  # noqa: E402
 
 
@@ -57,16 +58,20 @@ def test_64_wide_tiles_at_their_edges(dev, ns, tol):
     assert_records(U.run_and_compare(wl, dev, steps=2, want_rms=True), tol)
 
 
-@pytest.mark.parametrize("shape,longer", [((100, 130), 6), ((128, 256), 3), ((256, 300), 6), ((384, 200), 9), ((130, 520), 4), ((40, 900), 26), ((300, 1100), 7)])
-def test_same_bits_from_waves_and_both_rings(dev, shape, longer):
-    """Plain bf16: alone a matrix of these sizes runs as one wave per 32 x 32; in a list of some tens of entries, then of hundreds, as
-    64-wide blocks with a ring of four slabs, then of three, or in 128-wide tiles.  K of 2, 4, 6 and more slabs; the norm
-    added up by one wave, by a block, and by its own launch."""
+@pytest.mark.parametrize("shape", [(100, 130), (128, 256), (256, 300), (384, 200), (130, 520), (40, 900), (300, 1100)])
+def test_same_bits_from_waves_and_both_rings(dev, shape):
+    """Plain bf16: alone a matrix of these sizes runs as one wave per 32 x 32; in longer lists as 64-wide blocks with a ring of
+    four slabs, then of three, then in 128-wide tiles, the apply product (K-major operand) and the symmetric ones each in
+    every form.  K of 2, 4, 6 and more slabs; the norm added up by one wave, by a block, and by its own launch."""
     wl = workloads.custom("waves", [shape], seed_base=345)
     first = workloads.make_matrix(wl, 0, dev)
     hp = binding.default_hparams(lr=0.02, weight_decay=0.1)
-    results = []
-    for n in (1, longer, 60, 400):
+    results, seen = [], {"sym": set(), "apply": set()}
+    sym, _, app = table_sizes([shape], "bf16", 0)
+    for n in sorted({1, -(-40 // app), -(-40 // sym), -(-100 // app), -(-100 // sym), 400}):
+        gram, poly, apply = fine_forms([shape] * n, "bf16")
+        seen["sym"] |= {gram, poly}
+        seen["apply"].add(apply)
         tensors = [tuple(t.clone() for t in first) for _ in range(n)]
         st = binding.MuonStepper(tensors)
         for _ in range(2):
@@ -74,9 +79,24 @@ def test_same_bits_from_waves_and_both_rings(dev, shape, longer):
         torch.cuda.synchronize()
         results += [(n, i, st.read_update(i), tensors[i][0], tensors[i][2]) for i in {0, n // 2, n - 1}]
         st.close()
-    assert max(table_sizes([shape], "bf16", 0)) <= 36
+    assert all({"waves", "ring4", "quarters"} <= forms and forms & {"whole", "-"} for forms in seen.values()), seen
     for n, i, o, w, m in results[1:]:
         assert torch.equal(o, results[0][2]) and torch.equal(w, results[0][3]) and torch.equal(m, results[0][4]), (n, i)
+
+
+@pytest.mark.parametrize("ns", ["bf16x2", "bf16x3"])
+@pytest.mark.parametrize("shapes,forms", [
+    ([(129, 256), (300, 140), (65, 1200)], ["ring4", "ring4", "ring4"]),
+    ([(200, 384), (384, 200), (100, 700)] * 12, ["quarters", "quarters", "quarters"]),
+    ([(300, 700)] * 6 + [(700, 300)] * 6 + [(128, 4096)] * 8, ["ring4", "quarters", "quarters"]),
+    ([(128, 1100)] * 260, ["quarters", "quarters", "whole"]),
+])
+def test_planes_in_every_form_of_a_short_launch(dev, ns, shapes, forms):
+    """64-wide blocks with either ring, alone and where 128-wide ones would leave their last round badly filled, lists that mix K."""
+    assert fine_forms(shapes, ns) == forms
+    wl = workloads.custom("forms_" + ns, shapes, ns_dtype=ns, seed_base=327)
+    n = len(shapes)
+    assert_records(U.run_and_compare(wl, dev, check=sorted({0, 1, 2, n - 3, n - 2, n - 1}), steps=2, want_rms=True), U.TOL_SPLIT_FRO[ns])
 
 
 @pytest.mark.parametrize("ns", ["bf16x2", "bf16x3"])
@@ -169,8 +189,8 @@ def test_update_of_a_long_list_of_odd_widths(dev):
 @pytest.mark.timeout(600)
 @pytest.mark.parametrize("ns", ["bf16x2", "bf16x3"])
 def test_planes_in_coarse_tiles_and_strips(dev, ns):
-    """With several planes only large matrices get 256-wide tiles and, where the side is an odd multiple of 128, 512 x 128
-    strips; one of the two is iterated on its transpose."""
+    """With several planes only large matrices get coarse entries (256 x 256 and, where the side is an odd multiple of 128, 512 x 128,
+    each run as four 128 x 128 blocks); one of the two is iterated on its transpose."""
     shapes = [(3200, 3328), (3328, 3200)]
     assert min(coarse_tiles(shapes, ns)) > 0
     wl = workloads.custom("strips_" + ns, shapes, ns_dtype=ns, seed_base=350)
@@ -179,8 +199,8 @@ def test_planes_in_coarse_tiles_and_strips(dev, ns):
 
 @pytest.mark.timeout(600)
 def test_planes_in_both_launches_of_a_product(dev):
-    """Two planes, 2 x 136 symmetric tiles of one K: 256 stay in the persistent coarse launch, the last 16, all of the second
-    matrix, go to the fine launch as four 128 x 128 tiles each."""
+    """Two planes, 2 x 136 symmetric tiles of one K: 256 stay in the coarse launch, the last 16, all of the second matrix, go to
+    the fine launch as four 128 x 128 entries each."""
     shapes = [(4096, 4096)] * 2
     assert table_sizes(shapes, "bf16x2", 1) == [256, 256, 512] and table_sizes(shapes, "bf16x2", 0) == [64, 64, 0]
     wl = workloads.custom("planes_tail", shapes, ns_dtype="bf16x2", seed_base=355)

@@ -122,7 +122,7 @@ def test_random_shape_lists_are_covered_in_every_chunking(seed):
 @pytest.mark.parametrize("seed", range(6))
 def test_random_lists_of_large_matrices_with_planes_are_covered(seed):
     """Several planes get coarse tiles, strips and moved tails only where matrices are large: sides up to 5000, one list in
-    three of one shape (persistent launches, whose last round moves)."""
+    three of one shape (whose last round moves)."""
     rng = np.random.RandomState(2000 + seed)
     def dim():
         return int([rng.randint(3072, 5000), 128 * rng.randint(24, 40), 256 * rng.randint(12, 20)][rng.randint(3)])
@@ -322,7 +322,7 @@ def coarse_counts(shapes, ns):
     (binding.MUON_BF16, [(1536, 1536)] * 4, False, True),
     (binding.MUON_BF16, [(1280, 2560)] * 3, False, True),
     (binding.MUON_BF16, [(256, 8192)] * 5, False, False),
-    # planes: long K loops of large matrices in well-filled rounds pay for the coarse epilogue
+    # planes: large matrices, and long K loops in well-filled rounds
     (binding.MUON_BF16X2, [(1024, 1024)] * 48, False, False),
     (binding.MUON_BF16X2, [(1024, 4096)] * 24, False, False),
     (binding.MUON_BF16X2, [(1536, 8192)] * 6, False, False),
@@ -358,3 +358,49 @@ def test_one_more_matrix_does_not_move_all_the_others():
         assert coarse_counts([(1024, 1024)] * 48 + [(3072, 3072)], ns) == (0, 0)
     assert coarse_counts([(1024, 1024)] * 16, binding.MUON_BF16) == (0, 256)
     assert coarse_counts([(1024, 1024)] * 16 + [(16, 2100)], binding.MUON_BF16)[0] == 0
+
+
+@pytest.mark.parametrize("ns,shapes,forms", [
+    # plain bf16: waves up to 24 entries, up to 36 with K <= 512; the longer ring by the work, entries of the longest K
+    ("bf16", [(512, 512)] * 2, ["waves", "waves", "waves"]),                      # 20, 20, 32 of K = 512
+    ("bf16", [(512, 640)] * 2, ["waves", "waves", "ring4"]),                      # apply: 40
+    ("bf16", [(640, 640)] * 2, ["ring4", "ring4", "ring4"]),                      # 30, 30, 50 of K = 640
+    ("bf16", [(128, 300)] * 36, ["waves", "waves", "quarters"]),
+    ("bf16", [(128, 300)] * 37, ["ring4", "ring4", "quarters"]),
+    ("bf16", [(128, 300)] * 68, ["ring4", "ring4", "whole"]),
+    ("bf16", [(128, 300)] * 69, ["quarters", "quarters", "whole"]),
+    ("bf16", [(1024, 1024), (256, 8000), (256, 8000), (256, 8000)], ["ring4", "ring4", "quarters"]),   # Gram product: 45 entries, the work of 14; apply: 442, of 159
+    ("bf16", [(1000, 3001)] * 2 + [(777, 777)] * 2 + [(63, 4097)] * 2, ["ring4", "quarters", "whole"]),    # 130, of 67
+    # two planes: up to three quarters of the compute units, and a little more than all of them up to K = 2048
+    ("bf16x2", [(128, 300)] * 64, ["ring4", "ring4", "quarters"]),
+    ("bf16x2", [(128, 300)] * 65, ["quarters", "quarters", "whole"]),             # apply: 195
+    ("bf16x2", [(300, 700)] * 6 + [(700, 300)] * 6 + [(128, 4096)] * 8, ["ring4", "quarters", "quarters"]),  # 80 entries, the work of 22; apply: of 302
+    ("bf16x2", [(128, 900)] * 192, ["quarters", "quarters", "whole"]),
+    ("bf16x2", [(128, 900)] * 193, ["whole", "whole", "whole"]),
+    ("bf16x2", [(128, 128)] * 256, ["whole", "whole", "whole"]),
+    ("bf16x2", [(128, 128)] * 257, ["quarters", "quarters", "quarters"]),
+    ("bf16x2", [(128, 128)] * 320, ["quarters", "quarters", "quarters"]),
+    ("bf16x2", [(128, 128)] * 321, ["whole", "whole", "whole"]),
+    ("bf16x2", [(128, 2048)] * 300, ["quarters", "quarters", "whole"]),
+    ("bf16x2", [(128, 2176)] * 300, ["whole", "quarters", "whole"]),
+    # three planes: half of the compute units, more with a short K; a badly filled last round, by K
+    ("bf16x3", [(128, 128)] * 200, ["quarters"] * 3),
+    ("bf16x3", [(128, 128)] * 201, ["whole"] * 3),
+    ("bf16x3", [(128, 896)] * 150, ["quarters", "quarters", "whole"]),
+    ("bf16x3", [(128, 896)] * 151, ["whole", "quarters", "whole"]),               # apply: 1057, more than 1024
+    ("bf16x3", [(128, 4096)] * 128, ["quarters", "quarters", "whole"]),
+    ("bf16x3", [(128, 4096)] * 129, ["whole", "quarters", "whole"]),
+    ("bf16x3", [(128, 128)] * 257, ["quarters"] * 3),
+    ("bf16x3", [(128, 128)] * 435, ["quarters"] * 3),                             # 0.8496 of two rounds
+    ("bf16x3", [(128, 128)] * 436, ["whole"] * 3),
+    ("bf16x3", [(128, 1024)] * 409, ["quarters", "quarters", "whole"]),
+    ("bf16x3", [(128, 1024)] * 410, ["whole", "quarters", "whole"]),
+    ("bf16x3", [(128, 2048)] * 332, ["quarters", "quarters", "whole"]),
+    ("bf16x3", [(128, 2048)] * 333, ["whole", "quarters", "whole"]),
+    ("bf16x3", [(128, 4096)] * 291, ["quarters", "quarters", "whole"]),
+    ("bf16x3", [(128, 4096)] * 292, ["whole", "quarters", "whole"]),
+])
+def test_blocks_of_the_fine_launches(ns, shapes, forms):
+    """The lines between 128-wide blocks, 64-wide ones with either ring and single waves."""
+    from tests.plan_routes import fine_forms
+    assert fine_forms(shapes, ns) == forms
