@@ -69,15 +69,18 @@ void strip_tiles(int32_t prob, int rows, int col0, std::vector<GemmTile>& out, s
 // tiles only if the table length is a multiple of the number of blocks; the r tiles beyond that cost the launch a whole
 // extra round.  When r is small they are taken out of the coarse lists - plain 256 x 256 tiles from the end of the
 // problems that come last in the launch order - and handed to the fine launch, four 128 x 128 tiles each, where they
-// run side by side, one per compute unit.  `moved` receives them per problem; returns how many were moved.
+// run side by side, one per compute unit.  With several planes no launch is persistent, and what the moved tiles gain is that
+// they run as 64 x 64 blocks: `most` is then what a launch in quarters holds (2 of 4096^2, 16 tiles, 7590 / 7510 us without / with
+// the move, three planes 13550 / 13300; but 16 of 2048 x 8192, whose 64 would run 128 wide again, 24910 / 25350).
+// `moved` receives them per problem; returns how many were moved.
 constexpr int kMaxMovedTiles = 64;
 size_t move_tail_to_fine(const std::vector<int>& order, std::vector<std::vector<GemmTile>>& lists,
-                         std::vector<std::vector<int>>& cuts, int blocks, std::vector<std::vector<GemmTile>>& moved) {
+                         std::vector<std::vector<int>>& cuts, int blocks, int most, std::vector<std::vector<GemmTile>>& moved) {
   size_t total = 0;
   for (const auto& l : lists) total += l.size();
   if (blocks <= 0 || total <= (size_t)blocks) return 0;
   const size_t r = total % (size_t)blocks;
-  if (r == 0 || r > (size_t)kMaxMovedTiles) return 0;
+  if (r == 0 || r > (size_t)most) return 0;
   size_t plain = 0;
   for (const auto& l : lists)
     for (const GemmTile& t : l) plain += (t.shape == kShape256 && !(t.flags & kTileDiagonal)) ? 1 : 0;
@@ -234,21 +237,18 @@ struct CoarseLoad {
 // round small matrices stay fine a little longer: 16 of 1024^2 (160) 35 / 33 and 39 / 34, 25 of 1024^2 (250) 46 / 43 and 49
 // / 43, 12 of 2048 x 1408 (216) 68 / 67 and 56 / 51; but 8 of 2048 x 1536 (168) 53 / 56 and 48 / 46, 4 of 2048^2 (144) 50 /
 // 56 and 53 / 58, 7 of 2048^2 (252) 67 / 73 and 70 / 75.
-// With several planes both launches run 128 x 128 tiles (gemm_planes.h), and all that is left of the choice is the order of
-// the tiles and which die they run on.  Its line stems from 256-wide tiles whose epilogue spilled (about 50 us a tile at two
-// planes, 70 at three), which paid only with long K loops of large matrices in well-filled rounds.  As measured then: Gram and polynomial together, two planes:
-// 48 of 1024^2 553 / 437, 24 of 1024 x 4096 608 / 514, 25 of 1024 x 8192 992 / 963, 7 of 2048^2 443 / 405, 8 of 2560^2 1003
-// / 941, 7 of 2688 x 3200 1093 / 1042, 6 of 1536 x 8192 (126 tiles) 734 / 483, 4 of 2048 x 4096 471 / 442, 7 598 / 607 (the
-// line errs); 11 of 2304 x 3840 1206 / 1261, 12 of 1536 x 6144 780 / 797, 12 of 1536 x 8192 929 / 990, 4 of 2048 x 8192 732
-// / 786, 7 923 / 1026, 16 2321 / 2413, 4 of 2560 x 5120 674 / 714, 4 of 2560 x 10240 1084 / 1224, 4096^2 531 / 571.  Three
-// planes: 48 of 1024^2 959 / 822, 24 of 1024 x 4096 1118 / 1032, 6 of 2304^2 (270 tiles) 1112 / 1171 (errs); 14 of 2048^2
-// (504: two full rounds) 1630 / 1667, 25 of 1024 x 8192 1901 / 1939, 12 of 1536 x 6144 1511 / 1629, 7 of 2048 x 4096 1132 /
-// 1250, 4 of 2560^2 895 / 974.  A round that is little more than half full is not worth it below m = 3072: 4 of 2816 x
-// 11008 (264) 1481 / 1415 and 3009 / 2967.
-// Lists that mix K (or m) lose more of their coarse rounds: 7 of 2048 x 8192 and 4 of 1024^2 1559 / 1033 and 3212 / 2132, 3
-// of 2048 x 2816 and of 2944 x 8832 1386 / 1216 and 2762 / 2498, 12 of 1536 x 8192 and of 1536 x 2048 1784 / 1337 and 3529
-// / 2768, 48 of 1024^2 beside one 3072^2 1438 / 1118 and 2858 / 2350; three planes of one large m are the exception: 4 of
-// 2560 x 10240 and of 2560^2 1609 / 1610 and 3179 / 3369, 3 of 2816 x 8192 and 4 of 2816^2 1452 / 1441 and 2865 / 3044.
+// Several planes: both launches run 128 x 128 tiles (gemm_planes.h).  A coarse entry's four run on one die in the order of
+// coarse blocks; with two planes the symmetric ones have three accumulators, a compute unit each and the shorter polynomial.  A
+// fine launch mixes in whatever else is fine, runs in quarters where it is short, and folds the norm there.  Measured, Gram and
+// polynomial together, us per launch pair, coarse / fine.  Two planes: 48 of 1024^2 434 / 412, 24 of 1024 x 4096 491 / 444, 40 of
+// 1408 x 2048 976 / 940, 24 of 1536^2 663 / 613, 12 of 1536 x 6144 689 / 684, 12 of 1536 x 8192 826 / 847, 4 of 2048 x 8192
+// 563 / 675, 16 1939 / 2083, 11 of 2304 x 3840 1129 / 1153, 4 of 2560 x 5120 635 / 655, 4 of 2816 x 11008 (264 tiles) 1335 / 1251, 2 of
+// 3072^2 369 / 421, 3 of 3200^2 572 / 612, 7 of 4096^2 2636 / 3034; the line errs, by the old tile's leave, at 4 of 2048^2 258 /
+// 277, 4 of 2048 x 4096 357 / 400, 7 of 2688 x 3200 912 / 993.  Three planes: 48 of 1024^2 711 / 663, 25 of 1024 x 8192 1390 / 1358,
+// 16 of 1408 x 2048 702 / 677, 12 of 1536 x 6144 1177 / 1171, 7 of 2048^2 678 / 664, 7 of 2048 x 4096 961 / 964, 4 of 2560 x 5120
+// 1100 / 1398, 4 of 2816^2 (264 tiles) 1025 / 909, 2 of 3072^2 654 / 703, 4096^2 822 / 831; it errs at 24 of 1024 x 4096 805 / 865.
+// Lists that mix K (or m): two planes 7 of 2048 x 8192 and 4 of 1024^2 991 / 944, 48 of 1024^2 beside one 3072^2 955 / 943; three
+// planes of one large m: 4 of 2560 x 10240 and of 2560^2 2393 / 2372.
 bool few_coarse_sym(const CoarseLoad& c, int planes, int blocks) {
   if (c.per_256(blocks) < 112) return true;
   if (planes == 1) return c.per_256(blocks) < 256 && c.n <= 2048 && c.area <= 3.0 * (1 << 20);
@@ -263,13 +263,11 @@ bool few_coarse_sym(const CoarseLoad& c, int planes, int blocks) {
 // 512 x 4096 (160) 23 / 20, 3 of 640 x 5120 (150) 27 / 24, 4 of 768 x 3072 (144) 27 / 26, 10 of 1024^2 (160) 31 / 32, 4 of
 // 1000 x 2500 (160) 31 / 31; but 3 of 1280 x 2560 (150) 36 / 38, 4 of 1536^2 (144) 39 / 43, 3072^2 (144) 63 / 78, four of
 // 1024 x 4096 (256) 38 / 41.
-// Several planes, as above: two planes 48 of 1024^2 397 / 356, 24 of 1024 x 4096 741 / 674, 12 of 1536^2 320 / 296, 16 of 2048 x 1408 462 / 414, 8
-// of 1280 x 10240 910 / 873, 4 of 2048^2 203 / 202, 16 of 2048 x 8192 3115 / 3318, 4096^2 340 / 381; three planes: 24 of
-// 1024 x 4096 1428 / 1327, 24 of 1536^2 1259 / 1134, 7 of 2048^2 728 / 771, 4 of 2560^2 872 / 936.
-// At m = 1536 the largest are even in full rounds (two planes: 12 of 1536 x 6144 1129 / 1109, of 1536 x 8192 1445 / 1435;
-// three: 2231 / 2254 and 2858 / 2899), but the other launches of the step are quicker beside coarse ones, which draw less
-// power: 12 of 1536 x 8192 12.75 -> 12.6 ms and 25.2 -> 24.3 ms (6 of them, rounds 90 % full: 756 / 708, 1465 / 1436), 12
-// of 1536 x 6144 with three planes 19.7 -> 19.2 ms.
+// Several planes, as above, coarse / fine.  Two planes: 48 of 1024^2 302 / 307, 24 of 1024 x 4096 598 / 584, 40 of 1408 x 2048 899 /
+// 887, 24 of 1536^2 481 / 483, 12 of 1536 x 8192 1241 / 1234, 7 of 2048 x 4096 626 / 638, 16 of 2048 x 8192 2847 / 2887, 8 of 2560^2
+// 704 / 750, 4 of 2816 x 11008 1780 / 1823, 7 of 4096^2 2409 / 2496; where strips take many of the tiles it errs: 3 of 3200^2 577 /
+// 527.  Three planes: 24 of 1024 x 4096 1139 / 1124, 24 of 1536^2 905 / 895, 7 of 2048^2 593 / 591, 4 of 2560^2 670 / 695, 4 of
+// 2560 x 5120 1289 / 1320, 6 of 3072^2 1656 / 1666, 3 of 3200^2 1035 / 979.
 bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
   if (c.per_256(blocks) <= 128 || (c.per_256(blocks) < 176 && c.m <= 1024)) return true;
   if (planes == 1 || c.m > 1536) return false;
@@ -761,9 +759,10 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
           }
         }
         if (level == 1) {
-          // launches whose tiles all run the same K are persistent: even out their last round
-          if (uniform_n && uniform_m) move_tail_to_fine(by_n, sym, sym_cuts, plan.coarse_blocks, moved_sym);
-          if (uniform_m) move_tail_to_fine(by_m, app, app_cuts, plan.coarse_blocks, moved_app);
+          // launches whose tiles all run the same K: even out their last round
+          const int most = planes == 1 ? kMaxMovedTiles : lone_entries((int)planes, plan.coarse_blocks) / 4;
+          if (uniform_n && uniform_m) move_tail_to_fine(by_n, sym, sym_cuts, plan.coarse_blocks, most, moved_sym);
+          if (uniform_m) move_tail_to_fine(by_m, app, app_cuts, plan.coarse_blocks, most, moved_app);
         }
         for (size_t k = 0; k < np_; ++k) {
           n_sym += sym[k].size();
@@ -791,9 +790,9 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         ts.apply = take(n_app * sizeof(GemmTile));      // the last iteration runs the same tiles: only its outputs differ
         // The two symmetric products run the same tiles but not the same K (n for the Gram product, m for the
         // polynomial), so each gets its own table: dealt longest K first and weighted by its own K, and with the costs
-        // evened out over a die's blocks where its launch is persistent (where the hardware hands out the blocks the
-        // plain order measured better).
-        const int slots = level == 1 ? plan.coarse_blocks / kXcds : 0;
+        // evened out over a die's blocks where its launch is persistent (where the hardware hands out the blocks, with several
+        // planes always, the plain order measured better).
+        const int slots = level == 1 && planes == 1 ? plan.coarse_blocks / kXcds : 0;
         ts.n_sym = (int)deal_tiles(by_n, sym, sym_cuts, w_n, reinterpret_cast<GemmTile*>(img.data() + ts.sym), steady_n ? slots : 0, level == 0);
         ts.n_poly = (int)deal_tiles(by_m, sym, sym_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.poly), steady_m ? slots : 0, level == 0);
         ts.n_apply = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply), steady_m ? slots : 0, level == 0);

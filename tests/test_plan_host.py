@@ -404,3 +404,16 @@ def test_blocks_of_the_fine_launches(ns, shapes, forms):
     """The lines between 128-wide blocks, 64-wide ones with either ring and single waves."""
     from tests.plan_routes import fine_forms
     assert fine_forms(shapes, ns) == forms
+
+
+@pytest.mark.parametrize("ns,count,coarse,fine", [
+    ("bf16x2", 4, 512, 128), ("bf16x2", 6, 768, 192), ("bf16x2", 8, 1088, 0),
+    ("bf16x3", 4, 512, 128), ("bf16x3", 6, 816, 0), ("bf16x3", 8, 1088, 0), ("bf16", 8, 1024, 256)])
+def test_planes_move_a_tail_only_where_it_runs_in_quarters(ns, count, coarse, fine):
+    """136 symmetric tiles for each 4096 x 4096: 32, 48 or 64 are beyond a multiple of 256.  With planes they go to the fine launch
+    where four entries for each still run as 64-wide blocks; persistent launches (plain bf16) move up to 64."""
+    from tests.plan_routes import routes
+    tables, _ = routes([(4096, 4096)] * count, ns)
+    for product in ("gram", "poly"):
+        assert tables[product, 1][0] == coarse and tables[product, 0][0] == fine
+        assert fine == 0 or ns == "bf16" or tables[product, 0][1] != "whole"
