@@ -798,11 +798,14 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         ts.n_apply = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply), steady_m ? slots : 0, level == 0);
       }
       // Lists short enough for quarter blocks save the norm's own launch (about 4 us): every block adds up its matrix's
-      // partials, at most four per thread, while its first operands are on their way.
-      constexpr int kMaxFoldedPartials = 1024;
+      // partials while its first operands are on their way, at most four per thread, or per lane where it is a wave.  With
+      // waves the norm's launch / the fold, us per step: 64 x 4000 (126 partials) 110.0 / 109.2, 64 x 8000 (252) 170.0 / 170.4, 256 x
+      // 8000 (504) 185.0 / 186.1, 128 x 16000 (500) 279.6 / 281.6, 64 x 32000 (1000) 508.8 / 510.0.
+      constexpr int kFoldedPerThread = 4;
+      const int most_folded = kFoldedPerThread * (g.fine.few_sym == 2 ? 64 : 256);
       int most_parts = 0;
       for (int i = ch.first; i < ch.first + ch.count; ++i) most_parts = std::max(most_parts, h_mats[i].n_part);
-      ch.fold_norm = g.coarse.n_sym == 0 && g.fine.quarter_sym && most_parts <= kMaxFoldedPartials;
+      ch.fold_norm = g.coarse.n_sym == 0 && g.fine.quarter_sym && most_parts <= most_folded;
       ch.groups.push_back(g);
     }
   }

@@ -417,3 +417,16 @@ def test_planes_move_a_tail_only_where_it_runs_in_quarters(ns, count, coarse, fi
     for product in ("gram", "poly"):
         assert tables[product, 1][0] == coarse and tables[product, 0][0] == fine
         assert fine == 0 or ns == "bf16" or tables[product, 0][1] != "whole"
+
+
+@pytest.mark.parametrize("ns,shapes,fold", [
+    # one wave per 32 x 32: four partials (64 x 64 tiles of the padded matrix) per lane
+    ("bf16", [(64, 8192)], True), ("bf16", [(64, 8193)], False), ("bf16", [(512, 2048)], True), ("bf16", [(512, 2049)], False),
+    # blocks of four waves: four per thread
+    ("bf16", [(64, 8193)] * 25, True), ("bf16", [(64, 32768)] * 25, True), ("bf16", [(64, 32769)] * 25, False),
+    ("bf16x2", [(64, 32768)], True), ("bf16x2", [(64, 32769)], False), ("f32", [(64, 65536)], True), ("f32", [(64, 65537)], False),
+    # no quarters, no fold
+    ("bf16", [(128, 128)] * 177, False)])
+def test_norm_is_folded_up_to_four_partials_per_thread(ns, shapes, fold):
+    from tests.plan_routes import routes
+    assert routes(shapes, ns)[1] == fold
