@@ -1005,6 +1005,9 @@ __global__ __launch_bounds__(256, PL == 2 && LKM ? 2 : 1) void ns_gemm_bf16_kern
     const GemmProblem p = probs[tile.prob];
     const int row0 = tile.r0 * kTileUnit + 128 * (strip ? quarter : quarter >> 1), col0 = tile.c0 * kTileUnit + 128 * (strip ? 0 : quarter & 1);
     if (p.symmetric && row0 > col0) return;      // below the diagonal: a mirror image
+    // the last strip of a column is shifted up to end at the edge: what its neighbour computes too is left to that
+    const int own_row = strip ? (tile.r0 * kTileUnit + kShapeRows[kShape512x128] - 1) / kShapeRows[kShape512x128] * kShapeRows[kShape512x128] : 0;
+    if (row0 < own_row) return;
     planes_tile<128, planes_ring_coarse(LKM, PL), LKM, PL>(p, row0, col0, p.symmetric && row0 == col0, smem, beta_acc, beta_e, alpha_idx, 0.0);
   } else {
     const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
