@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import shutil
 import subprocess
+import sys
 from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
@@ -51,11 +52,28 @@ def _run(cmd, verbose):
         print(" ".join(cmd), flush=True)
     proc = subprocess.run(cmd, capture_output=True, text=True)
     if proc.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + " ".join(cmd) + "\n" + proc.stdout + proc.stderr)
+        raise RuntimeError(f"{os.path.basename(cmd[0])} failed:\n" + " ".join(cmd) + "\n" + proc.stdout + proc.stderr)
+
+
+def build_marshal(verbose: bool = False) -> bool:
+    """Builds the extension that marshals AdamW's tensors.  It is optional: where torch, its headers, Python's or g++ are
+    missing the library is complete without it and the binding reads the tensors in Python (False, the reason on stderr)."""
+    tmp = MARSHAL_PATH + ".tmp"
+    try:
+        _run(marshal_command(tmp), verbose)
+    except (ImportError, AttributeError, OSError, RuntimeError) as e:
+        if os.path.exists(tmp):
+            os.remove(tmp)
+        print(f"{os.path.basename(MARSHAL_PATH)} was not built, muon_adamw_step reads its tensors in Python: "
+              f"{type(e).__name__}: {e}", file=sys.stderr, flush=True)
+        return False
+    os.replace(tmp, MARSHAL_PATH)
+    return True
 
 
 def build_library(verbose: bool = False, extra_flags=()) -> str:
-    """Compiles every source (in parallel, one object each) and links the shared library.  Always recompiles."""
+    """Compiles every source (in parallel, one object each) and links the shared library, with hipcc alone; then the optional
+    extension.  Always recompiles."""
     hipcc = hipcc_path()
     os.makedirs(OBJ_DIR, exist_ok=True)
     objs = [os.path.join(OBJ_DIR, os.path.splitext(s)[0] + ".o") for s in SOURCES]
@@ -64,8 +82,7 @@ def build_library(verbose: bool = False, extra_flags=()) -> str:
         list(pool.map(lambda c: _run(c, verbose), cmds))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH + ".tmp"], verbose)
     os.replace(LIB_PATH + ".tmp", LIB_PATH)
-    _run(marshal_command(MARSHAL_PATH + ".tmp"), verbose)
-    os.replace(MARSHAL_PATH + ".tmp", MARSHAL_PATH)
+    build_marshal(verbose)
     return LIB_PATH
 
 

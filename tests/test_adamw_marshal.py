@@ -1,14 +1,16 @@
 """The extension that marshals AdamW's tensors takes plain tensors only and leaves everything else to the Python loop (no GPU:
-an invalid step number makes the library return before it looks at the device)."""
+an invalid step number makes the library return before it looks at the device); the library is built with or without it."""
 import ctypes as C
+import os
 
 import pytest
 import torch
 from torch.overrides import TorchFunctionMode
 
-from paper_2502_16982_amd import binding
+from paper_2502_16982_amd import binding, build
 
 F, H = torch.float32, torch.bfloat16
+REAL_RUN = build._run
 
 
 @pytest.fixture(scope="module")
@@ -67,3 +69,49 @@ def test_subclasses_and_modes_are_left_to_the_loop(native):
     with Mode():
         assert status(native, [quad()]) is None
     assert status(native, [quad()]) == -1
+
+
+@pytest.fixture
+def tree(tmp_path, monkeypatch):
+    """build.py pointed at an empty folder; compilers replaced by a record of what was run, which leaves the output file."""
+    ran = []
+
+    def run(cmd, verbose):
+        ran.append(cmd)
+        out = cmd[cmd.index("-o") + 1]
+        with open(out, "w") as f:
+            f.write(cmd[0])
+
+    monkeypatch.setattr(build, "PKG_DIR", str(tmp_path))
+    monkeypatch.setattr(build, "OBJ_DIR", str(tmp_path / "_build"))
+    monkeypatch.setattr(build, "LIB_PATH", str(tmp_path / build.LIB_NAME))
+    monkeypatch.setattr(build, "MARSHAL_PATH", str(tmp_path / "_adamw_marshal.so"))
+    monkeypatch.setattr(build, "_run", run)
+    return ran
+
+
+def without_headers(out):
+    raise ImportError("no torch here")
+
+
+def without_compiler(out):
+    return ["/nowhere/g++", "-o", out]
+
+
+@pytest.mark.parametrize("command,reason", [(without_headers, "ImportError: no torch here"), (without_compiler, "FileNotFoundError"),
+                                            (lambda out: ["false", "-o", out], "false failed")])
+def test_library_is_built_without_the_extension(tree, monkeypatch, capsys, command, reason):
+    """hipcc alone makes the library; what the optional extension lacks is said, under its own name."""
+    recorded = build._run
+    monkeypatch.setattr(build, "marshal_command", command)
+
+    def run(cmd, verbose):
+        if os.path.basename(cmd[0]) == "hipcc":
+            return recorded(cmd, verbose)
+        return REAL_RUN(cmd, verbose)
+
+    monkeypatch.setattr(build, "_run", run)
+    assert build.build_library() == build.LIB_PATH and os.path.exists(build.LIB_PATH)
+    assert not os.path.exists(build.MARSHAL_PATH) and not os.path.exists(build.MARSHAL_PATH + ".tmp")
+    err = capsys.readouterr().err
+    assert "_adamw_marshal.so was not built" in err and reason in err and "hipcc" not in err
