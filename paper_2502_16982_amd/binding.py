@@ -276,15 +276,18 @@ _MARSHAL = None
 
 
 def _marshal():
-    """The extension that reads tensors without a Python call per attribute; False where it does not load (built for another
-    torch, say): the loop below then does its work."""
+    """The extension that reads tensors without a Python call per attribute; False where it is missing, does not load, or was
+    built for another torch or another library: the loop below then does its work."""
     global _MARSHAL
     if _MARSHAL is None:
         lib()
         try:
             import torch  # noqa: F401           (the extension needs its libraries)
             from paper_2502_16982_amd import _adamw_marshal
-            _MARSHAL = _adamw_marshal
+            from paper_2502_16982_amd.build import marshal_stamp
+            same = (getattr(_adamw_marshal, "built_for", None) == marshal_stamp() and
+                    getattr(_adamw_marshal, "record_sizes", None) == (C.sizeof(muon_adamw_param), C.sizeof(muon_adamw_hparams)))
+            _MARSHAL = _adamw_marshal if same else False
         except ImportError:
             _MARSHAL = False
     return _MARSHAL

@@ -35,6 +35,12 @@ def hipcc_path() -> str:
     raise RuntimeError("hipcc not found: the Muon HIP library cannot be built")
 
 
+def marshal_stamp() -> str:
+    """What the extension is compiled for: it reads tensors through torch's inlined C++, whose layouts belong to one torch."""
+    import torch
+    return f"torch {torch.__version__} {torch.version.git_version} python {sys.version_info[0]}.{sys.version_info[1]}"
+
+
 def marshal_command(out):
     """The compiler line of the extension that marshals AdamW's tensors (host code only; torch's headers and libraries)."""
     import sysconfig
@@ -43,6 +49,7 @@ def marshal_command(out):
     lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
     include = [*cpp_extension.include_paths(), sysconfig.get_paths()["include"]]
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f'-DMUON_BUILT_FOR="{marshal_stamp()}"',
             *(f"-isystem{d}" for d in include), os.path.join(CSRC, "adamw_marshal.cpp"), "-o", out, f"-L{PKG_DIR}",
             f"-l:{LIB_NAME}", f"-L{lib_dir}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
 
@@ -81,6 +88,8 @@ def build_library(verbose: bool = False, extra_flags=()) -> str:
     with ThreadPoolExecutor(max_workers=min(8, len(cmds))) as pool:
         list(pool.map(lambda c: _run(c, verbose), cmds))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB_PATH + ".tmp"], verbose)
+    if os.path.exists(MARSHAL_PATH):             # of another library, maybe of another torch: never beside this one
+        os.remove(MARSHAL_PATH)
     os.replace(LIB_PATH + ".tmp", LIB_PATH)
     build_marshal(verbose)
     return LIB_PATH

@@ -63,4 +63,16 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_adamw_marshal", nullptr, -1, meth
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__adamw_marshal() { return PyModule_Create(&module); }
+// Reading a tensor is inlined code for one layout, so the module says which torch it was compiled for and how large the
+// library's records were; the binding does not use it with another.
+PyMODINIT_FUNC PyInit__adamw_marshal() {
+  PyObject* m = PyModule_Create(&module);
+  if (!m) return nullptr;
+  PyObject* sizes = Py_BuildValue("(nn)", (Py_ssize_t)sizeof(muon_adamw_param), (Py_ssize_t)sizeof(muon_adamw_hparams));
+  if (!sizes || PyModule_AddStringConstant(m, "built_for", MUON_BUILT_FOR) < 0 || PyModule_AddObject(m, "record_sizes", sizes) < 0) {
+    Py_XDECREF(sizes);
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -7,6 +7,7 @@ import pytest
 import torch
 from torch.overrides import TorchFunctionMode
 
+import paper_2502_16982_amd
 from paper_2502_16982_amd import binding, build
 
 F, H = torch.float32, torch.bfloat16
@@ -115,3 +116,48 @@ def test_library_is_built_without_the_extension(tree, monkeypatch, capsys, comma
     assert not os.path.exists(build.MARSHAL_PATH) and not os.path.exists(build.MARSHAL_PATH + ".tmp")
     err = capsys.readouterr().err
     assert "_adamw_marshal.so was not built" in err and reason in err and "hipcc" not in err
+
+
+def test_an_older_extension_goes_before_the_library_changes(tree, monkeypatch):
+    """One that an earlier build left, of another record layout maybe, is not there beside the new library, even where no new
+    one can be built."""
+    open(build.MARSHAL_PATH, "w").write("old")
+    open(build.LIB_PATH, "w").write("old")
+    replace = os.replace
+
+    def watched(src, dst):
+        assert dst != build.LIB_PATH or not os.path.exists(build.MARSHAL_PATH)
+        return replace(src, dst)
+
+    monkeypatch.setattr(build.os, "replace", watched)
+    monkeypatch.setattr(build, "marshal_command", without_headers)
+    build.build_library()
+    assert open(build.LIB_PATH).read() != "old" and not os.path.exists(build.MARSHAL_PATH)
+
+
+SIZES = (C.sizeof(binding.muon_adamw_param), C.sizeof(binding.muon_adamw_hparams))
+
+
+@pytest.mark.parametrize("marks,used", [
+    ({"built_for": build.marshal_stamp(), "record_sizes": SIZES}, True),
+    ({"built_for": build.marshal_stamp().replace("torch ", "torch 9."), "record_sizes": SIZES}, False),
+    ({"built_for": build.marshal_stamp().replace("python ", "python 9."), "record_sizes": SIZES}, False),
+    ({"built_for": build.marshal_stamp(), "record_sizes": (SIZES[0] + 8, SIZES[1])}, False),
+    ({"built_for": build.marshal_stamp(), "record_sizes": (SIZES[0], SIZES[1] - 8)}, False),
+    ({}, False)])
+def test_an_extension_of_another_torch_or_library_is_not_used(monkeypatch, marks, used):
+    class Extension:
+        def step(*args):
+            raise AssertionError("called")
+    for name, value in marks.items():
+        setattr(Extension, name, value)
+    monkeypatch.setattr(paper_2502_16982_amd, "_adamw_marshal", Extension, raising=False)
+    monkeypatch.setattr(binding, "_MARSHAL", None)
+    assert (binding._marshal() is Extension) == used and (used or binding._marshal() is False)
+    if not used:                                 # the loop does its work
+        with pytest.raises(binding.MuonError):
+            binding.muon_adamw_step([quad()], lr=1e-3, weight_decay=0.1, step=0)
+
+
+def test_the_built_extension_is_the_one_for_this_torch(native):
+    assert native.built_for == build.marshal_stamp() and native.record_sizes == SIZES
