@@ -3,6 +3,7 @@
 // on the device, and takes 8.6 like this.  It takes the ordinary case only - plain contiguous tensors of the types the step knows - and answers None
 // to everything else, which the binding then handles (and refuses, where it has to) in Python.
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <torch/csrc/PyInterpreter.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <vector>
@@ -34,13 +35,25 @@ bool record_of(PyObject* quad, muon_adamw_param* out) {
   return true;
 }
 
+PyObject* g_device_context = nullptr;            // torch.utils._device.DeviceContext, for as long as the process runs
+
+// Function modes see every call of the Python path, so a mode leaves the work to that, with one exception: the mode behind
+// torch.set_default_device and `with torch.device(..)` changes calls that make tensors and hands every other one through.
+bool modes_see_calls() {
+  using at::impl::PythonTorchFunctionTLS;
+  if (!at::impl::torch_function_mode_enabled()) return false;
+  for (int64_t i = 0, n = PythonTorchFunctionTLS::stack_len(); i < n; ++i)
+    if ((PyObject*)Py_TYPE(PythonTorchFunctionTLS::get_stack_at(i)->ptr(getPyInterpreter())) != g_device_context) return true;
+  return false;
+}
+
 // step(list of tuples, address of a muon_adamw_hparams, stream) -> status of muon_adamw_step, or None
 PyObject* step(PyObject*, PyObject* args) {
   PyObject* list = nullptr;
   unsigned long long hp = 0, stream = 0;
   if (!PyArg_ParseTuple(args, "O!KK", &PyList_Type, &list, &hp, &stream)) return nullptr;
   try {
-    if (at::impl::torch_function_mode_enabled()) Py_RETURN_NONE;   // and so do function modes
+    if (modes_see_calls()) Py_RETURN_NONE;
     const Py_ssize_t n = PyList_GET_SIZE(list);
     std::vector<muon_adamw_param> records((size_t)n);
     for (Py_ssize_t i = 0; i < n; ++i)
@@ -68,6 +81,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_adamw_marshal", nullptr, -1, meth
 PyMODINIT_FUNC PyInit__adamw_marshal() {
   PyObject* m = PyModule_Create(&module);
   if (!m) return nullptr;
+  if (PyObject* device = PyImport_ImportModule("torch.utils._device")) {
+    g_device_context = PyObject_GetAttrString(device, "DeviceContext");
+    Py_DECREF(device);
+  }
+  PyErr_Clear();                                 // (without it, modes of any kind go to Python)
   PyObject* sizes = Py_BuildValue("(nn)", (Py_ssize_t)sizeof(muon_adamw_param), (Py_ssize_t)sizeof(muon_adamw_hparams));
   if (!sizes || PyModule_AddStringConstant(m, "built_for", MUON_BUILT_FOR) < 0 || PyModule_AddObject(m, "record_sizes", sizes) < 0) {
     Py_XDECREF(sizes);

@@ -72,6 +72,30 @@ def test_subclasses_and_modes_are_left_to_the_loop(native):
     assert status(native, [quad()]) == -1
 
 
+def test_a_default_device_is_no_reason_for_the_loop(native):
+    """torch.set_default_device and `with torch.device(..)` are function modes too, of a kind that only changes factory calls."""
+    from torch.utils._device import DeviceContext
+
+    class Louder(DeviceContext):
+        pass
+
+    tensors = [quad()]
+    with torch.device("cpu"):
+        assert status(native, tensors) == -1
+        with Mode():
+            assert status(native, tensors) is None
+    with Louder(torch.device("cpu")):
+        assert status(native, tensors) is None
+    with Mode(), torch.device("cpu"):
+        assert status(native, tensors) is None
+    torch.set_default_device("cpu")
+    try:
+        assert status(native, tensors) == -1
+    finally:
+        torch.set_default_device(None)
+    assert status(native, tensors) == -1
+
+
 @pytest.fixture
 def tree(tmp_path, monkeypatch):
     """build.py pointed at an empty folder; compilers replaced by a record of what was run, which leaves the output file."""
