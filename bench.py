@@ -66,19 +66,32 @@ def executed_ns_flops(wl, ns_steps, ns_dtype="bf16"):
     """Matrix-core flops actually issued, summed over the tile tables of the launch plan (host-only call into the
     library): symmetric products compute only tiles on or above the diagonal and, in plain bf16, only the upper triangle
     of 32 x 32 blocks of a diagonal tile; strip tiles that were shifted to end at the matrix edge recompute what they
-    overlap."""
+    overlap.  With several planes every product is one for each plane pair (two planes: the polynomial's fourth pair over the
+    whole of K in fine tiles, over the block's own rows and columns in coarse ones), and coarse tiles run as 128 x 128
+    blocks, none below the diagonal and none twice."""
     from paper_2502_16982_amd import binding
     n = len(wl.shapes)
     p = binding.param_array(wl.shapes, [1] * n, [1] * n)
     ns = binding.NS_DTYPES[ns_dtype]
+    planes = PLANES[ns_dtype]
     ctx = binding.muon_plan_only(p, n, ns, binding.muon_workspace_bytes(p, n, ns, 0))
     try:
         desc = [binding.muon_plan_describe(ctx, i) for i in range(n)]
         flops = 0
         for product, k_of in (("gram", "n_pad"), ("poly", "m_pad"), ("apply", "m_pad")):
+            fourth = planes == 2 and product == "poly"
             for level in (0, 1):
-                for mat, _, _, _, _, blocks in binding.muon_plan_tiles(ctx, 0, product, level):
-                    flops += 2 * blocks * 1024 * desc[mat][k_of]
+                for mat, r0, c0, rows, cols, blocks in binding.muon_plan_tiles(ctx, 0, product, level):
+                    k = desc[mat][k_of]
+                    if planes == 1 or level == 0:
+                        flops += 2 * blocks * 1024 * k * (PLANE_PAIRS[planes] + (1 if fourth else 0))
+                        continue
+                    first = -(-r0 // rows) * rows if rows == 512 else r0      # a shifted strip: the neighbour's rows are not its own
+                    for r in range(first, r0 + rows, 128):
+                        for c in range(c0, c0 + cols, 128):
+                            if product == "apply" or r <= c:
+                                own = 0 if not fourth else 128 if r == c else 256
+                                flops += 2 * 128 * 128 * (PLANE_PAIRS[planes] * k + own)
     finally:
         binding.muon_destroy(ctx)
     return ns_steps * flops
@@ -150,7 +163,7 @@ def bench_adamw(dev, steps=5):
 
 
 PLANES = {"f32": 1, "bf16": 1, "bf16x2": 2, "bf16x3": 3}     # bf16 arrays per Newton-Schulz temporary
-SEGMENTS = {1: 1, 2: 3, 3: 6}                                 # matrix-core products behind one product of Eq. 2
+PLANE_PAIRS = {1: 1, 2: 3, 3: 6}                              # matrix-core products behind one product of Eq. 2
 
 
 def time_workload(name, steps, warmup, max_ws_gib, dev, ns_dtype=None):
@@ -192,7 +205,7 @@ def time_workload(name, steps, warmup, max_ws_gib, dev, ns_dtype=None):
     gemm_launches = sum(prof[k][1] for k in ("gram", "poly", "apply_poly"))
     bf16 = wl.ns_dtype != "f32"              # the matrix-core paths: plain bf16 and the split forms
     planes = PLANES[wl.ns_dtype]
-    executed = executed_ns_flops(wl, h.ns_steps, wl.ns_dtype) * SEGMENTS[planes]
+    executed = executed_ns_flops(wl, h.ns_steps, wl.ns_dtype)
     peak = PEAK_BF16_TFLOPS if bf16 else PEAK_F32_VALU_TFLOPS
     if gemm_launches:
         avg_launch_ms = gemm_ms / gemm_launches
@@ -303,7 +316,8 @@ def main() -> int:
                 "kernel_ms_per_step": {k: v[0] / o_steps for k, v in o["prof"].items() if v[1]},
                 "elementwise": o["elementwise"]})
         if args.ns_dtype is None:
-            # the accurate matrix-core path on the headline workload: two bf16 planes, three products per product of Eq. 2
+            # the accurate matrix-core path on the headline workload: two bf16 planes, three products (and, in the polynomial, a part
+            # of a fourth) per product of Eq. 2
             o = time_workload(args.config, min(5, max(2, args.steps // 2)), 2, args.max_workspace_gib, dev, "bf16x2")
             out["accurate_path"] = {
                 "workload": args.config, "ns_dtype": "bf16x2", "ms_per_step": o["ms_per_step"],

@@ -35,7 +35,8 @@ typedef enum {
   /* Newton-Schulz arithmetic only (ns_dtype), never a buffer dtype: every iterate and temporary is kept as the
    * sum of two / three bf16 arrays (value, rounding remainder, remainder of the remainder) and every product
    * of Eq. 2 runs on the bf16 matrix cores over the plane pairs (i, j) with i + j < planes: 3 / 6 times the
-   * work of MUON_BF16 for about 2^-16 / 2^-23 relative accuracy per product instead of 2^-8. */
+   * work of MUON_BF16 for about 2^-16 / 2^-23 relative accuracy per product instead of 2^-8.  With two planes the
+   * polynomial's A A takes the pair (1, 1) as well, on large matrices only around A's diagonal, where its worth is. */
   MUON_BF16X2 = 2,
   MUON_BF16X3 = 3
 } muon_dtype;
@@ -197,7 +198,9 @@ int muon_plan_only(muon_ctx** out, const muon_param* shapes, int32_t n, int32_t 
  * {matrix index in the list, first row, first column, rows, columns (in elements), number of 32 x 32 blocks of the
  * tile that are computed}, in launch order, and returns the number of records of the table (which may exceed
  * cap_records) or a negative status.  The block count is rows * columns / 1024 except for the 256 x 256 tiles on the
- * diagonal of a symmetric product in plain bf16, which are computed from the 36 blocks of their upper triangle.  Gram and polynomial tables
+ * diagonal of a symmetric product in plain bf16, which are computed from the 36 blocks of their upper triangle.  With
+ * several planes the entries of the coarse launch are run as 128 x 128 blocks: those below the diagonal and those a
+ * neighbouring strip tile covers as well are counted here but not computed.  Gram and polynomial tables
  * hold tiles on and above the diagonal of the m_pad x m_pad output; apply tables hold the tiles of X'^T
  * (n_pad x m_pad) on the matrix-core paths and of X' (m_pad x n_pad) on the fp32 path.  The last 512 x 128 tile of
  * a strip is shifted to end at the matrix edge and may overlap its neighbour (both then write the same values).

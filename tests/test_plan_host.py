@@ -430,3 +430,28 @@ def test_planes_move_a_tail_only_where_it_runs_in_quarters(ns, count, coarse, fi
 def test_norm_is_folded_up_to_four_partials_per_thread(ns, shapes, fold):
     from tests.plan_routes import routes
     assert routes(shapes, ns)[1] == fold
+
+
+def test_bench_counts_the_plane_pairs_that_are_multiplied():
+    """Two planes: three products a block, and the polynomial's fourth over the whole of K in fine tiles, over the block's own rows
+    and columns in coarse ones, whose blocks below the diagonal and in two strips count once.  Three planes: six products."""
+    import bench
+    from paper_2502_16982_amd import workloads
+    block = 2 * 128 * 128
+
+    def count(shapes, ns):
+        return bench.executed_ns_flops(workloads.custom("count", shapes, ns_dtype=ns), 1, ns)
+
+    def sides(s):
+        return s * (s + 1) // 2
+
+    # 1024 x 1280, all fine: 36 blocks on and above the diagonal, 80 of X'^T
+    assert count([(1024, 1280)], "bf16x2") == block * (36 * (3 * 1280 + 4 * 1024) + 80 * 3 * 1024)
+    assert count([(1024, 1280)], "bf16x3") == block * 6 * (36 * (1280 + 1024) + 80 * 1024)
+    # 4096^2 and, with strips, two of 3200 x 3328, all coarse
+    for m, n, copies in ((4096, 4096, 1), (3200, 3328, 2)):
+        tm, tn = m // 128, n // 128
+        gram, apply = sides(tm) * n, tm * tn * m
+        assert count([(m, n)] * copies, "bf16x3") == copies * block * 6 * (gram + sides(tm) * m + apply)
+        own = tm * 128 + (sides(tm) - tm) * 256
+        assert count([(m, n)] * copies, "bf16x2") == copies * block * (3 * (gram + sides(tm) * m + apply) + own)
