@@ -467,11 +467,11 @@ __device__ __forceinline__ void apply_tile(const MatDesc& d, const MatPtrs& pt, 
   if (tid == 0) d.partials[tr * d.ew_tiles_c + tc] = total;
 }
 
-template <typename XT, int PL, bool STREAM>
+template <typename XT, int PL>
 __global__ __launch_bounds__(256) void apply_update_kernel(const MatDesc* __restrict__ mats, const MatPtrs* __restrict__ ptrs,
                                                             const EwTile* __restrict__ tiles, float lr, float wd,
                                                             float rms_scale, int scale_mode, float sqrt_hidden, int o_sel,
-                                                            int use_s) {
+                                                            int use_s, int stream_w) {
   __shared__ float red[4];
   const EwTile t = load_item(tiles);
   const MatDesc& d = mats[t.mat];       // read in place (uniform address: scalar loads); see o_source
@@ -486,10 +486,12 @@ __global__ __launch_bounds__(256) void apply_update_kernel(const MatDesc* __rest
   }
   for (int k = 0; k < t.count; ++k) {
     if (k) __syncthreads();     // the reduction scratch is reused
-    if (d.w_dtype == kDtypeBF16)
-      apply_tile<u16, XT, PL, true, STREAM>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
+    if (d.w_dtype != kDtypeBF16)
+      apply_tile<float, XT, PL, true, true>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
+    else if (stream_w)
+      apply_tile<u16, XT, PL, true, true>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
     else
-      apply_tile<float, XT, PL, true, STREAM>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
+      apply_tile<u16, XT, PL, true, false>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
   }
 }
 
@@ -576,12 +578,8 @@ hipError_t launch_apply_update(const MatDesc* mats, const MatPtrs* ptrs, const E
                                float rms_scale, int scale_mode, float sqrt_hidden, int o_sel, int use_s, int stream_w,
                                int ns_dtype, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-#define MUON_CALL(XT, PL)                                                                                                          \
-  if (stream_w)                                                                                                                    \
-    apply_update_kernel<XT, PL, true><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, lr, wd, rms_scale, scale_mode, sqrt_hidden, o_sel, \
-                                                              use_s);                                                              \
-  else                                                                                                                             \
-    apply_update_kernel<XT, PL, false><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, lr, wd, rms_scale, scale_mode, sqrt_hidden, o_sel, use_s)
+#define MUON_CALL(XT, PL) \
+  apply_update_kernel<XT, PL><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, lr, wd, rms_scale, scale_mode, sqrt_hidden, o_sel, use_s, stream_w)
   MUON_NS_DISPATCH(ns_dtype, MUON_CALL)
 #undef MUON_CALL
   return hipGetLastError();
