@@ -6,9 +6,10 @@
 // one plane of one piece, L and R rows together; units come plane 0, 1, .. of a piece, then the next piece.  A wave keeps the
 // fragments of the planes it has read until the piece is done, and unit q adds the pairs whose larger plane is q: (0,0); then
 // (1,0), (0,1) and with three planes (1,1); then (2,0), (0,2).  So every plane passes through the memory path and the LDS
-// once per piece: 4 operand panels against 6 in a loop over the pairs (PL = 2), 6 against 12 (PL = 3).  That is what bounds
-// these launches, and through the power it takes the long ones too: a 64-wide wave tile reads 128 B of LDS per clock of MFMAs
-// in a loop over pairs, the whole rate of a compute unit, 85 and 64 B here.
+// once per piece: 4 operand panels against 6 in a loop over the pairs (PL = 2), 6 against 12 (PL = 3), and a 64-wide wave tile
+// reads 85 and 64 B of LDS per clock of MFMAs instead of 128.  What bounds the launches now, in shares of the cycles in which a
+// compute unit has work, matrix cores / LDS reads: width-1024 layer with two planes, Gram product in 64-wide tiles 0.51 / 0.36, apply
+// product in 128-wide ones 0.63 / 0.27; coarse tables of the 4096-wide block 0.74 to 0.75 / 0.27, which is power.
 // The LDS is a ring of NST units, requested as early as a stage is free and waited for with a partial s_waitcnt vmcnt; the
 // next unit's fragments are read while this one is multiplied; one barrier per unit.  The addend's planes come through the
 // same ring behind the last unit.  BT = 64: three stages, or four where a launch leaves a block alone on its compute unit: one

@@ -71,7 +71,8 @@ void strip_tiles(int32_t prob, int rows, int col0, std::vector<GemmTile>& out, s
 // problems that come last in the launch order - and handed to the fine launch, four 128 x 128 tiles each, where they
 // run side by side, one per compute unit.  With several planes no launch is persistent, and what the moved tiles gain is that
 // they run as 64 x 64 blocks: `most` is then what a launch in quarters holds (2 of 4096^2, 16 tiles, 7590 / 7510 us without / with
-// the move, three planes 13550 / 13300; but 16 of 2048 x 8192, whose 64 would run 128 wide again, 24910 / 25350).
+// the move, three planes 13550 / 13300; apply product of 2 of 2560 x 3328, 4 tiles, 2585 / 2504 and 4374 / 4260; but 16 of 2048 x
+// 8192, whose 64 would run 128 wide again, 24910 / 25350).
 // `moved` receives them per problem; returns how many were moved.
 constexpr int kMaxMovedTiles = 64;
 size_t move_tail_to_fine(const std::vector<int>& order, std::vector<std::vector<GemmTile>>& lists,

@@ -199,7 +199,7 @@ def test_split_large_tiles_and_strips(dev, ns):
     assert U.coarse_tiles(shapes, ns) == [0, 0]
     wl = workloads.custom("tiles_" + ns, shapes, ns_dtype=ns, seed_base=52)
     assert_records(U.run_and_compare(wl, dev, steps=2), U.TOL_SPLIT_FRO[ns])
-    # 256-wide tiles and 512 x 128 strips, and a small matrix in the fine launch beside them
+    # coarse entries, 256 x 256 and 512 x 128 strips, and a small matrix in the fine launch beside them
     shapes = [(3200, 3200), (200, 333), (3328, 3200)]
     assert min(U.coarse_tiles(shapes, ns)) > 0
     wl = workloads.custom("large_" + ns, shapes, ns_dtype=ns, seed_base=59)

@@ -61,7 +61,7 @@ def test_block_w4096_full_two_planes(dev):
 @pytest.mark.parametrize("ns", ["bf16x2", "bf16x3"])
 def test_moe_expert_shapes_split(dev, ns):
     """One expert's three matrices at their real shape (m = 1408, both orientations), and a list of 16 experts.  With planes
-    neither is computed in 256-wide tiles: at this side their epilogue does not pay."""
+    neither has a coarse launch."""
     one = [(2048, 1408), (2048, 1408), (1408, 2048)]
     assert U.coarse_tiles(one, ns) == [0, 0] and U.coarse_tiles(one * 16, ns) == [0, 0]
     wl = workloads.custom("expert_" + ns, one, ns_dtype=ns, seed_base=4100)
