@@ -784,8 +784,8 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         }
         ts.long_n = !mc && hi_n > kF32LongK;
         ts.long_m = !mc && hi_m > kF32LongK;
-        ts.persistent_n = steady_n;
-        ts.persistent_m = steady_m;
+        ts.persistent_n = planes == 1 && steady_n;
+        ts.persistent_m = planes == 1 && steady_m;
         ts.sym = take(n_sym * sizeof(GemmTile));
         ts.poly = take(n_sym * sizeof(GemmTile));
         ts.apply = take(n_app * sizeof(GemmTile));      // the last iteration runs the same tiles: only its outputs differ

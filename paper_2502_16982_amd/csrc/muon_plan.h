@@ -33,7 +33,7 @@ struct TileSet {
   int n_sym = 0, n_poly = 0, n_apply = 0;
   bool strips = false;    // the tables hold 512 x 128 tiles (the launch then needs the larger LDS allocation)
   // the K loops of the launch's tiles are of nearly the same length (Gram product: n_pad; the other two: m_pad), so
-  // the launch runs persistent blocks that take the planner's static assignment of tiles
+  // the launch, in plain bf16, runs persistent blocks that take the planner's static assignment of tiles
   bool persistent_n = false, persistent_m = false;
   bool long_n = false, long_m = false;    // fp32: some K (Gram product: n_pad; the other two: m_pad) is over kF32LongK
   bool quarter_sym = false, quarter_poly = false, quarter_apply = false;   // fine launches that run as one block per quarter of an entry
@@ -43,7 +43,8 @@ struct TileSet {
 // Launch group: all matrices of one chunk.  Each product is one launch per level: the coarse launch (matrix-core
 // paths only) runs 256 x 256 tiles over the part of every output that whole such tiles cover plus 512 x 128 tiles
 // over the 128-wide column strip an odd multiple of 128 leaves; the fine launch (128 x 128 bf16, 64 x 64 fp32) takes
-// what remains, so that nothing is padded beyond the fine tile.  A product whose coarse launch would leave much of the
+// what remains, so that nothing is padded beyond the fine tile.  (With several planes entries of the coarse tables run as four
+// 128 x 128 blocks.)  A product whose coarse launch would leave much of the
 // chip idle has no coarse launch: all its tiles are fine.
 struct Group {
   int n_prob = 0;
