@@ -341,7 +341,8 @@ __device__ __forceinline__ const void* o_source(const MatDesc& d, int o_sel) {
 // 0.81 GB of W and O on the 4096-wide block, 0.89 GB with the hint).  The hint leaves more of the caches to the next step's
 // momentum pass (50 of 2048 x 1408: update 164 us with it, 160 without, momentum 319 and 343).  Long lists whose
 // rows do not end on whole lines take W without it (STREAM = false): a line written in two pieces leaves the caches between
-// them.  Step of 50 of 2047 x 1401 4881 us with the hint on W, 4700 without, of 2048 x 1400 4806 / 4676.
+// them.  Step of 50 of 2047 x 1401 4881 us with the hint on W, 4700 without, of 2048 x 1400 4806 / 4676.  (Kernels of their own: with
+// both bodies in one and the hint as an argument short lists' updates took 0.7 us longer, 36 of up to 3456 columns 8.3 / 9.0.)
 template <bool STREAM = true>
 __device__ __forceinline__ void load8(const float* p, float* out) {
 #pragma unroll
@@ -467,11 +468,11 @@ __device__ __forceinline__ void apply_tile(const MatDesc& d, const MatPtrs& pt, 
   if (tid == 0) d.partials[tr * d.ew_tiles_c + tc] = total;
 }
 
-template <typename XT, int PL>
+template <typename XT, int PL, bool STREAM>
 __global__ __launch_bounds__(256) void apply_update_kernel(const MatDesc* __restrict__ mats, const MatPtrs* __restrict__ ptrs,
                                                             const EwTile* __restrict__ tiles, float lr, float wd,
                                                             float rms_scale, int scale_mode, float sqrt_hidden, int o_sel,
-                                                            int use_s, int stream_w) {
+                                                            int use_s) {
   __shared__ float red[4];
   const EwTile t = load_item(tiles);
   const MatDesc& d = mats[t.mat];       // read in place (uniform address: scalar loads); see o_source
@@ -486,12 +487,10 @@ __global__ __launch_bounds__(256) void apply_update_kernel(const MatDesc* __rest
   }
   for (int k = 0; k < t.count; ++k) {
     if (k) __syncthreads();     // the reduction scratch is reused
-    if (d.w_dtype != kDtypeBF16)
-      apply_tile<float, XT, PL, true, true>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
-    else if (stream_w)
-      apply_tile<u16, XT, PL, true, true>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
+    if (d.w_dtype == kDtypeBF16)
+      apply_tile<u16, XT, PL, true, STREAM>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
     else
-      apply_tile<u16, XT, PL, true, false>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
+      apply_tile<float, XT, PL, true, STREAM>(d, pt, t.tr, t.tc + k, lr, wd, scale, o_sel, red);
   }
 }
 
@@ -578,8 +577,12 @@ hipError_t launch_apply_update(const MatDesc* mats, const MatPtrs* ptrs, const E
                                float rms_scale, int scale_mode, float sqrt_hidden, int o_sel, int use_s, int stream_w,
                                int ns_dtype, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-#define MUON_CALL(XT, PL) \
-  apply_update_kernel<XT, PL><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, lr, wd, rms_scale, scale_mode, sqrt_hidden, o_sel, use_s, stream_w)
+#define MUON_CALL(XT, PL)                                                                                                          \
+  if (stream_w)                                                                                                                    \
+    apply_update_kernel<XT, PL, true><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, lr, wd, rms_scale, scale_mode, sqrt_hidden, o_sel, \
+                                                              use_s);                                                              \
+  else                                                                                                                             \
+    apply_update_kernel<XT, PL, false><<<n_tiles, 256, 0, s>>>(mats, ptrs, tiles, lr, wd, rms_scale, scale_mode, sqrt_hidden, o_sel, use_s)
   MUON_NS_DISPATCH(ns_dtype, MUON_CALL)
 #undef MUON_CALL
   return hipGetLastError();
