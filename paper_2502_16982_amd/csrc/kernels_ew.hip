@@ -342,7 +342,7 @@ __device__ __forceinline__ const void* o_source(const MatDesc& d, int o_sel) {
 // momentum pass (50 of 2048 x 1408: update 164 us with it, 160 without, momentum 319 and 343).  Long lists whose
 // rows do not end on whole lines take W without it (STREAM = false): a line written in two pieces leaves the caches between
 // them.  Step of 50 of 2047 x 1401 4881 us with the hint on W, 4700 without, of 2048 x 1400 4806 / 4676.  (Kernels of their own: with
-// both bodies in one and the hint as an argument short lists' updates took 0.7 us longer, 36 of up to 3456 columns 8.3 / 9.0.)
+// both bodies in one and the hint as an argument short lists' updates took 0.7 us longer, 43 of up to 3840 columns 8.3 / 9.0.)
 template <bool STREAM = true>
 __device__ __forceinline__ void load8(const float* p, float* out) {
 #pragma unroll

@@ -287,53 +287,69 @@ bool few_coarse_apply(const CoarseLoad& c, int planes, int blocks) {
 // 256 (apply products of 1024^2, of 4 of 512^2) 327 / 314, 215 / 207, 288 (8 of 512^2) 315 / 351; earlier, us per launch, apply
 // product of 64 of 128 x 256 (512) 17.7 / 13.6, Gram product of 16 of 512^2 (576) 34.4 / 34.1.
 constexpr int kFewFine = 176, kFewF32 = 180, kLittleOverF32 = 64;
-// Planes: 64-wide blocks pay while all of them have a place at the same time, three on a compute unit with two planes and two
-// with three, and again where 128-wide ones would leave their last round badly filled, the sooner the shorter K.  us per
-// launch, 128 / 64.  Two planes, up to 192 entries and from 256 to 320 with K up to 2048: 90 entries of K = 256 15.6 /
-// 10.8, 144 of 1024 33.8 / 29.9, 156 of 6144 136 / 123, 180 of 512 19.8 / 19.2, of 4096 126 / 100, 189 of 768 25.9 / 23.2; but 195 of 640
-// 26.7 / 27.2, of 1408 38.9 / 42.2, 200 of 512 20.0 / 22.0, of 2048 52.6 / 56.7, 240 of 256 18.5 / 18.8, of 512 20.8 / 23.5; 260 of 2048
-// 72.5 / 68.1, 288 of 1024 54.1 / 47.4, 300 of 512 34.7 / 29.2, of 1408 56.0 / 50.9, of 2048 82.3 / 81.9, 320 of 512 27.8 / 26.2; but 288
-// of 4096 136 / 143, 312 of 6144 204 / 258; 324 of 768 36.4 / 38.3, 360 of 256 20.7 / 21.4, 384 of 1024 45.9 / 49.3.
+// Planes: 64-wide blocks pay while all of them have a place at the same time (three on a compute unit with two planes, two
+// with three), and again where 128-wide ones would leave their last round badly filled, the sooner the shorter K.  us per
+// launch, 128 / 64, entries (work) of the longest K.
+// Two planes, up to 192 and from 257 to 320 with K up to 2048, with K = 256 and less all the way; mixed lists whose count (above
+// K = 512) or work with a block's fixed cost stays near that, too: 90 of 256 15.6 / 10.8, 144 of 1024
+// 33.8 / 29.9, 156 of 6144 136 / 123, 180 of 512 19.8 / 19.2, of 4096 126 / 100, 189 of 768 25.9 / 23.2; 213 of 128 12.0 / 11.1, 240 of 256 18.5 /
+// 18.8, 251 of 128 12.4 / 11.4, 316 (210) of 256 16.5 / 15.8; 260 of 2048 72.5 / 68.1, 272 of 128 14.0 / 12.7, 288 of 1024 54.1 / 47.4, 300 of
+// 512 34.7 / 29.2, of 1408 56.0 / 50.9, of 2048 82.3 / 81.9, 320 of 512 27.8 / 26.2; but 195 of 640 26.7 / 27.2, of 1408 38.9 / 42.2, 200 of 512
+// 20.0 / 22.0, of 2048 52.6 / 56.7, 240 of 512 20.8 / 23.5, 323 (232) of 640 25.9 / 29.0; 288 of 4096 136 / 143, 312 of 6144 204 / 258; 324 of
+// 768 36.4 / 38.3, 360 of 256 20.7 / 21.4, 384 of 1024 45.9 / 49.3, 481 (343) of 384 21.9 / 26.2.  Mixed, (work, with 512 of fixed
+// cost): 348 (296, 325) of 384 22.1 / 20.7, 333 (276, 308) of 384 25.1 / 24.1; but 477 (310, 393) of 512 a step of 529 / 536, 335 (300) of
+// 768 34.2 / 36.6, 408 (274) of 640 a step of 346 / 367.
 // Three planes: 72 of 256 20.9 / 12.4, 108 of 4096 121 / 88, 120 of 512 26.3 / 20.3, 126 of 3072 97 / 72; 144 of 1024 41.8 / 39.9, 168 of 768
-// 36.2 / 32.7, 190 of 128 17.5 / 15.5, 195 of 384 26.4 / 25.8; but 140 of 4096 131 / 137, 156 of 1536 55.8 / 61.5, 180 of 1024 44.1 /
-// 45.9, 200 of 512 30.7 / 30.3.  Beyond one round, by its fill: 272 of 512 50.5 / 38.3, 600 of 512 (0.78) 78 / 76, 570 of 256 57 / 46, 810 of
-// 128 (0.79) 58 / 43, 420 of 768 (0.82) 74 / 67; 360 of 1024 (0.70) 84 / 77, 576 of 1024 (0.75) 127 / 115; 272 of 2048 (0.53) 135 / 113, 312
-// of 1536 (0.61) 108 / 96; 288 of 4096 (0.56) 256 / 238, 272 of 8192 490 / 474; but 432 of 1024 (0.84) 85 / 90, 840 of 768 (0.82) 136 / 145,
-// 360 of 2048 (0.70) 139 / 145, 420 of 2560 (0.82) 177 / 211, 390 of 6144 (0.76) 407 / 537, 324 of 8192 (0.63) 506 / 578, 300 of 4096 (0.59) 264
-// / 275; 1080 of 1024 (0.84) 204 / 230, 1300 of 512 (0.85) 147 / 166.
-constexpr int64_t kLongKPlanes2 = 2048, kMostFine3 = 1024;
+// 36.2 / 32.7, 195 of 384 26.4 / 25.8, 204 of 128 17.1 / 14.7, 251 of 128 17.1 / 15.5, 512 of 128 30.1 / 25.2, 626 (583) of 256 58.2 / 45.1, 875 (837)
+// of 256 72.7 / 56.8; but 140 of 4096 131 / 137, 156 of 1536 55.8 / 61.5, 180 of 1024 44.1 / 45.9, 200 of 512 30.7 / 30.3, 255 of 384 26.5 / 27.2.
+// Beyond one round, by its fill: 272 of 512 50.5 / 38.3, 600 of 512 (0.78) 78 / 76, 420 of 768 (0.82) 74 / 67; 360 of 1024 (0.70) 84 / 77, 576
+// of 1024 (0.75) 127 / 115; 272 of 2048 (0.53) 135 / 113, 312 of 1536 (0.61) 108 / 96; 288 of 4096 (0.56) 256 / 238, 272 of 8192 490 / 474; but 432
+// of 1024 (0.84) 85 / 90, 840 of 768 (0.82) 136 / 145, 360 of 2048 (0.70) 139 / 145, 420 of 2560 (0.82) 177 / 211, 390 of 6144 (0.76) 407 / 537,
+// 324 of 8192 (0.63) 506 / 578, 300 of 4096 (0.59) 264 / 275; 1080 of 1024 (0.84) 204 / 230, of 384 (0.84) 114 / 121, 1300 of 512 (0.85) 147 / 166.
+// Where K is mixed a round is also counted with what a block costs beside its K, about 512 of it: 323 entries, the work of 232 of 640,
+// 272 so, 48.6 / 42.4; 333 (247, 281) of 768 52.8 / 45.7; but 260 (223, 237) of 768 38.0 / 42.3.
+constexpr int64_t kLongKPlanes2 = 2048, kShortKPlanes2 = 256, kMixedKPlanes2 = 512, kMostFine3 = 1024, kBlockK = 512;
 struct Fine3 {
   int64_t k;        // longest K
   int entries;      // of a launch in quarters within one round of 256 compute units
   int fill;         // per cent of the last round
 };
-constexpr Fine3 kFine3[] = {{768, 200, 85}, {1024, 150, 80}, {2048, 128, 65}, {INT64_MAX, 128, 57}};
+constexpr Fine3 kFine3[] = {{256, (int)kMostFine3, 100}, {768, 200, 85}, {1024, 150, 80}, {2048, 128, 65}, {INT64_MAX, 128, 57}};
 // entries whose 64-wide blocks all have a place at the same time
 int lone_entries(int planes, int blocks) { return planes == 2 ? 3 * blocks / 4 : blocks / 2; }
-// a launch's work in entries of its longest K
-int64_t entries_of_work(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k) {
+// a launch's work in entries of its longest K; `fixed`: what an entry costs beside its K
+int64_t entries_of_work(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int64_t fixed = 0) {
   int64_t longest = 1, total = 0;
   for (size_t i = 0; i < tiles.size(); ++i)
     if (!tiles[i].empty()) {
-      longest = std::max(longest, k[i]);
-      total += k[i] * (int64_t)tiles[i].size();
+      longest = std::max(longest, k[i] + fixed);
+      total += (k[i] + fixed) * (int64_t)tiles[i].size();
     }
   return (total + longest - 1) / longest;
 }
 bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, bool mc, int planes, int blocks) {
   const int64_t entries = entries_of_work(tiles, k);
-  int64_t longest = 0;
+  int64_t longest = 0, count = 0;
   for (size_t i = 0; i < tiles.size(); ++i)
-    if (!tiles[i].empty()) longest = std::max(longest, k[i]);
+    if (!tiles[i].empty()) {
+      longest = std::max(longest, k[i]);
+      count += (int64_t)tiles[i].size();
+    }
   const int64_t b = std::max(blocks, 1);
-  if (mc && planes == 2)
-    return entries <= lone_entries(2, blocks) || (entries > b && 4 * entries <= 5 * b && longest <= kLongKPlanes2);
+  if (mc && planes == 2) {
+    if (entries <= lone_entries(2, blocks)) return true;
+    if (4 * entries > 5 * b || longest > (entries > b ? kLongKPlanes2 : kShortKPlanes2)) return false;
+    return longest <= kMixedKPlanes2 ? 3 * entries_of_work(tiles, k, kBlockK) <= 4 * b : 4 * count <= 5 * b;
+  }
   if (mc && planes == 3) {
     const Fine3* f = kFine3;
     while (longest > f->k) ++f;
     if (entries <= f->entries * b / 256) return true;
-    const int64_t rounds = (entries + b - 1) / b;
-    return rounds > 1 && entries <= kMostFine3 && 100 * entries < f->fill * rounds * b;
+    for (int64_t e : {entries, entries_of_work(tiles, k, kBlockK)}) {
+      const int64_t rounds = (e + b - 1) / b;
+      if (rounds > 1 && e <= kMostFine3 && 100 * e < f->fill * rounds * b) return true;
+    }
+    return false;
   }
   if (mc) return entries <= kFewFine;
   return entries <= kFewF32 || (entries > blocks && entries <= blocks + kLittleOverF32);
@@ -342,18 +358,20 @@ bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std
 // Launches in quarters that leave most compute units with one block or none: 2 = each 32 x 32 as one wave of its
 // own (shortest chain of slabs; twice the operand traffic), 1 = 64 x 64 blocks with a ring of four slabs (two blocks on a
 // compute unit instead of three), 0 = with a ring of three.
-// Plain bf16, waves for the fewest entries, with K up to 512 a few more, us per step, 0 / 1 / 2: 256^2 (3 and 4 entries) 58.5 / 57.4 /
+// Plain bf16, waves for the fewest entries, with K up to 1024 a few more, us per step, 0 / 1 / 2: 256^2 (3 and 4 entries) 58.5 / 57.4 /
 // 51.8, 512^2 (10, 16) 78.0 / 73.4 / 68.3, 2 of 512^2 (20, 32) 81.4 / 78.7 / 77.1, 63 x 4097 (1, 33) 135.7 / 115.4 / 112.9; per launch 27
-// entries of K = 384 6.6 / 6.6 / 6.4, 36 of 1024 9.9 / 9.4 / 9.7, of 4096 21.7 / 18.4 / 21.9, 40 of 512 7.0 / 7.1 / 7.9.
+// entries of K = 384 6.6 / 6.6 / 6.4, 25 of 768 (the work of 22) a step of 143.9 / 142.1 for 1 / 2, 36 of 1024 9.9 / 9.4 / 9.7 (even in the
+// step: 112.5 / 112.9), of 4096 21.7 / 18.4 / 21.9, 40 of 512 7.0 / 7.1 / 7.9.
 // The longer ring goes by the work: entries that have a compute unit to themselves, or a few long ones among short ones.  us per launch,
 // 0 / 1: 60 entries of 512 8.3 / 8.0, 63 of 768 9.9 / 9.6; 72 of 1024 11.0 / 11.3, 80 of 512 8.0 / 8.5, 100 8.8 / 9.1, 140 11.3 / 11.9; lists
 // that mix K, work in brackets: 130 (67) 24.4 / 23.3, 133 (66) 25.9 / 22.7, 128 (61) 24.7 / 22.4, 112 (50) 23.0 / 20.6, 100 (62) 95.7 /
 // 72.8, 96 (42) 26.2 / 21.4, 80 (26) 22.1 / 18.5, 45 (14) 36.2 / 26.6.
 // Planes, 0 / 1, two and three: 40 of 512 9.8 / 9.8 and 12.3 / 11.8, 36 of 4096 36.6 / 30.1 and 50.8 / 45.7, 63 of 768 12.8 / 12.2 and 17.1 /
 // 16.8; 70 of 512 12.8 / 12.6 and 17.6 / 18.1, 72 of 1024 17.4 / 17.8 and 25.5 / 26.4, 100 of 512 13.5 / 13.7 and 18.7 / 19.1; mixed 80 (22)
-// 36.6 / 30.9 and 51.6 / 46.3, 66 (40) 37.0 / 33.0 and 52.3 / 48.8, 70 (44) 18.0 / 17.3 and 24.9 / 25.7, 66 (46) 29.0 / 26.8 and 40.4 / 41.9.
+// 36.6 / 30.9 and 51.6 / 46.3, 66 (40) 37.0 / 33.0 and 52.3 / 48.8, 70 (44) 18.0 / 17.3 and 24.9 / 25.7, 66 (46) 29.0 / 26.8 and 40.4 / 41.9
+// (two planes up to 51, three up to 40).
 constexpr size_t kFewest = 24, kFewestShort = 36;
-constexpr int64_t kShortK = 512;
+constexpr int64_t kShortK = 1024;
 int few_blocks(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int planes, int blocks) {
   size_t n = 0;
   int64_t longest = 0;
@@ -364,7 +382,7 @@ int few_blocks(const std::vector<std::vector<GemmTile>>& tiles, const std::vecto
     }
   if (planes == 1 && (n <= kFewest || (n <= kFewestShort && longest <= kShortK))) return 2;
   const int64_t work = entries_of_work(tiles, k), b = std::max(blocks, 1);
-  if (planes > 1) return 4 * (int64_t)n <= b || 6 * work <= b ? 1 : 0;
+  if (planes > 1) return 4 * (int64_t)n <= b || (planes == 2 ? 5 * work <= b : 32 * work <= 5 * b) ? 1 : 0;
   return 4 * work <= b + b / 16 ? 1 : 0;
 }
 

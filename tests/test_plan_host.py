@@ -361,10 +361,11 @@ def test_one_more_matrix_does_not_move_all_the_others():
 
 
 @pytest.mark.parametrize("ns,shapes,forms", [
-    # plain bf16: waves up to 24 entries, up to 36 with K <= 512; the longer ring by the work, entries of the longest K
+    # plain bf16: waves up to 24 entries, up to 36 with K <= 1024; the longer ring by the work, entries of the longest K
     ("bf16", [(512, 512)] * 2, ["waves", "waves", "waves"]),                      # 20, 20, 32 of K = 512
     ("bf16", [(512, 640)] * 2, ["waves", "waves", "ring4"]),                      # apply: 40
-    ("bf16", [(640, 640)] * 2, ["ring4", "ring4", "ring4"]),                      # 30, 30, 50 of K = 640
+    ("bf16", [(640, 1024)] * 2, ["waves", "waves", "quarters"]),                  # 30, 30 of K = 1024 and 640; apply: 80
+    ("bf16", [(640, 1152)] * 2, ["ring4", "waves", "quarters"]),
     ("bf16", [(128, 300)] * 36, ["waves", "waves", "quarters"]),
     ("bf16", [(128, 300)] * 37, ["ring4", "ring4", "quarters"]),
     ("bf16", [(128, 300)] * 68, ["ring4", "ring4", "whole"]),
@@ -373,32 +374,51 @@ def test_one_more_matrix_does_not_move_all_the_others():
     ("bf16", [(1000, 3001)] * 2 + [(777, 777)] * 2 + [(63, 4097)] * 2, ["ring4", "quarters", "whole"]),    # 130, of 67
     # two planes: up to three quarters of the compute units, and a little more than all of them up to K = 2048
     ("bf16x2", [(128, 300)] * 64, ["ring4", "ring4", "quarters"]),
-    ("bf16x2", [(128, 300)] * 65, ["quarters", "quarters", "whole"]),             # apply: 195
-    ("bf16x2", [(300, 700)] * 6 + [(700, 300)] * 6 + [(128, 4096)] * 8, ["ring4", "quarters", "quarters"]),  # 80 entries, the work of 22; apply: of 302
-    ("bf16x2", [(128, 900)] * 192, ["quarters", "quarters", "whole"]),
-    ("bf16x2", [(128, 900)] * 193, ["whole", "whole", "whole"]),
-    ("bf16x2", [(128, 128)] * 256, ["whole", "whole", "whole"]),
-    ("bf16x2", [(128, 128)] * 257, ["quarters", "quarters", "quarters"]),
+    ("bf16x2", [(128, 300)] * 65, ["quarters", "quarters", "quarters"]),
+    # Gram product: 80 entries, the work of 22; apply: 472, the work of 302, with a block's fixed cost of 399; 344, of 259 and 308
+    ("bf16x2", [(300, 700)] * 6 + [(700, 300)] * 6 + [(128, 4096)] * 8, ["ring4", "quarters", "whole"]),
+    ("bf16x2", [(300, 700)] * 6 + [(700, 300)] * 6 + [(128, 2048)] * 8, ["ring4", "quarters", "quarters"]),
+    ("bf16x2", [(128, 384)] * 192, ["quarters", "quarters", "whole"]),
+    ("bf16x2", [(128, 384)] * 193, ["whole", "quarters", "whole"]),
+    ("bf16x2", [(128, 384)] * 257, ["quarters", "quarters", "whole"]),
+    ("bf16x2", [(128, 256)] * 256, ["quarters", "quarters", "whole"]),
+    ("bf16x2", [(128, 256)] * 160, ["quarters", "quarters", "quarters"]),
+    ("bf16x2", [(128, 256)] * 161, ["quarters", "quarters", "whole"]),
     ("bf16x2", [(128, 128)] * 320, ["quarters", "quarters", "quarters"]),
     ("bf16x2", [(128, 128)] * 321, ["whole", "whole", "whole"]),
     ("bf16x2", [(128, 2048)] * 300, ["quarters", "quarters", "whole"]),
     ("bf16x2", [(128, 2176)] * 300, ["whole", "quarters", "whole"]),
+    # apply product, entries of a longer K and of K = 128: 270 and 72, the work of 294 of 384 (322); 240 and 168, of 296 (360), and of
+    # 274 of 640
+    ("bf16x2", [(384, 640)] * 18 + [(16, 768)] * 12, ["quarters", "quarters", "quarters"]),
+    ("bf16x2", [(592, 384)] * 16 + [(16, 768)] * 28, ["quarters", "quarters", "whole"]),
+    ("bf16x2", [(1984, 592)] * 3 + [(16, 768)] * 28, ["quarters", "ring4", "whole"]),
+    # the longer ring by work: two planes up to 51, three up to 40
+    ("bf16x2", [(250, 2048)] * 17 + [(16, 128)] * 14, ["quarters", "quarters", "whole"]),
+    ("bf16x2", [(250, 2048)] * 16 + [(16, 128)] * 48, ["ring4", "quarters", "whole"]),
+    ("bf16x3", [(250, 2048)] * 13 + [(16, 128)] * 32, ["quarters", "quarters", "quarters"]),
+    ("bf16x3", [(250, 2048)] * 12 + [(16, 128)] * 64, ["ring4", "quarters", "quarters"]),
     # three planes: half of the compute units, more with a short K; a badly filled last round, by K
-    ("bf16x3", [(128, 128)] * 200, ["quarters"] * 3),
-    ("bf16x3", [(128, 128)] * 201, ["whole"] * 3),
+    ("bf16x3", [(128, 256)] * 512, ["quarters"] * 3),                             # full rounds of K = 128 and 256
+    ("bf16x3", [(128, 256)] * 513, ["quarters", "quarters", "whole"]),            # apply: 1026, more than 1024
+    ("bf16x3", [(128, 384)] * 200, ["quarters"] * 3),
+    ("bf16x3", [(128, 384)] * 201, ["whole", "quarters", "quarters"]),
+    ("bf16x3", [(128, 384)] * 435, ["quarters", "quarters", "whole"]),            # Gram product: 0.8496 of two rounds
+    ("bf16x3", [(128, 384)] * 436, ["whole", "quarters", "whole"]),
     ("bf16x3", [(128, 896)] * 150, ["quarters", "quarters", "whole"]),
-    ("bf16x3", [(128, 896)] * 151, ["whole", "quarters", "whole"]),               # apply: 1057, more than 1024
+    ("bf16x3", [(128, 896)] * 151, ["whole", "quarters", "whole"]),
     ("bf16x3", [(128, 4096)] * 128, ["quarters", "quarters", "whole"]),
     ("bf16x3", [(128, 4096)] * 129, ["whole", "quarters", "whole"]),
-    ("bf16x3", [(128, 128)] * 257, ["quarters"] * 3),
-    ("bf16x3", [(128, 128)] * 435, ["quarters"] * 3),                             # 0.8496 of two rounds
-    ("bf16x3", [(128, 128)] * 436, ["whole"] * 3),
     ("bf16x3", [(128, 1024)] * 409, ["quarters", "quarters", "whole"]),
     ("bf16x3", [(128, 1024)] * 410, ["whole", "quarters", "whole"]),
     ("bf16x3", [(128, 2048)] * 332, ["quarters", "quarters", "whole"]),
     ("bf16x3", [(128, 2048)] * 333, ["whole", "quarters", "whole"]),
     ("bf16x3", [(128, 4096)] * 291, ["quarters", "quarters", "whole"]),
     ("bf16x3", [(128, 4096)] * 292, ["whole", "quarters", "whole"]),
+    # Gram product, K = 640 and 128: 215 and 108 entries, the work of 237, of 275 with a block's fixed cost: a second round, badly
+    # filled; 215 and 40 of 223 and 238: one round
+    ("bf16x3", [(128, 600)] * 215 + [(128, 128)] * 108, ["quarters", "quarters", "whole"]),
+    ("bf16x3", [(128, 600)] * 215 + [(128, 128)] * 40, ["whole", "quarters", "whole"]),
 ])
 def test_blocks_of_the_fine_launches(ns, shapes, forms):
     """The lines between 128-wide blocks, 64-wide ones with either ring and single waves."""
