@@ -19,7 +19,7 @@ SOURCES = ("muon_api.hip", "muon_plan.cpp", "kernels_ew.hip", "kernels_gemm_bf16
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
-    # packed-fp32 VALU forms are kept out of generated code on the test machines
+    # packed-fp32 VALU forms are kept out of generated code: some have given wrong results on this hardware
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # kernel arguments arrive in scalar registers with the wave instead of through a load it would start with: 0.25 to 0.3 us
     # of each dependent launch (step of one 128 x 256 matrix in fp32 64.3 -> 59.3 us, nine small matrices 107.9 -> 103.6)
