@@ -97,6 +97,31 @@ def executed_ns_flops(wl, ns_steps, ns_dtype="bf16"):
     return ns_steps * flops
 
 
+def issued_ns_flops(wl, ns_steps, ns_dtype="bf16"):
+    """What a step really issues: executed_ns_flops counts every product as Eq. 2 writes it; matrices of the Gram route run one
+    Gram and one apply product per group of two iterations (the last group of three where the number is odd) and 5 or 9
+    symmetric products of m x m."""
+    from paper_2502_16982_amd import binding
+    n = len(wl.shapes)
+    p = binding.param_array(wl.shapes, [1] * n, [1] * n)
+    ns = binding.NS_DTYPES[ns_dtype]
+    ctx = binding.muon_plan_only(p, n, ns, binding.muon_workspace_bytes(p, n, ns, 0))
+    try:
+        desc = [binding.muon_plan_describe(ctx, i) for i in range(n)]
+        total = executed_ns_flops(wl, ns_steps, ns_dtype)
+        if ns_steps < 4:
+            return total
+        groups, small = ns_steps // 2, 5 * (ns_steps // 2) + 4 * (ns_steps % 2)
+        for product, k_of, times in (("gram", "n_pad", groups), ("poly", "m_pad", small), ("apply", "m_pad", groups)):
+            for level in (0, 1):
+                for mat, _, _, _, _, blocks in binding.muon_plan_tiles(ctx, 0, product, level):
+                    if desc[mat]["gram_route"]:
+                        total += (times - ns_steps) * 2 * blocks * 1024 * desc[mat][k_of]
+    finally:
+        binding.muon_destroy(ctx)
+    return total
+
+
 def cpu_baseline(wl, budget_s=25.0):
     """Times the fp64 oracle (as it stands) on the host cores on a bounded sample of the workload."""
     import numpy as np
@@ -205,7 +230,7 @@ def time_workload(name, steps, warmup, max_ws_gib, dev, ns_dtype=None):
     gemm_launches = sum(prof[k][1] for k in ("gram", "poly", "apply_poly"))
     bf16 = wl.ns_dtype != "f32"              # the matrix-core paths: plain bf16 and the split forms
     planes = PLANES[wl.ns_dtype]
-    executed = executed_ns_flops(wl, h.ns_steps, wl.ns_dtype)
+    executed = issued_ns_flops(wl, h.ns_steps, wl.ns_dtype)
     peak = PEAK_BF16_TFLOPS if bf16 else PEAK_F32_VALU_TFLOPS
     if gemm_launches:
         avg_launch_ms = gemm_ms / gemm_launches

@@ -101,7 +101,10 @@ int muon_default_hparams(muon_hparams* hp);
  * null).  ns_dtype selects the Newton-Schulz arithmetic: MUON_BF16 (bf16 operands, fp32 accumulation;
  * section 2.3 notes bf16 suffices), MUON_F32 (fp32 matrix instructions; meant for small matrices), or the split
  * forms MUON_BF16X2 / MUON_BF16X3 (fp32-class accuracy on the matrix cores, the "more accurate"
- * direction of section 2.2 at model sizes).  The Newton-Schulz temporaries of all matrices are
+ * direction of section 2.2 at model sizes).  MUON_BF16 iterates wide matrices (min(rows, cols) of 384 and more, the other side
+ * 8 times as long, down to twice as long from 2560 on) on their Gram matrix, two or three iterations at a time and in f16 scaled by
+ * powers of two, where ns_steps is at least 4 and the coefficients keep everything in range: the same iteration, with a
+ * third to a half of the rounding error.  The Newton-Schulz temporaries of all matrices are
  * kept resident when they fit in `max_bytes`; otherwise the list is processed in consecutive chunks
  * that reuse the workspace.  max_bytes == 0 means "no limit".  *out receives the number of bytes to
  * allocate (256-byte aligned device memory); it is never below the minimum that muon_init accepts.
@@ -172,7 +175,8 @@ int muon_debug_read_update(muon_ctx* ctx, int32_t index, void* dst, int32_t dst_
 
 /*
  * Plan introspection (host only, no device work): writes up to `cap` int64 values describing matrix
- * `index`: {m, n, transposed, m_pad, n_pad, chunk, tile_m, tile_n}; tile_n is the side of the fine tile, tile_m
+ * `index`: {m, n, transposed, m_pad, n_pad, chunk, tile_m, tile_n, gram_route}; gram_route: 1 where MUON_BF16 iterates the
+ * matrix on its Gram matrix (see muon_workspace_bytes); tile_n is the side of the fine tile, tile_m
  * 256 where the plan computes some of the matrix's products in coarse tiles and tile_n where it does not.
  * Returns the number written or a negative status.
  */

@@ -219,11 +219,11 @@ def muon_debug_read_update(ctx, index: int, dst_ptr: int, dst_dtype: int, stream
 
 
 def muon_plan_describe(ctx, index: int) -> dict:
-    buf = (C.c_int64 * 8)()
-    k = lib().muon_plan_describe(ctx, index, buf, 8)
+    buf = (C.c_int64 * 9)()
+    k = lib().muon_plan_describe(ctx, index, buf, 9)
     if k < 0:
         raise MuonError(k, "muon_plan_describe")
-    keys = ("m", "n", "transposed", "m_pad", "n_pad", "chunk", "tile_m", "tile_n")
+    keys = ("m", "n", "transposed", "m_pad", "n_pad", "chunk", "tile_m", "tile_n", "gram_route")
     return dict(zip(keys, [int(v) for v in buf[:k]]))
 
 

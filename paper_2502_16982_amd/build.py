@@ -14,7 +14,7 @@ LIB_NAME = "libmuon_hip.so"
 LIB_PATH = os.path.join(PKG_DIR, LIB_NAME)
 MARSHAL_PATH = os.path.join(PKG_DIR, "_adamw_marshal.so")
 # the planner is plain C++ (it also builds with g++ alone, see tests/test_plan_sanitized.py); the rest is HIP
-SOURCES = ("muon_api.hip", "muon_plan.cpp", "kernels_ew.hip", "kernels_gemm_bf16.hip", "kernels_gemm_f32.hip",
+SOURCES = ("muon_api.hip", "muon_plan.cpp", "kernels_ew.hip", "kernels_gemm_bf16.hip", "kernels_gemm_pair.hip", "kernels_gemm_f32.hip",
            "kernels_adamw.hip", "probe_mfma.hip")
 
 HIPCC_FLAGS = [

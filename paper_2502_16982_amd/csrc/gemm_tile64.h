@@ -56,9 +56,11 @@ __device__ __forceinline__ void land64(Frag64<LKM>& f) {
 }
 
 // The tile at (row0, col0); `diagonal`: it lies on the diagonal of a symmetric product (its own mirror image).
-template <bool LKM, int NW, int NST>
+// IN, EITHER, out_f16: as in gemm_tile_body.
+template <bool LKM, int NW, int NST, typename IN = Bf16, bool EITHER = false>
 __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem,
-                                                 float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add) {
+                                                 float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add,
+                                                 bool out_f16 = false) {
   static_assert(NW == 4 || NW == 1, "a wave owns a 32 x 32 tile");
   constexpr int BT = NW == 4 ? 64 : 32;                         // tile side
   constexpr int LREQ = BT / 8 / NW, NLOAD = 2 * LREQ;           // 1 KB requests per wave and slab: L, both
@@ -143,7 +145,7 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
       } else {
         a = __builtin_bit_cast(bf16x8, fg[set][kk].a);
       }
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, fg[set][kk].b), acc, 0, 0, 0);
+      acc = IN::mfma(a, __builtin_bit_cast(bf16x8, fg[set][kk].b), acc);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (REFILL)
         static_for<kk * NLOAD / KSTEPS, (kk + 1) * NLOAD / KSTEPS>([&](auto n_tag) { request_one(kt + NST, stage, n_tag); });
@@ -242,15 +244,20 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
     ldct = p.ldc;
     if (diagonal) C = nullptr;
   }
+  if (EITHER && std::is_same_v<IN, Bf16> && out_f16) {           // (see kTwoFactors)
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] *= ab_acc;
+    for (int v = 0; v < 16; ++v) acc[v] = beta_acc * (alpha * acc[v]);
+  } else {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] *= ab_acc;
+  }
   if (has_e) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      acc[4 * q + 0] = fmaf(ab_e, __uint_as_float(ev[q].x << 16), acc[4 * q + 0]);
-      acc[4 * q + 1] = fmaf(ab_e, __uint_as_float(ev[q].x & 0xffff0000u), acc[4 * q + 1]);
-      acc[4 * q + 2] = fmaf(ab_e, __uint_as_float(ev[q].y << 16), acc[4 * q + 2]);
-      acc[4 * q + 3] = fmaf(ab_e, __uint_as_float(ev[q].y & 0xffff0000u), acc[4 * q + 3]);
+      acc[4 * q + 0] = fmaf(ab_e, IN::lo(ev[q].x), acc[4 * q + 0]);
+      acc[4 * q + 1] = fmaf(ab_e, IN::hi(ev[q].x), acc[4 * q + 1]);
+      acc[4 * q + 2] = fmaf(ab_e, IN::lo(ev[q].y), acc[4 * q + 2]);
+      acc[4 * q + 3] = fmaf(ab_e, IN::hi(ev[q].y), acc[4 * q + 3]);
     }
   }
   if (p.diag_add != 0 && row0 + wm * 32 == col0 + wn * 32) {     // wave-uniform
@@ -288,11 +295,31 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
   };
   u32x2 pk[4];
+  with_output_type<EITHER>(out_f16, [&](auto out) {
+    using OUT = decltype(out);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) pk[q] = u32x2{pack2f(acc[4 * q], acc[4 * q + 1]), pack2f(acc[4 * q + 2], acc[4 * q + 3])};
+    for (int q = 0; q < 4; ++q) pk[q] = u32x2{OUT::pack(acc[4 * q], acc[4 * q + 1]), OUT::pack(acc[4 * q + 2], acc[4 * q + 3])};
+  });
+  // kMirrored product, tile on the diagonal: the wave below it writes nothing, the one above it both blocks
+  const bool mirrors = EITHER && !LKM && diagonal && p.symmetric == kMirrored;
+  if constexpr (EITHER && !LKM) {
+    if (mirrors && wm <= wn) {
+      const Transposer transposed(fr, fh);
+      if (wm == wn) {
+        mirror_block(transposed, fr, fh, pk);
+      } else {
+        u32x2 m[4];
+        transposed(pk, m);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *slot(wm * 32 + fr, 4 * wn + q) = m[q];
+      }
+    }
+  }
   if (Ct) {
+    if (!mirrors || wm <= wn) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) *slot(wn * 32 + fr, 4 * wm + q) = pk[q];
+      for (int q = 0; q < 4; ++q) *slot(wn * 32 + fr, 4 * wm + q) = pk[q];
+    }
     __syncthreads();
     store_image(Ct, ldct, col0, row0);
   }

@@ -331,7 +331,9 @@ __global__ __launch_bounds__(256) void norm_finalize_kernel(const MatDesc* __res
 // into loads from a selected address of that copy, which put the whole 128-byte record into per-thread scratch memory
 // - 8 bytes of scratch traffic per matrix element; the HBM-side write counter of the update kernel read twice the
 // bytes of W because of it.
+// Bits 2 and 3: the same for matrices of the Gram route, whose iterate changes buffers once per group of iterations.
 __device__ __forceinline__ const void* o_source(const MatDesc& d, int o_sel) {
+  if (d.gram_route) o_sel >>= 2;
   if (d.transposed) return (o_sel & 1) ? d.Xt[1] : d.Xt[0];
   return (o_sel & 2) ? d.Xt[0] : d.X;
 }

@@ -53,6 +53,18 @@ static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 
 }  // namespace
 
+namespace {
+
+// One product of a group's sequence.
+struct GroupOp {
+  int product;        // PairProduct
+  size_t probs;       // offset of the problem table
+  float beta_acc, beta_e, diag_add;
+  int alpha_idx, kind;
+};
+
+}  // namespace
+
 struct muon_ctx {
   int n = 0;
   int ns_dtype = MUON_BF16;
@@ -72,6 +84,9 @@ struct muon_ctx {
   bool plan_only = false;
   // state of the last step, for the debug read
   int last_o_sel = 0, last_use_s = 0, last_chunk = -1;
+  // scratch of a step, kept from step to step: coefficients of every iteration, products of the two groups
+  std::vector<double> coeff;
+  std::vector<GroupOp> group_ops[2];
   // optional per-launch event timing
   bool profiling = false;
   std::vector<hipEvent_t> prof_events;   // pairs: start, stop
@@ -182,6 +197,111 @@ int quarter_flags(bool quarters, int few) {
   return quarters ? kGemmQuarters | (few == 2 ? kGemmSixteenths : few == 1 ? kGemmFewQuarters : 0) : 0;
 }
 
+// The products of a group's N iterations, in order.  coeff: a, b, c of every iteration.
+void list_ops(const Group& g, int N, const double* coeff, bool gram, bool fold, std::vector<GroupOp>& out) {
+  out.clear();
+  if (g.n_prob == 0) return;
+  const int norm = fold ? kAlphaFromPartials : 1;
+  if (!gram) {
+    for (int it = 0; it < N; ++it) {
+      const int first = it == 0, last = it == N - 1, par = it & 1;
+      const float a = (float)coeff[3 * it], b = (float)coeff[3 * it + 1], c = (float)coeff[3 * it + 2];
+      out.push_back({kPairGram, g.prob_gram[par], 1.f, 0.f, 0.f, first ? norm : -1, 0});
+      out.push_back({kPairSym, g.prob_poly, c, b, a, -1, 0});
+      out.push_back({kPairApply, g.prob_apply[par * 2 + last], 1.f, a, 0.f, first ? 0 : -1, kSideKMajor});
+    }
+    return;
+  }
+  // the Gram route (muon_plan.h); its scales are powers of two and change nothing but exponents
+  const float SA = kGramScaleA, SP = kGramScaleP, SX = kGramScaleX;
+  const int f16 = kSideInF16 | kSideOutF16;
+  int par = 0;
+  for (int it = 0; it < N; par ^= 1) {
+    const int steps = N - it == 3 ? 3 : 2;
+    const bool first = it == 0, last = it + steps == N;
+    auto op = [&](int o) { return g.prob_ops + sizeof(GemmProblem) * (size_t)g.n_prob * (size_t)(o < kGramParityOps ? par * kGramParityOps + o : o); };
+    float a = (float)coeff[3 * it], b = (float)coeff[3 * it + 1], c = (float)coeff[3 * it + 2];
+    out.push_back({kPairGram, g.prob_gram[par], first ? SA : SA / (SX * SX), 0.f, 0.f, first ? norm : -1, first ? kSideOutF16 : f16});
+    out.push_back({kPairSym, g.prob_poly, c * (SP / (SA * SA)), b * (SP / SA), a * SP, -1, f16});
+    out.push_back({kPairSym, op(kGramT), 1.f / SP, 0.f, 0.f, -1, f16});
+    out.push_back({kPairSym, op(kGramA), 1.f / SP, 0.f, 0.f, -1, f16});
+    for (int j = 1; j < steps; ++j) {
+      const double* k = coeff + 3 * (it + j);
+      a = (float)k[0], b = (float)k[1], c = (float)k[2];
+      out.push_back({kPairSym, op(kGramD), c * (SP / (SA * SA)), b * (SP / SA), 0.f, -1, f16});
+      const bool end = j == steps - 1, to_bf16 = end && first;     // the first apply product multiplies U, in bf16
+      const float o = to_bf16 ? 1.f : SP;
+      out.push_back({kPairSym, op(!end ? kGramQMid : steps == 2 ? kGramQ : kGramQ3), o / (SP * SP), a * (o / SP), 0.f, -1, to_bf16 ? kSideInF16 : f16});
+      if (!end) {
+        out.push_back({kPairSym, op(kGramT3), 1.f / SP, a, 0.f, -1, f16});
+        out.push_back({kPairSym, op(kGramA3), 1.f / SP, a, 0.f, -1, f16});
+      }
+    }
+    it += steps;
+    out.push_back({kPairApply, op(kGramApply + par * 2 + last), (last ? 1.f : SX) / (first ? 1.f : SP * SX), 0.f, 0.f, first ? 0 : -1,
+                   kSideKMajor | (first ? 0 : kSideInF16) | (last ? 0 : kSideOutF16)});
+  }
+}
+
+// Iterations of a chunk with matrices of the Gram route: the next product of either group in every launch.
+int enqueue_paired(muon_ctx* ctx, const Chunk& ch, const muon_hparams* hp, const double* coeff, bool gram, bool fold, hipStream_t s) {
+  std::vector<GroupOp>* const ops = ctx->group_ops;
+  for (int i = 0; i < 2; ++i) list_ops(ch.groups[i], hp->ns_steps, coeff, i == 1 && gram, fold, ops[i]);
+  size_t at[2] = {0, 0};
+  while (at[0] < ops[0].size() || at[1] < ops[1].size()) {
+    const GroupOp* op[2];
+    for (int i = 0; i < 2; ++i) op[i] = at[i] < ops[i].size() ? &ops[i][at[i]] : nullptr;
+    // An apply product in coarse tiles shares no launch with a symmetric product (kernels of their own): the other group waits
+    // and has its symmetric product beside the next one.
+    if (op[0] && op[1] && (op[0]->product == kPairApply) != (op[1]->product == kPairApply)) {
+      const int i = op[1]->product == kPairApply;
+      if (ch.groups[i].coarse.n_apply > 0) op[i ^ 1] = nullptr;
+    }
+    for (int i = 0; i < 2; ++i) at[i] += op[i] ? 1 : 0;
+    const int product[2] = {op[0] ? op[0]->product : kPairNone, op[1] ? op[1]->product : kPairNone};
+    const PairForm& form = ch.pair[product[0]][product[1]];
+    const int timed_as = product[1] == kPairApply || product[0] == kPairApply ? MUON_PROF_APPLY_POLY
+                         : product[1] == kPairGram || product[0] == kPairGram ? MUON_PROF_GRAM : MUON_PROF_POLY;
+    // a symmetric product by itself, with too few coarse tiles: all of it in a fine launch
+    const bool lone = !op[0] && op[1] && product[1] == kPairSym && ch.groups[1].n_lone > 0;
+    const bool both_sym = op[0] && op[1] && product[0] != kPairApply && product[1] != kPairApply;
+    for (int level = lone ? 0 : 1; level >= 0; --level) {
+      GemmSide side[2] = {};
+      int64_t longest[2] = {0, 0};
+      bool strips = false;
+      for (int i = 0; i < 2; ++i) {
+        side[i].alpha_idx = -1;
+        if (!op[i]) continue;
+        const Group& g = ch.groups[i];
+        const TileSet& ts = level ? g.coarse : g.fine;
+        const bool gram_product = product[i] == kPairGram, apply = product[i] == kPairApply;
+        side[i].n_tiles = lone ? g.n_lone : gram_product ? ts.n_sym : apply ? ts.n_apply : ts.n_poly;
+        if (side[i].n_tiles == 0) continue;
+        side[i].tiles = reinterpret_cast<const GemmTile*>(ctx->ws + (lone ? g.lone : gram_product ? ts.sym : apply ? ts.apply : ts.poly));
+        side[i].probs = reinterpret_cast<const GemmProblem*>(ctx->ws + op[i]->probs);
+        side[i].beta_acc = op[i]->beta_acc;
+        side[i].beta_e = op[i]->beta_e;
+        side[i].diag_add = op[i]->diag_add;
+        side[i].alpha_idx = op[i]->alpha_idx;
+        side[i].kind = op[i]->kind;
+        longest[i] = gram_product ? g.longest_n : g.longest_m;
+        strips = strips || ts.strips;
+      }
+      if (side[0].n_tiles + side[1].n_tiles == 0) continue;
+      const PairForm& fine_form = lone ? ch.groups[1].lone_form : form;
+      const int flags = level ? (strips ? kGemmStrips : 0) | (form.persistent ? kGemmPersistent : 0) : quarter_flags(fine_form.quarters, fine_form.few);
+      if (level && both_sym && ch.n_shared_sym > 0) {
+        const size_t tiles = ch.shared_sym[product[0] != kPairGram][product[1] != kPairGram];
+        MUON_TIMED(timed_as, launch_gemm_shared(flags, side[0], side[1], reinterpret_cast<const GemmTile*>(ctx->ws + tiles), ch.n_shared_sym, s));
+        continue;
+      }
+      const int x = longest[1] > longest[0];     // the longer K loops start first
+      MUON_TIMED(timed_as, launch_gemm_pair(level, flags, side[x], side[x ^ 1], hp->eps, s));
+    }
+  }
+  return MUON_OK;
+}
+
 // Enqueues every kernel of one step on stream s.  The pointer table is already on its way on the same stream, or (pack, plans
 // of one chunk) the first pass takes the pointers as an argument and fills it.
 int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* update_rms_out, const PtrPack* pack = nullptr) {
@@ -191,7 +311,12 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
   const int planes = planes_of(ctx->ns_dtype);
   // where O ends up (see o_source in the elementwise kernels): fp32 path: X in place, its transpose in Xt[N & 1];
   // bf16 path: X ping-pong index N & 1 (bit 1), transposed matrices in Xt[1], or Xt[0] when no iteration ran (bit 0)
-  const int o_sel = mc ? ((N & 1) << 1) | (N > 0 ? 1 : 0) : (N & 1);
+  const int o_written = mc ? ((N & 1) << 1) | (N > 0 ? 1 : 0) : (N & 1);
+  std::vector<double>& coeff = ctx->coeff;
+  coeff.resize(3 * (size_t)N);
+  for (int i = 0; i < 3 * N; ++i) coeff[i] = hp->coeff_schedule ? hp->coeff_schedule[i] : i % 3 == 0 ? hp->a : i % 3 == 1 ? hp->b : hp->c;
+  const bool gram = N >= kGramMinSteps && gram_coefficients_fit(coeff.data(), N);
+  const int o_sel = o_written | (gram ? ((N / 2) & 1) << 1 | 1 : o_written) << 2;       // N / 2 groups of iterations
 
   for (size_t ci = 0; ci < ctx->plan.chunks.size(); ++ci) {
     const Chunk& ch = ctx->plan.chunks[ci];
@@ -200,7 +325,11 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
                                                              hp->nesterov != 0, (!mc || N == 0) ? 1 : 0, ctx->ns_dtype, s));
     const bool fold = ch.fold_norm && N > 0;
     if (!fold) MUON_TIMED(MUON_PROF_NORM, launch_norm_finalize(ctx->d_mats, ch.first, ch.count, hp->eps, s));
-    for (int it = 0; it < N; ++it) {
+    if (ch.paired) {
+      const int st = enqueue_paired(ctx, ch, hp, coeff.data(), gram, fold, s);
+      if (st != MUON_OK) return st;
+    }
+    for (int it = 0; it < N && !ch.paired; ++it) {
       const int first = it == 0, last = it == N - 1, par = it & 1;
       const double* sch = hp->coeff_schedule ? hp->coeff_schedule + 3 * it : nullptr;
       const float a = (float)(sch ? sch[0] : hp->a), b = (float)(sch ? sch[1] : hp->b), c = (float)(sch ? sch[2] : hp->c);
@@ -462,8 +591,8 @@ int muon_debug_read_update(muon_ctx* ctx, int32_t index, void* dst, int32_t dst_
 int muon_plan_describe(const muon_ctx* ctx, int32_t index, int64_t* out, int32_t cap) {
   if (!ctx || !out || index < 0 || index >= ctx->n || cap < 0) return MUON_E_INVALID_ARG;
   const MatPlan& q = ctx->plan.mats[index];
-  const int64_t v[8] = {q.m, q.n, q.transposed, q.mp, q.np, q.chunk, q.coarse ? kCoarse : q.tile, q.tile};
-  const int k = std::min<int>(cap, 8);
+  const int64_t v[9] = {q.m, q.n, q.transposed, q.mp, q.np, q.chunk, q.coarse ? kCoarse : q.tile, q.tile, q.gram};
+  const int k = std::min<int>(cap, 9);
   for (int i = 0; i < k; ++i) out[i] = v[i];
   return k;
 }

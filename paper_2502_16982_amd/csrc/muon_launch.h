@@ -97,6 +97,21 @@ constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmQuarters = 4, kGemmLong
 hipError_t launch_gemm_bf16(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
                             float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add, int l_kmajor, int planes,
                             hipStream_t s);
+// Two products in one launch (kernels_gemm_pair.hip), either of them empty (n_tiles = 0).  coarse, flags, eps: as above; in a
+// coarse launch both sides' tables are coarse ones.
+struct GemmSide {
+  const GemmProblem* probs;
+  const GemmTile* tiles;
+  int n_tiles;
+  float beta_acc, beta_e, diag_add;
+  int alpha_idx;
+  int kind;           // kSide*: operand layout, type of the operands and the addend, type of the results
+};
+constexpr int kSideKMajor = 1, kSideInF16 = 2, kSideOutF16 = 4;
+hipError_t gemm_pair_setup();
+hipError_t launch_gemm_pair(int coarse, int flags, const GemmSide& x, const GemmSide& y, double eps, hipStream_t s);
+// Coarse symmetric products of both from one table; the sides' own tables are not used.
+hipError_t launch_gemm_shared(int flags, const GemmSide& x, const GemmSide& y, const GemmTile* tiles, int n_tiles, hipStream_t s);
 hipError_t gemm_f32_setup();
 hipError_t launch_gemm_f32(int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
                            float beta_acc, float beta_e, int alpha_idx, double eps, hipStream_t s);

@@ -317,35 +317,46 @@ struct Fine3 {
 constexpr Fine3 kFine3[] = {{256, (int)kMostFine3, 100}, {768, 200, 85}, {1024, 150, 80}, {2048, 128, 65}, {INT64_MAX, 128, 57}};
 // entries whose 64-wide blocks all have a place at the same time
 int lone_entries(int planes, int blocks) { return planes == 2 ? 3 * blocks / 4 : blocks / 2; }
+// What a fine launch holds: entries of one K after the other.
+struct Load {
+  int64_t entries, k;
+};
+std::vector<Load> load_of(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k) {
+  std::vector<Load> out;
+  for (size_t i = 0; i < tiles.size(); ++i) {
+    if (tiles[i].empty()) continue;
+    if (!out.empty() && out.back().k == k[i]) out.back().entries += (int64_t)tiles[i].size();
+    else out.push_back({(int64_t)tiles[i].size(), k[i]});
+  }
+  return out;
+}
 // a launch's work in entries of its longest K; `fixed`: what an entry costs beside its K
-int64_t entries_of_work(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int64_t fixed = 0) {
+int64_t entries_of_work(const std::vector<Load>& load, int64_t fixed = 0) {
   int64_t longest = 1, total = 0;
-  for (size_t i = 0; i < tiles.size(); ++i)
-    if (!tiles[i].empty()) {
-      longest = std::max(longest, k[i] + fixed);
-      total += (k[i] + fixed) * (int64_t)tiles[i].size();
-    }
+  for (const Load& l : load) {
+    longest = std::max(longest, l.k + fixed);
+    total += (l.k + fixed) * l.entries;
+  }
   return (total + longest - 1) / longest;
 }
-bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, bool mc, int planes, int blocks) {
-  const int64_t entries = entries_of_work(tiles, k);
+bool runs_in_quarters(const std::vector<Load>& load, bool mc, int planes, int blocks) {
+  const int64_t entries = entries_of_work(load);
   int64_t longest = 0, count = 0;
-  for (size_t i = 0; i < tiles.size(); ++i)
-    if (!tiles[i].empty()) {
-      longest = std::max(longest, k[i]);
-      count += (int64_t)tiles[i].size();
-    }
+  for (const Load& l : load) {
+    longest = std::max(longest, l.k);
+    count += l.entries;
+  }
   const int64_t b = std::max(blocks, 1);
   if (mc && planes == 2) {
     if (entries <= lone_entries(2, blocks)) return true;
     if (4 * entries > 5 * b || longest > (entries > b ? kLongKPlanes2 : kShortKPlanes2)) return false;
-    return longest <= kMixedKPlanes2 ? 3 * entries_of_work(tiles, k, kBlockK) <= 4 * b : 4 * count <= 5 * b;
+    return longest <= kMixedKPlanes2 ? 3 * entries_of_work(load, kBlockK) <= 4 * b : 4 * count <= 5 * b;
   }
   if (mc && planes == 3) {
     const Fine3* f = kFine3;
     while (longest > f->k) ++f;
     if (entries <= f->entries * b / 256) return true;
-    for (int64_t e : {entries, entries_of_work(tiles, k, kBlockK)}) {
+    for (int64_t e : {entries, entries_of_work(load, kBlockK)}) {
       const int64_t rounds = (e + b - 1) / b;
       if (rounds > 1 && e <= kMostFine3 && 100 * e < f->fill * rounds * b) return true;
     }
@@ -372,18 +383,35 @@ bool runs_in_quarters(const std::vector<std::vector<GemmTile>>& tiles, const std
 // (two planes up to 51, three up to 40).
 constexpr size_t kFewest = 24, kFewestShort = 36;
 constexpr int64_t kShortK = 1024;
-int few_blocks(const std::vector<std::vector<GemmTile>>& tiles, const std::vector<int64_t>& k, int planes, int blocks) {
+int few_blocks(const std::vector<Load>& load, int planes, int blocks) {
   size_t n = 0;
   int64_t longest = 0;
-  for (size_t i = 0; i < tiles.size(); ++i)
-    if (!tiles[i].empty()) {
-      n += tiles[i].size();
-      longest = std::max(longest, k[i]);
-    }
+  for (const Load& l : load) {
+    n += (size_t)l.entries;
+    longest = std::max(longest, l.k);
+  }
   if (planes == 1 && (n <= kFewest || (n <= kFewestShort && longest <= kShortK))) return 2;
-  const int64_t work = entries_of_work(tiles, k), b = std::max(blocks, 1);
+  const int64_t work = entries_of_work(load), b = std::max(blocks, 1);
   if (planes > 1) return 4 * (int64_t)n <= b || (planes == 2 ? 5 * work <= b : 32 * work <= 5 * b) ? 1 : 0;
   return 4 * work <= b + b / 16 ? 1 : 0;
+}
+
+// What a group brings to the fine level of paired launches, by PairProduct, and the shortest and longest K of each product.
+struct PairSide {
+  std::vector<Load> load[4];
+  std::vector<std::vector<GemmTile>> coarse_sym;       // and the coarse tiles of its symmetric products
+  std::vector<std::vector<int>> coarse_cuts;
+  std::vector<int64_t> w_n, w_m;
+  int64_t lo[4] = {kMaxDim, kMaxDim, kMaxDim, kMaxDim}, hi[4] = {};
+};
+PairForm pair_form(const PairSide& x, int px, const PairSide& y, int py, int blocks) {
+  std::vector<Load> load = x.load[px];
+  load.insert(load.end(), y.load[py].begin(), y.load[py].end());
+  PairForm f;
+  f.persistent = 2 * std::max(x.hi[px], y.hi[py]) <= 3 * std::min(x.lo[px], y.lo[py]);
+  f.quarters = runs_in_quarters(load, true, 1, blocks);
+  f.few = few_blocks(load, 1, blocks);
+  return f;
 }
 
 void plan_matrices(const muon_param* p, int n, int ns_dtype, std::vector<MatPlan>& out, size_t& total_partials) {
@@ -411,6 +439,7 @@ void plan_matrices(const muon_param* p, int n, int ns_dtype, std::vector<MatPlan
     total_partials += (size_t)q.ew_tr * q.ew_tc;
     q.chunk = 0;
     q.coarse = false;
+    q.gram = gram_route(q, ns_dtype);
   }
 }
 
@@ -421,6 +450,8 @@ struct TableLayout {
 
 // No tile shape is smaller than the fine tile, so the fine-tile counts bound the table sizes.  (An upper bound: there is one
 // apply table, not two, but callers' workspaces are sized by this.)
+// (The tables of the Gram route have their place in the second apply table's and in the slack.)
+constexpr size_t kTableAlign = 128;
 size_t gemm_tables_bytes_for(const MatPlan& q) {
   const int tm = q.mp / q.tile, tn = q.np / q.tile;
   const size_t sym = (size_t)tm * (tm + 1) / 2 + 1, app = (size_t)tm * tn + 1;
@@ -467,6 +498,57 @@ int planes_of(int ns_dtype) { return ns_dtype == MUON_BF16X2 ? 2 : ns_dtype == M
 // The split forms keep the explicit addend: folded into B's diagonal it would be rounded at the diagonal's magnitude
 // (a = 3.44), not the iterate's.
 bool folds_identity(const MatPlan& q, int ns_dtype) { return ns_dtype == MUON_BF16 && q.m >= 64; }
+
+// Whether a matrix takes the Gram route: from its own sides, so that its result does not depend on the list.  A group of k iterations
+// then has one Gram and one apply product instead of k of each, and 5 or 9 products of m x m instead of k: with five iterations three
+// Gram and three apply products against nine more of m x m.  Where a launch is a chain of slabs and little else that pays from a
+// ratio n / m on that falls with m (the chain of the Gram product is n long, that of the nine m); in lists that fill the chip sooner, so
+// the line is where a matrix alone does not lose.  us per step, all products of Eq. 2 / Gram route, one matrix and several: 384 x 1536
+// 84.2 / 88.0, 24 291 / 242, x 3072 116 / 101, 500 -> 375 (24); 512 x 2048 101.0 / 101.6, x 4096 143 / 122, 24 847 / 612; 640 x 1664
+// 107 / 115, x 2560 125.7 / 122.6, 24 1054 / 925, x 5120 177 / 142; 768 x 3072 156 / 149, 8 466 / 374; 1024 x 2816 171 / 179, 3 330 / 287, x
+// 4096 198 / 192, 3 376 / 312; 1408 x 2816 253 / 260, x 3840 300 / 281, 8 1463 / 1297; 2048 x 4096 519 / 509, 8 2527 / 2655, x 5632 654 /
+// 576; 3072 x 6144 1181 / 1077, x 8448 1521 / 1244.  Beside other matrices: 4 of 512^2 and 3 of 1024 x 4096 413 / 351, 30 of 1024^2 and 6 of
+// 1408 x 5632 2425 / 2143, 48 of 1024^2 and 36 of 1024 x 4096 4609 / 4065; a few beside much more of the other kind, which the longer chain of launches
+// shows: 3000^2 and one of 1024 x 4096 873 / 941, 4 of 1536^2 and one of 640 x 5000 555 / 581.  Fewer rows than 384 gain alone (256 x
+// 4096 121 / 99) and lose beside anything longer.  (np >= 2 mp is also what the places of U and V need.)
+bool gram_route(const MatPlan& q, int ns_dtype) {
+  if (ns_dtype != MUON_BF16 || q.mp < 384) return false;
+  const double least = q.mp >= 2560 ? 2.0 : q.mp >= 1280 ? 2.6 : q.mp >= 640 ? 4.0 : 8.0;
+  return q.np >= least * q.mp;
+}
+
+bool gram_coefficients_fit(const double* coeff, int steps) {
+  // An element is at most its matrix's spectral norm.  s: bound on X's, which is 1 at the start (the Frobenius norm); the maximum of
+  // |a x + b x^3 + c x^5| over [0, s] is at an end or where the derivative vanishes.  A quarter is added for rounding.
+  const double slack = 1.25, most = 65504.0 / slack;
+  double s = 1.0;
+  for (int k = 0, left = steps; left > 0;) {
+    const int group = left == 3 ? 3 : 2;         // (left is never 1: see kGramMinSteps)
+    double q = 1.0;
+    for (int j = 0; j < group; ++j, ++k) {
+      const double a = coeff[3 * k], b = coeff[3 * k + 1], c = coeff[3 * k + 2], t = s * s;
+      auto f = [&](double x) { return std::fabs(x * (a + x * x * (b + c * x * x))); };
+      double next = f(s), p = std::max(std::fabs(a), std::fabs(a + t * (b + c * t)));
+      if (c != 0.0) {
+        const double v = -b / (2.0 * c), disc = 9.0 * b * b - 20.0 * a * c;
+        if (v > 0.0 && v < t) p = std::max(p, std::fabs(a + v * (b + c * v)));
+        if (disc >= 0.0)
+          for (double root : {(-3.0 * b + std::sqrt(disc)) / (10.0 * c), (-3.0 * b - std::sqrt(disc)) / (10.0 * c)})
+            if (root > 0.0 && root < t) next = std::max(next, f(std::sqrt(root)));
+      } else if (b != 0.0) {
+        const double root = -a / (3.0 * b);
+        if (root > 0.0 && root < t) next = std::max(next, f(std::sqrt(root)));
+      }
+      q *= std::max(p, 1.0);
+      // A and T = P A; D = P - a I and Q; the next X
+      const double worst = std::max({kGramScaleA * t * std::max(1.0, p), kGramScaleP * std::max(p + std::fabs(a), q), kGramScaleX * next});
+      if (!(worst <= most)) return false;        // not a number, too
+      s = next;
+    }
+    left -= group;
+  }
+  return true;
+}
 
 int validate_shapes(const muon_param* p, int32_t n, int32_t ns_dtype) {
   if (!p || n <= 0) return MUON_E_INVALID_ARG;
@@ -575,7 +657,7 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
       d.Ag = ns_base + ns_off; ns_off += ab * planes;
       d.Bp = ns_base + ns_off; ns_off += ab * planes;
       d.x_plane = planes > 1 ? (int64_t)(xb / es) : 0;
-      d.pad_ = 0;
+      d.gram_route = q.gram;
       d.partials = reinterpret_cast<float*>(dev(off_part)) + q.part_off;
       d.scal = reinterpret_cast<float*>(dev(off_scal)) + 4 * (size_t)i;
       d.rows = (int)q.rows; d.cols = (int)q.cols;
@@ -618,16 +700,42 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
       cursor += (size_t)ch.n_ew_tiles * sizeof(EwTile);
     }
 
-    // GEMM group of the chunk
-    {
-      std::vector<int> members;
-      for (int i = ch.first; i < ch.first + ch.count; ++i) members.push_back(i);
+    // Whether the products go to the fine launch altogether is decided for the chunk, not for a group.
+    // (Apply products: for a group where there are two, whose apply products never meet in a launch.)
+    CoarseLoad coarse_sym, coarse_sym_of[2], coarse_app[2];
+    std::vector<int> members_of[2];              // Eq. 2 as it is written, Gram route
+    for (int i = ch.first; i < ch.first + ch.count; ++i) {
+      const MatPlan& q = plan.mats[i];
+      members_of[q.gram].push_back(i);
+      if (!mc) continue;
+      const size_t cm = (size_t)(q.mp / kCoarse), cn = (size_t)(q.np / kCoarse);
+      const int strip_h = kShapeRows[kShape512x128];
+      const bool odd_m = (q.mp % kCoarse) != 0;
+      const size_t sym_tiles = cm * (cm + 1) / 2 + (odd_m && q.mp >= strip_h ? (size_t)((q.mp + strip_h - 1) / strip_h) : 0);
+      coarse_sym.add(sym_tiles, q.mp, q.np);
+      coarse_sym_of[q.gram].add(sym_tiles, q.mp, q.np);
+      coarse_app[q.gram].add(cm * cn + (odd_m && q.np >= strip_h ? (size_t)((q.np + strip_h - 1) / strip_h) : 0), q.mp, q.np);
+    }
+    const bool few_sym = few_coarse_sym(coarse_sym, (int)planes, plan.coarse_blocks);
+    ch.paired = !members_of[1].empty();
+    PairSide pair_sides[2];
+
+    // GEMM groups of the chunk
+    for (int route = 0; route < 2; ++route) {
+      const std::vector<int>& members = members_of[route];
+      if (members.empty()) {
+        if (route == 0) ch.groups.push_back(Group{});        // groups[1] is the Gram route's
+        continue;
+      }
+      const bool few_app = few_coarse_apply(coarse_app[route], (int)planes, plan.coarse_blocks);
+      const CoarseLoad& coarse_own = coarse_sym_of[route];
       Group g{};
+      g.gram = route == 1;
       g.n_prob = (int)members.size();
       g.members = members;
       const size_t np_ = members.size();
       auto take = [&](size_t bytes) {
-        cursor = align_up(cursor, 256);
+        cursor = align_up(cursor, kTableAlign);
         const size_t o = cursor;
         cursor += bytes;
         return o;
@@ -635,6 +743,7 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
       for (int v = 0; v < 2; ++v) g.prob_gram[v] = take(sizeof(GemmProblem) * np_);
       g.prob_poly = take(sizeof(GemmProblem) * np_);
       for (int v = 0; v < 4; ++v) g.prob_apply[v] = take(sizeof(GemmProblem) * np_);
+      if (g.gram) g.prob_ops = take(sizeof(GemmProblem) * np_ * kGramOps);
       for (size_t k = 0; k < np_; ++k) {
         const MatPlan& q = plan.mats[members[k]];
         const MatDesc& d = h_mats[members[k]];
@@ -684,7 +793,27 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
               }
             }
             reinterpret_cast<GemmProblem*>(img.data() + g.prob_apply[par * 2 + last])[k] = gp;
+            if (g.gram) {                        // the same with Q
+              gp.R = d.Ag;
+              reinterpret_cast<GemmProblem*>(img.data() + g.prob_ops)[(kGramApply + par * 2 + last) * np_ + k] = gp;
+            }
           }
+        if (g.gram) {
+          for (int par = 0; par < 2; ++par) {
+            unsigned char* const u = static_cast<unsigned char*>(xbuf[par ^ 1]);
+            void *const U = u, *const V = u + es * (size_t)q.mp * q.mp;      // both fit: np >= 2 mp
+            struct { void *l, *r, *e, *c; } const ops[kGramParityOps] = {
+                {d.Bp, d.Ag, nullptr, U}, {U, d.Bp, nullptr, d.Ag}, {d.Ag, d.Ag, d.Ag, U}, {U, d.Bp, d.Bp, d.Ag},
+                {U, d.Bp, d.Bp, V}, {U, d.Ag, d.Ag, d.Bp}, {d.Bp, U, d.Bp, d.Ag}, {U, V, V, d.Ag}};
+            for (int op = 0; op < kGramParityOps; ++op) {
+              GemmProblem s = reinterpret_cast<const GemmProblem*>(img.data() + g.prob_poly)[k];
+              s.L = ops[op].l; s.R = ops[op].r; s.Et = ops[op].e; s.C = ops[op].c;
+              s.diag_add = 0;
+              if (op != kGramD) s.symmetric = kMirrored;     // (D is a polynomial of one matrix, symmetric to the bit)
+              reinterpret_cast<GemmProblem*>(img.data() + g.prob_ops)[(par * kGramParityOps + op) * np_ + k] = s;
+            }
+          }
+        }
       }
       // Launch order of the problems, longest K loop first (the tail of a launch is then made of short tiles):
       // the Gram product runs over n, the other two over m.
@@ -719,18 +848,9 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         lo_n = std::min(lo_n, w_n[k]); hi_n = std::max(hi_n, w_n[k]);
         lo_m = std::min(lo_m, w_m[k]); hi_m = std::max(hi_m, w_m[k]);
       }
+      g.longest_n = hi_n;
+      g.longest_m = hi_m;
       const bool steady_n = 2 * hi_n <= 3 * lo_n, steady_m = 2 * hi_m <= 3 * lo_m;
-      CoarseLoad coarse_sym, coarse_app;
-      for (size_t k = 0; mc && k < np_; ++k) {
-        const MatPlan& q = plan.mats[members[k]];
-        const size_t cm = (size_t)(q.mp / kCoarse), cn = (size_t)(q.np / kCoarse);
-        const int strip_h = kShapeRows[kShape512x128];
-        const bool odd_m = (q.mp % kCoarse) != 0;
-        coarse_sym.add(cm * (cm + 1) / 2 + (odd_m && q.mp >= strip_h ? (size_t)((q.mp + strip_h - 1) / strip_h) : 0), q.mp, q.np);
-        coarse_app.add(cm * cn + (odd_m && q.np >= strip_h ? (size_t)((q.np + strip_h - 1) / strip_h) : 0), q.mp, q.np);
-      }
-      const bool few_sym = few_coarse_sym(coarse_sym, (int)planes, plan.coarse_blocks);
-      const bool few_app = few_coarse_apply(coarse_app, (int)planes, plan.coarse_blocks);
       std::vector<std::vector<GemmTile>> moved_sym(np_), moved_app(np_);   // coarse tiles handed to the fine level
       for (int level = 1; level >= 0; --level) {
         if (level == 1 && !mc) continue;
@@ -778,9 +898,10 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
           }
         }
         if (level == 1) {
-          // launches whose tiles all run the same K: even out their last round
+          // launches whose tiles all run the same K: even out their last round (paired symmetric launches have the other
+          // group's tiles there)
           const int most = planes == 1 ? kMaxMovedTiles : lone_entries((int)planes, plan.coarse_blocks) / 4;
-          if (uniform_n && uniform_m) move_tail_to_fine(by_n, sym, sym_cuts, plan.coarse_blocks, most, moved_sym);
+          if (uniform_n && uniform_m && !ch.paired) move_tail_to_fine(by_n, sym, sym_cuts, plan.coarse_blocks, most, moved_sym);
           if (uniform_m) move_tail_to_fine(by_m, app, app_cuts, plan.coarse_blocks, most, moved_app);
         }
         for (size_t k = 0; k < np_; ++k) {
@@ -790,14 +911,26 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         }
         TileSet& ts = level ? g.coarse : g.fine;
         ts.strips = strips;
+        if (ch.paired) {
+          PairSide& side = pair_sides[route];
+          side.lo[kPairGram] = lo_n; side.hi[kPairGram] = hi_n;
+          side.lo[kPairSym] = side.lo[kPairApply] = lo_m; side.hi[kPairSym] = side.hi[kPairApply] = hi_m;
+          if (level == 1) side.coarse_sym = sym, side.coarse_cuts = sym_cuts, side.w_n = w_n, side.w_m = w_m;
+          if (level == 0) {
+            side.load[kPairGram] = load_of(sym, w_n);
+            side.load[kPairSym] = load_of(sym, w_m);
+            side.load[kPairApply] = load_of(app, w_m);
+          }
+        }
         if (level == 0) {
-          ts.quarter_sym = runs_in_quarters(sym, w_n, mc, (int)planes, plan.coarse_blocks);
-          ts.quarter_poly = runs_in_quarters(sym, w_m, mc, (int)planes, plan.coarse_blocks);
-          ts.quarter_apply = runs_in_quarters(app, w_m, mc, (int)planes, plan.coarse_blocks);
+          const std::vector<Load> l_sym = load_of(sym, w_n), l_poly = load_of(sym, w_m), l_app = load_of(app, w_m);
+          ts.quarter_sym = runs_in_quarters(l_sym, mc, (int)planes, plan.coarse_blocks);
+          ts.quarter_poly = runs_in_quarters(l_poly, mc, (int)planes, plan.coarse_blocks);
+          ts.quarter_apply = runs_in_quarters(l_app, mc, (int)planes, plan.coarse_blocks);
           if (mc) {
-            ts.few_sym = few_blocks(sym, w_n, (int)planes, plan.coarse_blocks);
-            ts.few_poly = few_blocks(sym, w_m, (int)planes, plan.coarse_blocks);
-            ts.few_apply = few_blocks(app, w_m, (int)planes, plan.coarse_blocks);
+            ts.few_sym = few_blocks(l_sym, (int)planes, plan.coarse_blocks);
+            ts.few_poly = few_blocks(l_poly, (int)planes, plan.coarse_blocks);
+            ts.few_apply = few_blocks(l_app, (int)planes, plan.coarse_blocks);
           }
         }
         ts.long_n = !mc && hi_n > kF32LongK;
@@ -816,16 +949,77 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         ts.n_poly = (int)deal_tiles(by_m, sym, sym_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.poly), steady_m ? slots : 0, level == 0);
         ts.n_apply = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply), steady_m ? slots : 0, level == 0);
       }
+      if (g.gram && g.coarse.n_sym > 0 && few_coarse_sym(coarse_own, (int)planes, plan.coarse_blocks)) {
+        std::vector<std::vector<GemmTile>> sym(np_);
+        std::vector<std::vector<int>> sym_cuts(np_);
+        size_t count = 0;
+        for (size_t k = 0; k < np_; ++k) {
+          const MatPlan& q = plan.mats[members[k]];
+          blocked_tiles((int32_t)k, q.tile, kShape128, q.mp / q.tile, q.mp / q.tile, true, 0, 0, -1, sym[k], sym_cuts[k]);
+          count += sym[k].size();
+        }
+        g.lone = take(count * sizeof(GemmTile));
+        g.n_lone = (int)deal_tiles(by_m, sym, sym_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + g.lone), 0, true);
+        const std::vector<Load> load = load_of(sym, w_m);
+        g.lone_form.quarters = runs_in_quarters(load, true, 1, plan.coarse_blocks);
+        g.lone_form.few = few_blocks(load, 1, plan.coarse_blocks);
+      }
+      ch.groups.push_back(g);
+    }
+    if (ch.paired && ch.groups[0].coarse.n_sym > 0 && ch.groups[1].coarse.n_sym > 0) {
+      // one list of both groups' coarse symmetric tiles, dealt as one for every pair of products
+      std::vector<std::vector<GemmTile>> tiles = pair_sides[0].coarse_sym;
+      std::vector<std::vector<int>> cuts = pair_sides[0].coarse_cuts;
+      const int n0 = (int)tiles.size();
+      for (size_t k = 0; k < pair_sides[1].coarse_sym.size(); ++k) {
+        tiles.push_back(pair_sides[1].coarse_sym[k]);
+        for (GemmTile& t : tiles.back()) t.prob += n0;
+        cuts.push_back(pair_sides[1].coarse_cuts[k]);
+      }
+      ch.n_shared_sym = ch.groups[0].coarse.n_sym + ch.groups[1].coarse.n_sym;
+      for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < 2; ++j) {
+          if (i && pair_sides[0].w_m == pair_sides[0].w_n) {      // (square matrices: the same K)
+            ch.shared_sym[i][j] = ch.shared_sym[0][j];
+            continue;
+          }
+          std::vector<int64_t> w = i ? pair_sides[0].w_m : pair_sides[0].w_n;
+          const std::vector<int64_t>& w1 = j ? pair_sides[1].w_m : pair_sides[1].w_n;
+          w.insert(w.end(), w1.begin(), w1.end());
+          std::vector<int> order(w.size());
+          std::iota(order.begin(), order.end(), 0);
+          std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return w[x] > w[y]; });
+          const int64_t lo = *std::min_element(w.begin(), w.end()), hi = *std::max_element(w.begin(), w.end());
+          cursor = align_up(cursor, kTableAlign);
+          ch.shared_sym[i][j] = cursor;
+          GemmTile* const out = reinterpret_cast<GemmTile*>(img.data() + cursor);
+          deal_tiles(order, tiles, cuts, w, out, 2 * hi <= 3 * lo ? plan.coarse_blocks / kXcds : 0, false);
+          for (int t = 0; t < ch.n_shared_sym; ++t)
+            if (out[t].prob >= n0) {
+              out[t].prob -= n0;
+              out[t].flags |= kTileSecond;
+            }
+          cursor += (size_t)ch.n_shared_sym * sizeof(GemmTile);
+        }
+    }
+    if (ch.paired) {
+      for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 4; ++j) ch.pair[i][j] = pair_form(pair_sides[0], i, pair_sides[1], j, plan.coarse_blocks);
+    }
+    {
       // Lists short enough for quarter blocks save the norm's own launch (about 4 us): every block adds up its matrix's
       // partials while its first operands are on their way, at most four per thread, or per lane where it is a wave.  With
       // waves the norm's launch / the fold, us per step: 64 x 4000 (126 partials) 110.0 / 109.2, 64 x 8000 (252) 170.0 / 170.4, 256 x
       // 8000 (504) 185.0 / 186.1, 128 x 16000 (500) 279.6 / 281.6, 64 x 32000 (1000) 508.8 / 510.0.
       constexpr int kFoldedPerThread = 4;
-      const int most_folded = kFoldedPerThread * (g.fine.few_sym == 2 ? 64 : 256);
+      const PairForm& first = ch.pair[ch.groups[0].n_prob > 0 ? kPairGram : kPairNone][kPairGram];
+      const int few = ch.paired ? first.few : ch.groups[0].fine.few_sym;
+      const int most_folded = kFoldedPerThread * (few == 2 ? 64 : 256);
       int most_parts = 0;
       for (int i = ch.first; i < ch.first + ch.count; ++i) most_parts = std::max(most_parts, h_mats[i].n_part);
-      ch.fold_norm = g.coarse.n_sym == 0 && g.fine.quarter_sym && most_parts <= most_folded;
-      ch.groups.push_back(g);
+      bool coarse = false;
+      for (const Group& g : ch.groups) coarse = coarse || g.coarse.n_sym > 0;
+      ch.fold_norm = !coarse && (ch.paired ? first.quarters : ch.groups[0].fine.quarter_sym) && most_parts <= most_folded;
     }
   }
   if (cursor > tl.total) return MUON_E_WORKSPACE_TOO_SMALL;   // the layout bound is conservative; this cannot happen

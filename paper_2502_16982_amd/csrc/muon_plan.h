@@ -22,6 +22,7 @@ struct MatPlan {
   int tile;         // fine GEMM block tile = padding granule, in elements
   int chunk;
   bool coarse;      // some of its outputs are computed in coarse tiles
+  bool gram;        // takes the Gram route (gram_route)
   int ew_tr, ew_tc; // 64x64 tiles in U's orientation (padded)
   size_t ns_bytes;  // X + Xt[0] (+ Xt[1], see x_buffers) + Ag + Bp
   size_t part_off;  // first partial (floats)
@@ -40,7 +41,48 @@ struct TileSet {
   int few_sym = 0, few_poly = 0, few_apply = 0;   // quarters on the matrix cores: 1 with the longer ring, 2 (plain bf16) as one wave per 32 x 32
 };
 
-// Launch group: all matrices of one chunk.  Each product is one launch per level: the coarse launch (matrix-core
+// The Gram route.  X' = P X with P = a I + b A + c A A, A = X X^T commutes with everything made of A, so the next iteration's Gram
+// matrix is P A P and two or three iterations in a row are one product with Q = P_k .. P_1:
+//     A = X X^T;  P = a I + b A + c A A, Q = P;  then for each further iteration
+//     T = P A, A = T P;  D = b A + c A A, P = a I + D;  Q = a Q + D Q;      and at the end of the group X = Q X
+// (the first T is P A with P as stored, the others are a A + D A and A = a T + T D).  Groups of two, the last of three where the
+// number of iterations is odd.  The iteration is the same; of m x m matrices it takes 5 and 9 products for a group instead of 2 and
+// 3, of m x n ones one Gram and one apply product instead of two or three of each.
+// Everything but the first operands (U, bf16 of any magnitude, and the Q that multiplies it) and the last results (O) is held in
+// f16, scaled by a power of two: as wide as bf16, at the same rate, with 8 times its precision, which the route needs: an error of A
+// is amplified a^2-fold by every iteration of a group.  Error of O against 64 bits (numpy model, N = 5; Gaussian, with outliers, and
+// singular values that fall like 1/i): 128 x 256 0.90e-2, 1.12e-2, 1.63e-2 written as Eq. 2 in bf16, 0.41e-2, 0.65e-2, 1.30e-2 here; 1024
+// x 4096 0.67e-2, 0.75e-2 and 0.35e-2, 0.31e-2.  Groups of four and five lose small singular values to the rounding of A.
+// f16 holds 65504: coefficients under which a bound on some matrix could pass that (gram_coefficients_fit) take Eq. 2's products.
+enum GramOp : int {
+  kGramT = 0,      // T = Bp Ag -> U                    (U, V: m x m matrices in the other buffer of the iterate)
+  kGramA,          // A = U Bp -> Ag
+  kGramD,          // D from Ag -> U
+  kGramQ,          // Q = a Bp + U Bp -> Ag              (last of a group of two)
+  kGramQMid,       // Q = a Bp + U Bp -> V
+  kGramT3,         // T = a Ag + U Ag -> Bp
+  kGramA3,         // A = a Bp + Bp U -> Ag
+  kGramQ3,         // Q = a V + U V -> Ag                (last of a group of three)
+  kGramParityOps   // each of the above for the two places of U and V
+};
+constexpr int kGramApply = 2 * kGramParityOps;       // X = Ag X: [parity * 2 + last]
+constexpr int kGramOps = kGramApply + 4;
+constexpr int kGramMinSteps = 4;                     // fewer iterations have nothing to gain
+// Powers of two by which the f16 matrices are larger than what they stand for: A and T; P, D and Q; X.
+constexpr float kGramScaleA = 8192.f, kGramScaleP = 512.f, kGramScaleX = 8192.f;
+bool gram_route(const MatPlan& q, int ns_dtype);
+// Whether `steps` iterations with the coefficients coeff[3 * k] .. (a, b, c) stay inside f16 on the Gram route.
+bool gram_coefficients_fit(const double* coeff, int steps);
+
+// What a group contributes to a paired launch: nothing, its Gram product, another symmetric product, its apply product.
+enum PairProduct : int { kPairNone = 0, kPairGram = 1, kPairSym = 2, kPairApply = 3 };
+struct PairForm {
+  bool persistent = false;                        // coarse launch
+  bool quarters = false;                          // fine launch, as in TileSet
+  int few = 0;
+};
+
+// Launch group: the matrices of one chunk that take one route.  Each product is one launch per level: the coarse launch (matrix-core
 // paths only) runs 256 x 256 tiles over the part of every output that whole such tiles cover plus 512 x 128 tiles
 // over the 128-wide column strip an odd multiple of 128 leaves; the fine launch (128 x 128 bf16, 64 x 64 fp32) takes
 // what remains, so that nothing is padded beyond the fine tile.  (With several planes entries of the coarse tables run as four
@@ -48,9 +90,17 @@ struct TileSet {
 // chip idle has no coarse launch: all its tiles are fine.
 struct Group {
   int n_prob = 0;
+  bool gram = false;                              // its matrices take the Gram route
+  int64_t longest_n = 0, longest_m = 0;           // longest K of the Gram product, of the other two
+  size_t prob_ops = 0;                            // Gram route: kGramOps tables of n_prob problems, one after the other
   std::vector<int> members;                       // problem index -> matrix index in the caller's list
   size_t prob_gram[2] = {0, 0}, prob_poly = 0, prob_apply[4] = {0, 0, 0, 0};  // byte offsets ([parity], [parity * 2 + last])
   TileSet fine, coarse;
+  // Gram route: symmetric products that run without the other group's, where those would have too few coarse tiles of their
+  // own: all tiles in a fine launch of this form (n_lone = 0: no such table).
+  size_t lone = 0;
+  int n_lone = 0;
+  PairForm lone_form;
 };
 
 struct Chunk {
@@ -59,7 +109,15 @@ struct Chunk {
   int n_ew_tiles = 0;
   bool stream_w = true;      // no long list of bf16 weights whose rows end inside 128-byte lines
   bool fold_norm = false;    // the blocks of the first Gram launch add up the partial sums of squares themselves
-  std::vector<Group> groups;
+  std::vector<Group> groups; // one, or the matrices iterated as Eq. 2 is written and then those of the Gram route
+  // With a group of the Gram route: forms of the launches that pair a product of groups[0] with one of groups[1].
+  // pair[i][j]: kPair* of the first and of the second group (kPairNone: nothing is left to do there, or there is no second group).
+  bool paired = false;
+  PairForm pair[4][4];
+  // Where both groups have coarse symmetric tiles: one table of both for every pair of symmetric products, dealt as one.
+  // [first group's Gram product / another][second group's Gram product / another]
+  size_t shared_sym[2][2] = {};
+  int n_shared_sym = 0;
 };
 
 struct Plan {

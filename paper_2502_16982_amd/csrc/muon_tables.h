@@ -30,7 +30,7 @@ struct MatDesc {
   int32_t n_part;     // number of partials
   int32_t ew_tiles_c; // 64-wide tile columns in U's orientation (padded)
   float sqrt_max;     // sqrt(max(A, B))
-  int32_t pad_;
+  int32_t gram_route; // iterated on its Gram matrix (muon_plan.h)
   int64_t x_plane;    // split-bf16 path: elements from one bf16 plane of X / Xt[] to the next (0 otherwise)
 };
 
@@ -65,11 +65,15 @@ struct GemmProblem {
   const float* scal;  // per-matrix scalars (alpha source)
   int32_t K;
   int32_t ldl, ldr, n_part, ldet, ldc, ldct;
-  int32_t symmetric;  // output is symmetric: off-diagonal tiles are also stored mirrored into C
+  int32_t symmetric;  // output is symmetric: off-diagonal tiles are also stored mirrored into C.  kMirrored: it is so only up to
+                      // rounding (a product of two different matrices that commute), and tiles on the diagonal too put the
+                      // elements above the diagonal in the place of those below it
   int32_t diag_add;   // square output only: add the launch's diagonal constant to C[i][i] before rounding
   // split-bf16 launches (every matrix = sum of several bf16 planes): elements from one plane to the next
   int64_t l_plane, r_plane, et_plane, c_plane, ct_plane;
 };
+
+constexpr int kMirrored = 2;
 
 // One block's output tile.  Rows and columns are counted in units of kTileUnit elements, so that tiles of several
 // block shapes (and tiles shifted to end at the matrix edge) share one table format.
@@ -84,6 +88,7 @@ constexpr int kF32Tile = 64;       // block tile of the fp32 Newton-Schulz GEMM
 constexpr int kF32LongK = 4096;    // longest K whose four partial sums (of at most 1024 terms) are one accumulator each
 constexpr int kTileDiagonal = 1;   // GemmTile::flags: tile on the diagonal of a symmetric product: it is its own mirror
                                    // image, so only one of the two stores is made
+constexpr int kTileSecond = 2;     // a shared table of two sides (kernels_gemm_pair.hip): the tile is the second's
 struct GemmTile {
   int32_t prob;
   uint16_t r0, c0;    // first output row / column, in units of kTileUnit

@@ -1,0 +1,141 @@
+"""The Gram route of plain bf16 on the GPU: parity in every form of its launches, the same bits in any list, other numbers of
+iterations, coefficients that f16 cannot hold, the smallest norms, replays of a captured step.  Bar of O: half of plain bf16's (a
+numpy model of the arithmetic gives 0.35 to 0.45e-2 at these sides, written as Eq. 2 in bf16 0.7 to 1.1e-2)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2502_16982_amd import binding, workloads  # noqa: E402
+from tests import gpu_util as U  # noqa: E402
+from tests.gpu_util import table_sizes  # noqa: E402
+from tests.test_gpu_parity import assert_records  # noqa: E402
+
+TOL = 0.5 * U.TOL_BF16_FRO
+
+
+@pytest.fixture(scope="module")
+def dev():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    binding.lib()
+    return torch.device("cuda:0")
+
+
+def on_route(shapes):
+    p = binding.param_array(shapes, [1] * len(shapes), [1] * len(shapes))
+    ctx = binding.muon_plan_only(p, len(shapes), binding.MUON_BF16, binding.muon_workspace_bytes(p, len(shapes), binding.MUON_BF16, 0))
+    try:
+        return [bool(binding.muon_plan_describe(ctx, i)["gram_route"]) for i in range(len(shapes))]
+    finally:
+        binding.muon_destroy(ctx)
+
+
+@pytest.mark.parametrize("shapes,check", [
+    ([(384, 3072)], [0]),                                           # lone waves, 64-wide tiles
+    ([(2433, 640), (640, 2500), (513, 2561)], [0, 1, 2]),           # one padded row short of a tile, both orientations
+    ([(1024, 4096)] * 2 + [(4000, 1000)], [0, 2]),                  # 128-wide tiles
+    ([(1408, 3840)] * 10 + [(4000, 1409)] * 2, [0, 9, 10]),         # coarse tiles and strips, whose last holds a piece of the diagonal
+    ([(2560, 5200)] * 3, [1]),                                      # coarse tiles, the diagonal's with two operand panels
+])
+@pytest.mark.timeout(600)
+def test_parity_alone(dev, shapes, check):
+    assert all(on_route(shapes))
+    wl = workloads.custom("gram", shapes, seed_base=500)
+    assert_records(U.run_and_compare(wl, dev, check=check, steps=2, want_rms=True), TOL)
+
+
+@pytest.mark.parametrize("shapes,gram,other,coarse", [
+    ([(640, 2560)] * 2 + [(300, 200), (64, 64), (777, 777)], [0, 1], [2, 3, 4], False),
+    ([(1024, 1024)] * 30 + [(1024, 4096), (4096, 1024)], [30, 31], [0, 29], True),            # lone products in the fine launch
+    ([(1408, 1600)] * 8 + [(1300, 3700)] * 10 + [(3700, 1300)], [8, 18], [0, 7], True),
+])
+@pytest.mark.timeout(600)
+def test_parity_beside_matrices_of_the_other_route(dev, shapes, gram, other, coarse):
+    flags = on_route(shapes)
+    assert all(flags[i] for i in gram) and not any(flags[i] for i in other) and (table_sizes(shapes, "bf16", 1)[0] > 0) == coarse
+    wl = workloads.custom("gram_beside", shapes, seed_base=510)
+    assert_records(U.run_and_compare(wl, dev, check=gram, steps=2, want_rms=True), TOL)
+    assert_records(U.run_and_compare(wl, dev, check=other, steps=2, want_rms=True), U.TOL_BF16_FRO)
+
+
+@pytest.mark.parametrize("ns_steps", [4, 5])
+@pytest.mark.parametrize("shape,long", [((384, 3100), 130), ((2560, 640), 40), ((1300, 3700), 12)])
+def test_same_bits_in_any_list(dev, shape, long, ns_steps):
+    """Alone, in a few copies, in coarse tiles, beside matrices of the other route and in a workspace that holds a part of the list."""
+    wl = workloads.custom("gram_bits", [shape], seed_base=520)
+    first = workloads.make_matrix(wl, 0, dev)
+    rest = [workloads.make_matrix(workloads.custom("rest", [s], seed_base=521 + i), 0, dev) for i, s in enumerate([(1024, 1024), (300, 200)])]
+    hp = binding.default_hparams(lr=0.02, weight_decay=0.1, ns_steps=ns_steps)
+    results = []
+    for n, beside, parts in ((1, 0, 1), (3, 1, 1), (long, 0, 1), (long, 30, 1), (long, 0, 3)):
+        tensors = [tuple(t.clone() for t in first) for _ in range(n)] + [tuple(t.clone() for t in x) for x in rest for _ in range(beside)]
+        whole = binding.MuonStepper(tensors).workspace_bytes
+        st = binding.MuonStepper(tensors, max_workspace_bytes=0 if parts == 1 else whole // parts)
+        st.step(hp)
+        torch.cuda.synchronize()
+        results += [(n, beside, parts, i, tensors[i][0], tensors[i][2]) for i in sorted({0, n // 2, n - 1})]
+        st.close()
+    assert table_sizes([shape], "bf16", 1)[0] == 0 and table_sizes([shape] * long, "bf16", 1)[0] > 0
+    for n, beside, parts, i, w, m in results[1:]:
+        assert torch.equal(w, results[0][4]) and torch.equal(m, results[0][5]), (n, beside, parts, i)
+
+
+@pytest.mark.parametrize("ns_steps", [3, 4, 6, 7, 10])
+def test_numbers_of_iterations(dev, ns_steps):
+    """Three are iterated as Eq. 2 is written; the model gives 0.33, 0.45, 0.5 and 0.65e-2 for 4, 6, 7 and 10."""
+    wl = workloads.custom("gram_steps", [(512, 4096), (4096, 512), (200, 300)], seed_base=530)
+    recs = U.run_and_compare(wl, dev, hp_over={"ns_steps": ns_steps}, check=[0, 1])
+    assert_records(recs, U.TOL_BF16_FRO if ns_steps == 3 else TOL)
+
+
+def test_coefficients_that_f16_cannot_hold(dev):
+    """X grows a hundredfold and shrinks again, then three iterations: elements up to 100 times 2^13 are outside f16."""
+    paper = (3.4445, -4.7750, 2.0315)
+    sched = [(100.0, 0.0, 0.0), (0.01, 0.0, 0.0), paper, paper, paper]
+    wl = workloads.custom("gram_far", [(512, 4096), (4200, 512)], seed_base=540)
+    assert_records(U.run_and_compare(wl, dev, hp_over={"coeff_schedule": sched}), U.TOL_BF16_FRO)
+    textbook = [paper, paper, paper, (1.875, -1.25, 0.375), (1.875, -1.25, 0.375)]
+    assert_records(U.run_and_compare(wl, dev, hp_over={"coeff_schedule": textbook}), TOL)
+
+
+@pytest.mark.parametrize("g_std", [2e-21, 1e-12, 1e8])
+def test_smallest_and_largest_norms(dev, g_std):
+    """||U|| of 2e-18 (its reciprocal's square times 2^13 is outside fp32) up to 1e11."""
+    wl = workloads.custom("gram_norm", [(384, 3072)], w_dtype=torch.float32, g_dtype=torch.float32, g_std=g_std, seed_base=550)
+    assert_records(U.run_and_compare(wl, dev, hp_over={"eps": 0.0}), TOL)
+
+
+def test_captured_step_replays(dev):
+    wl = workloads.custom("gram_graph", [(512, 4096), (4096, 512), (640, 2560), (200, 300), (768, 768)], seed_base=560)
+    tensors = workloads.make_all(wl, dev)
+    hp, _ = U.hp_from(wl.hyper)
+    st = binding.MuonStepper(tensors)
+    side = torch.cuda.Stream(device=dev)
+    try:
+        side.wait_stream(torch.cuda.current_stream(dev))
+        st.step(hp, stream=side)
+        side.synchronize()
+        start = [tuple(t.clone() for t in trip) for trip in tensors]
+        eager = []
+        for _ in range(3):
+            st.step(hp, stream=side)
+            side.synchronize()
+            eager.append([(t[0].clone(), t[2].clone()) for t in tensors])
+        for t, s in zip(tensors, start):
+            t[0].copy_(s[0])
+            t[2].copy_(s[2])
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            st.step(hp, stream=side)
+        scratch = torch.zeros(1 << 16, device=dev)
+        for k in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            scratch.add_(1.0)
+            torch.cuda.synchronize()
+            for t, (w, m) in zip(tensors, eager[k]):
+                assert torch.equal(t[0], w) and torch.equal(t[2], m), k
+    finally:
+        st.close()

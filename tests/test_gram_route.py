@@ -1,0 +1,34 @@
+"""The Gram route of plain bf16 (two or three iterations at a time on the Gram matrix) without a GPU: its line and tables from the
+planner under sanitizers, and the LDS waits in the generated code of its kernels."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from tests import asm_lds_hazards as hz
+from tests.test_kmajor_asm_hazards import compile_to_asm
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def test_tables_of_the_gram_route(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not found")
+    exe = str(tmp_path / "gram_route")
+    build = subprocess.run([gxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-Wall", "-Wextra",
+                            os.path.join(ROOT, "paper_2502_16982_amd", "csrc", "muon_plan.cpp"), os.path.join(ROOT, "tests", "gram_route_main.cpp"), "-o", exe],
+                           capture_output=True, text=True)
+    assert build.returncode == 0, build.stdout + build.stderr
+    env = dict(os.environ, ASAN_OPTIONS="detect_leaks=1:abort_on_error=0:verify_asan_link_order=0")
+    run = subprocess.run([exe], capture_output=True, text=True, env=env, timeout=600)
+    assert run.returncode == 0 and "gram route ok" in run.stdout, run.stdout + run.stderr
+
+
+def test_generated_code_of_the_paired_kernels_waits_for_every_lds_read_it_uses(tmp_path_factory):
+    kernels = {k: v for k, v in hz.split_kernels(compile_to_asm(tmp_path_factory, "kernels_gemm_pair.hip")).items() if "ns_pair" in k}
+    assert len(kernels) == 9         # fine, 64-wide with two rings, lone waves, shared symmetric, coarse x {k-contiguous, K-major} x {bf16, f16}
+    for name, lines in kernels.items():
+        assert any("v_mfma_f32_32x32x16_f16" in t for _, t in lines) or "4Bf16" in name, name
+        assert hz.check_kernel(lines) == [], name
