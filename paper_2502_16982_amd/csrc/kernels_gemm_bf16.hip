@@ -34,6 +34,7 @@
 #include "gemm_tile256.h"
 #include "gemm_planes.h"
 #include "gemm_tile64.h"
+#include "gemm_ring128.h"
 
 namespace muon {
 namespace {
@@ -65,6 +66,17 @@ __global__ __launch_bounds__(256, PL == 3 ? 1 : 2) void ns_gemm_bf16_fine_kernel
   else
     gemm_tile_body<128, 128, 2, 2, 2, LKM>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add,
                                                __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+}
+
+// Each table entry as one block with a compute unit to itself.
+template <bool LKM>
+__global__ __launch_bounds__(256, 1) void ns_ring128_bf16_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles,
+                                                                 float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const GemmTile tile = load_tile(tiles, blockIdx.x);
+  const GemmProblem p = probs[tile.prob];
+  gemm_ring128_body<LKM>(p, tile.r0 * kTileUnit, tile.c0 * kTileUnit, (tile.flags & kTileDiagonal) != 0, smem, beta_acc, beta_e, alpha_idx, eps,
+                         diag_add);
 }
 
 // Each 128 x 128 table entry as four blocks of 64 x 64.  Block b: entry 8 (b / 32) + b % 8, so that an entry's quarters
@@ -172,6 +184,8 @@ hipError_t setup_pair() {
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_ring4_gemm_bf16_kernel<LKM, PL>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)(lds_few_quarters(PL) + kLdsFold64));
+  if (e == hipSuccess && PL == 1)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_ring128_bf16_kernel<LKM>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsRing128 + kLdsFold64));
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_gemm_bf16_kernel<LKM, PL>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)(PL > 1 ? lds_coarse(LKM, PL) : kLds512));
@@ -191,6 +205,9 @@ void launch_one(int coarse, int flags, const GemmProblem* probs, const GemmTile*
     ns_tile64_gemm_bf16_kernel<LKM, PL><<<(n_tiles + 7) / 8 * 32, 256,
                                           lds_quarters(PL) + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(
         probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, diag_add);
+  else if (PL == 1 && !coarse && (flags & kGemmRing128))
+    ns_ring128_bf16_kernel<LKM><<<n_tiles, 256, kLdsRing128 + (alpha_idx == kAlphaFromPartials ? kLdsFold64 : 0), s>>>(probs, tiles, beta_acc, beta_e,
+                                                                                                                     alpha_idx, eps, diag_add);
   else if (!coarse)
     ns_gemm_bf16_fine_kernel<LKM, PL><<<n_tiles, 256, lds_fine(PL), s>>>(probs, tiles, beta_acc, beta_e, alpha_idx, diag_add);
   else
@@ -229,7 +246,7 @@ hipError_t launch_gemm_bf16(int coarse, int flags, const GemmProblem* probs, con
                             float beta_e, int alpha_idx, double eps, float diag_add, int l_kmajor, int planes, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
   if (planes < 1 || planes > kMaxPlanes) return hipErrorInvalidValue;
-  if (alpha_idx == kAlphaFromPartials && (coarse || l_kmajor || !(flags & kGemmQuarters))) return hipErrorInvalidValue;
+  if (alpha_idx == kAlphaFromPartials && (coarse || l_kmajor || !(flags & (kGemmQuarters | kGemmRing128)))) return hipErrorInvalidValue;
 #define MUON_GEMM_CASE(K, P)                                                                                     \
   if ((l_kmajor != 0) == K && planes == P) launch_one<K, P>(coarse, flags, probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, diag_add, s)
   MUON_GEMM_CASE(false, 1);

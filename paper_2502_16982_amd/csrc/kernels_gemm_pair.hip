@@ -10,7 +10,9 @@
 // took 82 us per polynomial launch, from one table 70, where all of them as Eq. 2 take 69): a kernel with the K-major bodies too had 27 spilled registers and took a third
 // longer on every product.
 #include "gemm_tile256.h"
+#include "gemm_planes.h"
 #include "gemm_tile64.h"
+#include "gemm_ring128.h"
 
 namespace muon {
 namespace {
@@ -56,6 +58,21 @@ __global__ __launch_bounds__(256, 2) void ns_pair_fine_kernel(GemmSide x, GemmSi
   with_operands(s.kind, [&](auto lkm, auto in) {
     gemm_tile_body<128, 128, 2, 2, 2, decltype(lkm)::value, decltype(in), true>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add,
                                                                                 __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), (s.kind & kSideOutF16) != 0);
+  });
+}
+
+// One block of a compute unit per entry: as ns_ring128_bf16_kernel.
+__global__ __launch_bounds__(256, 1) void ns_pair_ring128_kernel(GemmSide x, GemmSide y, int blocks_x, double eps) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const bool first = (int)blockIdx.x < blocks_x;
+  const GemmSide s = pick_side(x, y, first);
+  const int t = first ? (int)blockIdx.x : (int)blockIdx.x - blocks_x;
+  if (t >= s.n_tiles) return;
+  const GemmTile tile = load_tile(s.tiles, t);
+  const GemmProblem p = s.probs[tile.prob];
+  with_operands(s.kind, [&](auto lkm, auto in) {
+    gemm_ring128_body<decltype(lkm)::value, decltype(in), true>(p, tile.r0 * kTileUnit, tile.c0 * kTileUnit, (tile.flags & kTileDiagonal) != 0, smem,
+                                                                s.beta_acc, s.beta_e, s.alpha_idx, eps, s.diag_add, (s.kind & kSideOutF16) != 0);
   });
 }
 
@@ -174,6 +191,9 @@ void launch_coarse(int flags, const GemmSide& x, hipStream_t s) {
 hipError_t gemm_pair_setup() {
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_pair_fine_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds128);
   if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_pair_ring128_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)(kLdsRing128 + kLdsFold64));
+  if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_pair_tile64_kernel<kRing64, 3>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(lds_ring64(kRing64) + kLdsFold64));
   if (e == hipSuccess)
@@ -192,7 +212,7 @@ hipError_t launch_gemm_pair(int coarse, int flags, const GemmSide& x, const Gemm
   if (x.n_tiles < 0 || y.n_tiles < 0) return hipErrorInvalidValue;
   if (x.n_tiles + y.n_tiles == 0) return hipSuccess;
   const bool fold = x.alpha_idx == kAlphaFromPartials || y.alpha_idx == kAlphaFromPartials;
-  if (fold && (coarse || !(flags & kGemmQuarters) || ((x.kind | y.kind) & kSideKMajor))) return hipErrorInvalidValue;
+  if (fold && (coarse || !(flags & (kGemmQuarters | kGemmRing128)) || ((x.kind | y.kind) & kSideKMajor))) return hipErrorInvalidValue;
   const size_t fold_lds = fold ? kLdsFold64 : 0;
   if (coarse) {
     for (const GemmSide* p : {&x, &y}) {
@@ -216,6 +236,9 @@ hipError_t launch_gemm_pair(int coarse, int flags, const GemmSide& x, const Gemm
   } else if (flags & kGemmQuarters) {
     const int bx = (x.n_tiles + 7) / 8 * 32;
     ns_pair_tile64_kernel<kRing64, 3><<<bx + (y.n_tiles + 7) / 8 * 32, 256, lds_ring64(kRing64) + fold_lds, s>>>(x, y, bx, eps);
+  } else if (flags & kGemmRing128) {
+    const int bx = (x.n_tiles + 7) / 8 * 8;
+    ns_pair_ring128_kernel<<<bx + y.n_tiles, 256, kLdsRing128 + fold_lds, s>>>(x, y, bx, eps);
   } else {
     const int bx = (x.n_tiles + 7) / 8 * 8;
     ns_pair_fine_kernel<<<bx + y.n_tiles, 256, kLds128, s>>>(x, y, bx);

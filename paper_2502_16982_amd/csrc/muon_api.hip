@@ -194,7 +194,7 @@ int check_step_args(const muon_ctx* ctx, const muon_param* params, int32_t n, co
 }
 
 int quarter_flags(bool quarters, int few) {
-  return quarters ? kGemmQuarters | (few == 2 ? kGemmSixteenths : few == 1 ? kGemmFewQuarters : 0) : 0;
+  return !quarters && few == 3 ? kGemmRing128 : quarters ? kGemmQuarters | (few == 2 ? kGemmSixteenths : few == 1 ? kGemmFewQuarters : 0) : 0;
 }
 
 // The products of a group's N iterations, in order.  coeff: a, b, c of every iteration.

@@ -78,7 +78,7 @@ hipError_t launch_momentum_norm_cast(const MatDesc* mats, MatPtrs* ptrs, const P
 hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, double eps, hipStream_t s);
 
 // a4-a6: grouped NT GEMM with fused epilogue.  alpha_idx: -1 none, 0 -> scal[0], 1 -> scal[1], kAlphaFromPartials (first
-// Gram product, kGemmQuarters launches only) -> what scal[1] has to be, from the partial sums of squares and eps; the block
+// Gram product, kGemmQuarters and kGemmRing128 launches only) -> what scal[1] has to be, from the partial sums of squares and eps; the block
 // of the first tile leaves scal[0] and scal[1] behind.  diag_add: constant
 // added to the diagonal of the outputs of problems that ask for it (GemmProblem::diag_add), bf16 kernel only.
 // coarse: 0 = every tile of the table is 128 x 128 (two blocks per compute unit); 1 = the table mixes 256 x 256 and,
@@ -88,12 +88,13 @@ hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, 
 // the hardware's dynamic block dispatch does better).
 // kGemmQuarters (coarse = 0): every entry of the table runs as four blocks, one per quarter of it.  kGemmFewQuarters
 // (with kGemmQuarters): with a longer ring; kGemmSixteenths (plain bf16, with kGemmQuarters): as sixteen blocks of one wave.
+// kGemmRing128 (coarse = 0, plain bf16, K >= 256): one block per entry, with a compute unit to itself.
 // kGemmLongK (fp32): needed where a problem of the launch has K > kF32LongK.
 // l_kmajor: every problem of the launch stores its L operand K-major (element (i, k) at L[k * ldl + i]).
 // planes: 1 = plain bf16; 2 or 3 = every matrix is a sum of that many bf16 planes (GemmProblem::*_plane strides); entries of a
 // coarse table then run as four 128 x 128 blocks each.
 constexpr int kAlphaFromPartials = 2;
-constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmQuarters = 4, kGemmLongK = 8, kGemmSixteenths = 16, kGemmFewQuarters = 32;
+constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmQuarters = 4, kGemmLongK = 8, kGemmSixteenths = 16, kGemmFewQuarters = 32, kGemmRing128 = 64;
 hipError_t launch_gemm_bf16(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
                             float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add, int l_kmajor, int planes,
                             hipStream_t s);

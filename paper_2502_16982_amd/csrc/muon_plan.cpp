@@ -339,6 +339,25 @@ int64_t entries_of_work(const std::vector<Load>& load, int64_t fixed = 0) {
   }
   return (total + longest - 1) / longest;
 }
+// Plain bf16: 128-wide blocks with a ring of four slabs (gemm_ring128.h) where every entry has a compute unit to itself, from where
+// 64-wide ones stop paying.  us per launch, 64-wide / 128-wide with two stages / with the ring, polynomial (entries) and apply product:
+// K = 256 180 9.5 / 9.7 / 10.0, 240 9.2 / 9.0 / 8.9; 384 180 11.2 / 11.7 / 11.6, 243 11.2 / 10.7 / 10.3; 512 150 11.9 / 12.4 / 11.8, 180
+// 12.1 / 12.6 / 12.0, 240 13.8 / 12.7 / 12.3, 144 9.6 / 10.5 / 9.8, 176 9.9 / 10.8 / 10.1, 208 11.6 / 10.8 / 10.3; 768 126 11.5 / 15.2 / 13.3, 147 13.8 /
+// 15.0 / 13.1, 252 16.9 / 15.4 / 14.3, 144 11.6 / 13.1 / 11.8, 180 12.2 / 13.7 / 11.9; 1024 108 12.0 / 16.0 / 13.7, 144 15.0 / 16.3 / 14.0, 252 19.3 /
+// 17.4 / 15.2, 192 14.0 / 15.4 / 13.0; 1408 66 12.6 / 19.3 / 15.2, 132 17.4 / 20.0 / 16.1, 198 22.0 / 20.9 / 16.8, 242 21.2 / 20.1 / 15.9; 2048 136 22.7
+// / 25.3 / 18.9; 2816 253 40.1 / 33.9 / 27.6; with more entries than compute units 512 260 15.6 / 14.2 / 18.2, 1408 264 24.9 / 22.8 / 27.8.
+constexpr int64_t kRingK = 256, kRingFewK = 768;   // shortest K of a launch; longest K from which fewer entries do
+bool runs_on_ring128(const std::vector<Load>& load, int blocks) {
+  int64_t count = 0, longest = 0;
+  for (const Load& l : load) {
+    if (l.k < kRingK) return false;
+    count += l.entries;
+    longest = std::max(longest, l.k);
+  }
+  const int64_t work = entries_of_work(load), b = std::max(blocks, 1);
+  if (count > b) return false;
+  return longest >= kRingFewK ? work > b / 2 + 8 : longest > kRingK && work > kFewFine;
+}
 bool runs_in_quarters(const std::vector<Load>& load, bool mc, int planes, int blocks) {
   const int64_t entries = entries_of_work(load);
   int64_t longest = 0, count = 0;
@@ -362,11 +381,11 @@ bool runs_in_quarters(const std::vector<Load>& load, bool mc, int planes, int bl
     }
     return false;
   }
-  if (mc) return entries <= kFewFine;
+  if (mc) return entries <= kFewFine && !runs_on_ring128(load, blocks);
   return entries <= kFewF32 || (entries > blocks && entries <= blocks + kLittleOverF32);
 }
 
-// Launches in quarters that leave most compute units with one block or none: 2 = each 32 x 32 as one wave of its
+// 3: 128-wide blocks with a ring of four slabs (runs_on_ring128).  Launches in quarters that leave most compute units with one block or none: 2 = each 32 x 32 as one wave of its
 // own (shortest chain of slabs; twice the operand traffic), 1 = 64 x 64 blocks with a ring of four slabs (two blocks on a
 // compute unit instead of three), 0 = with a ring of three.
 // Plain bf16, waves for the fewest entries, with K up to 1024 a few more, us per step, 0 / 1 / 2: 256^2 (3 and 4 entries) 58.5 / 57.4 /
@@ -390,6 +409,7 @@ int few_blocks(const std::vector<Load>& load, int planes, int blocks) {
     n += (size_t)l.entries;
     longest = std::max(longest, l.k);
   }
+  if (planes == 1 && runs_on_ring128(load, blocks)) return 3;
   if (planes == 1 && (n <= kFewest || (n <= kFewestShort && longest <= kShortK))) return 2;
   const int64_t work = entries_of_work(load), b = std::max(blocks, 1);
   if (planes > 1) return 4 * (int64_t)n <= b || (planes == 2 ? 5 * work <= b : 32 * work <= 5 * b) ? 1 : 0;
@@ -1007,7 +1027,7 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         for (int j = 0; j < 4; ++j) ch.pair[i][j] = pair_form(pair_sides[0], i, pair_sides[1], j, plan.coarse_blocks);
     }
     {
-      // Lists short enough for quarter blocks save the norm's own launch (about 4 us): every block adds up its matrix's
+      // Lists short enough for quarter blocks or the 128-wide ring save the norm's own launch (about 4 us): every block adds up its matrix's
       // partials while its first operands are on their way, at most four per thread, or per lane where it is a wave.  With
       // waves the norm's launch / the fold, us per step: 64 x 4000 (126 partials) 110.0 / 109.2, 64 x 8000 (252) 170.0 / 170.4, 256 x
       // 8000 (504) 185.0 / 186.1, 128 x 16000 (500) 279.6 / 281.6, 64 x 32000 (1000) 508.8 / 510.0.
@@ -1019,7 +1039,7 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
       for (int i = ch.first; i < ch.first + ch.count; ++i) most_parts = std::max(most_parts, h_mats[i].n_part);
       bool coarse = false;
       for (const Group& g : ch.groups) coarse = coarse || g.coarse.n_sym > 0;
-      ch.fold_norm = !coarse && (ch.paired ? first.quarters : ch.groups[0].fine.quarter_sym) && most_parts <= most_folded;
+      ch.fold_norm = !coarse && (ch.paired ? first.quarters || first.few == 3 : ch.groups[0].fine.quarter_sym || few == 3) && most_parts <= most_folded;
     }
   }
   if (cursor > tl.total) return MUON_E_WORKSPACE_TOO_SMALL;   // the layout bound is conservative; this cannot happen

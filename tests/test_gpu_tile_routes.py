@@ -272,3 +272,25 @@ def test_large_two_plane_polynomial_costs_what_the_gram_product_costs(dev):
     st.close()
     print("polynomial / Gram product:", sorted(ratios), flush=True)
     assert sorted(ratios)[2] < 1.15
+
+
+@pytest.mark.parametrize("shape,copies", [((256, 300), 64), ((384, 400), 30), ((1024, 1000), 7), ((1152, 1300), 2), ((1300, 3000), 2)])
+def test_same_bits_from_the_128_wide_ring(dev, shape, copies):
+    """Plain bf16: in lists of about one 128-wide entry per compute unit (the symmetric products, the apply product or both) blocks have a
+    ring of four slabs.  K of four slabs (the loop not run) and more, with and without the addend, the norm folded or not, tiles on
+    the diagonal; the same bits as alone and in a list too long for it."""
+    wl = workloads.custom("ring128", [shape], seed_base=347)
+    first = workloads.make_matrix(wl, 0, dev)
+    hp = binding.default_hparams(lr=0.02, weight_decay=0.1)
+    sym, _, app = table_sizes([shape], "bf16", 0)
+    results = []
+    for n in sorted({1, copies, 230 // sym, 250 // app, -(-260 // sym) * 2} - {0}):
+        tensors = [tuple(t.clone() for t in first) for _ in range(n)]
+        st = binding.MuonStepper(tensors)
+        for _ in range(2):
+            st.step(hp)
+        torch.cuda.synchronize()
+        results += [(n, i, st.read_update(i), tensors[i][0], tensors[i][2]) for i in sorted({0, n // 2, n - 1})]
+        st.close()
+    for n, i, o, w, m in results[1:]:
+        assert torch.equal(o, results[0][2]) and torch.equal(w, results[0][3]) and torch.equal(m, results[0][4]), (n, i)

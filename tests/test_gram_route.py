@@ -28,7 +28,15 @@ def test_tables_of_the_gram_route(tmp_path):
 
 def test_generated_code_of_the_paired_kernels_waits_for_every_lds_read_it_uses(tmp_path_factory):
     kernels = {k: v for k, v in hz.split_kernels(compile_to_asm(tmp_path_factory, "kernels_gemm_pair.hip")).items() if "ns_pair" in k}
-    assert len(kernels) == 9         # fine, 64-wide with two rings, lone waves, shared symmetric, coarse x {k-contiguous, K-major} x {bf16, f16}
+    assert len(kernels) == 10        # fine, 128-wide ring, 64-wide with two rings, lone waves, shared symmetric, coarse x {k-contiguous, K-major} x {bf16, f16}
     for name, lines in kernels.items():
         assert any("v_mfma_f32_32x32x16_f16" in t for _, t in lines) or "4Bf16" in name, name
+        assert hz.check_kernel(lines) == [], name
+
+
+def test_generated_code_of_the_128_wide_ring_waits_for_every_lds_read_it_uses(tmp_path_factory):
+    kernels = {k: v for k, v in hz.split_kernels(compile_to_asm(tmp_path_factory, "kernels_gemm_bf16.hip")).items() if "ns_ring128" in k}
+    assert len(kernels) == 2         # {k-contiguous, K-major}
+    for name, lines in kernels.items():
+        assert not any("scratch_" in t for _, t in lines), name          # no spills
         assert hz.check_kernel(lines) == [], name
