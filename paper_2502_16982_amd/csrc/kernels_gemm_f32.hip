@@ -339,13 +339,17 @@ hipError_t setup_f32() {
 }
 
 template <bool LONG>
-void launch_f32(int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc, float beta_e, int alpha_idx,
+void launch_f32(int flags, int tail, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc, float beta_e, int alpha_idx,
                 double eps, hipStream_t s) {
   if (flags & kGemmQuarters)
     ns_gemm_f32_kernel<true, LONG><<<(n_tiles + 7) / 8 * 32, 256, lds_bytes(true) + (alpha_idx == kAlphaFromPartials ? kLdsFold : 0), s>>>(
         probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps);
-  else
-    ns_gemm_f32_kernel<false, LONG><<<n_tiles, 256, lds_bytes(false), s>>>(probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps);
+  else {
+    ns_gemm_f32_kernel<false, LONG><<<n_tiles - tail, 256, lds_bytes(false), s>>>(probs, tiles, n_tiles - tail, beta_acc, beta_e, alpha_idx, eps);
+    if (tail > 0)
+      ns_gemm_f32_kernel<true, LONG><<<(tail + 7) / 8 * 32, 256, lds_bytes(true), s>>>(probs, tiles + (n_tiles - tail), tail, beta_acc, beta_e,
+                                                                                       alpha_idx, eps);
+  }
 }
 
 }  // namespace
@@ -355,12 +359,13 @@ hipError_t gemm_f32_setup() {
   return e != hipSuccess ? e : setup_f32<true>();
 }
 
-hipError_t launch_gemm_f32(int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc, float beta_e,
+hipError_t launch_gemm_f32(int flags, int tail, const GemmProblem* probs, const GemmTile* tiles, int n_tiles, float beta_acc, float beta_e,
                            int alpha_idx, double eps, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
+  if (tail < 0 || tail >= n_tiles) return hipErrorInvalidValue;
   if (alpha_idx == kAlphaFromPartials && !(flags & kGemmQuarters)) return hipErrorInvalidValue;
-  if (flags & kGemmLongK) launch_f32<true>(flags, probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, s);
-  else launch_f32<false>(flags, probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, s);
+  if (flags & kGemmLongK) launch_f32<true>(flags, tail, probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, s);
+  else launch_f32<false>(flags, tail, probs, tiles, n_tiles, beta_acc, beta_e, alpha_idx, eps, s);
   return hipGetLastError();
 }
 

@@ -344,7 +344,7 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
             MUON_TIMED(MUON_PROF_GRAM, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_n ? kGemmPersistent : 0) | quarter_flags(ts.quarter_sym, ts.few_sym), P(g.prob_gram[par]), T(ts.sym), ts.n_sym, 1.f, 0.f,
                                                         first ? (fold ? kAlphaFromPartials : 1) : -1, hp->eps, 0.f, 0, planes, s));
           else
-            MUON_TIMED(MUON_PROF_GRAM, launch_gemm_f32((ts.quarter_sym ? kGemmQuarters : 0) | (ts.long_n ? kGemmLongK : 0), P(g.prob_gram[par]), T(ts.sym), ts.n_sym, 1.f, 0.f,
+            MUON_TIMED(MUON_PROF_GRAM, launch_gemm_f32((ts.quarter_sym ? kGemmQuarters : 0) | (ts.long_n ? kGemmLongK : 0), ts.tail_sym, P(g.prob_gram[par]), T(ts.sym), ts.n_sym, 1.f, 0.f,
                                                        first ? (fold ? kAlphaFromPartials : 1) : -1, hp->eps, s));
         }
         for (int level = 1; level >= 0; --level) {
@@ -353,7 +353,7 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
           if (mc)
             MUON_TIMED(MUON_PROF_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | quarter_flags(ts.quarter_poly, ts.few_poly), P(g.prob_poly), T(ts.poly), ts.n_poly, c, b, -1, 0.0, a, 0, planes, s));
           else
-            MUON_TIMED(MUON_PROF_POLY, launch_gemm_f32((ts.quarter_poly ? kGemmQuarters : 0) | (ts.long_m ? kGemmLongK : 0), P(g.prob_poly), T(ts.poly), ts.n_poly, c, b, -1, 0.0, s));
+            MUON_TIMED(MUON_PROF_POLY, launch_gemm_f32((ts.quarter_poly ? kGemmQuarters : 0) | (ts.long_m ? kGemmLongK : 0), ts.tail_poly, P(g.prob_poly), T(ts.poly), ts.n_poly, c, b, -1, 0.0, s));
         }
         for (int level = 1; level >= 0; --level) {
           const TileSet& ts = level ? g.coarse : g.fine;
@@ -362,7 +362,7 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
             MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_bf16(level, (ts.strips ? kGemmStrips : 0) | (ts.persistent_m ? kGemmPersistent : 0) | quarter_flags(ts.quarter_apply, ts.few_apply), P(g.prob_apply[par * 2 + last]), T(ts.apply),
                                                               ts.n_apply, 1.f, a, first ? 0 : -1, 0.0, 0.f, 1, planes, s));
           else
-            MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_f32((ts.quarter_apply ? kGemmQuarters : 0) | (ts.long_m ? kGemmLongK : 0), P(g.prob_apply[par * 2 + last]), T(ts.apply), ts.n_apply, 1.f, a,
+            MUON_TIMED(MUON_PROF_APPLY_POLY, launch_gemm_f32((ts.quarter_apply ? kGemmQuarters : 0) | (ts.long_m ? kGemmLongK : 0), ts.tail_apply, P(g.prob_apply[par * 2 + last]), T(ts.apply), ts.n_apply, 1.f, a,
                                                              first ? 0 : -1, 0.0, s));
         }
       }

@@ -114,7 +114,8 @@ hipError_t launch_gemm_pair(int coarse, int flags, const GemmSide& x, const Gemm
 // Coarse symmetric products of both from one table; the sides' own tables are not used.
 hipError_t launch_gemm_shared(int flags, const GemmSide& x, const GemmSide& y, const GemmTile* tiles, int n_tiles, hipStream_t s);
 hipError_t gemm_f32_setup();
-hipError_t launch_gemm_f32(int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
+// tail: the last entries of a table of whole ones, as many, that run in quarters in a launch of their own.
+hipError_t launch_gemm_f32(int flags, int tail, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
                            float beta_acc, float beta_e, int alpha_idx, double eps, hipStream_t s);
 
 // a8: W <- W - lr*(scale*O + wd*W); also leaves per-tile sums of O^2 in the partials.

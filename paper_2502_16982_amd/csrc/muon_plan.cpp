@@ -385,6 +385,20 @@ bool runs_in_quarters(const std::vector<Load>& load, bool mc, int planes, int bl
   return entries <= kFewF32 || (entries > blocks && entries <= blocks + kLittleOverF32);
 }
 
+// fp32: entries beyond full rounds of whole ones (three to a compute unit) that run in quarters in a launch of their own, where they
+// are few and the round they would add is long.  us per apply product, with that round / with the second launch: 832 entries of K = 512
+// 43.3 / 40.8, 800 of 640 55.0 / 51.0, 832 of 1024 77.4 / 69.2; but 896 of 512 43.8 / 44.3, 900 of 640 53.3 / 57.3, 832 of 256 27.4 / 27.8.
+constexpr int64_t kTailK = 512;
+int tail_in_quarters(const std::vector<Load>& load, bool whole, bool long_k, int blocks) {
+  int64_t count = 0;
+  for (const Load& l : load) {
+    if (l.k < kTailK) return 0;
+    count += l.entries;
+  }
+  const int64_t places = (long_k ? 2 : 3) * (int64_t)std::max(blocks, 1), tail = count % places;
+  return whole && count > places && 4 * tail <= blocks ? (int)tail : 0;
+}
+
 // 3: 128-wide blocks with a ring of four slabs (runs_on_ring128).  Launches in quarters that leave most compute units with one block or none: 2 = each 32 x 32 as one wave of its
 // own (shortest chain of slabs; twice the operand traffic), 1 = 64 x 64 blocks with a ring of four slabs (two blocks on a
 // compute unit instead of three), 0 = with a ring of three.
@@ -947,6 +961,11 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
           ts.quarter_sym = runs_in_quarters(l_sym, mc, (int)planes, plan.coarse_blocks);
           ts.quarter_poly = runs_in_quarters(l_poly, mc, (int)planes, plan.coarse_blocks);
           ts.quarter_apply = runs_in_quarters(l_app, mc, (int)planes, plan.coarse_blocks);
+          if (!mc) {
+            ts.tail_sym = tail_in_quarters(l_sym, !ts.quarter_sym, hi_n > kF32LongK, plan.coarse_blocks);
+            ts.tail_poly = tail_in_quarters(l_poly, !ts.quarter_poly, hi_m > kF32LongK, plan.coarse_blocks);
+            ts.tail_apply = tail_in_quarters(l_app, !ts.quarter_apply, hi_m > kF32LongK, plan.coarse_blocks);
+          }
           if (mc) {
             ts.few_sym = few_blocks(l_sym, (int)planes, plan.coarse_blocks);
             ts.few_poly = few_blocks(l_poly, (int)planes, plan.coarse_blocks);

@@ -37,6 +37,7 @@ struct TileSet {
   // the launch, in plain bf16, runs persistent blocks that take the planner's static assignment of tiles
   bool persistent_n = false, persistent_m = false;
   bool long_n = false, long_m = false;    // fp32: some K (Gram product: n_pad; the other two: m_pad) is over kF32LongK
+  int tail_sym = 0, tail_poly = 0, tail_apply = 0;      // fp32: the last entries of a launch in whole entries that run in quarters behind it
   bool quarter_sym = false, quarter_poly = false, quarter_apply = false;   // fine launches that run as one block per quarter of an entry
   int few_sym = 0, few_poly = 0, few_apply = 0;   // quarters on the matrix cores: 1 with the longer ring, 2 (plain bf16) as one wave per 32 x 32;
                                                   // 3 (plain bf16, not in quarters): 128-wide with a ring of four slabs

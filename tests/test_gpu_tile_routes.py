@@ -294,3 +294,19 @@ def test_same_bits_from_the_128_wide_ring(dev, shape, copies):
         st.close()
     for n, i, o, w, m in results[1:]:
         assert torch.equal(o, results[0][2]) and torch.equal(w, results[0][3]) and torch.equal(m, results[0][4]), (n, i)
+
+
+def test_f32_bits_where_the_last_entries_run_in_quarters(dev):
+    """13 of 512 x 512: 832 entries of the apply product, 64 more than three per compute unit hold; one alone; 12, exactly one round."""
+    wl = workloads.custom("f32_tail", [(512, 512)], w_dtype=torch.float32, g_dtype=torch.float32, ns_dtype="f32", seed_base=349)
+    first = workloads.make_matrix(wl, 0, dev)
+    results = []
+    for n in (1, 12, 13):
+        tensors = [tuple(t.clone() for t in first) for _ in range(n)]
+        st = binding.MuonStepper(tensors, ns_dtype="f32")
+        st.step(binding.default_hparams(lr=0.02, weight_decay=0.1))
+        torch.cuda.synchronize()
+        results += [(n, i, tensors[i][0], tensors[i][2]) for i in sorted({0, n // 2, n - 1})]
+        st.close()
+    for n, i, w, m in results[1:]:
+        assert torch.equal(w, results[0][2]) and torch.equal(m, results[0][3]), (n, i)
