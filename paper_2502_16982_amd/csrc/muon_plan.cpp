@@ -988,7 +988,13 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         ts.n_poly = (int)deal_tiles(by_m, sym, sym_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.poly), steady_m ? slots : 0, level == 0);
         ts.n_apply = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply), steady_m ? slots : 0, level == 0);
       }
-      if (g.gram && g.coarse.n_sym > 0 && few_coarse_sym(coarse_own, (int)planes, plan.coarse_blocks)) {
+      // Where the other group has finished, a group's coarse tiles may be too few, or leave their rounds badly filled with a K that
+      // two-stage tiles handle well: all of them in a fine launch.  us per step, coarse / fine: 30 of 1024^2 with 3 of 1024 x 4096 (30
+      // tiles) 1613 / 1465, 12 of 1024 x 4096 (120) 1971 / 1905, 48 with 36 (360 tiles on 256 compute units) 4062 / 4036, 30 with 18 of 1408 x
+      // 3840 (324) 3607 / 3442.
+      constexpr double kLoneFill = 0.75, kLoneM = 1536;
+      if (g.gram && g.coarse.n_sym > 0 && (few_coarse_sym(coarse_own, (int)planes, plan.coarse_blocks) ||
+                                           (coarse_own.m <= kLoneM && coarse_own.fill(plan.coarse_blocks) < kLoneFill))) {
         std::vector<std::vector<GemmTile>> sym(np_);
         std::vector<std::vector<int>> sym_cuts(np_);
         size_t count = 0;

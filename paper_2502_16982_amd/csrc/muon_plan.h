@@ -98,8 +98,8 @@ struct Group {
   std::vector<int> members;                       // problem index -> matrix index in the caller's list
   size_t prob_gram[2] = {0, 0}, prob_poly = 0, prob_apply[4] = {0, 0, 0, 0};  // byte offsets ([parity], [parity * 2 + last])
   TileSet fine, coarse;
-  // Gram route: symmetric products that run without the other group's, where those would have too few coarse tiles of their
-  // own: all tiles in a fine launch of this form (n_lone = 0: no such table).
+  // Gram route: symmetric products that run without the other group's, where their own coarse tiles would be few or fill their rounds
+  // badly: all tiles in a fine launch of this form (n_lone = 0: no such table).
   size_t lone = 0;
   int n_lone = 0;
   PairForm lone_form;
