@@ -313,9 +313,13 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
   // bf16 path: X ping-pong index N & 1 (bit 1), transposed matrices in Xt[1], or Xt[0] when no iteration ran (bit 0)
   const int o_written = mc ? ((N & 1) << 1) | (N > 0 ? 1 : 0) : (N & 1);
   std::vector<double>& coeff = ctx->coeff;
-  coeff.resize(3 * (size_t)N);
-  for (int i = 0; i < 3 * N; ++i) coeff[i] = hp->coeff_schedule ? hp->coeff_schedule[i] : i % 3 == 0 ? hp->a : i % 3 == 1 ? hp->b : hp->c;
-  const bool gram = N >= kGramMinSteps && gram_coefficients_fit(coeff.data(), N);
+  bool gram = false;                 // (lists without matrices of the Gram route spend no host time on its coefficients)
+  for (const Chunk& ch : ctx->plan.chunks) gram = gram || ch.paired;
+  if (gram) {
+    coeff.resize(3 * (size_t)N);
+    for (int i = 0; i < 3 * N; ++i) coeff[i] = hp->coeff_schedule ? hp->coeff_schedule[i] : i % 3 == 0 ? hp->a : i % 3 == 1 ? hp->b : hp->c;
+    gram = N >= kGramMinSteps && gram_coefficients_fit(coeff.data(), N);
+  }
   const int o_sel = o_written | (gram ? ((N / 2) & 1) << 1 | 1 : o_written) << 2;       // N / 2 groups of iterations
 
   for (size_t ci = 0; ci < ctx->plan.chunks.size(); ++ci) {
