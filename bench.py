@@ -7,9 +7,9 @@ One "step" is one muon_step over the whole matrix list of the workload: momentum
 cast/orient, N Newton-Schulz iterations (three grouped GEMMs each) and the scaled weight-decayed update.
 Inputs are generated on the device before the timed region.  Prints ONE JSON line.
 
-The roofline object describes the dominant kernel (the bf16 MFMA GEMM of the Newton-Schulz products):
-nominal flops per launch = N*(4 m^2 n + 2 m^3) summed over matrices / launches per step, divided by the
-average launch duration measured with HIP events on the step's stream inside the timed region.
+The roofline object describes the dominant kernels (the MFMA GEMMs of the Newton-Schulz products): nominal flops per
+launch = N*(4 m^2 n + 2 m^3), Eq. 2 as it is written, summed over matrices / launches per step, divided by the
+average launch duration (executed_*: the flops that are issued, which symmetry and the Gram route make fewer) measured with HIP events on the step's stream inside the timed region.
 """
 from __future__ import annotations
 
@@ -120,6 +120,19 @@ def issued_ns_flops(wl, ns_steps, ns_dtype="bf16"):
     finally:
         binding.muon_destroy(ctx)
     return total
+
+
+def on_gram_route(wl):
+    """Whether plain bf16 iterates any matrix of the list on its Gram matrix."""
+    from paper_2502_16982_amd import binding
+    n = len(wl.shapes)
+    ns = binding.NS_DTYPES[wl.ns_dtype]
+    p = binding.param_array(wl.shapes, [1] * n, [1] * n)
+    ctx = binding.muon_plan_only(p, n, ns, binding.muon_workspace_bytes(p, n, ns, 0))
+    try:
+        return any(binding.muon_plan_describe(ctx, i)["gram_route"] for i in range(n))
+    finally:
+        binding.muon_destroy(ctx)
 
 
 def cpu_baseline(wl, budget_s=25.0):
@@ -241,7 +254,8 @@ def time_workload(name, steps, warmup, max_ws_gib, dev, ns_dtype=None):
     traffic, traffic_source = measured_traffic(wl.name, wl.ns_dtype)
     roofline = {"bound": "mfma" if bf16 else "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                 "frac": achieved / peak, "traffic": traffic, "traffic_source": traffic_source,
-                "kernel": "ns_gemm_bf16_kernel" if bf16 else "ns_gemm_f32_kernel",
+                "kernel": "ns_gemm_f32_kernel" if not bf16 else
+                          "ns_pair_sym_kernel, ns_pair_coarse_kernel, ns_gemm_bf16_kernel" if on_gram_route(wl) else "ns_gemm_bf16_kernel",
                 "avg_launch_ms": avg_launch_ms, "launches_per_step": gemm_launches / max(steps, 1),
                 "nominal_flops_per_launch": flops_per_launch,
                 "executed_tflops": executed * steps / (gemm_ms * 1e-3) / 1e12 if gemm_ms else 0.0,
