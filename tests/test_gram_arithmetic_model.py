@@ -36,19 +36,20 @@ def written(x, s):
 
 
 def gram_route(x, s, groups=(2, 3), mirror=mirrored):
+    """A product is L R^T and takes its addend transposed, as in the kernels: the same unless a matrix is not quite symmetric."""
     eye = torch.eye(len(x))
     for n, steps in enumerate(groups):
         first, last = n == 0, n == len(groups) - 1
         g = f16((x @ x.T) * (s * s if first else 1.0), SCALE_A)
-        q = p = f16(B * g + C * (g @ g) + A * eye, SCALE_P)
-        g = mirror(f16(mirror(f16(p @ g, SCALE_A)) @ p, SCALE_A))
+        q = p = f16(B * g.T + C * (g @ g.T) + A * eye, SCALE_P)
+        g = mirror(f16(mirror(f16(p @ g.T, SCALE_A)) @ p.T, SCALE_A))
         for j in range(1, steps):
-            d = f16(B * g + C * (g @ g), SCALE_P)
-            q = A * q + d @ q
+            d = f16(B * g.T + C * (g @ g.T), SCALE_P)
+            q = A * q.T + d @ q.T
             q = mirror(bf16(q) if first and j == steps - 1 else f16(q, SCALE_P))
             if j < steps - 1:
-                t = mirror(f16(A * g + d @ g, SCALE_A))
-                g = mirror(f16(A * t + t @ d, SCALE_A))
+                t = mirror(f16(A * g.T + d @ g.T, SCALE_A))
+                g = mirror(f16(A * t.T + t @ d.T, SCALE_A))
         x = q @ x * (s if first else 1.0)
         x = bf16(x) if last else f16(x, SCALE_X)
     return x
@@ -82,4 +83,4 @@ def test_groups_need_a_symmetric_gram_matrix():
     ref, x, s = exact(u), bf16(u), 1.0 / float(u.norm())
     err = [float((gram_route(x, s, mirror=m).double() - ref).norm() / ref.norm()) for m in (mirrored, lambda v: v)]
     print(err)
-    assert err[0] < 5e-3
+    assert err[0] < 5e-3 and err[1] > 2 * err[0]
