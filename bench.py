@@ -99,8 +99,8 @@ def executed_ns_flops(wl, ns_steps, ns_dtype="bf16"):
 
 def issued_ns_flops(wl, ns_steps, ns_dtype="bf16"):
     """What a step really issues: executed_ns_flops counts every product as Eq. 2 writes it; matrices of the Gram route run one
-    Gram and one apply product per group of two iterations (the last group of three where the number is odd) and 5 or 9
-    symmetric products of m x m."""
+    Gram, one polynomial and one apply product per group (the first iteration, groups of two, the last iteration where the number is
+    even) and four more symmetric products of m x m per group of two."""
     from paper_2502_16982_amd import binding
     n = len(wl.shapes)
     p = binding.param_array(wl.shapes, [1] * n, [1] * n)
@@ -111,7 +111,8 @@ def issued_ns_flops(wl, ns_steps, ns_dtype="bf16"):
         total = executed_ns_flops(wl, ns_steps, ns_dtype)
         if ns_steps < 4:
             return total
-        groups, small = ns_steps // 2, 5 * (ns_steps // 2) + 4 * (ns_steps % 2)
+        groups = ns_steps // 2 + 1
+        small = groups + 4 * (ns_steps - groups)
         for product, k_of, times in (("gram", "n_pad", groups), ("poly", "m_pad", small), ("apply", "m_pad", groups)):
             for level in (0, 1):
                 for mat, _, _, _, _, blocks in binding.muon_plan_tiles(ctx, 0, product, level):

@@ -101,10 +101,11 @@ int muon_default_hparams(muon_hparams* hp);
  * null).  ns_dtype selects the Newton-Schulz arithmetic: MUON_BF16 (bf16 operands, fp32 accumulation;
  * section 2.3 notes bf16 suffices), MUON_F32 (fp32 matrix instructions; meant for small matrices), or the split
  * forms MUON_BF16X2 / MUON_BF16X3 (fp32-class accuracy on the matrix cores, the "more accurate"
- * direction of section 2.2 at model sizes).  MUON_BF16 iterates wide matrices (min(rows, cols) of 384 and more, the other side
- * 8 times as long, down to twice as long from 2560 on) on their Gram matrix, two or three iterations at a time and in f16 scaled by
- * powers of two, where ns_steps is at least 4 and the coefficients keep everything in range: the same iteration, with a
- * third to a half of the rounding error.  The Newton-Schulz temporaries of all matrices are
+ * direction of section 2.2 at model sizes).  MUON_BF16 iterates wide matrices (shorter side, padded to a multiple of 128, of
+ * 384 and more, the other side 8 times as long, down to twice as long from 2560 on) on their Gram matrix, two iterations at a time
+ * and in f16 scaled by powers of two, where ns_steps is at least 4 and the coefficients keep everything in range: the same
+ * iteration, with no more rounding error (a third to a half on flat spectra and on inputs that fill a few directions, nearly the
+ * same where singular values decay).  The Newton-Schulz temporaries of all matrices are
  * kept resident when they fit in `max_bytes`; otherwise the list is processed in consecutive chunks
  * that reuse the workspace.  max_bytes == 0 means "no limit".  *out receives the number of bytes to
  * allocate (256-byte aligned device memory); it is never below the minimum that muon_init accepts.

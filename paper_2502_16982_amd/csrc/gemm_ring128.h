@@ -18,7 +18,7 @@ constexpr int kRing128 = 4;
 constexpr size_t kLdsRing128 = (size_t)kRing128 * 2 * 128 * ROWB;
 
 // K >= 256.  ADD: the product has an addend.
-template <bool LKM, typename IN, bool EITHER, bool ADD>
+template <bool LKM, typename IN, typename OUT, bool ADD>
 __device__ __forceinline__ void gemm_ring128_tile(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem, float beta_acc,
                                                   float beta_e, int alpha_idx, double eps, float diag_add, bool out_f16) {
   constexpr int BT = 128, NW = 4, F = 2, WT = 64, NST = kRing128;
@@ -188,13 +188,13 @@ __device__ __forceinline__ void gemm_ring128_tile(const GemmProblem& p, int row0
     if (diagonal) C = nullptr;
   }
   const int below = (row0 + wm * WT) - (col0 + wn * WT);        // rows minus columns of this wave's MFMA tile (i, j): below + 32 (i - j)
-  const bool mirrors = EITHER && !LKM && diagonal && p.symmetric == kMirrored;
+  const bool mirrors = kMayMirror<IN> && !LKM && diagonal && p.symmetric == kMirrored;
   auto slot = [&](int row, int chunk) -> u32x2* {
     return reinterpret_cast<u32x2*>(img + row * (2 * BT) + ((chunk ^ (row & 15)) * 16) + fh * 8);
   };
   u32x2 pk[F][F][4];
-  with_output_type<EITHER>(out_f16, [&](auto out) {
-    using OUT = decltype(out);
+  with_output_type<OUT>(out_f16, [&](auto out) {
+    using O = decltype(out);
 #pragma unroll
     for (int i = 0; i < F; ++i)
 #pragma unroll
@@ -203,7 +203,7 @@ __device__ __forceinline__ void gemm_ring128_tile(const GemmProblem& p, int row0
         for (int q = 0; q < 4; ++q) {
           float x[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = kTwoFactors<IN, OUT> ? beta_acc * (alpha * acc[i][j][4 * q + e]) : ab_acc * acc[i][j][4 * q + e];
+          for (int e = 0; e < 4; ++e) x[e] = ab_acc * acc[i][j][4 * q + e];
           if constexpr (ADD) {
             const u32x2 ev = *slot(wn * WT + 32 * j + fr, (wm * WT + 32 * i) / 8 + q);
             x[0] = fmaf(ab_e, IN::lo(ev.x), x[0]);
@@ -215,7 +215,7 @@ __device__ __forceinline__ void gemm_ring128_tile(const GemmProblem& p, int row0
 #pragma unroll
             for (int e = 0; e < 4; ++e) x[e] += (fr == 8 * q + 4 * fh + e) ? diag_add : 0.f;
           }
-          pk[i][j][q] = u32x2{OUT::pack(x[0], x[1]), OUT::pack(x[2], x[3])};
+          pk[i][j][q] = u32x2{O::pack(x[0], x[1]), O::pack(x[2], x[3])};
         }
   });
 
@@ -270,11 +270,11 @@ __device__ __forceinline__ void gemm_ring128_tile(const GemmProblem& p, int row0
 }
 
 // (one branch in front of the tile: a branch while fragment reads are in flight would have their registers copied before they land)
-template <bool LKM, typename IN = Bf16, bool EITHER = false>
+template <bool LKM, typename IN = Bf16, typename OUT = Bf16>
 __device__ __forceinline__ void gemm_ring128_body(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem, float beta_acc,
                                                   float beta_e, int alpha_idx, double eps, float diag_add, bool out_f16 = false) {
-  if (p.Et) gemm_ring128_tile<LKM, IN, EITHER, true>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps, diag_add, out_f16);
-  else gemm_ring128_tile<LKM, IN, EITHER, false>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps, diag_add, out_f16);
+  if (p.Et) gemm_ring128_tile<LKM, IN, OUT, true>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps, diag_add, out_f16);
+  else gemm_ring128_tile<LKM, IN, OUT, false>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps, diag_add, out_f16);
 }
 
 }  // namespace

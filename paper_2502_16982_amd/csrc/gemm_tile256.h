@@ -53,10 +53,11 @@ struct F16 {
   static __device__ __forceinline__ float lo(unsigned v) { return (float)__builtin_bit_cast(f16x2, v)[0]; }
   static __device__ __forceinline__ float hi(unsigned v) { return (float)__builtin_bit_cast(f16x2, v)[1]; }
 };
-// From bf16 to f16 (the first Gram product, with 1 / ||U||^2): one factor after the other, since their product can pass the range
-// of fp32 where the result is far inside it.
-template <typename IN, typename OUT>
-constexpr bool kTwoFactors = std::is_same_v<IN, Bf16> && std::is_same_v<OUT, F16>;
+// Type of the results where the launch says which (apply products of the Gram route).
+struct Any16 {};
+// Symmetric products in f16 are those of the Gram route, some of them kMirrored.
+template <typename IN>
+constexpr bool kMayMirror = std::is_same_v<IN, F16>;
 // The transpose of a 32 x 32 block of packed results on the matrix cores: `w` as the accumulators hold it (lane (r, h): column r,
 // rows 8q + 4h + e), the result with row r and those columns.  One times a 16-bit pattern and zeros added leave the pattern
 // as it is (but for -0), read as bf16 or not.
@@ -96,16 +97,12 @@ __device__ __forceinline__ void mirror_block(const Transposer& transposed, int f
     w[q] = u32x2{x, y};
   }
 }
-// f(Out{}) with the type of a product's results: bf16, or (EITHER) what the launch says.
-template <bool EITHER, typename F>
+// f(Out{}) with the type of a product's results.
+template <typename OUT, typename F>
 __device__ __forceinline__ void with_output_type(bool out_f16, F&& f) {
-  if constexpr (EITHER) {
-    if (out_f16) {
-      f(F16{});
-      return;
-    }
-  }
-  f(Bf16{});
+  if constexpr (!std::is_same_v<OUT, Any16>) f(OUT{});
+  else if (out_f16) f(F16{});
+  else f(Bf16{});
 }
 
 __device__ __forceinline__ float bf16_to_f32(u16 h) { return __uint_as_float(((unsigned)h) << 16); }
@@ -181,8 +178,8 @@ __device__ __forceinline__ int thread_index(int wave_id) {
   return (wave_id << 6) | (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
 }
 
-// IN: type of the operands and of the addend; the results are bf16, or with EITHER f16 where out_f16 says so.
-template <int BM, int BN, int WM_, int WN_, int NSTAGE, bool LKM, typename IN = Bf16, bool EITHER = false>
+// IN: type of the operands and of the addend; OUT: of the results, Any16: f16 where out_f16 says so, otherwise bf16.
+template <int BM, int BN, int WM_, int WN_, int NSTAGE, bool LKM, typename IN = Bf16, typename OUT = Bf16>
 __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmTile& tile, unsigned char* smem, float beta_acc,
                                                float beta_e, int alpha_idx, float diag_add, int wave_id, bool out_f16 = false) {
   constexpr int NW = WM_ * WN_, NT = NW * 64;
@@ -552,7 +549,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
   // kMirrored products, tiles that hold part of the diagonal (128 x 128 and strips): rows minus columns of this wave's MFMA tile
   // (i, j) is below + 32 (i - j); tiles below the diagonal are not written, those above it twice where both places lie
   // in the tile.
-  constexpr bool MIRRORS = EITHER && !LKM && BM != 256;
+  constexpr bool MIRRORS = kMayMirror<IN> && !LKM && BM != 256;
   const bool mirrors = MIRRORS && p.symmetric == kMirrored && row0 < col0 + BN && col0 < row0 + BM;
   const int below = (row0 + wm * WTM) - (col0 + wn * WTN);
   auto twice = [&](int i, int j) {
@@ -561,7 +558,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
   };
   auto combine = [&](auto has_e, auto out) {
     constexpr bool HAS_E = decltype(has_e)::value;
-    using OUT = decltype(out);
+    using O = decltype(out);
     u32x2 ev[2][4];
     if (HAS_E) {
 #pragma unroll
@@ -579,7 +576,7 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
       for (int q = 0; q < 4; ++q) {
         float x[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = kTwoFactors<IN, OUT> ? beta_acc * (alpha * acc[i][j][4 * q + e]) : ab_acc * acc[i][j][4 * q + e];
+        for (int e = 0; e < 4; ++e) x[e] = ab_acc * acc[i][j][4 * q + e];
         if (HAS_E) {
           const u32x2 e2 = ev[t & 1][q];
           x[0] = fmaf(ab_e, IN::lo(e2.x), x[0]);
@@ -591,14 +588,14 @@ __device__ __forceinline__ void gemm_tile_body(const GemmProblem& p, const GemmT
 #pragma unroll
           for (int e = 0; e < 4; ++e) x[e] += (fr == 8 * q + 4 * fh + e) ? diag_add : 0.f;
         }
-        pk[i][j][q].x = OUT::pack(x[0], x[1]);
-        pk[i][j][q].y = OUT::pack(x[2], x[3]);
+        pk[i][j][q].x = O::pack(x[0], x[1]);
+        pk[i][j][q].y = O::pack(x[2], x[3]);
         if (!MIRRORS || !mirrors) *reinterpret_cast<u32x2*>(slot_of(i, j, q)) = pk[i][j][q];   // this slot belongs to this lane alone
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  with_output_type<EITHER>(out_f16, [&](auto out) {
+  with_output_type<OUT>(out_f16, [&](auto out) {
     if (Et) combine(std::true_type{}, out); else combine(std::false_type{}, out);
   });
   if constexpr (MIRRORS) {
@@ -783,9 +780,9 @@ template <> struct DiagTwo<DiagWave3> {
   static constexpr int fa[9] = {0, 0, 1, 1, 2, 2, 3, 3, 4}, fc[9] = {0, 1, 0, 1, 0, 1, 0, 1, 1};
 };
 
-template <typename W, typename IN, bool EITHER, bool TWO>
+template <typename W, typename IN, bool TWO>
 __device__ __forceinline__ void diag_wave_body(const GemmProblem& p, int row0, unsigned char* smem, float beta_acc, float beta_e,
-                                               int alpha_idx, float diag_add, int tid, bool out_f16) {
+                                               int alpha_idx, float diag_add, int tid) {
   using W2 = DiagTwo<W>;
   constexpr int BM = 256, NW = 4, N = W::N, NA = W2::A::N, NF = TWO ? NA + W2::B::N : W::NF;
   constexpr int PI = BM / 8 / NW, LI = TWO ? 2 * PI : PI;          // DMA instructions per wave per panel, per slab
@@ -939,8 +936,6 @@ __device__ __forceinline__ void diag_wave_body(const GemmProblem& p, int row0, u
       sel[sx][t] = (__bf16)(fr == row ? 1.0f : 0.0f);
     }
   const bool add_diag = p.diag_add != 0;
-  with_output_type<EITHER>(out_f16, [&](auto out) {
-  using OUT = decltype(out);
 #pragma unroll
   for (int t = 0; t < N; ++t) {
     u32x2 pk[4];
@@ -948,7 +943,7 @@ __device__ __forceinline__ void diag_wave_body(const GemmProblem& p, int row0, u
     for (int q = 0; q < 4; ++q) {
       float x[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x[e] = kTwoFactors<IN, OUT> ? beta_acc * (alpha * acc[t][4 * q + e]) : ab_acc * acc[t][4 * q + e];
+      for (int e = 0; e < 4; ++e) x[e] = ab_acc * acc[t][4 * q + e];
       if (Et) {
         const u32x2 e2 = *reinterpret_cast<const u32x2*>(slot(W::bj[t], W::bi[t], q));
         x[0] = fmaf(ab_e, IN::lo(e2.x), x[0]);
@@ -960,12 +955,12 @@ __device__ __forceinline__ void diag_wave_body(const GemmProblem& p, int row0, u
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] += (fr == 8 * q + 4 * fh + e) ? diag_add : 0.f;
       }
-      pk[q].x = OUT::pack(x[0], x[1]);
-      pk[q].y = OUT::pack(x[2], x[3]);
-      if (!EITHER || W::bi[t] != W::bj[t]) *reinterpret_cast<u32x2*>(slot(W::bj[t], W::bi[t], q)) = pk[q];
+      pk[q].x = IN::pack(x[0], x[1]);
+      pk[q].y = IN::pack(x[2], x[3]);
+      if (!TWO || W::bi[t] != W::bj[t]) *reinterpret_cast<u32x2*>(slot(W::bj[t], W::bi[t], q)) = pk[q];
     }
-    if (EITHER && W::bi[t] == W::bj[t]) {
-      if (p.symmetric == kMirrored) mirror_block(Transposer(fr, fh), fr, fh, pk);
+    if (TWO && W::bi[t] == W::bj[t]) {           // two operands: kMirrored
+      mirror_block(Transposer(fr, fh), fr, fh, pk);
 #pragma unroll
       for (int q = 0; q < 4; ++q) *reinterpret_cast<u32x2*>(slot(W::bj[t], W::bi[t], q)) = pk[q];
     }
@@ -990,7 +985,6 @@ __device__ __forceinline__ void diag_wave_body(const GemmProblem& p, int row0, u
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  });
   __syncthreads();
   // the image leaves with coalesced 16-byte stores (image row c = output row row0 + c)
   {
@@ -1019,28 +1013,29 @@ __device__ __forceinline__ void diag_wave_body(const GemmProblem& p, int row0, u
   }
 }
 
-template <typename IN = Bf16, bool EITHER = false>
+// The results are of the operands' type.
+template <typename IN = Bf16>
 __device__ __forceinline__ void diag_tile_body(const GemmProblem& p, const GemmTile& tile, unsigned char* smem, float beta_acc,
-                                               float beta_e, int alpha_idx, float diag_add, int wave_id, bool out_f16 = false) {
+                                               float beta_e, int alpha_idx, float diag_add, int wave_id) {
   int tid = thread_index(wave_id);
   asm volatile("" : "+v"(tid));                  // see gemm_tile_body
   const int row0 = tile.r0 * kTileUnit;
-  if constexpr (EITHER && std::is_same_v<IN, F16>) {
+  if constexpr (kMayMirror<IN>) {
     if (p.symmetric == kMirrored) {
       switch (__builtin_amdgcn_readfirstlane(tid >> 6)) {
-        case 0: diag_wave_body<DiagWave0, IN, EITHER, true>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid, out_f16); break;
-        case 1: diag_wave_body<DiagWave1, IN, EITHER, true>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid, out_f16); break;
-        case 2: diag_wave_body<DiagWave2, IN, EITHER, true>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid, out_f16); break;
-        default: diag_wave_body<DiagWave3, IN, EITHER, true>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid, out_f16); break;
+        case 0: diag_wave_body<DiagWave0, IN, true>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid); break;
+        case 1: diag_wave_body<DiagWave1, IN, true>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid); break;
+        case 2: diag_wave_body<DiagWave2, IN, true>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid); break;
+        default: diag_wave_body<DiagWave3, IN, true>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid); break;
       }
       return;
     }
   }
   switch (__builtin_amdgcn_readfirstlane(tid >> 6)) {
-    case 0: diag_wave_body<DiagWave0, IN, EITHER, false>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid, out_f16); break;
-    case 1: diag_wave_body<DiagWave1, IN, EITHER, false>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid, out_f16); break;
-    case 2: diag_wave_body<DiagWave2, IN, EITHER, false>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid, out_f16); break;
-    default: diag_wave_body<DiagWave3, IN, EITHER, false>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid, out_f16); break;
+    case 0: diag_wave_body<DiagWave0, IN, false>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid); break;
+    case 1: diag_wave_body<DiagWave1, IN, false>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid); break;
+    case 2: diag_wave_body<DiagWave2, IN, false>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid); break;
+    default: diag_wave_body<DiagWave3, IN, false>(p, row0, smem, beta_acc, beta_e, alpha_idx, diag_add, tid); break;
   }
 }
 

@@ -56,8 +56,8 @@ __device__ __forceinline__ void land64(Frag64<LKM>& f) {
 }
 
 // The tile at (row0, col0); `diagonal`: it lies on the diagonal of a symmetric product (its own mirror image).
-// IN, EITHER, out_f16: as in gemm_tile_body.
-template <bool LKM, int NW, int NST, typename IN = Bf16, bool EITHER = false>
+// IN, OUT, out_f16: as in gemm_tile_body.
+template <bool LKM, int NW, int NST, typename IN = Bf16, typename OUT = Bf16>
 __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem,
                                                  float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add,
                                                  bool out_f16 = false) {
@@ -244,13 +244,8 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
     ldct = p.ldc;
     if (diagonal) C = nullptr;
   }
-  if (EITHER && std::is_same_v<IN, Bf16> && out_f16) {           // (see kTwoFactors)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = beta_acc * (alpha * acc[v]);
-  } else {
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] *= ab_acc;
-  }
+  for (int v = 0; v < 16; ++v) acc[v] *= ab_acc;
   if (has_e) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -295,14 +290,14 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
   };
   u32x2 pk[4];
-  with_output_type<EITHER>(out_f16, [&](auto out) {
-    using OUT = decltype(out);
+  with_output_type<OUT>(out_f16, [&](auto out) {
+    using O = decltype(out);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) pk[q] = u32x2{OUT::pack(acc[4 * q], acc[4 * q + 1]), OUT::pack(acc[4 * q + 2], acc[4 * q + 3])};
+    for (int q = 0; q < 4; ++q) pk[q] = u32x2{O::pack(acc[4 * q], acc[4 * q + 1]), O::pack(acc[4 * q + 2], acc[4 * q + 3])};
   });
   // kMirrored product, tile on the diagonal: the wave below it writes nothing, the one above it both blocks
-  const bool mirrors = EITHER && !LKM && diagonal && p.symmetric == kMirrored;
-  if constexpr (EITHER && !LKM) {
+  const bool mirrors = kMayMirror<IN> && !LKM && diagonal && p.symmetric == kMirrored;
+  if constexpr (kMayMirror<IN> && !LKM) {
     if (mirrors && wm <= wn) {
       const Transposer transposed(fr, fh);
       if (wm == wn) {

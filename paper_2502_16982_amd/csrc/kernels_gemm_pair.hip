@@ -1,7 +1,7 @@
 // Newton-Schulz products of lists with matrices iterated on their Gram matrix (the planner's gram_route).  A launch takes two
 // sides: the next product of the matrices iterated as Eq. 2 is written, and the next product of the others; either may be empty.
-// A side has its own tables, coefficients and types: operands bf16 or f16, results bf16 or f16, the L operand contiguous along
-// k or K-major.  The tiles, their pipelines and what bounds them are those of kernels_gemm_bf16.hip and gemm_tile64.h; what is new is that
+// A side has its own tables, coefficients and types: operands bf16 or f16, the L operand contiguous along k or K-major; symmetric
+// products write the type they read, apply products bf16 or f16.  The tiles, their pipelines and what bounds them are those of kernels_gemm_bf16.hip and gemm_tile64.h; what is new is that
 // two sides share a launch, since each alone leaves compute units idle in its last round and one chain of launches is shorter than
 // two.  us per step, all matrices as Eq. 2 / this: 4 of 1024^2 with 3 of 1024 x 4096 (fine launches) 485 / 442, twelve of those (coarse
 // ones) 4609 / 4065, 4 of 4096^2 with 3 of 4096 x 11008 12888 / 11096.
@@ -35,15 +35,15 @@ __device__ __forceinline__ GemmSide pick_side(const GemmSide& x, const GemmSide&
   return s;
 }
 
-// f(LKM, IN{}) for a side's operand layout and type
+// f(LKM, IN{}, OUT{}) for a side's operand layout and types
 template <typename F>
 __device__ __forceinline__ void with_operands(int kind, F&& f) {
   if (kind & kSideKMajor) {
-    if (kind & kSideInF16) f(std::true_type{}, F16{});
-    else f(std::true_type{}, Bf16{});
+    if (kind & kSideInF16) f(std::true_type{}, F16{}, Any16{});
+    else f(std::true_type{}, Bf16{}, Any16{});
   } else {
-    if (kind & kSideInF16) f(std::false_type{}, F16{});
-    else f(std::false_type{}, Bf16{});
+    if (kind & kSideInF16) f(std::false_type{}, F16{}, F16{});
+    else f(std::false_type{}, Bf16{}, Bf16{});
   }
 }
 
@@ -55,8 +55,8 @@ __global__ __launch_bounds__(256, 2) void ns_pair_fine_kernel(GemmSide x, GemmSi
   if (t >= s.n_tiles) return;
   const GemmTile tile = load_tile(s.tiles, t);
   const GemmProblem p = s.probs[tile.prob];
-  with_operands(s.kind, [&](auto lkm, auto in) {
-    gemm_tile_body<128, 128, 2, 2, 2, decltype(lkm)::value, decltype(in), true>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add,
+  with_operands(s.kind, [&](auto lkm, auto in, auto out) {
+    gemm_tile_body<128, 128, 2, 2, 2, decltype(lkm)::value, decltype(in), decltype(out)>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add,
                                                                                 __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), (s.kind & kSideOutF16) != 0);
   });
 }
@@ -70,8 +70,8 @@ __global__ __launch_bounds__(256, 1) void ns_pair_ring128_kernel(GemmSide x, Gem
   if (t >= s.n_tiles) return;
   const GemmTile tile = load_tile(s.tiles, t);
   const GemmProblem p = s.probs[tile.prob];
-  with_operands(s.kind, [&](auto lkm, auto in) {
-    gemm_ring128_body<decltype(lkm)::value, decltype(in), true>(p, tile.r0 * kTileUnit, tile.c0 * kTileUnit, (tile.flags & kTileDiagonal) != 0, smem,
+  with_operands(s.kind, [&](auto lkm, auto in, auto out) {
+    gemm_ring128_body<decltype(lkm)::value, decltype(in), decltype(out)>(p, tile.r0 * kTileUnit, tile.c0 * kTileUnit, (tile.flags & kTileDiagonal) != 0, smem,
                                                                 s.beta_acc, s.beta_e, s.alpha_idx, eps, s.diag_add, (s.kind & kSideOutF16) != 0);
   });
 }
@@ -90,8 +90,8 @@ __global__ __launch_bounds__(256, BLOCKS) void ns_pair_tile64_kernel(GemmSide x,
   if (on_diag && quarter == 2) return;           // below the diagonal: the mirror image of quarter 1
   const GemmProblem p = s.probs[tile.prob];
   const int row0 = tile.r0 * kTileUnit + 64 * (quarter >> 1), col0 = tile.c0 * kTileUnit + 64 * (quarter & 1);
-  with_operands(s.kind, [&](auto lkm, auto in) {
-    gemm_tile64_body<decltype(lkm)::value, 4, NST, decltype(in), true>(p, row0, col0, on_diag && quarter != 1, smem, s.beta_acc, s.beta_e,
+  with_operands(s.kind, [&](auto lkm, auto in, auto out) {
+    gemm_tile64_body<decltype(lkm)::value, 4, NST, decltype(in), decltype(out)>(p, row0, col0, on_diag && quarter != 1, smem, s.beta_acc, s.beta_e,
                                                                        s.alpha_idx, eps, s.diag_add, (s.kind & kSideOutF16) != 0);
   });
 }
@@ -108,15 +108,15 @@ __global__ __launch_bounds__(64) void ns_pair_tile32_kernel(GemmSide x, GemmSide
   const bool on_diag = (tile.flags & kTileDiagonal) != 0;
   if (on_diag && (part >> 2) > (part & 3)) return;   // below the diagonal: a mirror image
   const GemmProblem p = s.probs[tile.prob];
-  with_operands(s.kind, [&](auto lkm, auto in) {
-    gemm_tile64_body<decltype(lkm)::value, 1, kRing32, decltype(in), true>(p, tile.r0 * kTileUnit + 32 * (part >> 2), tile.c0 * kTileUnit + 32 * (part & 3),
+  with_operands(s.kind, [&](auto lkm, auto in, auto out) {
+    gemm_tile64_body<decltype(lkm)::value, 1, kRing32, decltype(in), decltype(out)>(p, tile.r0 * kTileUnit + 32 * (part >> 2), tile.c0 * kTileUnit + 32 * (part & 3),
                                                                            on_diag && (part >> 2) == (part & 3), smem, s.beta_acc, s.beta_e,
                                                                            s.alpha_idx, eps, s.diag_add, (s.kind & kSideOutF16) != 0);
   });
 }
 
-// One side, one block per entry or, persistent, per compute unit: as in ns_gemm_bf16_kernel.
-template <bool LKM, typename IN>
+// One side with f16 among its types, one block per entry or, persistent, per compute unit: as in ns_gemm_bf16_kernel.
+template <bool LKM, typename IN, typename OUT>
 __global__ __launch_bounds__(256, 1) void ns_pair_coarse_kernel(const GemmProblem* __restrict__ probs, const GemmTile* __restrict__ tiles, int n_tiles,
                                                                 float beta_acc, float beta_e, int alpha_idx, float diag_add, int out_f16) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -126,11 +126,11 @@ __global__ __launch_bounds__(256, 1) void ns_pair_coarse_kernel(const GemmProble
     const GemmProblem p = probs[tile.prob];
     const int shape = __builtin_amdgcn_readfirstlane(tile.shape);
     if (shape == kShape512x128) {
-      gemm_tile_body<512, 128, 4, 1, 2, LKM, IN, true>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id, out_f16 != 0);
+      gemm_tile_body<512, 128, 4, 1, 2, LKM, IN, OUT>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id, out_f16 != 0);
     } else if (!LKM && shape == kShape256Diag) {
-      if constexpr (!LKM) diag_tile_body<IN, true>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id, out_f16 != 0);
+      if constexpr (!LKM) diag_tile_body<IN>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id);
     } else {
-      gemm_tile_body<256, 256, 2, 2, 2, LKM, IN, true>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id, out_f16 != 0);
+      gemm_tile_body<256, 256, 2, 2, 2, LKM, IN, OUT>(p, tile, smem, beta_acc, beta_e, alpha_idx, diag_add, wave_id, out_f16 != 0);
     }
     __syncthreads();        // every wave has read its part of the LDS images: the next tile may overwrite them
   }
@@ -141,13 +141,12 @@ template <typename IN>
 __device__ __forceinline__ void coarse_sym_tile(const GemmSide& s, const GemmTile& tile, unsigned char* smem, int wave_id) {
   const GemmProblem p = s.probs[tile.prob];
   const int shape = __builtin_amdgcn_readfirstlane(tile.shape);
-  const bool out_f16 = (s.kind & kSideOutF16) != 0;
   if (shape == kShape512x128)
-    gemm_tile_body<512, 128, 4, 1, 2, false, IN, true>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add, wave_id, out_f16);
+    gemm_tile_body<512, 128, 4, 1, 2, false, IN, IN>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add, wave_id);
   else if (shape == kShape256Diag)
-    diag_tile_body<IN, true>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add, wave_id, out_f16);
+    diag_tile_body<IN>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add, wave_id);
   else
-    gemm_tile_body<256, 256, 2, 2, 2, false, IN, true>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add, wave_id, out_f16);
+    gemm_tile_body<256, 256, 2, 2, 2, false, IN, IN>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add, wave_id);
 }
 struct SharedArgs {
   GemmSide side[2];
@@ -175,14 +174,14 @@ __global__ __launch_bounds__(256, 1) void ns_pair_sym_kernel(SharedArgs args) {
   }
 }
 
-template <bool LKM, typename IN>
+template <bool LKM, typename IN, typename OUT>
 hipError_t setup_coarse() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_pair_coarse_kernel<LKM, IN>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds512);
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_pair_coarse_kernel<LKM, IN, OUT>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds512);
 }
-template <bool LKM, typename IN>
+template <bool LKM, typename IN, typename OUT>
 void launch_coarse(int flags, const GemmSide& x, hipStream_t s) {
   const int grid = gemm_coarse_blocks();
-  ns_pair_coarse_kernel<LKM, IN><<<(flags & kGemmPersistent) && x.n_tiles > grid ? grid : x.n_tiles, 256, (flags & kGemmStrips) ? kLds512 : kLds256, s>>>(
+  ns_pair_coarse_kernel<LKM, IN, OUT><<<(flags & kGemmPersistent) && x.n_tiles > grid ? grid : x.n_tiles, 256, (flags & kGemmStrips) ? kLds512 : kLds256, s>>>(
       x.probs, x.tiles, x.n_tiles, x.beta_acc, x.beta_e, x.alpha_idx, x.diag_add, (x.kind & kSideOutF16) != 0);
 }
 
@@ -201,16 +200,17 @@ hipError_t gemm_pair_setup() {
                             (int)(lds_ring64(kRing64Few) + kLdsFold64));
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_pair_sym_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds512);
-  if (e == hipSuccess) e = setup_coarse<false, Bf16>();
-  if (e == hipSuccess) e = setup_coarse<true, Bf16>();
-  if (e == hipSuccess) e = setup_coarse<false, F16>();
-  if (e == hipSuccess) e = setup_coarse<true, F16>();
+  if (e == hipSuccess) e = setup_coarse<true, Bf16, F16>();
+  if (e == hipSuccess) e = setup_coarse<false, F16, F16>();
+  if (e == hipSuccess) e = setup_coarse<true, F16, Any16>();
   return e;
 }
 
 hipError_t launch_gemm_pair(int coarse, int flags, const GemmSide& x, const GemmSide& y, double eps, hipStream_t s) {
   if (x.n_tiles < 0 || y.n_tiles < 0) return hipErrorInvalidValue;
   if (x.n_tiles + y.n_tiles == 0) return hipSuccess;
+  for (const GemmSide* p : {&x, &y})             // a symmetric product writes what it reads
+    if (!(p->kind & kSideKMajor) && ((p->kind & kSideInF16) != 0) != ((p->kind & kSideOutF16) != 0)) return hipErrorInvalidValue;
   const bool fold = x.alpha_idx == kAlphaFromPartials || y.alpha_idx == kAlphaFromPartials;
   if (fold && (coarse || !(flags & (kGemmQuarters | kGemmRing128)) || ((x.kind | y.kind) & kSideKMajor))) return hipErrorInvalidValue;
   const size_t fold_lds = fold ? kLdsFold64 : 0;
@@ -224,8 +224,9 @@ hipError_t launch_gemm_pair(int coarse, int flags, const GemmSide& x, const Gemm
         if (e != hipSuccess) return e;
         continue;
       }
-      if (p->kind & kSideKMajor) f16 ? launch_coarse<true, F16>(flags, *p, s) : launch_coarse<true, Bf16>(flags, *p, s);
-      else f16 ? launch_coarse<false, F16>(flags, *p, s) : launch_coarse<false, Bf16>(flags, *p, s);
+      if (!(p->kind & kSideKMajor)) launch_coarse<false, F16, F16>(flags, *p, s);
+      else if (f16) launch_coarse<true, F16, Any16>(flags, *p, s);
+      else launch_coarse<true, Bf16, F16>(flags, *p, s);
     }
   } else if (flags & kGemmSixteenths) {
     const int bx = (x.n_tiles + 7) / 8 * 128;

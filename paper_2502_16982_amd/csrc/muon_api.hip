@@ -217,29 +217,28 @@ void list_ops(const Group& g, int N, const double* coeff, bool gram, bool fold, 
   const int f16 = kSideInF16 | kSideOutF16;
   int par = 0;
   for (int it = 0; it < N; par ^= 1) {
-    const int steps = N - it == 3 ? 3 : 2;
+    const int steps = gram_group(it, N);
     const bool first = it == 0, last = it + steps == N;
     auto op = [&](int o) { return g.prob_ops + sizeof(GemmProblem) * (size_t)g.n_prob * (size_t)(o < kGramParityOps ? par * kGramParityOps + o : o); };
     float a = (float)coeff[3 * it], b = (float)coeff[3 * it + 1], c = (float)coeff[3 * it + 2];
-    out.push_back({kPairGram, g.prob_gram[par], first ? SA : SA / (SX * SX), 0.f, 0.f, first ? norm : -1, first ? kSideOutF16 : f16});
-    out.push_back({kPairSym, g.prob_poly, c * (SP / (SA * SA)), b * (SP / SA), a * SP, -1, f16});
-    out.push_back({kPairSym, op(kGramT), 1.f / SP, 0.f, 0.f, -1, f16});
-    out.push_back({kPairSym, op(kGramA), 1.f / SP, 0.f, 0.f, -1, f16});
-    for (int j = 1; j < steps; ++j) {
-      const double* k = coeff + 3 * (it + j);
+    if (first) {                     // U, in bf16: as it is written
+      out.push_back({kPairGram, g.prob_gram[par], 1.f, 0.f, 0.f, norm, 0});
+      out.push_back({kPairSym, g.prob_poly, c, b, a, -1, 0});
+    } else {
+      out.push_back({kPairGram, g.prob_gram[par], SA / (SX * SX), 0.f, 0.f, -1, f16});
+      out.push_back({kPairSym, g.prob_poly, c * (SP / (SA * SA)), b * (SP / SA), a * SP, -1, f16});
+    }
+    if (steps == 2) {
+      const double* k = coeff + 3 * (it + 1);
       a = (float)k[0], b = (float)k[1], c = (float)k[2];
+      out.push_back({kPairSym, op(kGramT), 1.f / SP, 0.f, 0.f, -1, f16});
+      out.push_back({kPairSym, op(kGramA), 1.f / SP, 0.f, 0.f, -1, f16});
       out.push_back({kPairSym, op(kGramD), c * (SP / (SA * SA)), b * (SP / SA), 0.f, -1, f16});
-      const bool end = j == steps - 1, to_bf16 = end && first;     // the first apply product multiplies U, in bf16
-      const float o = to_bf16 ? 1.f : SP;
-      out.push_back({kPairSym, op(!end ? kGramQMid : steps == 2 ? kGramQ : kGramQ3), o / (SP * SP), a * (o / SP), 0.f, -1, to_bf16 ? kSideInF16 : f16});
-      if (!end) {
-        out.push_back({kPairSym, op(kGramT3), 1.f / SP, a, 0.f, -1, f16});
-        out.push_back({kPairSym, op(kGramA3), 1.f / SP, a, 0.f, -1, f16});
-      }
+      out.push_back({kPairSym, op(kGramQ), 1.f / SP, a, 0.f, -1, f16});
     }
     it += steps;
-    out.push_back({kPairApply, op(kGramApply + par * 2 + last), (last ? 1.f : SX) / (first ? 1.f : SP * SX), 0.f, 0.f, first ? 0 : -1,
-                   kSideKMajor | (first ? 0 : kSideInF16) | (last ? 0 : kSideOutF16)});
+    out.push_back({kPairApply, steps == 2 ? op(kGramApply + par * 2 + last) : g.prob_apply[par * 2 + last], (last ? 1.f : SX) / (first ? 1.f : SP * SX),
+                   0.f, 0.f, first ? 0 : -1, kSideKMajor | (first ? 0 : kSideInF16) | (last ? 0 : kSideOutF16)});
   }
 }
 
@@ -320,7 +319,7 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
     for (int i = 0; i < 3 * N; ++i) coeff[i] = hp->coeff_schedule ? hp->coeff_schedule[i] : i % 3 == 0 ? hp->a : i % 3 == 1 ? hp->b : hp->c;
     gram = N >= kGramMinSteps && gram_coefficients_fit(coeff.data(), N);
   }
-  const int o_sel = o_written | (gram ? ((N / 2) & 1) << 1 | 1 : o_written) << 2;       // N / 2 groups of iterations
+  const int o_sel = o_written | (gram ? (gram_groups(N) & 1) << 1 | 1 : o_written) << 2;
 
   for (size_t ci = 0; ci < ctx->plan.chunks.size(); ++ci) {
     const Chunk& ch = ctx->plan.chunks[ci];

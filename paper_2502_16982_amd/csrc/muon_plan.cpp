@@ -544,7 +544,7 @@ bool folds_identity(const MatPlan& q, int ns_dtype) { return ns_dtype == MUON_BF
 // 576; 3072 x 6144 1181 / 1077, x 8448 1521 / 1244.  Beside other matrices: 4 of 512^2 and 3 of 1024 x 4096 413 / 351, 30 of 1024^2 and 6 of
 // 1408 x 5632 2425 / 2143, 48 of 1024^2 and 36 of 1024 x 4096 4609 / 4065; a few beside much more of the other kind, which the longer chain of launches
 // shows: 3000^2 and one of 1024 x 4096 873 / 941, 4 of 1536^2 and one of 640 x 5000 555 / 581.  Fewer rows than 384 gain alone (256 x
-// 4096 121 / 99) and lose beside anything longer.  (np >= 2 mp is also what the places of U and V need.)
+// 4096 121 / 99) and lose beside anything longer.
 bool gram_route(const MatPlan& q, int ns_dtype) {
   if (ns_dtype != MUON_BF16 || q.mp < 384) return false;
   const double least = q.mp >= 2560 ? 2.0 : q.mp >= 1280 ? 2.6 : q.mp >= 640 ? 4.0 : 8.0;
@@ -556,8 +556,9 @@ bool gram_coefficients_fit(const double* coeff, int steps) {
   // |a x + b x^3 + c x^5| over [0, s] is at an end or where the derivative vanishes.  A quarter is added for rounding.
   const double slack = 1.25, most = 65504.0 / slack;
   double s = 1.0;
-  for (int k = 0, left = steps; left > 0;) {
-    const int group = left == 3 ? 3 : 2;         // (left is never 1: see kGramMinSteps)
+  for (int k = 0; k < steps;) {
+    const int group = gram_group(k, steps);
+    const bool first = k == 0;                   // of the first, which is in bf16, X alone
     double q = 1.0;
     for (int j = 0; j < group; ++j, ++k) {
       const double a = coeff[3 * k], b = coeff[3 * k + 1], c = coeff[3 * k + 2], t = s * s;
@@ -575,11 +576,11 @@ bool gram_coefficients_fit(const double* coeff, int steps) {
       }
       q *= std::max(p, 1.0);
       // A and T = P A; D = P - a I and Q; the next X
-      const double worst = std::max({kGramScaleA * t * std::max(1.0, p), kGramScaleP * std::max(p + std::fabs(a), q), kGramScaleX * next});
+      const double worst = std::max(first ? 0.0 : std::max(kGramScaleA * t * std::max(1.0, p), kGramScaleP * std::max(p + std::fabs(a), q)),
+                                    kGramScaleX * next);
       if (!(worst <= most)) return false;        // not a number, too
       s = next;
     }
-    left -= group;
   }
   return true;
 }
@@ -834,11 +835,9 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
           }
         if (g.gram) {
           for (int par = 0; par < 2; ++par) {
-            unsigned char* const u = static_cast<unsigned char*>(xbuf[par ^ 1]);
-            void *const U = u, *const V = u + es * (size_t)q.mp * q.mp;      // both fit: np >= 2 mp
+            void* const U = xbuf[par ^ 1];
             struct { void *l, *r, *e, *c; } const ops[kGramParityOps] = {
-                {d.Bp, d.Ag, nullptr, U}, {U, d.Bp, nullptr, d.Ag}, {d.Ag, d.Ag, d.Ag, U}, {U, d.Bp, d.Bp, d.Ag},
-                {U, d.Bp, d.Bp, V}, {U, d.Ag, d.Ag, d.Bp}, {d.Bp, U, d.Bp, d.Ag}, {U, V, V, d.Ag}};
+                {d.Bp, d.Ag, nullptr, U}, {U, d.Bp, nullptr, d.Ag}, {d.Ag, d.Ag, d.Ag, U}, {U, d.Bp, d.Bp, d.Ag}};
             for (int op = 0; op < kGramParityOps; ++op) {
               GemmProblem s = reinterpret_cast<const GemmProblem*>(img.data() + g.prob_poly)[k];
               s.L = ops[op].l; s.R = ops[op].r; s.Et = ops[op].e; s.C = ops[op].c;

@@ -44,32 +44,32 @@ struct TileSet {
 };
 
 // The Gram route.  X' = P X with P = a I + b A + c A A, A = X X^T commutes with everything made of A, so the next iteration's Gram
-// matrix is P A P and two or three iterations in a row are one product with Q = P_k .. P_1:
-//     A = X X^T;  P = a I + b A + c A A, Q = P;  then for each further iteration
-//     T = P A, A = T P;  D = b A + c A A, P = a I + D;  Q = a Q + D Q;      and at the end of the group X = Q X
-// (the first T is P A with P as stored, the others are a A + D A and A = a T + T D).  Groups of two, the last of three where the
-// number of iterations is odd.  The iteration is the same; of m x m matrices it takes 5 and 9 products for a group instead of 2 and
-// 3, of m x n ones one Gram and one apply product instead of two or three of each.
-// Everything but the first operands (U, bf16 of any magnitude, and the Q that multiplies it) and the last results (O) is held in
-// f16, scaled by a power of two: as wide as bf16, at the same rate, with 8 times its precision, which the route needs: an error of A
-// is amplified a^2-fold by every iteration of a group.  Error of O against 64 bits (numpy model, N = 5; Gaussian, with outliers, and
-// singular values that fall like 1/i): 128 x 256 0.90e-2, 1.12e-2, 1.63e-2 written as Eq. 2 in bf16, 0.41e-2, 0.65e-2, 1.30e-2 here; 1024
-// x 4096 0.67e-2, 0.75e-2 and 0.35e-2, 0.31e-2.  Groups of four and five lose small singular values to the rounding of A.
+// matrix is P A P and two iterations in a row are one product with Q = P_2 P_1:
+//     A = X X^T;  P = a I + b A + c A A;  T = P A, A = T P;  D = b A + c A A;  Q = a P + D P;  X = Q X
+// (the second iteration's a, b, c from D on).  Of m x m matrices a group takes 5 products instead of 2, of m x n ones one Gram and one
+// apply product instead of two of each.  The first iteration is as it is written and in bf16: U is bf16 of any magnitude.  Then come
+// groups of two, and at the end a single iteration where the number of iterations is even (gram_group).
+// Everything between the first iteration and O is held in f16, scaled by a power of two: as wide as bf16, at the same rate, with 8 times its
+// precision, which the route needs.  The identity that Q carries is what limits it: directions outside the range of X put
+// a^2 = 12 on Q's diagonal where the directions that matter need values near 1.  Error of O against 64 bits (model of the arithmetic, N =
+// 5, 384 x 3072; all of Eq. 2 in bf16 / groups of two and three from the first iteration on / these): Gaussian 1.4, 0.39, 0.38e-2; U
+// zero outside 1 column 1.9, 6.2, 0.80e-2, 16 columns 1.2, 4.8, 0.66e-2, 96 columns 1.2, 4.1, 0.66e-2; singular values that fall like 1 / i
+// 3.0, 2.5, 2.4e-2; equal columns 1.9, 6.6, 0.85e-2.  Groups of two from the first iteration on (its Q in bf16) 1.9e-2 with two columns, where
+// Eq. 2 has 1.4.
 // f16 holds 65504: coefficients under which a bound on some matrix could pass that (gram_coefficients_fit) take Eq. 2's products.
 enum GramOp : int {
-  kGramT = 0,      // T = Bp Ag -> U                    (U, V: m x m matrices in the other buffer of the iterate)
+  kGramT = 0,      // T = Bp Ag -> U                    (U: an m x m matrix in the other buffer of the iterate)
   kGramA,          // A = U Bp -> Ag
   kGramD,          // D from Ag -> U
-  kGramQ,          // Q = a Bp + U Bp -> Ag              (last of a group of two)
-  kGramQMid,       // Q = a Bp + U Bp -> V
-  kGramT3,         // T = a Ag + U Ag -> Bp
-  kGramA3,         // A = a Bp + Bp U -> Ag
-  kGramQ3,         // Q = a V + U V -> Ag                (last of a group of three)
-  kGramParityOps   // each of the above for the two places of U and V
+  kGramQ,          // Q = a Bp + U Bp -> Ag
+  kGramParityOps   // each of the above for the two places of U
 };
 constexpr int kGramApply = 2 * kGramParityOps;       // X = Ag X: [parity * 2 + last]
 constexpr int kGramOps = kGramApply + 4;
 constexpr int kGramMinSteps = 4;                     // fewer iterations have nothing to gain
+// Iterations of the group that starts with iteration `it` of n, and the number of groups.
+inline int gram_group(int it, int n) { return it > 0 && n - it >= 2 ? 2 : 1; }
+inline int gram_groups(int n) { return n / 2 + 1; }
 // Powers of two by which the f16 matrices are larger than what they stand for: A and T; P, D and Q; X.
 constexpr float kGramScaleA = 8192.f, kGramScaleP = 512.f, kGramScaleX = 8192.f;
 bool gram_route(const MatPlan& q, int ns_dtype);

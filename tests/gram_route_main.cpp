@@ -51,7 +51,7 @@ static void walk(const std::vector<muon_param>& p, size_t cap) {
       const MatPlan& q = plan.mats[g.members[k]];
       const MatDesc& d = mats[g.members[k]];
       const size_t ab = 2 * (size_t)q.mp * q.mp, xb = 2 * (size_t)q.mp * q.np;
-      CHECK(2 * ab <= xb);
+      CHECK(ab <= xb);
       auto in = [](const void* v, size_t n, const void* from, size_t room) {
         const uintptr_t a = (uintptr_t)v, f = (uintptr_t)from;
         return a >= f && a + n <= f + room;
@@ -133,6 +133,16 @@ int main() {
     walk(p, 0);
     walk(p, 1);                       // one matrix at a time
     walk(p, (size_t)64 << 20);
+  }
+  // groups: one iteration as it is written, twos, and one where one is left
+  for (int n = kGramMinSteps; n <= 40; ++n) {
+    int it = 0, count = 0;
+    for (; it < n; ++count) {
+      const int k = gram_group(it, n);
+      CHECK(k == (it == 0 || it == n - 1 ? 1 : 2));
+      it += k;
+    }
+    CHECK(it == n && count == gram_groups(n));
   }
   // coefficients: the paper's at any number of steps; large ones, and ones that only grow on the way
   std::vector<double> c;

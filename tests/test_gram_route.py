@@ -1,4 +1,4 @@
-"""The Gram route of plain bf16 (two or three iterations at a time on the Gram matrix) without a GPU: its line and tables from the
+"""The Gram route of plain bf16 (two iterations at a time on the Gram matrix) without a GPU: its line and tables from the
 planner under sanitizers, and the LDS waits in the generated code of its kernels."""
 import os
 import shutil
@@ -28,9 +28,9 @@ def test_tables_of_the_gram_route(tmp_path):
 
 def test_generated_code_of_the_paired_kernels_waits_for_every_lds_read_it_uses(tmp_path_factory):
     kernels = {k: v for k, v in hz.split_kernels(compile_to_asm(tmp_path_factory, "kernels_gemm_pair.hip")).items() if "ns_pair" in k}
-    assert len(kernels) == 10        # fine, 128-wide ring, 64-wide with two rings, lone waves, shared symmetric, coarse x {k-contiguous, K-major} x {bf16, f16}
+    assert len(kernels) == 9         # fine, 128-wide ring, 64-wide with two rings, lone waves, shared symmetric, coarse in f16, K-major coarse from bf16 and f16
     for name, lines in kernels.items():
-        assert any("v_mfma_f32_32x32x16_f16" in t for _, t in lines) or "4Bf16" in name, name
+        assert any("v_mfma_f32_32x32x16_f16" in t for _, t in lines) or "Lb1E" in name and "4Bf16" in name, name
         assert hz.check_kernel(lines) == [], name
 
 
