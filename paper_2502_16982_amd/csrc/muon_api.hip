@@ -250,33 +250,41 @@ int enqueue_paired(muon_ctx* ctx, const Chunk& ch, const muon_hparams* hp, const
   while (at[0] < ops[0].size() || at[1] < ops[1].size()) {
     const GroupOp* op[2];
     for (int i = 0; i < 2; ++i) op[i] = at[i] < ops[i].size() ? &ops[i][at[i]] : nullptr;
-    // An apply product in coarse tiles shares no launch with a symmetric product (kernels of their own): the other group waits
-    // and has its symmetric product beside the next one.
-    if (op[0] && op[1] && (op[0]->product == kPairApply) != (op[1]->product == kPairApply)) {
-      const int i = op[1]->product == kPairApply;
-      if (ch.groups[i].coarse.n_apply > 0) op[i ^ 1] = nullptr;
+    // An apply product in coarse tiles shares its launch with a product of the other group that is all fine tiles and not too many.
+    // Otherwise it runs alone and a symmetric product of the other group waits for the next one of this.
+    int applied = -1;                // group of that apply product
+    bool beside = false;
+    for (int i = 0; i < 2 && op[0] && op[1] && applied < 0; ++i)
+      if (op[i]->product == kPairApply && ch.groups[i].coarse.n_apply > 0) {
+        beside = ch.beside[i ^ 1][op[i ^ 1]->product];
+        if (beside || op[i ^ 1]->product != kPairApply) applied = i;
+      }
+    for (int i = 0; i < 2; ++i) {
+      if (applied >= 0 && i != applied && !beside) op[i] = nullptr;
+      at[i] += op[i] ? 1 : 0;
     }
-    for (int i = 0; i < 2; ++i) at[i] += op[i] ? 1 : 0;
     const int product[2] = {op[0] ? op[0]->product : kPairNone, op[1] ? op[1]->product : kPairNone};
     const PairForm& form = ch.pair[product[0]][product[1]];
     const int timed_as = product[1] == kPairApply || product[0] == kPairApply ? MUON_PROF_APPLY_POLY
                          : product[1] == kPairGram || product[0] == kPairGram ? MUON_PROF_GRAM : MUON_PROF_POLY;
-    // a symmetric product by itself, with too few coarse tiles: all of it in a fine launch
-    const bool lone = !op[0] && op[1] && product[1] == kPairSym && ch.groups[1].n_lone > 0;
+    // a symmetric product with too few coarse tiles and no other beside it: all of it in the fine launch
+    const bool lone = op[1] && product[1] == kPairSym && ch.groups[1].n_lone > 0 && (!op[0] || product[0] == kPairApply);
     const bool both_sym = op[0] && op[1] && product[0] != kPairApply && product[1] != kPairApply;
-    for (int level = lone ? 0 : 1; level >= 0; --level) {
+    for (int level = lone && !beside ? 0 : 1; level >= 0; --level) {
       GemmSide side[2] = {};
       int64_t longest[2] = {0, 0};
       bool strips = false;
       for (int i = 0; i < 2; ++i) {
         side[i].alpha_idx = -1;
-        if (!op[i]) continue;
+        const bool guest = beside && i != applied;            // all of it in the coarse launch
+        if (!op[i] || (guest && level == 0)) continue;
         const Group& g = ch.groups[i];
-        const TileSet& ts = level ? g.coarse : g.fine;
+        const TileSet& ts = level && !guest ? g.coarse : g.fine;
         const bool gram_product = product[i] == kPairGram, apply = product[i] == kPairApply;
-        side[i].n_tiles = lone ? g.n_lone : gram_product ? ts.n_sym : apply ? ts.n_apply : ts.n_poly;
+        const bool from_lone = lone && i == 1;
+        side[i].n_tiles = from_lone ? g.n_lone : gram_product ? ts.n_sym : apply ? ts.n_apply : ts.n_poly;
         if (side[i].n_tiles == 0) continue;
-        side[i].tiles = reinterpret_cast<const GemmTile*>(ctx->ws + (lone ? g.lone : gram_product ? ts.sym : apply ? ts.apply : ts.poly));
+        side[i].tiles = reinterpret_cast<const GemmTile*>(ctx->ws + (from_lone ? g.lone : gram_product ? ts.sym : apply ? ts.apply : ts.poly));
         side[i].probs = reinterpret_cast<const GemmProblem*>(ctx->ws + op[i]->probs);
         side[i].beta_acc = op[i]->beta_acc;
         side[i].beta_e = op[i]->beta_e;
@@ -287,11 +295,16 @@ int enqueue_paired(muon_ctx* ctx, const Chunk& ch, const muon_hparams* hp, const
         strips = strips || ts.strips;
       }
       if (side[0].n_tiles + side[1].n_tiles == 0) continue;
-      const PairForm& fine_form = lone ? ch.groups[1].lone_form : form;
+      const PairForm& fine_form = beside ? ch.pair[applied == 0 ? kPairApply : kPairNone][applied == 1 ? kPairApply : kPairNone]
+                                  : lone ? ch.groups[1].lone_form[op[0] != nullptr] : form;
       const int flags = level ? (strips ? kGemmStrips : 0) | (form.persistent ? kGemmPersistent : 0) : quarter_flags(fine_form.quarters, fine_form.few);
       if (level && both_sym && ch.n_shared_sym > 0) {
         const size_t tiles = ch.shared_sym[product[0] != kPairGram][product[1] != kPairGram];
         MUON_TIMED(timed_as, launch_gemm_shared(flags, side[0], side[1], reinterpret_cast<const GemmTile*>(ctx->ws + tiles), ch.n_shared_sym, s));
+        continue;
+      }
+      if (level && beside) {
+        MUON_TIMED(timed_as, launch_gemm_beside(flags, side[applied], side[applied ^ 1], s));
         continue;
       }
       const int x = longest[1] > longest[0];     // the longer K loops start first

@@ -436,16 +436,36 @@ struct PairSide {
   std::vector<std::vector<GemmTile>> coarse_sym;       // and the coarse tiles of its symmetric products
   std::vector<std::vector<int>> coarse_cuts;
   std::vector<int64_t> w_n, w_m;
+  std::vector<Load> lone;                               // its lone table
   int64_t lo[4] = {kMaxDim, kMaxDim, kMaxDim, kMaxDim}, hi[4] = {};
 };
-PairForm pair_form(const PairSide& x, int px, const PairSide& y, int py, int blocks) {
-  std::vector<Load> load = x.load[px];
-  load.insert(load.end(), y.load[py].begin(), y.load[py].end());
+PairForm fine_form(std::vector<Load> load, const std::vector<Load>& more, int blocks) {
+  load.insert(load.end(), more.begin(), more.end());
   PairForm f;
-  f.persistent = 2 * std::max(x.hi[px], y.hi[py]) <= 3 * std::min(x.lo[px], y.lo[py]);
   f.quarters = runs_in_quarters(load, true, 1, blocks);
   f.few = few_blocks(load, 1, blocks);
   return f;
+}
+PairForm pair_form(const PairSide& x, int px, const PairSide& y, int py, int blocks) {
+  PairForm f = fine_form(x.load[px], y.load[py], blocks);
+  f.persistent = 2 * std::max(x.hi[px], y.hi[py]) <= 3 * std::min(x.lo[px], y.lo[py]);
+  return f;
+}
+
+// Whether a product in 128-wide blocks shares a launch with an apply product in coarse tiles (`g`'s): where the compute units that the
+// last round of those leaves idle can take it.  A coarse tile takes about 1.65 us per slab and 8, a block 0.3 and 5.  Step, in parts of the
+// one without the Gram route, alone / beside: 3000^2 with one of 1024 x 4096 (144 tiles; 36 and 256 blocks) 1.085 / 1.030, 4 of 1536^2 with
+// one of 640 x 5000 (144; 15 and 200) 1.048 / 1.031, 4 of 1024^2 with 3 of 1024 x 4096 (192; 256) 0.999 / 0.994, three iterations 1.11 / 1.08;
+// but 48 of 1024^2 with 4 of 1024 x 4096 (768, full rounds; 144) 1.011 / 1.026, 8 of 2048^2 with 2 (512; 72) 1.010 / 1.032.
+bool fits_beside(const Group& g, const std::vector<Load>& load, int blocks) {
+  const int64_t b = std::max(blocks, 1), rest = g.coarse.n_apply % b;
+  double need = 0.0;
+  int64_t entries = 0;
+  for (const Load& l : load) {
+    entries += l.entries;
+    need += (double)l.entries * (0.3 * (double)l.k / 64.0 + 5.0);
+  }
+  return rest > 0 && entries > 0 && entries <= b && need <= 1.25 * (double)(b - rest) * (1.65 * (double)g.longest_m / 64.0 + 8.0);
 }
 
 void plan_matrices(const muon_param* p, int n, int ns_dtype, std::vector<MatPlan>& out, size_t& total_partials) {
@@ -533,18 +553,22 @@ int planes_of(int ns_dtype) { return ns_dtype == MUON_BF16X2 ? 2 : ns_dtype == M
 // (a = 3.44), not the iterate's.
 bool folds_identity(const MatPlan& q, int ns_dtype) { return ns_dtype == MUON_BF16 && q.m >= 64; }
 
-// Whether a matrix takes the Gram route: from its own sides, so that its result does not depend on the list.  A group of k iterations
-// then has one Gram and one apply product instead of k of each, and 5 or 9 products of m x m instead of k: with five iterations three
-// Gram and three apply products against nine more of m x m.  Where a launch is a chain of slabs and little else that pays from a
-// ratio n / m on that falls with m (the chain of the Gram product is n long, that of the nine m); in lists that fill the chip sooner, so
-// the line is where a matrix alone does not lose.  us per step, all products of Eq. 2 / Gram route, one matrix and several: 384 x 1536
-// 84.2 / 88.0, 24 291 / 242, x 3072 116 / 101, 500 -> 375 (24); 512 x 2048 101.0 / 101.6, x 4096 143 / 122, 24 847 / 612; 640 x 1664
-// 107 / 115, x 2560 125.7 / 122.6, 24 1054 / 925, x 5120 177 / 142; 768 x 3072 156 / 149, 8 466 / 374; 1024 x 2816 171 / 179, 3 330 / 287, x
-// 4096 198 / 192, 3 376 / 312; 1408 x 2816 253 / 260, x 3840 300 / 281, 8 1463 / 1297; 2048 x 4096 519 / 509, 8 2527 / 2655, x 5632 654 /
-// 576; 3072 x 6144 1181 / 1077, x 8448 1521 / 1244.  Beside other matrices: 4 of 512^2 and 3 of 1024 x 4096 413 / 351, 30 of 1024^2 and 6 of
-// 1408 x 5632 2425 / 2143, 48 of 1024^2 and 36 of 1024 x 4096 4609 / 4065; a few beside much more of the other kind, which the longer chain of launches
-// shows: 3000^2 and one of 1024 x 4096 873 / 941, 4 of 1536^2 and one of 640 x 5000 555 / 581.  Fewer rows than 384 gain alone (256 x
-// 4096 121 / 99) and lose beside anything longer.
+// Whether a matrix takes the Gram route: from its own sides, so that its result does not depend on the list.  A group of two iterations
+// then has one Gram and one apply product instead of two of each, and 5 products of m x m instead of 2: with five iterations three
+// Gram and three apply products against six more of m x m.  Where a launch is a chain of slabs and little else that pays from a
+// ratio n / m on that falls with m (the chain of the Gram product is n long, that of the six m); in lists that fill the chip sooner, so
+// the line is where a matrix alone does not lose.  us per step, all products of Eq. 2 / Gram route, one matrix and several:
+//   384 x 1536 84 / 87, 24 282 / 260; x 2304 96.5 / 94.7; x 3072 116 / 108, 24 496 / 421
+//   512 x 2048 101.6 / 103.2, 8 198 / 186; x 3072 124 / 119; x 4096 141 / 129, 24 791 / 676
+//   640 x 1664 106 / 112, 24 618 / 565; x 2560 123.8 / 124.4, 8 316 / 279; x 5120 173 / 155;  768 x 3072 147.5 / 147.2, 8 446 / 406
+//   1024 x 2816 158 / 169, 3 333 / 304; x 4096 195.1 / 196.5, 3 383 / 341, 12 1307 / 1034
+//   1408 x 2816 240 / 253, 8 1142 / 1102; x 3840 304 / 292, 8 1478 / 1320;  2048 x 4096 530 / 523, 8 2588 / 2788; x 5632 663 / 619, 4 1819 / 1636
+//   2560 x 5120 693 / 667;  3072 x 4608 960 / 985; x 6144 1219 / 1165;  4096 x 8192 2363 / 2164; x 11008 3057 / 2610;  2 of 4096 x 6144 3407 / 4072
+// Fewer rows than 384 gain alone (256 x 4096 122 / 108) and lose beside anything longer.  Beside other matrices: 4 of 512^2 and 2 of 512 x
+// 4096 173 / 164, 4 of 1024^2 and 3 of 1024 x 4096 458 / 456, 8 and 6 1050 / 960, 48 and 36 4622 / 4276, 4 of 4096^2 and 3 of 4096 x 11008 12992 / 11960;
+// a few beside much more of the other kind pay for the longer chain of launches: 3000^2 and one of 1024 x 4096 825 / 850, 4 of 1536^2 and
+// one of 640 x 5000 528 / 544, 8 of 2048^2 and 2 of 1024 x 4096 1931 / 1978, 48 of 1024^2 and 4 1934 / 1959.  (Three iterations, which no
+// matrix takes on its Gram matrix, but in two groups all the same: 4 of 1024^2 and 3 of 1024 x 4096 296 / 320, 3000^2 and one 518 / 533, alone even.)
 bool gram_route(const MatPlan& q, int ns_dtype) {
   if (ns_dtype != MUON_BF16 || q.mp < 384) return false;
   const double least = q.mp >= 2560 ? 2.0 : q.mp >= 1280 ? 2.6 : q.mp >= 640 ? 4.0 : 8.0;
@@ -987,10 +1011,10 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         ts.n_poly = (int)deal_tiles(by_m, sym, sym_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.poly), steady_m ? slots : 0, level == 0);
         ts.n_apply = (int)deal_tiles(by_m, app, app_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + ts.apply), steady_m ? slots : 0, level == 0);
       }
-      // Where the other group has finished, a group's coarse tiles may be too few, or leave their rounds badly filled with a K that
+      // Where the other group has no symmetric product to share a launch with, a group's coarse tiles may be too few, or leave their rounds badly filled with a K that
       // two-stage tiles handle well: all of them in a fine launch.  us per step, coarse / fine: 30 of 1024^2 with 3 of 1024 x 4096 (30
       // tiles) 1613 / 1465, 12 of 1024 x 4096 (120) 1971 / 1905, 48 with 36 (360 tiles on 256 compute units) 4062 / 4036, 30 with 18 of 1408 x
-      // 3840 (324) 3607 / 3442.
+      // 3840 (324) 3607 / 3442; beside an apply product in fine tiles, 8 of 1024^2 with 6 (60 tiles, 31 us, then the 22 of the apply product) 1057 / 960.
       constexpr double kLoneFill = 0.75, kLoneM = 1536;
       if (g.gram && g.coarse.n_sym > 0 && (few_coarse_sym(coarse_own, (int)planes, plan.coarse_blocks) ||
                                            (coarse_own.m <= kLoneM && coarse_own.fill(plan.coarse_blocks) < kLoneFill))) {
@@ -1004,9 +1028,7 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
         }
         g.lone = take(count * sizeof(GemmTile));
         g.n_lone = (int)deal_tiles(by_m, sym, sym_cuts, w_m, reinterpret_cast<GemmTile*>(img.data() + g.lone), 0, true);
-        const std::vector<Load> load = load_of(sym, w_m);
-        g.lone_form.quarters = runs_in_quarters(load, true, 1, plan.coarse_blocks);
-        g.lone_form.few = few_blocks(load, 1, plan.coarse_blocks);
+        pair_sides[1].lone = load_of(sym, w_m);
       }
       ch.groups.push_back(g);
     }
@@ -1049,6 +1071,15 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
     if (ch.paired) {
       for (int i = 0; i < 4; ++i)
         for (int j = 0; j < 4; ++j) ch.pair[i][j] = pair_form(pair_sides[0], i, pair_sides[1], j, plan.coarse_blocks);
+      for (int i = 0; i < 2; ++i)
+        for (int p : {kPairGram, kPairSym, kPairApply}) {
+          const Group& g = ch.groups[i];
+          const bool lone = p == kPairSym && g.n_lone > 0;
+          ch.beside[i][p] = (lone || (p == kPairApply ? g.coarse.n_apply : g.coarse.n_sym) == 0) && pair_sides[i].lo[p] >= kRingK &&
+                            fits_beside(ch.groups[i ^ 1], lone ? pair_sides[i].lone : pair_sides[i].load[p], plan.coarse_blocks);
+        }
+      ch.groups[1].lone_form[0] = fine_form(pair_sides[1].lone, {}, plan.coarse_blocks);
+      ch.groups[1].lone_form[1] = fine_form(pair_sides[1].lone, pair_sides[0].load[kPairApply], plan.coarse_blocks);
     }
     {
       // Lists short enough for quarter blocks or the 128-wide ring save the norm's own launch (about 4 us): every block adds up its matrix's

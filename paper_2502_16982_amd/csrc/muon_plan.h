@@ -99,10 +99,10 @@ struct Group {
   size_t prob_gram[2] = {0, 0}, prob_poly = 0, prob_apply[4] = {0, 0, 0, 0};  // byte offsets ([parity], [parity * 2 + last])
   TileSet fine, coarse;
   // Gram route: symmetric products that run without the other group's, where their own coarse tiles would be few or fill their rounds
-  // badly: all tiles in a fine launch of this form (n_lone = 0: no such table).
+  // badly: all tiles in a fine launch (n_lone = 0: no such table), alone or with the other group's apply product in fine tiles.
   size_t lone = 0;
   int n_lone = 0;
-  PairForm lone_form;
+  PairForm lone_form[2];
 };
 
 struct Chunk {
@@ -116,6 +116,8 @@ struct Chunk {
   // pair[i][j]: kPair* of the first and of the second group (kPairNone: nothing is left to do there, or there is no second group).
   bool paired = false;
   PairForm pair[4][4];
+  // [group][kPair*]: the product can share a launch with the other group's apply product in coarse tiles, from its fine or its lone table
+  bool beside[2][4] = {};
   // Where both groups have coarse symmetric tiles: one table of both for every pair of symmetric products, dealt as one.
   // [first group's Gram product / another][second group's Gram product / another]
   size_t shared_sym[2][2] = {};

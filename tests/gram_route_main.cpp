@@ -10,7 +10,7 @@
 #include "../paper_2502_16982_amd/csrc/muon_plan.h"
 
 using namespace muon;
-static int failures = 0;
+static int failures = 0, beside = 0;
 #define CHECK(c) do { if (!(c)) { if (failures++ < 20) std::printf("line %d: %s\n", __LINE__, #c); } } while (0)
 
 typedef std::tuple<int, int, int, int> Key;      // problem, row, column, shape
@@ -82,6 +82,16 @@ static void walk(const std::vector<muon_param>& p, size_t cap) {
           const TileSet& c = ch.groups[r].coarse;
           CHECK(keys(t, ch.n_shared_sym, r) == keys(reinterpret_cast<const GemmTile*>(img + c.sym), c.n_sym, -1));
         }
+      }
+    for (int i = 0; i < 2; ++i)
+      for (int p : {kPairGram, kPairSym, kPairApply}) {        // blocks of a ring beside coarse tiles: all of the product in them, K of four slabs
+        if (!ch.beside[i][p]) continue;
+        const Group& h = ch.groups[i];
+        const bool lone = p == kPairSym && h.n_lone > 0;
+        CHECK(lone || (p == kPairApply ? h.coarse.n_apply == 0 && h.fine.n_apply > 0 : h.coarse.n_sym == 0 && h.fine.n_sym > 0));
+        CHECK(ch.groups[i ^ 1].coarse.n_apply > 0);
+        for (int k : h.members) CHECK(plan.mats[k].mp >= 256);
+        ++beside;
       }
     if (g.n_lone > 0) {
       CHECK(g.lone + sizeof(GemmTile) * (size_t)g.n_lone <= plan.image.size());
@@ -156,6 +166,13 @@ int main() {
   CHECK(!gram_coefficients_fit(far.data(), 5) && !gram_coefficients_fit(far.data(), 4));
   const double textbook[12] = {1.875, -1.25, 0.375, 1.875, -1.25, 0.375, 1.5, -0.5, 0.0, 1.0, 0.0, 0.0};
   CHECK(gram_coefficients_fit(textbook, 4));
+  const std::vector<muon_param> few = {mat(3000, 3000), mat(1024, 4096)}, full = {mat(2048, 2048), mat(2048, 2048), mat(2048, 2048), mat(2048, 2048),
+                                                                                   mat(2048, 2048), mat(2048, 2048), mat(2048, 2048), mat(2048, 2048), mat(1024, 4096)};
+  beside = 0;
+  walk(few, 0);
+  CHECK(beside == 3);
+  walk(full, 0);                      // 512 apply tiles: no compute unit is idle
+  CHECK(beside == 3);
   std::printf(failures ? "failed\n" : "gram route ok\n");
   return failures ? 1 : 0;
 }

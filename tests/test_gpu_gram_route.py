@@ -83,6 +83,34 @@ def test_same_bits_in_any_list(dev, shape, long, ns_steps):
         assert torch.equal(w, results[0][4]) and torch.equal(m, results[0][5]), (n, beside, parts, i)
 
 
+@pytest.mark.parametrize("ns_steps", [3, 5])
+@pytest.mark.parametrize("shapes", [
+    [(3000, 3000), (1024, 4096)],                                  # an apply product in coarse tiles, everything of the other group beside it
+    [(1408, 1408)] * 6 + [(513, 2600)],                            # strips among those tiles
+    [(1024, 1024)] * 8 + [(1024, 4096)] * 3 + [(4096, 1024)] * 3,  # apply products in fine tiles with symmetric ones that have few coarse tiles
+    [(600, 300)] * 4 + [(2560, 5200)] * 2])                        # a wide matrix's apply product with the fine ones of the others
+def test_same_bits_beside_the_other_route(dev, shapes, ns_steps):
+    """Products of one route in the launches of the other's: as alone."""
+    assert len(set(on_route(shapes))) == 2
+    tensors = workloads.make_all(workloads.custom("gram_pairs", shapes, seed_base=525), dev)
+    hp = binding.default_hparams(lr=0.02, weight_decay=0.1, ns_steps=ns_steps)
+    kinds = {s: i for i, s in enumerate(shapes)}
+    alone = {}
+    for i in kinds.values():
+        t = tuple(x.clone() for x in tensors[i])
+        st = binding.MuonStepper([t])
+        st.step(hp)
+        alone[i] = t
+        torch.cuda.synchronize()
+        st.close()
+    st = binding.MuonStepper(tensors)
+    st.step(hp)
+    torch.cuda.synchronize()
+    st.close()
+    for i, t in alone.items():
+        assert torch.equal(t[0], tensors[i][0]) and torch.equal(t[2], tensors[i][2]), (i, shapes[i])
+
+
 @pytest.mark.parametrize("ns_steps", [3, 4, 6, 7, 10])
 def test_numbers_of_iterations(dev, ns_steps):
     """Three are iterated as Eq. 2 is written; the model gives 0.31, 0.45, 0.53 and 0.91e-2 for 4, 6, 7 and 10 at 384 x 3072, less at these sides."""
