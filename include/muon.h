@@ -103,7 +103,8 @@ int muon_default_hparams(muon_hparams* hp);
  * forms MUON_BF16X2 / MUON_BF16X3 (fp32-class accuracy on the matrix cores, the "more accurate"
  * direction of section 2.2 at model sizes).  MUON_BF16 iterates wide matrices (shorter side, padded to a multiple of 128, of
  * 384 and more, the other side 8 times as long, down to twice as long from 2560 on) on their Gram matrix, two iterations at a time
- * and in f16 scaled by powers of two, where ns_steps is at least 4 and the coefficients keep everything in range: the same
+ * and in f16 scaled by powers of two, where ns_steps is at least 4 and the coefficients keep everything in its range (the
+ * paper's: up to ten iterations): the same
  * iteration, with no more rounding error (a third to a half on flat spectra and on inputs that fill a few directions, nearly the
  * same where singular values decay).  The Newton-Schulz temporaries of all matrices are
  * kept resident when they fit in `max_bytes`; otherwise the list is processed in consecutive chunks

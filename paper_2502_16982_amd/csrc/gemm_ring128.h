@@ -20,7 +20,7 @@ constexpr size_t kLdsRing128 = (size_t)kRing128 * 2 * 128 * ROWB;
 // K >= 256.  ADD: the product has an addend.
 template <bool LKM, typename IN, typename OUT, bool ADD>
 __device__ __forceinline__ void gemm_ring128_tile(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem, float beta_acc,
-                                                  float beta_e, int alpha_idx, double eps, float diag_add, bool out_f16) {
+                                                  float beta_e, int alpha_idx, double eps, float diag_add, bool out_f16, float gain) {
   constexpr int BT = 128, NW = 4, F = 2, WT = 64, NST = kRing128;
   constexpr int LREQ = BT / 8 / NW, NLOAD = 2 * LREQ;           // 1 KB requests per wave and slab: L, both
   constexpr int STAGE_B = 2 * BT * ROWB, KSTEPS = BK / 16;
@@ -150,12 +150,9 @@ __device__ __forceinline__ void gemm_ring128_tile(const GemmProblem& p, int row0
   if (!LKM && !ADD && alpha_idx == kAlphaFromPartials) {
     // first Gram product: the norm, from the partial sums (see gemm_tile64_body)
     float s, s2;
-    norm_scalars(block_sum_f64(p.partials, p.n_part, reinterpret_cast<double*>(smem + kLdsRing128)), eps, &s, &s2);
-    if (row0 == 0 && col0 == 0 && tid == 0) {
-      float* scal = const_cast<float*>(p.scal);
-      scal[0] = s;
-      scal[1] = s2;
-    }
+    const double sum = block_sum_f64(p.partials, p.n_part, reinterpret_cast<double*>(smem + kLdsRing128));
+    norm_scalars(sum, eps, &s, &s2);
+    if (row0 == 0 && col0 == 0 && tid == 0) store_norm(const_cast<float*>(p.scal), sum, eps, gain, s, s2);
     alpha = s2;
   } else if (alpha_idx >= 0) {
     alpha = p.scal[alpha_idx];
@@ -272,9 +269,10 @@ __device__ __forceinline__ void gemm_ring128_tile(const GemmProblem& p, int row0
 // (one branch in front of the tile: a branch while fragment reads are in flight would have their registers copied before they land)
 template <bool LKM, typename IN = Bf16, typename OUT = Bf16>
 __device__ __forceinline__ void gemm_ring128_body(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem, float beta_acc,
-                                                  float beta_e, int alpha_idx, double eps, float diag_add, bool out_f16 = false) {
-  if (p.Et) gemm_ring128_tile<LKM, IN, OUT, true>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps, diag_add, out_f16);
-  else gemm_ring128_tile<LKM, IN, OUT, false>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps, diag_add, out_f16);
+                                                  float beta_e, int alpha_idx, double eps, float diag_add, bool out_f16 = false,
+                                                  float gain = 0.f) {
+  if (p.Et) gemm_ring128_tile<LKM, IN, OUT, true>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps, diag_add, out_f16, gain);
+  else gemm_ring128_tile<LKM, IN, OUT, false>(p, row0, col0, diagonal, smem, beta_acc, beta_e, alpha_idx, eps, diag_add, out_f16, gain);
 }
 
 }  // namespace

@@ -60,7 +60,7 @@ __device__ __forceinline__ void land64(Frag64<LKM>& f) {
 template <bool LKM, int NW, int NST, typename IN = Bf16, typename OUT = Bf16>
 __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0, int col0, bool diagonal, unsigned char* smem,
                                                  float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add,
-                                                 bool out_f16 = false) {
+                                                 bool out_f16 = false, float gain = 0.f) {
   static_assert(NW == 4 || NW == 1, "a wave owns a 32 x 32 tile");
   constexpr int BT = NW == 4 ? 64 : 32;                         // tile side
   constexpr int LREQ = BT / 8 / NW, NLOAD = 2 * LREQ;           // 1 KB requests per wave and slab: L, both
@@ -181,13 +181,11 @@ __device__ __forceinline__ void gemm_tile64_body(const GemmProblem& p, int row0,
   if (!LKM && alpha_idx == kAlphaFromPartials) {
     // first Gram product: the norm, from the partial sums (K-major launches are never first)
     float s, s2;
-    if constexpr (NW == 4) norm_scalars(block_sum_f64(p.partials, p.n_part, reinterpret_cast<double*>(smem + lds_ring64(NST))), eps, &s, &s2);
-    else norm_scalars(wave_sum_f64(p.partials, p.n_part), eps, &s, &s2);
-    if (row0 == 0 && col0 == 0 && tid == 0) {
-      float* scal = const_cast<float*>(p.scal);
-      scal[0] = s;
-      scal[1] = s2;
-    }
+    double sum;
+    if constexpr (NW == 4) sum = block_sum_f64(p.partials, p.n_part, reinterpret_cast<double*>(smem + lds_ring64(NST)));
+    else sum = wave_sum_f64(p.partials, p.n_part);
+    norm_scalars(sum, eps, &s, &s2);
+    if (row0 == 0 && col0 == 0 && tid == 0) store_norm(const_cast<float*>(p.scal), sum, eps, gain, s, s2);
     alpha = s2;
   } else if (alpha_idx >= 0) {
     alpha = p.scal[alpha_idx];

@@ -310,15 +310,14 @@ __global__ __launch_bounds__(256) void momentum_norm_cast_pack_kernel(const MatD
 // ------------------------------------------------------------------------------------------------------
 // a2 second stage: one block per matrix sums its partials in a fixed order, in double.
 // ------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void norm_finalize_kernel(const MatDesc* __restrict__ mats, int first_mat, double eps) {
+__global__ __launch_bounds__(256) void norm_finalize_kernel(const MatDesc* __restrict__ mats, int first_mat, double eps, float gram_gain) {
   __shared__ double red[256];
   const MatDesc& d = mats[first_mat + blockIdx.x];
   const double sum = block_sum_f64(d.partials, d.n_part, red);
   if (threadIdx.x == 0) {
     float s, s2;
     norm_scalars(sum, eps, &s, &s2);
-    d.scal[0] = s;
-    d.scal[1] = s2;
+    store_norm(d.scal, sum, eps, d.gram_route ? gram_gain : 0.f, s, s2);
   }
 }
 
@@ -569,9 +568,9 @@ hipError_t launch_momentum_norm_cast(const MatDesc* mats, MatPtrs* ptrs, const P
   return hipGetLastError();
 }
 
-hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, double eps, hipStream_t s) {
+hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, double eps, float gram_gain, hipStream_t s) {
   if (n_mats <= 0) return hipSuccess;
-  norm_finalize_kernel<<<n_mats, 256, 0, s>>>(mats, first_mat, eps);
+  norm_finalize_kernel<<<n_mats, 256, 0, s>>>(mats, first_mat, eps, gram_gain);
   return hipGetLastError();
 }
 

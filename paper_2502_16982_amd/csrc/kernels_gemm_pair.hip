@@ -34,6 +34,7 @@ __device__ __forceinline__ GemmSide pick_side(const GemmSide& x, const GemmSide&
   s.diag_add = first ? x.diag_add : y.diag_add;
   s.alpha_idx = first ? x.alpha_idx : y.alpha_idx;
   s.kind = first ? x.kind : y.kind;
+  s.gain = first ? x.gain : y.gain;
   return s;
 }
 
@@ -74,7 +75,7 @@ __global__ __launch_bounds__(256, 1) void ns_pair_ring128_kernel(GemmSide x, Gem
   const GemmProblem p = s.probs[tile.prob];
   with_operands(s.kind, [&](auto lkm, auto in, auto out) {
     gemm_ring128_body<decltype(lkm)::value, decltype(in), decltype(out)>(p, tile.r0 * kTileUnit, tile.c0 * kTileUnit, (tile.flags & kTileDiagonal) != 0, smem,
-                                                                s.beta_acc, s.beta_e, s.alpha_idx, eps, s.diag_add, (s.kind & kSideOutF16) != 0);
+                                                                s.beta_acc, s.beta_e, s.alpha_idx, eps, s.diag_add, (s.kind & kSideOutF16) != 0, s.gain);
   });
 }
 
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(256, BLOCKS) void ns_pair_tile64_kernel(GemmSide x,
   const int row0 = tile.r0 * kTileUnit + 64 * (quarter >> 1), col0 = tile.c0 * kTileUnit + 64 * (quarter & 1);
   with_operands(s.kind, [&](auto lkm, auto in, auto out) {
     gemm_tile64_body<decltype(lkm)::value, 4, NST, decltype(in), decltype(out)>(p, row0, col0, on_diag && quarter != 1, smem, s.beta_acc, s.beta_e,
-                                                                       s.alpha_idx, eps, s.diag_add, (s.kind & kSideOutF16) != 0);
+                                                                       s.alpha_idx, eps, s.diag_add, (s.kind & kSideOutF16) != 0, s.gain);
   });
 }
 
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(64) void ns_pair_tile32_kernel(GemmSide x, GemmSide
   with_operands(s.kind, [&](auto lkm, auto in, auto out) {
     gemm_tile64_body<decltype(lkm)::value, 1, kRing32, decltype(in), decltype(out)>(p, tile.r0 * kTileUnit + 32 * (part >> 2), tile.c0 * kTileUnit + 32 * (part & 3),
                                                                            on_diag && (part >> 2) == (part & 3), smem, s.beta_acc, s.beta_e,
-                                                                           s.alpha_idx, eps, s.diag_add, (s.kind & kSideOutF16) != 0);
+                                                                           s.alpha_idx, eps, s.diag_add, (s.kind & kSideOutF16) != 0, s.gain);
   });
 }
 
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(256, 1) void ns_pair_sym_kernel(SharedArgs args) {
     GemmSide s;
     s.probs = side.probs; s.tiles = nullptr; s.n_tiles = 0;
     s.beta_acc = side.beta_acc; s.beta_e = side.beta_e; s.diag_add = side.diag_add;
-    s.alpha_idx = side.alpha_idx; s.kind = side.kind;
+    s.alpha_idx = side.alpha_idx; s.kind = side.kind; s.gain = 0.f;
     if (s.kind & kSideInF16) coarse_sym_tile<F16>(s, tile, smem, wave_id);
     else coarse_sym_tile<Bf16>(s, tile, smem, wave_id);
     __syncthreads();        // every wave has read its part of the LDS images: the next tile may overwrite them

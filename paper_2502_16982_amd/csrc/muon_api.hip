@@ -225,7 +225,7 @@ void list_ops(const Group& g, int N, const double* coeff, bool gram, bool fold, 
       out.push_back({kPairGram, g.prob_gram[par], 1.f, 0.f, 0.f, norm, 0});
       out.push_back({kPairSym, g.prob_poly, c, b, a, -1, 0});
     } else {
-      out.push_back({kPairGram, g.prob_gram[par], SA / (SX * SX), 0.f, 0.f, -1, f16});
+      out.push_back({kPairGram, g.prob_gram[par], SA / (SX * SX), 0.f, 0.f, 2, f16});           // (alphas: store_norm)
       out.push_back({kPairSym, g.prob_poly, c * (SP / (SA * SA)), b * (SP / SA), a * SP, -1, f16});
     }
     if (steps == 2) {
@@ -238,12 +238,12 @@ void list_ops(const Group& g, int N, const double* coeff, bool gram, bool fold, 
     }
     it += steps;
     out.push_back({kPairApply, steps == 2 ? op(kGramApply + par * 2 + last) : g.prob_apply[par * 2 + last], (last ? 1.f : SX) / (first ? 1.f : SP * SX),
-                   0.f, 0.f, first ? 0 : -1, kSideKMajor | (first ? 0 : kSideInF16) | (last ? 0 : kSideOutF16)});
+                   0.f, 0.f, first ? 0 : last ? 3 : -1, kSideKMajor | (first ? 0 : kSideInF16) | (last ? 0 : kSideOutF16)});
   }
 }
 
 // Iterations of a chunk with matrices of the Gram route: the next product of either group in every launch.
-int enqueue_paired(muon_ctx* ctx, const Chunk& ch, const muon_hparams* hp, const double* coeff, bool gram, bool fold, hipStream_t s) {
+int enqueue_paired(muon_ctx* ctx, const Chunk& ch, const muon_hparams* hp, const double* coeff, bool gram, float gain, bool fold, hipStream_t s) {
   std::vector<GroupOp>* const ops = ctx->group_ops;
   for (int i = 0; i < 2; ++i) list_ops(ch.groups[i], hp->ns_steps, coeff, i == 1 && gram, fold, ops[i]);
   size_t at[2] = {0, 0};
@@ -291,6 +291,7 @@ int enqueue_paired(muon_ctx* ctx, const Chunk& ch, const muon_hparams* hp, const
         side[i].diag_add = op[i]->diag_add;
         side[i].alpha_idx = op[i]->alpha_idx;
         side[i].kind = op[i]->kind;
+        side[i].gain = i == 1 ? gain : 0.f;
         longest[i] = gram_product ? g.longest_n : g.longest_m;
         strips = strips || ts.strips;
       }
@@ -325,13 +326,15 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
   // bf16 path: X ping-pong index N & 1 (bit 1), transposed matrices in Xt[1], or Xt[0] when no iteration ran (bit 0)
   const int o_written = mc ? ((N & 1) << 1) | (N > 0 ? 1 : 0) : (N & 1);
   std::vector<double>& coeff = ctx->coeff;
+  double gain = 0.0;
   bool gram = false;                 // (lists without matrices of the Gram route spend no host time on its coefficients)
   for (const Chunk& ch : ctx->plan.chunks) gram = gram || ch.paired;
   if (gram) {
     coeff.resize(3 * (size_t)N);
     for (int i = 0; i < 3 * N; ++i) coeff[i] = hp->coeff_schedule ? hp->coeff_schedule[i] : i % 3 == 0 ? hp->a : i % 3 == 1 ? hp->b : hp->c;
-    gram = N >= kGramMinSteps && gram_coefficients_fit(coeff.data(), N);
+    gram = N >= kGramMinSteps && gram_coefficients_fit(coeff.data(), N, &gain);
   }
+  const float gram_gain = gram ? (float)gain : 0.f;
   const int o_sel = o_written | (gram ? (gram_groups(N) & 1) << 1 | 1 : o_written) << 2;
 
   for (size_t ci = 0; ci < ctx->plan.chunks.size(); ++ci) {
@@ -340,9 +343,9 @@ int enqueue_step(muon_ctx* ctx, const muon_hparams* hp, hipStream_t s, float* up
     MUON_TIMED(MUON_PROF_MOMENTUM, launch_momentum_norm_cast(ctx->d_mats, ctx->d_ptrs, pack, ew, ch.n_ew_tiles, (float)hp->momentum,
                                                              hp->nesterov != 0, (!mc || N == 0) ? 1 : 0, ctx->ns_dtype, s));
     const bool fold = ch.fold_norm && N > 0;
-    if (!fold) MUON_TIMED(MUON_PROF_NORM, launch_norm_finalize(ctx->d_mats, ch.first, ch.count, hp->eps, s));
+    if (!fold) MUON_TIMED(MUON_PROF_NORM, launch_norm_finalize(ctx->d_mats, ch.first, ch.count, hp->eps, gram_gain, s));
     if (ch.paired) {
-      const int st = enqueue_paired(ctx, ch, hp, coeff.data(), gram, fold, s);
+      const int st = enqueue_paired(ctx, ch, hp, coeff.data(), gram, gram_gain, fold, s);
       if (st != MUON_OK) return st;
     }
     for (int it = 0; it < N && !ch.paired; ++it) {

@@ -58,6 +58,20 @@ __device__ __forceinline__ void norm_scalars(double sum, double eps, float* s, f
   *s = ok ? (float)inv : 0.f;
   *s2 = ok ? (float)(inv * inv) : 0.f;
 }
+// They go to scal[0] and scal[1].  gain > 0 (Gram route: no iteration sequence of the launch makes X larger than that many times): where
+// eps leaves X so small that it stays below 4, X between the first and the last iteration is kept 2^k times as large, up to 4, well inside
+// f16; scal[0] then carries 2^k, [2] and [3] are 2^-2k and 2^-k.
+__device__ __forceinline__ void store_norm(float* scal, double sum, double eps, float gain, float s, float s2) {
+  if (gain > 0.f) {
+    const double x = sqrt(sum), most = x / (x + eps) * (double)gain;           // (all zero: any scale will do)
+    const int k = most < 4.0 && most > 0.0 ? min(1 - ilogb(most), 40) : 0;
+    s *= ldexpf(1.f, k);
+    scal[2] = ldexpf(1.f, -2 * k);
+    scal[3] = ldexpf(1.f, -k);
+  }
+  scal[0] = s;
+  scal[1] = s2;
+}
 
 // One-time per-process kernel attribute setup (large dynamic LDS).  Returns a hipError_t.
 hipError_t gemm_setup();
@@ -75,11 +89,12 @@ hipError_t launch_momentum_norm_cast(const MatDesc* mats, MatPtrs* ptrs, const P
                                      float mu, int nesterov, int both_layouts, int ns_dtype, hipStream_t s);
 
 // a2 second stage: fixed-order sum of the partials of each matrix, s = 1/(sqrt(sum)+eps).
-hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, double eps, hipStream_t s);
+// gram_gain: store_norm's gain for matrices of the Gram route (0: they are iterated as Eq. 2 is written).
+hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, double eps, float gram_gain, hipStream_t s);
 
-// a4-a6: grouped NT GEMM with fused epilogue.  alpha_idx: -1 none, 0 -> scal[0], 1 -> scal[1], kAlphaFromPartials (first
+// a4-a6: grouped NT GEMM with fused epilogue.  alpha_idx: -1 none, 0 .. 3 -> that scal[], kAlphaFromPartials (first
 // Gram product, kGemmQuarters and kGemmRing128 launches only) -> what scal[1] has to be, from the partial sums of squares and eps; the block
-// of the first tile leaves scal[0] and scal[1] behind.  diag_add: constant
+// of the first tile leaves them behind (store_norm).  diag_add: constant
 // added to the diagonal of the outputs of problems that ask for it (GemmProblem::diag_add), bf16 kernel only.
 // coarse: 0 = every tile of the table is 128 x 128 (two blocks per compute unit); 1 = the table mixes 256 x 256 and,
 // with kGemmStrips in `flags`, 512 x 128 tiles (one block per compute unit; the flag selects the larger LDS
@@ -93,7 +108,7 @@ hipError_t launch_norm_finalize(const MatDesc* mats, int first_mat, int n_mats, 
 // l_kmajor: every problem of the launch stores its L operand K-major (element (i, k) at L[k * ldl + i]).
 // planes: 1 = plain bf16; 2 or 3 = every matrix is a sum of that many bf16 planes (GemmProblem::*_plane strides); entries of a
 // coarse table then run as four 128 x 128 blocks each.
-constexpr int kAlphaFromPartials = 2;
+constexpr int kAlphaFromPartials = 4;
 constexpr int kGemmStrips = 1, kGemmPersistent = 2, kGemmQuarters = 4, kGemmLongK = 8, kGemmSixteenths = 16, kGemmFewQuarters = 32, kGemmRing128 = 64;
 hipError_t launch_gemm_bf16(int coarse, int flags, const GemmProblem* probs, const GemmTile* tiles, int n_tiles,
                             float beta_acc, float beta_e, int alpha_idx, double eps, float diag_add, int l_kmajor, int planes,
@@ -107,6 +122,7 @@ struct GemmSide {
   float beta_acc, beta_e, diag_add;
   int alpha_idx;
   int kind;           // kSide*: operand layout, type of the operands and the addend, type of the results
+  float gain;         // kAlphaFromPartials: store_norm's
 };
 constexpr int kSideKMajor = 1, kSideInF16 = 2, kSideOutF16 = 4;
 hipError_t gemm_pair_setup();

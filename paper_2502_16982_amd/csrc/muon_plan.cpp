@@ -575,11 +575,12 @@ bool gram_route(const MatPlan& q, int ns_dtype) {
   return q.np >= least * q.mp;
 }
 
-bool gram_coefficients_fit(const double* coeff, int steps) {
+bool gram_coefficients_fit(const double* coeff, int steps, double* gain) {
   // An element is at most its matrix's spectral norm.  s: bound on X's, which is 1 at the start (the Frobenius norm); the maximum of
   // |a x + b x^3 + c x^5| over [0, s] is at an end or where the derivative vanishes.  A quarter is added for rounding.
   const double slack = 1.25, most = 65504.0 / slack;
-  double s = 1.0;
+  double s = 1.0, shrunk = 1.0;
+  *gain = slack;
   for (int k = 0; k < steps;) {
     const int group = gram_group(k, steps);
     const bool first = k == 0;                   // of the first, which is in bf16, X alone
@@ -604,6 +605,11 @@ bool gram_coefficients_fit(const double* coeff, int steps) {
                                     kGramScaleX * next);
       if (!(worst <= most)) return false;        // not a number, too
       s = next;
+      *gain *= std::max(p, 1.0);
+      // What f16 holds as well as bf16 would: small singular values, which follow a, must not shrink much, and an X that eps leaves small must
+      // not grow so far (store_norm keeps one scale for all iterations).  The paper's coefficients: up to ten iterations.
+      shrunk *= std::min(std::fabs(a), 1.0);
+      if (!(shrunk >= 1.0 / 64.0 && *gain <= (double)(1 << 19))) return false;
     }
   }
   return true;

@@ -73,8 +73,9 @@ inline int gram_groups(int n) { return n / 2 + 1; }
 // Powers of two by which the f16 matrices are larger than what they stand for: A and T; P, D and Q; X.
 constexpr float kGramScaleA = 8192.f, kGramScaleP = 512.f, kGramScaleX = 8192.f;
 bool gram_route(const MatPlan& q, int ns_dtype);
-// Whether `steps` iterations with the coefficients coeff[3 * k] .. (a, b, c) stay inside f16 on the Gram route.
-bool gram_coefficients_fit(const double* coeff, int steps);
+// Whether `steps` iterations with the coefficients coeff[3 * k] .. (a, b, c) stay inside f16 on the Gram route.  *gain: a bound on how much
+// larger X gets, for store_norm.
+bool gram_coefficients_fit(const double* coeff, int steps, double* gain);
 
 // What a group contributes to a paired launch: nothing, its Gram product, another symmetric product, its apply product.
 enum PairProduct : int { kPairNone = 0, kPairGram = 1, kPairSym = 2, kPairApply = 3 };

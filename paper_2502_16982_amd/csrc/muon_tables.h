@@ -21,7 +21,7 @@ struct MatDesc {
   void* Ag;           // m_pad x m_pad: Gram matrix X X^T
   void* Bp;           // m_pad x m_pad: b*A + c*A*A
   float* partials;    // one partial sum of squares per 64x64 tile
-  float* scal;        // [0] = 1/(||U||_F + eps), [1] = its square, [2] = sum(O^2) scratch, [3] spare
+  float* scal;        // [0] = 1/(||U||_F + eps), [1] = its square; Gram route: see store_norm; then [2] = sum(O^2) scratch
   int32_t rows, cols; // A, B
   int32_t m, n;       // min, max
   int32_t mp, np;     // padded to the GEMM tile

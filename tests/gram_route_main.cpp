@@ -154,18 +154,23 @@ int main() {
     }
     CHECK(it == n && count == gram_groups(n));
   }
-  // coefficients: the paper's at any number of steps; large ones, and ones that only grow on the way
+  // coefficients: the paper's up to ten iterations; large ones, ones that only grow on the way, and ones under which X shrinks
+  double gain = 0.0;
   std::vector<double> c;
   for (int i = 0; i < 40; ++i) for (double v : {3.4445, -4.7750, 2.0315}) c.push_back(v);
-  for (int n = kGramMinSteps; n <= 40; ++n) CHECK(gram_coefficients_fit(c.data(), n));
+  for (int n = kGramMinSteps; n <= 40; ++n) CHECK(gram_coefficients_fit(c.data(), n, &gain) == (n <= 10));
   std::vector<double> far = c;
   far[0] = 100.0; far[1] = far[2] = 0.0;
-  CHECK(!gram_coefficients_fit(far.data(), 5));
+  CHECK(!gram_coefficients_fit(far.data(), 5, &gain));
   far = c;
   for (int i = 6; i < 15; ++i) far[i] = i % 3 ? 0.0 : 6.0;
-  CHECK(!gram_coefficients_fit(far.data(), 5) && !gram_coefficients_fit(far.data(), 4));
+  CHECK(!gram_coefficients_fit(far.data(), 5, &gain) && !gram_coefficients_fit(far.data(), 4, &gain));
+  CHECK(gram_coefficients_fit(c.data(), 5, &gain) && gain >= 484.9 && gain <= 1.25 * 485.0);           // 3.4445^5
+  far = c;
+  far[0] = 0.01; far[3] = 100.0; far[1] = far[2] = far[4] = far[5] = 0.0;
+  CHECK(!gram_coefficients_fit(far.data(), 5, &gain));                                                 // X shrinks
   const double textbook[12] = {1.875, -1.25, 0.375, 1.875, -1.25, 0.375, 1.5, -0.5, 0.0, 1.0, 0.0, 0.0};
-  CHECK(gram_coefficients_fit(textbook, 4));
+  CHECK(gram_coefficients_fit(textbook, 4, &gain));
   const std::vector<muon_param> few = {mat(3000, 3000), mat(1024, 4096)}, full = {mat(2048, 2048), mat(2048, 2048), mat(2048, 2048), mat(2048, 2048),
                                                                                    mat(2048, 2048), mat(2048, 2048), mat(2048, 2048), mat(2048, 2048), mat(1024, 4096)};
   beside = 0;
