@@ -31,13 +31,32 @@ def _routes(shapes, ns, compute_units):
     lines = [line.split() for line in run.stdout.splitlines()]
     fold = [bool(int(line[1])) for line in lines if line[0] == "fold"]
     tables = {(line[1], int(line[2])): (int(line[3]), line[4]) for line in lines if line[0] == "0"}
-    return tables, fold[0]
+    tails = {line[1]: int(line[5]) for line in lines if line[0] == "0" and line[2] == "0"}
+    pairs = {"pairs": {(line[2], line[3]): (int(line[4]), line[5]) for line in lines if line[0] == "pair" and line[1] == "0"},
+             "coarse": [tuple(int(v) for v in line[3:]) for line in lines if line[0] == "coarse" and line[1] == "0"],
+             "lone": next(((int(line[2]), line[3], line[4]) for line in lines if line[0] == "lone" and line[1] == "0"), None),
+             "shared": next((int(line[2]) for line in lines if line[0] == "shared" and line[1] == "0"), 0),
+             "beside": {(int(line[2]), line[3]) for line in lines if line[0] == "beside" and line[1] == "0"}}
+    return tables, fold[0], tails, pairs
 
 
 def routes(shapes, ns, compute_units=256):
     """{(product, level): (entries, form)} of a list planned whole, form one of "whole", "quarters" (64-wide blocks, ring of
-    three), "ring4" (of four), "waves" (32-wide); and whether the first Gram launch adds up the norm."""
-    return _routes(tuple(tuple(s) for s in shapes), ns, compute_units)
+    three), "ring4" (of four), "waves" (32-wide), "ring128" (128-wide, ring of four); and whether the first Gram launch adds up the norm.
+    Empty for lists with matrices of the Gram route (pair_routes)."""
+    return _routes(tuple(tuple(s) for s in shapes), ns, compute_units)[:2]
+
+
+def tails(shapes, ns="f32", compute_units=256):
+    """{product: last entries of its fine launch that run in quarters behind it}."""
+    return _routes(tuple(tuple(s) for s in shapes), ns, compute_units)[2]
+
+
+def pair_routes(shapes, compute_units=256):
+    """Of a list with matrices of the Gram route, planned whole.  "pairs": {(product of the others, product of theirs): (entries, form) of the
+    fine launch}, "coarse": coarse entries of the symmetric and of the apply products of either group, "lone": entries and forms of their symmetric
+    products without the others', "shared": entries of the table of both, "beside": {(group, product)} that share the other's apply launch."""
+    return _routes(tuple(tuple(s) for s in shapes), "bf16", compute_units)[3]
 
 
 def fine_forms(shapes, ns):

@@ -12,6 +12,7 @@ pytestmark = pytest.mark.gpu
 from paper_2502_16982_amd import binding, workloads  # noqa: E402
 from tests import gpu_util as U  # noqa: E402
 from tests.gpu_util import coarse_tiles, table_sizes  # noqa: E402
+from tests import plan_routes  # noqa: E402
 from tests.plan_routes import fine_forms  # noqa: E402
 from tests.test_gpu_parity import assert_records  # noqa: E402
 
@@ -284,7 +285,9 @@ def test_same_bits_from_the_128_wide_ring(dev, shape, copies):
     hp = binding.default_hparams(lr=0.02, weight_decay=0.1)
     sym, _, app = table_sizes([shape], "bf16", 0)
     results = []
-    for n in sorted({1, copies, 230 // sym, 250 // app, -(-260 // sym) * 2} - {0}):
+    lengths = sorted({1, copies, 230 // sym, 250 // app, -(-260 // sym) * 2} - {0})
+    assert "ring128" in {f for n in lengths for f in fine_forms([shape] * n, "bf16")}
+    for n in lengths:
         tensors = [tuple(t.clone() for t in first) for _ in range(n)]
         st = binding.MuonStepper(tensors)
         for _ in range(2):
@@ -296,12 +299,15 @@ def test_same_bits_from_the_128_wide_ring(dev, shape, copies):
         assert torch.equal(o, results[0][2]) and torch.equal(w, results[0][3]) and torch.equal(m, results[0][4]), (n, i)
 
 
-def test_f32_bits_where_the_last_entries_run_in_quarters(dev):
-    """13 of 512 x 512: 832 entries of the apply product, 64 more than three per compute unit hold; one alone; 12, exactly one round."""
-    wl = workloads.custom("f32_tail", [(512, 512)], w_dtype=torch.float32, g_dtype=torch.float32, ns_dtype="f32", seed_base=349)
+@pytest.mark.parametrize("shape,lengths,product", [((512, 512), (1, 12, 13), "apply"), ((512, 4160), (1, 14, 15), "gram")])
+def test_f32_bits_where_the_last_entries_run_in_quarters(dev, shape, lengths, product):
+    """13 of 512 x 512: 832 entries of the apply product, 64 more than three per compute unit hold; one alone; 12, exactly one round.  15 of
+    512 x 4160: 540 entries of the Gram product, whose sums over K > 4096 have two levels and two places per compute unit; 14, none over."""
+    assert [plan_routes.tails([shape] * n)[product] > 0 for n in lengths] == [False, False, True]
+    wl = workloads.custom("f32_tail", [shape], w_dtype=torch.float32, g_dtype=torch.float32, ns_dtype="f32", seed_base=349)
     first = workloads.make_matrix(wl, 0, dev)
     results = []
-    for n in (1, 12, 13):
+    for n in lengths:
         tensors = [tuple(t.clone() for t in first) for _ in range(n)]
         st = binding.MuonStepper(tensors, ns_dtype="f32")
         st.step(binding.default_hparams(lr=0.02, weight_decay=0.1))

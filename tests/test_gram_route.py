@@ -26,11 +26,31 @@ def test_tables_of_the_gram_route(tmp_path):
     assert run.returncode == 0 and "gram route ok" in run.stdout, run.stdout + run.stderr
 
 
+def scratch_of(lines):
+    """Scratch instructions of a kernel, and those in the loops over K (8 and more MFMAs between a label and the nearest branch back to it,
+    within 600 lines of code and without an inner loop)."""
+    text = [t for _, t in lines]
+    at = {t[:-1]: i for i, t in enumerate(text) if t.endswith(":")}
+    loops = []
+    for i, t in enumerate(text):
+        to = t.split()[-1] if t.startswith(("s_branch", "s_cbranch")) else None
+        if to in at and at[to] < i and sum("v_mfma" in x for x in text[at[to]:i]) >= 8:
+            loops.append((at[to], i))
+    inner = [(a, b) for a, b in loops if b - a < 600 and not any((c, d) != (a, b) and a <= c and d <= b for c, d in loops)]
+    assert inner
+    spills = [i for i, t in enumerate(text) if t.startswith("scratch_")]
+    return len(spills), sum(a <= i <= b for i in spills for a, b in inner)
+
+
 def test_generated_code_of_the_paired_kernels_waits_for_every_lds_read_it_uses(tmp_path_factory):
     kernels = {k: v for k, v in hz.split_kernels(compile_to_asm(tmp_path_factory, "kernels_gemm_pair.hip")).items() if "ns_pair" in k}
     assert len(kernels) == 11        # fine, 128-wide ring, 64-wide with two rings, lone waves, shared symmetric, beside K-major coarse tiles of bf16 and f16, coarse in
                                      # f16, K-major coarse of bf16 and f16
+    # registers spilled around the epilogues of the kernels that hold several coarse bodies, none in a loop over K
+    most = {"ns_pair_sym_kernel": 32, "ns_pair_beside_kernel": 8, "ns_pair_coarse_kernel": 4}
     for name, lines in kernels.items():
+        spilled, in_loops = scratch_of(lines)
+        assert spilled <= next((n for k, n in most.items() if k in name), 0) and in_loops == 0, (name, spilled, in_loops)
         assert any("v_mfma_f32_32x32x16_f16" in t for _, t in lines) or "Lb1E" in name and "4Bf16" in name, name
         assert hz.check_kernel(lines) == [], name
 
