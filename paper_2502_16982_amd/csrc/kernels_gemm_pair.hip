@@ -181,6 +181,28 @@ __global__ __launch_bounds__(256, 1) void ns_pair_sym_kernel(SharedArgs args) {
   }
 }
 
+// Apply products of both sides in coarse tiles from one table, with bf16 operands: those of the first iteration, and of all iterations where
+// nothing takes the Gram route.
+__global__ __launch_bounds__(256, 1) void ns_pair_apply_kernel(SharedArgs args) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int wave_id = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  (void)args;
+  for (int t = blockIdx.x;; t += gridDim.x) {
+    const __attribute__((address_space(4))) SharedArgs* a = (const __attribute__((address_space(4))) SharedArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));                  // see ns_pair_sym_kernel
+    if (t >= a->n_tiles) break;
+    const GemmTile tile = load_tile(a->tiles, t);
+    const auto& s = a->side[(__builtin_amdgcn_readfirstlane(tile.flags) & kTileSecond) ? 1 : 0];
+    const GemmProblem p = s.probs[tile.prob];
+    const bool out_f16 = (s.kind & kSideOutF16) != 0;
+    if (__builtin_amdgcn_readfirstlane(tile.shape) == kShape512x128)
+      gemm_tile_body<512, 128, 4, 1, 2, true, Bf16, Any16>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add, wave_id, out_f16);
+    else
+      gemm_tile_body<256, 256, 2, 2, 2, true, Bf16, Any16>(p, tile, smem, s.beta_acc, s.beta_e, s.alpha_idx, s.diag_add, wave_id, out_f16);
+    __syncthreads();        // every wave has read its part of the LDS images: the next tile may overwrite them
+  }
+}
+
 // An apply product in coarse tiles and, in the same launch, a product of the other side in 128-wide ones: the K-major tiles of 256
 // leave compute units idle in their last round, and the side beside them would wait for a launch of its own.  The long tiles start first.
 template <typename IN>
@@ -238,6 +260,8 @@ hipError_t gemm_pair_setup() {
                             (int)(lds_ring64(kRing64Few) + kLdsFold64));
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_pair_sym_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds512);
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_pair_apply_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds512);
   if (e == hipSuccess)
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(&ns_pair_beside_kernel<Bf16>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds512);
   if (e == hipSuccess)
@@ -301,10 +325,14 @@ hipError_t launch_gemm_pair(int coarse, int flags, const GemmSide& x, const Gemm
 
 hipError_t launch_gemm_shared(int flags, const GemmSide& x, const GemmSide& y, const GemmTile* tiles, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return hipSuccess;
-  if (((x.kind | y.kind) & kSideKMajor) || x.alpha_idx == kAlphaFromPartials || y.alpha_idx == kAlphaFromPartials) return hipErrorInvalidValue;
-  const int grid = gemm_coarse_blocks();
-  ns_pair_sym_kernel<<<(flags & kGemmPersistent) && n_tiles > grid ? grid : n_tiles, 256, (flags & kGemmStrips) ? kLds512 : kLds256, s>>>(
-      SharedArgs{{x, y}, tiles, n_tiles});
+  const bool apply = (x.kind & kSideKMajor) != 0;
+  if (apply != ((y.kind & kSideKMajor) != 0) || (apply && ((x.kind | y.kind) & kSideInF16)) || x.alpha_idx == kAlphaFromPartials || y.alpha_idx == kAlphaFromPartials)
+    return hipErrorInvalidValue;
+  const int grid = (flags & kGemmPersistent) && n_tiles > gemm_coarse_blocks() ? gemm_coarse_blocks() : n_tiles;
+  const size_t lds = (flags & kGemmStrips) ? kLds512 : kLds256;
+  const SharedArgs args{{x, y}, tiles, n_tiles};
+  if (apply) ns_pair_apply_kernel<<<grid, 256, lds, s>>>(args);
+  else ns_pair_sym_kernel<<<grid, 256, lds, s>>>(args);
   return hipGetLastError();
 }
 

@@ -252,9 +252,12 @@ int enqueue_paired(muon_ctx* ctx, const Chunk& ch, const muon_hparams* hp, const
     for (int i = 0; i < 2; ++i) op[i] = at[i] < ops[i].size() ? &ops[i][at[i]] : nullptr;
     // An apply product in coarse tiles shares its launch with a product of the other group that is all fine tiles and not too many.
     // Otherwise it runs alone and a symmetric product of the other group waits for the next one of this.
+    // Two apply products that read bf16, the first iteration's, have a table of both where that saves a round.
+    const bool joint = op[0] && op[1] && op[0]->product == kPairApply && op[1]->product == kPairApply && ch.n_shared_app > 0 &&
+                       !((op[0]->kind | op[1]->kind) & kSideInF16);
     int applied = -1;                // group of that apply product
     bool beside = false;
-    for (int i = 0; i < 2 && op[0] && op[1] && applied < 0; ++i)
+    for (int i = 0; i < 2 && op[0] && op[1] && applied < 0 && !joint; ++i)
       if (op[i]->product == kPairApply && ch.groups[i].coarse.n_apply > 0) {
         beside = ch.beside[i ^ 1][op[i ^ 1]->product];
         if (beside || op[i ^ 1]->product != kPairApply) applied = i;
@@ -277,12 +280,12 @@ int enqueue_paired(muon_ctx* ctx, const Chunk& ch, const muon_hparams* hp, const
       for (int i = 0; i < 2; ++i) {
         side[i].alpha_idx = -1;
         const bool guest = beside && i != applied;            // all of it in the coarse launch
-        if (!op[i] || (guest && level == 0)) continue;
         const Group& g = ch.groups[i];
+        if (!op[i] || (guest && level == 0) || (joint && level == 0 && g.coarse.n_apply == 0)) continue;
         const TileSet& ts = level && !guest ? g.coarse : g.fine;
         const bool gram_product = product[i] == kPairGram, apply = product[i] == kPairApply;
         const bool from_lone = lone && i == 1;
-        side[i].n_tiles = from_lone ? g.n_lone : gram_product ? ts.n_sym : apply ? ts.n_apply : ts.n_poly;
+        side[i].n_tiles = joint && level ? ch.n_shared_app : from_lone ? g.n_lone : gram_product ? ts.n_sym : apply ? ts.n_apply : ts.n_poly;
         if (side[i].n_tiles == 0) continue;
         side[i].tiles = reinterpret_cast<const GemmTile*>(ctx->ws + (from_lone ? g.lone : gram_product ? ts.sym : apply ? ts.apply : ts.poly));
         side[i].probs = reinterpret_cast<const GemmProblem*>(ctx->ws + op[i]->probs);
@@ -296,12 +299,18 @@ int enqueue_paired(muon_ctx* ctx, const Chunk& ch, const muon_hparams* hp, const
         strips = strips || ts.strips;
       }
       if (side[0].n_tiles + side[1].n_tiles == 0) continue;
-      const PairForm& fine_form = beside ? ch.pair[applied == 0 ? kPairApply : kPairNone][applied == 1 ? kPairApply : kPairNone]
+      const auto own = [&](int i) { return ch.groups[i].coarse.n_apply > 0 ? kPairApply : kPairNone; };
+      const PairForm& fine_form = joint ? ch.pair[own(0)][own(1)] : beside ? ch.pair[applied == 0 ? kPairApply : kPairNone][applied == 1 ? kPairApply : kPairNone]
                                   : lone ? ch.groups[1].lone_form[op[0] != nullptr] : form;
       const int flags = level ? (strips ? kGemmStrips : 0) | (form.persistent ? kGemmPersistent : 0) : quarter_flags(fine_form.quarters, fine_form.few);
       if (level && both_sym && ch.n_shared_sym > 0) {
         const size_t tiles = ch.shared_sym[product[0] != kPairGram][product[1] != kPairGram];
         MUON_TIMED(timed_as, launch_gemm_shared(flags, side[0], side[1], reinterpret_cast<const GemmTile*>(ctx->ws + tiles), ch.n_shared_sym, s));
+        continue;
+      }
+      if (level && joint) {
+        const int joint_flags = (ch.shared_app_strips ? kGemmStrips : 0) | (ch.shared_app_steady ? kGemmPersistent : 0);
+        MUON_TIMED(timed_as, launch_gemm_shared(joint_flags, side[0], side[1], reinterpret_cast<const GemmTile*>(ctx->ws + ch.shared_app), ch.n_shared_app, s));
         continue;
       }
       if (level && beside) {

@@ -129,7 +129,7 @@ hipError_t gemm_pair_setup();
 hipError_t launch_gemm_pair(int coarse, int flags, const GemmSide& x, const GemmSide& y, double eps, hipStream_t s);
 // x, an apply product in coarse tiles, and y in 128-wide ones (K >= 256), one block per compute unit.
 hipError_t launch_gemm_beside(int flags, const GemmSide& x, const GemmSide& y, hipStream_t s);
-// Coarse symmetric products of both from one table; the sides' own tables are not used.
+// Coarse symmetric products of both, or apply products with bf16 operands, from one table; the sides' own tables are not used.
 hipError_t launch_gemm_shared(int flags, const GemmSide& x, const GemmSide& y, const GemmTile* tiles, int n_tiles, hipStream_t s);
 hipError_t gemm_f32_setup();
 // tail: the last entries of a table of whole ones, as many, that run in quarters in a launch of their own.

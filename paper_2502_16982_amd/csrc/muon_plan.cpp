@@ -435,6 +435,8 @@ struct PairSide {
   std::vector<Load> load[4];
   std::vector<std::vector<GemmTile>> coarse_sym;       // and the coarse tiles of its symmetric products
   std::vector<std::vector<int>> coarse_cuts;
+  std::vector<std::vector<GemmTile>> coarse_app;       // of its apply product, where that is not all fine tiles
+  std::vector<std::vector<int>> app_cuts;
   std::vector<int64_t> w_n, w_m;
   std::vector<Load> lone;                               // its lone table
   int64_t lo[4] = {kMaxDim, kMaxDim, kMaxDim, kMaxDim}, hi[4] = {};
@@ -452,6 +454,15 @@ PairForm pair_form(const PairSide& x, int px, const PairSide& y, int py, int blo
   return f;
 }
 
+// In a table of both groups: problems from n0 on are the second's.
+void mark_second(GemmTile* tiles, int count, int n0) {
+  for (int t = 0; t < count; ++t)
+    if (tiles[t].prob >= n0) {
+      tiles[t].prob -= n0;
+      tiles[t].flags |= kTileSecond;
+    }
+}
+
 // Whether a product in 128-wide blocks shares a launch with an apply product in coarse tiles (`g`'s): where the compute units that the
 // last round of those leaves idle can take it.  A coarse tile takes about 1.65 us per slab and 8, a block 0.3 and 5.  Step, in parts of the
 // one without the Gram route, alone / beside: 3000^2 with one of 1024 x 4096 (144 tiles; 36 and 256 blocks) 1.085 / 1.030, 4 of 1536^2 with
@@ -466,6 +477,16 @@ bool fits_beside(const Group& g, const std::vector<Load>& load, int blocks) {
     need += (double)l.entries * (0.3 * (double)l.k / 64.0 + 5.0);
   }
   return rest > 0 && entries > 0 && entries <= b && need <= 1.25 * (double)(b - rest) * (1.65 * (double)g.longest_m / 64.0 + 8.0);
+}
+
+// Whether the apply products of both groups, where they come together, take one table of coarse tiles: where that saves a round.  An
+// all-fine one counts as a round.  us per step of three iterations, where all of them meet, without the route / two launches or beside / one
+// table: 4 of 1024^2 with 3 of 1024 x 4096 (64 tiles and 192) 306 / 325 / 311, 3000^2 with one (144, 64) 526 / 542 / 530, 4 of 1536^2 with one of 640 x 5000
+// (144, 50) 339 / 359 / 345, 10 of 1536^2 with 6 of 1024 x 4096 (360, 384) 1063 / 1171 / 1085.
+bool saves_a_round(size_t tiles0, bool fine0, size_t tiles1, bool fine1, int blocks) {
+  const size_t b = (size_t)std::max(blocks, 1);
+  auto rounds = [b](size_t t) { return (t + b - 1) / b; };
+  return rounds(tiles0 + tiles1) < (fine0 ? 1 : rounds(tiles0)) + (fine1 ? 1 : rounds(tiles1));
 }
 
 void plan_matrices(const muon_param* p, int n, int ns_dtype, std::vector<MatPlan>& out, size_t& total_partials) {
@@ -568,7 +589,7 @@ bool folds_identity(const MatPlan& q, int ns_dtype) { return ns_dtype == MUON_BF
 // 4096 173 / 164, 4 of 1024^2 and 3 of 1024 x 4096 458 / 456, 8 and 6 1050 / 960, 48 and 36 4622 / 4276, 4 of 4096^2 and 3 of 4096 x 11008 12992 / 11960;
 // a few beside much more of the other kind pay for the longer chain of launches: 3000^2 and one of 1024 x 4096 825 / 850, 4 of 1536^2 and
 // one of 640 x 5000 528 / 544, 8 of 2048^2 and 2 of 1024 x 4096 1931 / 1978, 48 of 1024^2 and 4 1934 / 1959.  (Three iterations, which no
-// matrix takes on its Gram matrix, but in two groups all the same: 4 of 1024^2 and 3 of 1024 x 4096 296 / 320, 3000^2 and one 518 / 533, alone even.)
+// matrix takes on its Gram matrix, but in two groups all the same: 4 of 1024^2 and 3 of 1024 x 4096 306 / 311, 3000^2 and one 526 / 530, alone even.)
 bool gram_route(const MatPlan& q, int ns_dtype) {
   if (ns_dtype != MUON_BF16 || q.mp < 384) return false;
   const double least = q.mp >= 2560 ? 2.0 : q.mp >= 1280 ? 2.6 : q.mp >= 640 ? 4.0 : 8.0;
@@ -767,7 +788,7 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
 
     // Whether the products go to the fine launch altogether is decided for the chunk, not for a group.
     // (Apply products: for a group where there are two, whose apply products never meet in a launch.)
-    CoarseLoad coarse_sym, coarse_sym_of[2], coarse_app[2];
+    CoarseLoad coarse_sym, coarse_sym_of[2], coarse_app[2], coarse_app_all;
     std::vector<int> members_of[2];              // Eq. 2 as it is written, Gram route
     for (int i = ch.first; i < ch.first + ch.count; ++i) {
       const MatPlan& q = plan.mats[i];
@@ -779,7 +800,9 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
       const size_t sym_tiles = cm * (cm + 1) / 2 + (odd_m && q.mp >= strip_h ? (size_t)((q.mp + strip_h - 1) / strip_h) : 0);
       coarse_sym.add(sym_tiles, q.mp, q.np);
       coarse_sym_of[q.gram].add(sym_tiles, q.mp, q.np);
-      coarse_app[q.gram].add(cm * cn + (odd_m && q.np >= strip_h ? (size_t)((q.np + strip_h - 1) / strip_h) : 0), q.mp, q.np);
+      const size_t app_tiles = cm * cn + (odd_m && q.np >= strip_h ? (size_t)((q.np + strip_h - 1) / strip_h) : 0);
+      coarse_app[q.gram].add(app_tiles, q.mp, q.np);
+      coarse_app_all.add(app_tiles, q.mp, q.np);
     }
     const bool few_sym = few_coarse_sym(coarse_sym, (int)planes, plan.coarse_blocks);
     ch.paired = !members_of[1].empty();
@@ -978,7 +1001,10 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
           PairSide& side = pair_sides[route];
           side.lo[kPairGram] = lo_n; side.hi[kPairGram] = hi_n;
           side.lo[kPairSym] = side.lo[kPairApply] = lo_m; side.hi[kPairSym] = side.hi[kPairApply] = hi_m;
-          if (level == 1) side.coarse_sym = sym, side.coarse_cuts = sym_cuts, side.w_n = w_n, side.w_m = w_m;
+          if (level == 1) {
+            side.coarse_sym = sym, side.coarse_cuts = sym_cuts, side.w_n = w_n, side.w_m = w_m;
+            side.coarse_app = app, side.app_cuts = app_cuts;
+          }
           if (level == 0) {
             side.load[kPairGram] = load_of(sym, w_n);
             side.load[kPairSym] = load_of(sym, w_m);
@@ -1066,13 +1092,57 @@ int plan_build(Plan& plan, const muon_param* shapes, int32_t n, int32_t ns_dtype
           ch.shared_sym[i][j] = cursor;
           GemmTile* const out = reinterpret_cast<GemmTile*>(img.data() + cursor);
           deal_tiles(order, tiles, cuts, w, out, 2 * hi <= 3 * lo ? plan.coarse_blocks / kXcds : 0, false);
-          for (int t = 0; t < ch.n_shared_sym; ++t)
-            if (out[t].prob >= n0) {
-              out[t].prob -= n0;
-              out[t].flags |= kTileSecond;
-            }
+          mark_second(out, ch.n_shared_sym, n0);
           cursor += (size_t)ch.n_shared_sym * sizeof(GemmTile);
         }
+    }
+    if (ch.paired && !members_of[0].empty() && !few_coarse_apply(coarse_app_all, (int)planes, plan.coarse_blocks)) {
+      // one list of both groups' coarse tiles of the apply products
+      std::vector<std::vector<GemmTile>> tiles;
+      std::vector<std::vector<int>> cuts;
+      std::vector<int64_t> w;
+      size_t count[2] = {0, 0};
+      bool fits = true;                          // all-fine products: nothing may be left beside the coarse tiles
+      const int n0 = (int)members_of[0].size();
+      for (int r = 0; r < 2; ++r) {
+        const bool fine = ch.groups[r].coarse.n_apply == 0;
+        for (size_t k = 0; k < members_of[r].size(); ++k) {
+          const MatPlan& q = plan.mats[members_of[r][k]];
+          std::vector<GemmTile> own;
+          std::vector<int> own_cuts;
+          if (!fine) {
+            own = pair_sides[r].coarse_app[k];
+            own_cuts = pair_sides[r].app_cuts[k];
+          } else {
+            const bool strip = q.mp % kCoarse != 0;
+            fits = fits && q.np % kCoarse == 0 && (!strip || q.np >= kShapeRows[kShape512x128]);
+            if (!fits) break;
+            blocked_tiles((int32_t)k, kCoarse, kShape256, q.np / kCoarse, q.mp / kCoarse, false, 0, 0, -1, own, own_cuts, 8, 2);
+            if (strip) strip_tiles((int32_t)k, q.np, q.mp - q.tile, own, own_cuts);
+            ch.shared_app_strips = ch.shared_app_strips || strip;
+          }
+          count[r] += own.size();
+          for (GemmTile& t : own) t.prob += r * n0;
+          tiles.push_back(std::move(own));
+          cuts.push_back(std::move(own_cuts));
+        }
+        ch.shared_app_strips = ch.shared_app_strips || (!fine && ch.groups[r].coarse.strips);
+        w.insert(w.end(), pair_sides[r].w_m.begin(), pair_sides[r].w_m.end());
+      }
+      const size_t start = align_up(cursor, kTableAlign), bytes = (count[0] + count[1]) * sizeof(GemmTile);
+      if (fits && start + bytes <= tl.total &&
+          saves_a_round(count[0], ch.groups[0].coarse.n_apply == 0, count[1], ch.groups[1].coarse.n_apply == 0, plan.coarse_blocks)) {
+        std::vector<int> order(w.size());
+        std::iota(order.begin(), order.end(), 0);
+        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return w[x] > w[y]; });
+        ch.shared_app_steady = 2 * *std::max_element(w.begin(), w.end()) <= 3 * *std::min_element(w.begin(), w.end());
+        ch.shared_app = start;
+        ch.n_shared_app = (int)(count[0] + count[1]);
+        GemmTile* const out = reinterpret_cast<GemmTile*>(img.data() + start);
+        deal_tiles(order, tiles, cuts, w, out, ch.shared_app_steady ? plan.coarse_blocks / kXcds : 0, false);
+        mark_second(out, ch.n_shared_app, n0);
+        cursor = start + bytes;
+      }
     }
     if (ch.paired) {
       for (int i = 0; i < 4; ++i)

@@ -123,6 +123,11 @@ struct Chunk {
   // [first group's Gram product / another][second group's Gram product / another]
   size_t shared_sym[2][2] = {};
   int n_shared_sym = 0;
+  // Apply products of both groups in one launch of coarse tiles, where they read the same type: n_shared_app entries (0: no such table).  A
+  // group without coarse apply tiles of its own has all of its product in here, the other its fine tiles in a launch of theirs.
+  size_t shared_app = 0;
+  int n_shared_app = 0;
+  bool shared_app_strips = false, shared_app_steady = false;
 };
 
 struct Plan {

@@ -10,7 +10,7 @@
 #include "../paper_2502_16982_amd/csrc/muon_plan.h"
 
 using namespace muon;
-static int failures = 0, beside = 0;
+static int failures = 0, beside = 0, joint = 0;
 #define CHECK(c) do { if (!(c)) { if (failures++ < 20) std::printf("line %d: %s\n", __LINE__, #c); } } while (0)
 
 typedef std::tuple<int, int, int, int> Key;      // problem, row, column, shape
@@ -83,6 +83,34 @@ static void walk(const std::vector<muon_param>& p, size_t cap) {
           CHECK(keys(t, ch.n_shared_sym, r) == keys(reinterpret_cast<const GemmTile*>(img + c.sym), c.n_sym, -1));
         }
       }
+    if (ch.n_shared_app > 0) {           // a group's own coarse tiles, or coarse tiles over all of its outputs
+      CHECK(ch.shared_app + sizeof(GemmTile) * (size_t)ch.n_shared_app <= plan.image.size());
+      const GemmTile* t = reinterpret_cast<const GemmTile*>(img + ch.shared_app);
+      for (int r = 0; r < 2; ++r) {
+        const Group& h = ch.groups[r];
+        const std::multiset<Key> own = keys(t, ch.n_shared_app, r);
+        if (h.coarse.n_apply > 0) {
+          CHECK(own == keys(reinterpret_cast<const GemmTile*>(img + h.coarse.apply), h.coarse.n_apply, -1));
+          continue;
+        }
+        std::vector<std::set<std::pair<int, int>>> seen(h.members.size());
+        for (const Key& k : own) {
+          const int rows = kShapeRows[std::get<3>(k)] / kTileUnit, cols = kShapeCols[std::get<3>(k)] / kTileUnit;
+          CHECK(std::get<0>(k) >= 0 && std::get<0>(k) < h.n_prob);
+          CHECK(std::get<3>(k) == (int)kShape256 || (std::get<3>(k) == (int)kShape512x128 && ch.shared_app_strips));
+          for (int a = 0; a < rows; ++a)
+            for (int b = 0; b < cols; ++b) seen[std::get<0>(k)].insert({std::get<1>(k) + a, std::get<2>(k) + b});
+        }
+        for (size_t k = 0; k < seen.size(); ++k) {
+          const MatPlan& q = plan.mats[h.members[k]];
+          CHECK(seen[k].size() == (size_t)(q.np / kTileUnit) * (q.mp / kTileUnit) && seen[k].rbegin()->first == q.np / kTileUnit - 1);
+          int last = 0;
+          for (const auto& at : seen[k]) last = std::max(last, at.second);
+          CHECK(last == q.mp / kTileUnit - 1);
+        }
+        joint += 1;
+      }
+    }
     for (int i = 0; i < 2; ++i)
       for (int p : {kPairGram, kPairSym, kPairApply}) {        // blocks of a ring beside coarse tiles: all of the product in them, K of four slabs
         if (!ch.beside[i][p]) continue;
@@ -173,11 +201,12 @@ int main() {
   CHECK(gram_coefficients_fit(textbook, 4, &gain));
   const std::vector<muon_param> few = {mat(3000, 3000), mat(1024, 4096)}, full = {mat(2048, 2048), mat(2048, 2048), mat(2048, 2048), mat(2048, 2048),
                                                                                    mat(2048, 2048), mat(2048, 2048), mat(2048, 2048), mat(2048, 2048), mat(1024, 4096)};
-  beside = 0;
+  CHECK(joint > 0);
+  beside = joint = 0;
   walk(few, 0);
-  CHECK(beside == 3);
+  CHECK(beside == 3 && joint == 1);
   walk(full, 0);                      // 512 apply tiles: no compute unit is idle
-  CHECK(beside == 3);
+  CHECK(beside == 3 && joint == 1);
   std::printf(failures ? "failed\n" : "gram route ok\n");
   return failures ? 1 : 0;
 }

@@ -36,6 +36,7 @@ def _routes(shapes, ns, compute_units):
              "coarse": [tuple(int(v) for v in line[3:]) for line in lines if line[0] == "coarse" and line[1] == "0"],
              "lone": next(((int(line[2]), line[3], line[4]) for line in lines if line[0] == "lone" and line[1] == "0"), None),
              "shared": next((int(line[2]) for line in lines if line[0] == "shared" and line[1] == "0"), 0),
+             "joint": next(((int(line[2]), bool(int(line[3]))) for line in lines if line[0] == "joint" and line[1] == "0"), (0, False)),
              "beside": {(int(line[2]), line[3]) for line in lines if line[0] == "beside" and line[1] == "0"}}
     return tables, fold[0], tails, pairs
 
@@ -55,7 +56,8 @@ def tails(shapes, ns="f32", compute_units=256):
 def pair_routes(shapes, compute_units=256):
     """Of a list with matrices of the Gram route, planned whole.  "pairs": {(product of the others, product of theirs): (entries, form) of the
     fine launch}, "coarse": coarse entries of the symmetric and of the apply products of either group, "lone": entries and forms of their symmetric
-    products without the others', "shared": entries of the table of both, "beside": {(group, product)} that share the other's apply launch."""
+    products without the others', "shared": entries of the table of both, "joint": those of both apply products' and whether strips are among them,
+    "beside": {(group, product)} that share the other's apply launch."""
     return _routes(tuple(tuple(s) for s in shapes), "bf16", compute_units)[3]
 
 

@@ -4,7 +4,8 @@
 // line per product and level: chunk, product, level, entries of the table, form (whole, quarters, ring4, waves, ring128), last entries that
 // run in quarters behind it.  Chunks with them: "pair", chunk, product of the matrices iterated as Eq. 2 is written (none, gram, sym,
 // apply), of the others, entries of the fine launch, its form; "coarse", chunk, group, entries of the symmetric and of the apply product;
-// "lone", chunk, entries, form alone, form with an apply product; "shared", chunk, entries; "beside", chunk, group, product.
+// "lone", chunk, entries, form alone, form with an apply product; "shared", chunk, entries; "joint", chunk, entries of both apply products,
+// strips among them; "beside", chunk, group, product.
 #include <cstdio>
 #include <cstdlib>
 #include <vector>
@@ -31,6 +32,7 @@ static void paired(size_t c, const Chunk& ch) {
   const Group& g = ch.groups[1];
   if (g.n_lone > 0)
     std::printf("lone %zu %d %s %s\n", c, g.n_lone, form(g.lone_form[0].quarters, g.lone_form[0].few), form(g.lone_form[1].quarters, g.lone_form[1].few));
+  if (ch.n_shared_app > 0) std::printf("joint %zu %d %d\n", c, ch.n_shared_app, ch.shared_app_strips ? 1 : 0);
   if (ch.n_shared_sym > 0) std::printf("shared %zu %d\n", c, ch.n_shared_sym);
   for (int i = 0; i < 2; ++i)
     for (int p = 1; p < 4; ++p)

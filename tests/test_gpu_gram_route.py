@@ -53,6 +53,8 @@ PAIRED = [
     [(1024, 1024)] * 4 + [(1024, 4096)] * 2 + [(4096, 1024)],      # the Gram route's apply product with everything of the others
     [(1024, 1024)] * 8 + [(1024, 4096)] * 3 + [(4096, 1024)] * 3,  # apply products in fine tiles with symmetric ones that have few coarse tiles
     [(600, 300)] * 4 + [(2560, 5200)] * 2,                         # the others' apply product alone is fine
+    [(1536, 1536)] * 4 + [(640, 5000)],                            # the first iteration's apply products from one table, strips among them
+    [(1536, 1536)] * 10 + [(1024, 4096)] * 6,                      # the same, both coarse by themselves
 ]
 
 

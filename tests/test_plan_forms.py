@@ -31,6 +31,9 @@ def test_launches_of_the_gram_route():
     assert any(r["shared"] for r in both)
     assert {p for r in both for p in r["beside"]} == {(i, p) for i in (0, 1) for p in ("gram", "sym", "apply")}
     assert {r["lone"][1] for r in both if r["lone"]} >= {"quarters", "ring128", "whole"}
+    joint = [r["joint"] for r in both]                                  # both apply products from one table, strips among them
+    assert {n > 0 for n, _ in joint} == {True, False} and {s for n, s in joint if n} == {True, False}
+    assert {tuple(c[1] > 0 for c in r["coarse"]) for r in both if r["joint"][0]} >= {(True, False), (False, True), (True, True)}
     few = plan_routes.pair_routes(PAIRED[3])                            # an apply product in fine tiles, symmetric ones with coarse tiles
     assert few["coarse"][0][1] == 0 and few["coarse"][1][0] > 0 and few["lone"][2] == "whole"
 
