@@ -3,12 +3,12 @@
 //
 // Such a launch is bound by the trip of its slabs from the memory-side cache: with two stages (the tile of the fine launch, which
 // shares a compute unit with a second block where there is one) a lone block takes 0.6 us per slab, and 64-wide blocks move twice
-// the operands through the LDS.  With four stages three slabs are on their way, 0.29 us per slab at K = 2048 (64 KB/us of operands per
+// the operands through the LDS.  With four stages three slabs are on their way, 0.29 us per slab at K = 2048 (110 KB/us of operands per
 // compute unit; the MFMAs of a slab are 0.22).  The fragments of the next slab are read behind the first half of this slab's MFMAs, the
 // requests go out one behind every second MFMA; the addend comes as an image into the first stage that no slab is left for,
 // and the results leave from there.  Addresses, swizzles and the order of an element's products are those of the other tiles (same
 // bits).  muon_plan.cpp holds the line and both sides' times; us per step: 2560^2 523 -> 440, 1536^2 x 3 369 -> 312, 1408 x 2048 x 3 419 -> 366, 12 of
-// 640 x 1408 295 -> 260, 7 of 1024^2 277 -> 250, ragged list of six 296 -> 282, layer of 4 x 1024^2 and 3 x 1024 x 4096 445 -> 432.
+// 640 x 1408 295 -> 260, 7 of 1024^2 277 -> 250, ragged list of six 296 -> 282.
 #pragma once
 
 namespace muon {

@@ -4,13 +4,14 @@
 // products write the type they read, apply products bf16 or f16.  The tiles, their pipelines and what bounds them are those of
 // kernels_gemm_bf16.hip, gemm_tile64.h and gemm_ring128.h; what is new is that
 // two sides share a launch, since each alone leaves compute units idle in its last round and one chain of launches is shorter than
-// two.  us per step, all matrices as Eq. 2 / this: 4 of 1024^2 with 3 of 1024 x 4096 (fine launches) 458 / 456, twelve of those (coarse
+// two.  us per step, all matrices as Eq. 2 / this: 4 of 1024^2 with 3 of 1024 x 4096 (fine launches) 472 / 453, twelve of those (coarse
 // ones) 4622 / 4276, 4 of 4096^2 with 3 of 4096 x 11008 12992 / 11960.
 // Fine launches pair anything with anything: blocks below blocks_x are the first side's.  In coarse launches the symmetric
 // products share a kernel, from one table that is dealt as one (side by side, each dealt by itself, 30 of 1024^2 with 3 of 1024 x 4096
 // took 82 us per polynomial launch, from one table 70, where all of them as Eq. 2 take 69): a kernel with the K-major bodies too
 // spilled more and took a third longer on every product.  An apply product in coarse tiles takes in a product that is all 128-wide blocks
-// (ns_pair_beside_kernel; one tile per block: 5 to 9 registers are spilled, none in a K loop).
+// (ns_pair_beside_kernel; one tile per block: 5 to 9 registers are spilled, none in a K loop), and the other side's apply product where one table of both
+// saves a round (ns_pair_apply_kernel).
 #include "gemm_tile256.h"
 #include "gemm_planes.h"
 #include "gemm_tile64.h"

@@ -318,7 +318,12 @@ int enqueue_paired(muon_ctx* ctx, const Chunk& ch, const muon_hparams* hp, const
         continue;
       }
       const int x = longest[1] > longest[0];     // the longer K loops start first
-      MUON_TIMED(timed_as, launch_gemm_pair(level, flags, side[x], side[x ^ 1], hp->eps, s));
+      if (level) {                               // a launch for each
+        for (int i : {x, x ^ 1})
+          if (side[i].n_tiles > 0) MUON_TIMED(timed_as, launch_gemm_pair(1, flags, side[i], GemmSide{}, hp->eps, s));
+        continue;
+      }
+      MUON_TIMED(timed_as, launch_gemm_pair(0, flags, side[x], side[x ^ 1], hp->eps, s));
     }
   }
   return MUON_OK;

@@ -340,12 +340,15 @@ int64_t entries_of_work(const std::vector<Load>& load, int64_t fixed = 0) {
   return (total + longest - 1) / longest;
 }
 // Plain bf16: 128-wide blocks with a ring of four slabs (gemm_ring128.h) where every entry has a compute unit to itself, from where
-// 64-wide ones stop paying.  us per launch, 64-wide / 128-wide with two stages / with the ring, polynomial (entries) and apply product:
-// K = 256 180 9.5 / 9.7 / 10.0, 240 9.2 / 9.0 / 8.9; 384 180 11.2 / 11.7 / 11.6, 243 11.2 / 10.7 / 10.3; 512 150 11.9 / 12.4 / 11.8, 180
-// 12.1 / 12.6 / 12.0, 240 13.8 / 12.7 / 12.3, 144 9.6 / 10.5 / 9.8, 176 9.9 / 10.8 / 10.1, 208 11.6 / 10.8 / 10.3; 768 126 11.5 / 15.2 / 13.3, 147 13.8 /
-// 15.0 / 13.1, 252 16.9 / 15.4 / 14.3, 144 11.6 / 13.1 / 11.8, 180 12.2 / 13.7 / 11.9; 1024 108 12.0 / 16.0 / 13.7, 144 15.0 / 16.3 / 14.0, 252 19.3 /
-// 17.4 / 15.2, 192 14.0 / 15.4 / 13.0; 1408 66 12.6 / 19.3 / 15.2, 132 17.4 / 20.0 / 16.1, 198 22.0 / 20.9 / 16.8, 242 21.2 / 20.1 / 15.9; 2048 136 22.7
-// / 25.3 / 18.9; 2816 253 40.1 / 33.9 / 27.6; with more entries than compute units 512 260 15.6 / 14.2 / 18.2, 1408 264 24.9 / 22.8 / 27.8.
+// 64-wide ones stop paying.  us per launch, 64-wide / 128-wide with two stages / with the ring, polynomial products (K, entries):
+//   256  180 9.5 / 9.7 / 10.0, 240 9.2 / 9.0 / 8.9;  384  180 11.2 / 11.7 / 11.6, 243 11.2 / 10.7 / 10.3
+//   512  150 11.9 / 12.4 / 11.8, 180 12.1 / 12.6 / 12.0, 240 13.8 / 12.7 / 12.3;  768  126 11.5 / 15.2 / 13.3, 147 13.8 / 15.0 / 13.1, 252 16.9 / 15.4 / 14.3
+//   1024  108 12.0 / 16.0 / 13.7, 144 15.0 / 16.3 / 14.0, 252 19.3 / 17.4 / 15.2
+//   1408  66 12.6 / 19.3 / 15.2, 132 17.4 / 20.0 / 16.1, 198 22.0 / 20.9 / 16.8;  2048  136 22.7 / 25.3 / 18.9;  2816  253 40.1 / 33.9 / 27.6
+// apply products:
+//   512  144 9.6 / 10.5 / 9.8, 176 9.9 / 10.8 / 10.1, 208 11.6 / 10.8 / 10.3;  768  144 11.6 / 13.1 / 11.8, 180 12.2 / 13.7 / 11.9
+//   1024  192 14.0 / 15.4 / 13.0;  1408  242 21.2 / 20.1 / 15.9
+// with more entries than compute units: 512  260 15.6 / 14.2 / 18.2;  1408  264 24.9 / 22.8 / 27.8
 constexpr int64_t kRingK = 256, kRingFewK = 768;   // shortest K of a launch; longest K from which fewer entries do
 bool runs_on_ring128(const std::vector<Load>& load, int blocks) {
   int64_t count = 0, longest = 0;
@@ -388,6 +391,8 @@ bool runs_in_quarters(const std::vector<Load>& load, bool mc, int planes, int bl
 // fp32: entries beyond full rounds of whole ones (three to a compute unit) that run in quarters in a launch of their own, where they
 // are few and the round they would add is long.  us per apply product, with that round / with the second launch: 832 entries of K = 512
 // 43.3 / 40.8, 800 of 640 55.0 / 51.0, 832 of 1024 77.4 / 69.2; but 896 of 512 43.8 / 44.3, 900 of 640 53.3 / 57.3, 832 of 256 27.4 / 27.8.
+// us per step of other lists: 784 of 512 410 / 398, 800 of 512 394 / 394; beyond the line nothing is sure: 864 of 512 431 / 427, 837 of 576 475 / 476, 840
+// of 640 497 / 494, but 834 of 384 317 / 322, 868 of 448 394 / 398.
 constexpr int64_t kTailK = 512;
 int tail_in_quarters(const std::vector<Load>& load, bool whole, bool long_k, int blocks) {
   int64_t count = 0;
@@ -582,13 +587,14 @@ bool folds_identity(const MatPlan& q, int ns_dtype) { return ns_dtype == MUON_BF
 //   384 x 1536 84 / 87, 24 282 / 260; x 2304 96.5 / 94.7; x 3072 116 / 108, 24 496 / 421
 //   512 x 2048 101.6 / 103.2, 8 198 / 186; x 3072 124 / 119; x 4096 141 / 129, 24 791 / 676
 //   640 x 1664 106 / 112, 24 618 / 565; x 2560 123.8 / 124.4, 8 316 / 279; x 5120 173 / 155;  768 x 3072 147.5 / 147.2, 8 446 / 406
-//   1024 x 2816 158 / 169, 3 333 / 304; x 4096 195.1 / 196.5, 3 383 / 341, 12 1307 / 1034
+//   768 x 2304 133 / 136, x 2688 136 / 141;  1024 x 2816 158 / 169, 3 333 / 304; x 3072 166 / 173, 3 341 / 311; x 3584 182 / 186, 3 363 / 329; x 3840
+//   189 / 190; x 4096 195.1 / 196.5, 3 383 / 341, 12 1307 / 1034;  1152 x 4096 222 / 214
 //   1408 x 2816 240 / 253, 8 1142 / 1102; x 3840 304 / 292, 8 1478 / 1320;  2048 x 4096 530 / 523, 8 2588 / 2788; x 5632 663 / 619, 4 1819 / 1636
 //   2560 x 5120 693 / 667;  3072 x 4608 960 / 985; x 6144 1219 / 1165;  4096 x 8192 2363 / 2164; x 11008 3057 / 2610;  2 of 4096 x 6144 3407 / 4072
 // Fewer rows than 384 gain alone (256 x 4096 122 / 108) and lose beside anything longer.  Beside other matrices: 4 of 512^2 and 2 of 512 x
-// 4096 173 / 164, 4 of 1024^2 and 3 of 1024 x 4096 458 / 456, 8 and 6 1050 / 960, 48 and 36 4622 / 4276, 4 of 4096^2 and 3 of 4096 x 11008 12992 / 11960;
-// a few beside much more of the other kind pay for the longer chain of launches: 3000^2 and one of 1024 x 4096 825 / 850, 4 of 1536^2 and
-// one of 640 x 5000 528 / 544, 8 of 2048^2 and 2 of 1024 x 4096 1931 / 1978, 48 of 1024^2 and 4 1934 / 1959.  (Three iterations, which no
+// 4096 173 / 164, 4 of 1024^2 and 3 of 1024 x 4096 472 / 453, 8 and 6 1065 / 978, 48 and 36 4622 / 4276, 4 of 4096^2 and 3 of 4096 x 11008 12992 / 11960;
+// a few beside much more of the other kind pay for the longer chain of launches: 3000^2 and one of 1024 x 4096 827 / 866 (on a slower card
+// 850 / 905), 4 of 1536^2 and one of 640 x 5000 528 / 544, 8 of 2048^2 and 2 of 1024 x 4096 1931 / 1957, 48 of 1024^2 and 4 1934 / 1965.  (Three iterations, which no
 // matrix takes on its Gram matrix, but in two groups all the same: 4 of 1024^2 and 3 of 1024 x 4096 306 / 311, 3000^2 and one 526 / 530, alone even.)
 bool gram_route(const MatPlan& q, int ns_dtype) {
   if (ns_dtype != MUON_BF16 || q.mp < 384) return false;

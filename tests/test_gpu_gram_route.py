@@ -9,6 +9,7 @@ pytestmark = pytest.mark.gpu
 
 from paper_2502_16982_amd import binding, workloads  # noqa: E402
 from tests import gpu_util as U  # noqa: E402
+from tests import plan_routes  # noqa: E402
 from tests.gpu_util import table_sizes  # noqa: E402
 from tests.test_gpu_parity import assert_records  # noqa: E402
 from tests.test_gram_arithmetic_model import bf16, matrix, written  # noqa: E402
@@ -120,6 +121,23 @@ def test_same_bits_beside_the_other_route(dev, shapes, ns_steps):
     st.close()
     for i, t in alone.items():
         assert torch.equal(t[0], tensors[i][0]) and torch.equal(t[2], tensors[i][2]), (i, shapes[i])
+
+
+@pytest.mark.timeout(600)
+def test_profile_counts_every_launch(dev):
+    """Two apply products in coarse tiles that share no table are two launches; the two symmetric products share one each."""
+    shapes = [(1024, 1024)] * 48 + [(1024, 4096)] * 4
+    routes = plan_routes.pair_routes(shapes)
+    assert routes["coarse"] == [(480, 768), (40, 256)] and routes["joint"][0] == 0 and routes["shared"] == 520
+    st = binding.MuonStepper(workloads.make_all(workloads.custom("gram_profile", shapes, seed_base=527), dev))
+    try:
+        binding.muon_profile_enable(st.ctx, True)
+        st.step(binding.default_hparams(lr=0.02, weight_decay=0.1, ns_steps=1))
+        torch.cuda.synchronize()
+        counts = {k: v[1] for k, v in binding.muon_profile_read(st.ctx, reset=True).items()}
+    finally:
+        st.close()
+    assert (counts["gram"], counts["poly"], counts["apply_poly"]) == (1, 1, 2)
 
 
 @pytest.mark.parametrize("ns_steps", [3, 4, 6, 7, 10, 11])
