@@ -471,7 +471,7 @@ void mark_second(GemmTile* tiles, int count, int n0) {
 // Whether a product in 128-wide blocks shares a launch with an apply product in coarse tiles (`g`'s): where the compute units that the
 // last round of those leaves idle can take it.  A coarse tile takes about 1.65 us per slab and 8, a block 0.3 and 5.  Step, in parts of the
 // one without the Gram route, alone / beside: 3000^2 with one of 1024 x 4096 (144 tiles; 36 and 256 blocks) 1.085 / 1.030, 4 of 1536^2 with
-// one of 640 x 5000 (144; 15 and 200) 1.048 / 1.031, 4 of 1024^2 with 3 of 1024 x 4096 (192; 256) 0.999 / 0.994, three iterations 1.11 / 1.08;
+// one of 640 x 5000 (144; 15 and 200) 1.048 / 1.031, 4 of 1024^2 with 3 of 1024 x 4096 (192; 256) 0.999 / 0.994;
 // but 48 of 1024^2 with 4 of 1024 x 4096 (768, full rounds; 144) 1.011 / 1.026, 8 of 2048^2 with 2 (512; 72) 1.010 / 1.032.
 bool fits_beside(const Group& g, const std::vector<Load>& load, int blocks) {
   const int64_t b = std::max(blocks, 1), rest = g.coarse.n_apply % b;
